@@ -50,7 +50,10 @@ constexpr int kMaxRows = 2;                   // rows of the tallest tile
 constexpr int kRow = kVec * kWave;            // parameters per row (256); a workgroup is one wavefront
 constexpr int kPad = kRow * kMaxRows;          // message and staging layouts pad every piece to this many
                                               // parameters (512): a whole number of tiles of either height
-constexpr int kMaxRuns = 16;                  // runs per launch
+constexpr int kRunGroup = 16;                 // runs whose first workgroups a workgroup compares at once
+constexpr int kMaxRuns = 7 * kRunGroup;       // runs per launch (3.8 KB of kernel arguments)
+constexpr int kCheckedRuns = 16;              // pieces over which a fragment's workgroups are added up for the size check
+constexpr uint64_t kMaxRunElems = 1ull << 31;  // longest run of a launch (its numbers are 32-bit); longer ones are cut here
 
 enum Mode { kQuantize = 0, kReduce = 1, kMerge = 2, kFused = 3, kReceive = 5 };   // kReceive = kReduce + kMerge
 
@@ -94,15 +97,15 @@ enum TilePath : uint32_t {
     kPathVector = 2,    // the message arrays are, the model arrays start at some other element
 };
 
+// A run of a launch.  32-bit numbers relative to the launch's bases, so that many runs fit the kernel arguments.
 struct Run {
-    uint64_t offset;     // first element of the run in the flat arrays
-    uint64_t numel;
-    uint64_t msg;        // where the run starts in the message arrays, in elements (a multiple of 512)
-    uint64_t soff;       // where the run starts in staged g / mom arrays, in elements (staged state only)
     uint32_t first_wg;   // first workgroup of the launch that works on this run
-    uint32_t path;       // TilePath of the run's whole tiles
-    uint32_t sidx;       // whole-span scale: index of the run's 4-byte scale word
-    uint32_t pad_;
+    uint32_t offset;     // first element of the run in the flat arrays, from Args::offset0
+    uint32_t numel;
+    uint32_t msg;        // where the run starts in the message arrays, in units of 512 elements
+    uint32_t soff;       // where the run starts in g / mom, from Args::soff0 (the same as offset unless they are staged)
+    uint32_t sidx_path;  // TilePath of the run's whole tiles in the two low bits; above them, for the whole-span
+                         // scale, the index of the run's 4-byte scale word
 };
 
 struct Args {
@@ -112,14 +115,19 @@ struct Args {
     uint16_t* w_now[SDL_MAX_WORKERS];
     uint8_t* codes[SDL_MAX_WORKERS];
     uint8_t* scales[SDL_MAX_WORKERS];
-    Run runs[kMaxRuns];
+    uint64_t offset0;    // what the runs' offsets count from, in the replicas and in g / mom
+    uint64_t soff0;
     uint32_t n_runs;
     uint32_t M;
     float lr, mu, alpha, one_minus_alpha;
     uint32_t aliased;    // w_send[m] == w_now[m]
     uint32_t emit;       // fused kernel: also write the messages
     uint32_t staged;     // g / mom point at a staging buffer that holds only this fragment
+    uint32_t group_wg[kMaxRuns / kRunGroup];   // first workgroup of every 16th run
+    uint32_t first_wg[kMaxRuns];               // first workgroup of each run, ascending; 0xffffffff behind the last
+    Run runs[kMaxRuns];
 };
+static_assert(sizeof(Args) <= 4096, "kernel arguments");
 
 // Cache policy bits of the buffer instructions on gfx950: 1 = sc0, 2 = nt, 16 = sc1.
 constexpr int kAuxLoad = 2;      // loads: non-temporal (every byte is touched once)
@@ -826,32 +834,62 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
 
 // ------------------------------------------------------------------ the kernel
 
+// Has the addresses that a call's loads need in scalar registers from here on (the compiler would ask for each where it is
+// first used, one wait after the other).
+template <int MODE, int MT, bool ALIASED>
+__device__ __forceinline__ void touch_arguments(const Args& a)
+{
+    asm volatile("" :: "s"(a.g), "s"(a.n_runs), "s"(a.first_wg[1]));
+    if constexpr (MODE == kReduce || MODE == kFused || MODE == kReceive) asm volatile("" :: "s"(a.mom));
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        if constexpr (MODE == kQuantize || MODE == kFused) asm volatile("" :: "s"(a.w_send[m]));
+        if constexpr (MODE == kMerge || MODE == kReceive || (MODE == kFused && !ALIASED)) asm volatile("" :: "s"(a.w_now[m]));
+        if constexpr (MODE == kReduce || MODE == kReceive) asm volatile("" :: "s"(a.codes[m]));
+    }
+}
+
 template <int MODE, int FMT, int MT, bool ALIASED, bool EMIT>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kWavesPerEu)))
 void sdl_kernel(const Args a)
 {
-    // which run does this workgroup work on (uniform scan of at most kMaxRuns entries)
+    // The start of a wavefront is a chain of dependent scalar loads, and with 8 wavefronts on a compute unit nothing
+    // hides it: what does not depend on the run (the arrays' addresses, the first 16 first workgroups) is asked for at once.
+    touch_arguments<MODE, MT, ALIASED>(a);
+    // Which run does this workgroup work on.  The first workgroups of 16 runs are one scalar load, compared all at once;
+    // with more runs than that, those of every 16th run come first.  (Entry by entry it was a chain of scalar loads as long
+    // as the list: 8.5 us for a launch of 16 small runs.  One vector load and a ballot are two dependent loads as well, but
+    // the streams push the arguments out of the vector caches: 7 % slower on a fragment of 6 large runs.)
     const uint32_t wg = blockIdx.x;
-    uint32_t r = 0;
-    for (uint32_t i = 1; i < a.n_runs; ++i)
-        if (wg >= a.runs[i].first_wg) r = i;
-    const uint64_t run_off = a.runs[r].offset;
-    const uint64_t run_n = a.runs[r].numel;
+    uint32_t base = 0;
+    if (a.n_runs > (uint32_t)kRunGroup) {
+#pragma unroll
+        for (int i = 1; i < kMaxRuns / kRunGroup; ++i)
+            if (wg >= a.group_wg[i]) base = (uint32_t)(i * kRunGroup);
+    }
+    uint32_t r = base;
+#pragma unroll
+    for (int i = 1; i < kRunGroup; ++i)
+        if (wg >= a.first_wg[base + i]) r = base + i;
+    const Run run = a.runs[r];
+    asm volatile("" :: "s"(run.first_wg), "s"(run.offset), "s"(run.numel), "s"(run.msg), "s"(run.soff), "s"(run.sidx_path),
+                 "s"(a.offset0), "s"(a.soff0));
+    const uint32_t path = run.sidx_path & 3u, sidx = run.sidx_path >> 2;
     constexpr int ROWS = tile_rows(MODE, MT, FMT);
-    constexpr int kTile = ROWS * kRow;
-    const uint64_t tile = (uint64_t)(wg - a.runs[r].first_wg) * kTile;   // first element of the tile in the run
-    const bool whole = run_n - tile >= (uint64_t)kTile;
-    if (whole && a.runs[r].path == kPathBuffer) {
-        const TileIOT<true, ROWS> io{a, run_off + tile, a.runs[r].msg + tile, threadIdx.x, a.runs[r].sidx,
-                                     a.staged ? a.runs[r].soff + tile : run_off + tile};
+    constexpr uint32_t kTile = ROWS * kRow;
+    const uint32_t tile = (wg - run.first_wg) * kTile;   // first element of the tile in the run
+    const uint64_t t0 = a.offset0 + run.offset + tile;
+    const uint64_t tb = (uint64_t)run.msg * kPad + tile;
+    const uint64_t s0 = a.soff0 + run.soff + tile;
+    const bool whole = run.numel - tile >= kTile;
+    if (whole && path == kPathBuffer) {
+        const TileIOT<true, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0};
         process<MODE, FMT, MT, ALIASED, EMIT, ROWS>(a, io);
-    } else if (whole && a.runs[r].path == kPathVector) {
-        const TileIOT<false, ROWS> io{a, run_off + tile, a.runs[r].msg + tile, threadIdx.x, a.runs[r].sidx,
-                                      a.staged ? a.runs[r].soff + tile : run_off + tile};
+    } else if (whole && path == kPathVector) {
+        const TileIOT<false, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0};
         process<MODE, FMT, MT, ALIASED, EMIT, ROWS>(a, io);
     } else {
-        const GuardedIO io{a, run_off + tile, tile, a.runs[r].msg + tile, run_n, threadIdx.x, a.runs[r].sidx,
-                           a.staged ? a.runs[r].soff + tile : run_off + tile};
+        const GuardedIO io{a, t0, tile, tb, run.numel, threadIdx.x, sidx, s0};
         process<MODE, FMT, 0, ALIASED, EMIT, ROWS>(a, io);
     }
 }
@@ -1194,19 +1232,38 @@ uint32_t tile_elems(int mode, const Args& a, sdl_format_t fmt)
     return (uint32_t)(tile_rows(mode, (int)variant_mt(mode, a.M, a.emit != 0u), (int)fmt) * kRow);
 }
 
-// Fill a.runs from a list of (offset, numel); returns the number of workgroups.
+// Fills a.runs from a list of pieces, launch by launch.  A piece longer than kMaxRunElems takes several runs (they start at
+// multiples of 512 elements, so scale blocks and tiles stay where they were).
 struct RunBuilder {
     Args* a;
     uint64_t tile;       // parameters per workgroup
     uint64_t n_wg = 0;
-    RunBuilder(Args* args, uint32_t tile_elems) : a(args), tile(tile_elems) { a->n_runs = 0; }
-    bool full() const { return a->n_runs == kMaxRuns; }
-    void add(uint64_t offset, uint64_t numel, TilePath path, uint64_t msg = 0, uint32_t sidx = 0, uint64_t soff = 0)
+    RunBuilder(Args* args, uint32_t tile_elems) : a(args), tile(tile_elems) { reset(); }
+    void reset()
     {
-        Run& r = a->runs[a->n_runs++];
-        r.offset = offset; r.numel = numel; r.msg = msg; r.soff = soff; r.first_wg = (uint32_t)n_wg;
-        r.path = path; r.sidx = sidx; r.pad_ = 0;
-        n_wg += (numel + tile - 1) / tile;
+        a->n_runs = 0;
+        n_wg = 0;
+        std::memset(a->first_wg, 0xff, sizeof(a->first_wg));
+        std::memset(a->group_wg, 0xff, sizeof(a->group_wg));
+    }
+    // Whether a run of n elements still fits this launch: a free entry, numbers that fit 32 bits from the first run's,
+    // and a grid that stays within the launch limit.
+    bool fits(uint64_t offset, uint64_t n, uint64_t msg, uint64_t soff) const
+    {
+        if (a->n_runs == 0) return true;
+        return a->n_runs < (uint32_t)kMaxRuns && offset >= a->offset0 && offset - a->offset0 <= 0xffffffffull
+               && (!a->staged || (soff >= a->soff0 && soff - a->soff0 <= 0xffffffffull)) && n_wg + (n + tile - 1) / tile <= 0x7fffffffull
+               && msg / kPad <= 0xffffffffull;
+    }
+    void add(uint64_t offset, uint64_t n, TilePath path, uint64_t msg, uint32_t sidx, uint64_t soff)
+    {
+        if (!a->staged) soff = offset;
+        if (a->n_runs == 0) { a->offset0 = offset; a->soff0 = soff; }
+        a->first_wg[a->n_runs] = (uint32_t)n_wg;
+        if (a->n_runs % kRunGroup == 0) a->group_wg[a->n_runs / kRunGroup] = (uint32_t)n_wg;
+        a->runs[a->n_runs++] = Run{(uint32_t)n_wg, (uint32_t)(offset - a->offset0), (uint32_t)n, (uint32_t)(msg / kPad),
+                                   (uint32_t)(soff - a->soff0), (sidx << 2) | (uint32_t)path};
+        n_wg += (n + tile - 1) / tile;
     }
 };
 
@@ -1241,6 +1298,29 @@ bool arrays_clash(const Args& a, sdl_format_t fmt, uint64_t model_elems, uint64_
     return false;
 }
 
+// Launches what the builder holds; false if the launch failed.
+template <int MODE>
+bool flush(RunBuilder& rb, sdl_format_t fmt, void* stream)
+{
+    if (rb.a->n_runs == 0) return true;
+    const hipError_t e = launch<MODE>(*rb.a, fmt, (uint32_t)rb.n_wg, (hipStream_t)stream);
+    rb.reset();
+    return e == hipSuccess;
+}
+
+// Adds one piece, cut to kMaxRunElems, launching whenever the launch is full.
+template <int MODE>
+bool add_piece(RunBuilder& rb, sdl_format_t fmt, uint64_t offset, uint64_t numel, TilePath path, uint64_t msg, uint32_t sidx,
+               uint64_t soff, void* stream)
+{
+    for (uint64_t at = 0; at < numel; at += kMaxRunElems) {
+        const uint64_t n = numel - at < kMaxRunElems ? numel - at : kMaxRunElems;
+        if (!rb.fits(offset + at, n, msg + at, soff + at) && !flush<MODE>(rb, fmt, stream)) return false;
+        rb.add(offset + at, n, path, msg + at, sidx, soff + at);
+    }
+    return true;
+}
+
 // One span starting at the given pointers (offset 0).
 template <int MODE>
 int run_single_span(Args& a, uint64_t n, sdl_format_t fmt, Align16 al, void* stream)
@@ -1253,8 +1333,6 @@ int run_single_span(Args& a, uint64_t n, sdl_format_t fmt, Align16 al, void* str
         sdl_exchange_bytes(fmt, n, &cb, &sb);
         if (arrays_clash<MODE>(a, fmt, n, n, cb, sb)) return SDL_ERR_INVALID_ARG;
     }
-    RunBuilder rb(&a, tile);
-    rb.add(0, n, al.path());
     if constexpr (MODE == kQuantize || MODE == kFused) {
         if (is_span_scaled(fmt)) {
             // whole-span scale: clear the scale word, take the grid-wide maximum, then encode
@@ -1262,8 +1340,8 @@ int run_single_span(Args& a, uint64_t n, sdl_format_t fmt, Align16 al, void* str
             if (launch_span_prepass(a, &one, 1, (hipStream_t)stream) != hipSuccess) return SDL_ERR_DEVICE;
         }
     }
-    hipError_t e = launch<MODE>(a, fmt, (uint32_t)rb.n_wg, (hipStream_t)stream);
-    return e == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
+    RunBuilder rb(&a, tile);
+    return add_piece<MODE>(rb, fmt, 0, n, al.path(), 0, 0, 0, stream) && flush<MODE>(rb, fmt, stream) ? SDL_OK : SDL_ERR_DEVICE;
 }
 
 }  // namespace
@@ -1509,7 +1587,7 @@ static int launch_fragment(Args& a, const sdl_plan_t* plan, uint32_t p, Align16 
         for (uint32_t in_group = 0; walk.next(&pc);) {
             n_wg += (pc.numel + tile - 1) / tile;
             if (n_wg > 0x7fffffffull) return SDL_ERR_UNSUPPORTED;
-            if (++in_group == (uint32_t)kMaxRuns) { in_group = 0; n_wg = 0; }
+            if (++in_group == (uint32_t)kCheckedRuns) { in_group = 0; n_wg = 0; }
         }
     }
     {
@@ -1539,14 +1617,9 @@ static int launch_fragment(Args& a, const sdl_plan_t* plan, uint32_t p, Align16 
     }
     RunBuilder rb(&a, tile);
     PieceWalk walk = start;
-    for (bool more = walk.next(&pc); more || a.n_runs;) {
-        if (more) rb.add(pc.offset, pc.numel, pc.al.path(), pc.msg, pc.sidx, pc.soff);
-        more = more && walk.next(&pc);
-        if (rb.full() || !more) {
-            if (launch<MODE>(a, fmt, (uint32_t)rb.n_wg, (hipStream_t)stream) != hipSuccess) return SDL_ERR_DEVICE;
-            rb = RunBuilder(&a, tile);
-        }
-    }
+    while (walk.next(&pc))
+        if (!add_piece<MODE>(rb, fmt, pc.offset, pc.numel, pc.al.path(), pc.msg, pc.sidx, pc.soff, stream)) return SDL_ERR_DEVICE;
+    if (!flush<MODE>(rb, fmt, stream)) return SDL_ERR_DEVICE;
     return SDL_OK;
 }
 
