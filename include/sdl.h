@@ -38,8 +38,8 @@
  *     on alignment, speed does: full speed needs every array to start on a 128-byte
  *     boundary (a cache line); model arrays (g, mom, replicas) that start elsewhere,
  *     at any element, cost up to a fifth (lines shared between neighbouring tiles
- *     are fetched twice); code arrays that are not 16-byte aligned put the whole
- *     call on an element-by-element path at a quarter of the speed.
+ *     are fetched twice); code arrays that are not 16-byte aligned (messages packed
+ *     back to back) cost about a tenth.
  *   - 1 <= M <= SDL_MAX_WORKERS.
  *   - An array that a call writes must not overlap any other array of the call, except that
  *     w_send[m] may be the very same pointer as w_now[m] for every m (no overlap delay,

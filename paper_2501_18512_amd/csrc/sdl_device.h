@@ -21,6 +21,8 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_f32elem __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4_bf16elem __attribute__((ext_vector_type(4), aligned(2)));
 typedef float f32x4_elem __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t u16_byte __attribute__((aligned(1)));
+typedef uint32_t u32_byte __attribute__((aligned(1)));
 typedef uint32_t u32x2_elem __attribute__((ext_vector_type(2), aligned(2)));
 
 __device__ __forceinline__ uint32_t f2u(float x) { return __builtin_bit_cast(uint32_t, x); }

@@ -15,9 +15,9 @@
 //     is three DPP exchanges (two inside the quad, one across the half row); wider
 //     blocks add a row mirror and ds_bpermute exchanges.  No LDS storage is used.
 // Full, 16-byte aligned tiles use buffer instructions with non-temporal cache policy
-// (every byte is touched once); full tiles of runs whose model arrays start at some other
-// element use vector accesses of element alignment in the same lane layout; ragged tails
-// and calls with unaligned message arrays use guarded element-wise accesses.  A launch covers up to kMaxRuns contiguous runs of the flat
+// (every byte is touched once); full tiles of runs in which some array starts at some other
+// element use vector accesses of element alignment in the same lane layout; ragged tails use
+// range-checked accesses of one element each.  A launch covers up to kMaxRuns contiguous runs of the flat
 // model; every workgroup belongs to exactly one run, so scale blocks never straddle
 // runs.
 //
@@ -90,11 +90,10 @@ constexpr int block_elems(int f)
     return f == SDL_FMT_E3M0_B64 ? 64 : f == SDL_FMT_E3M0_B128 ? 128 : f == SDL_FMT_E3M0_SPAN ? 0 : SDL_BLOCK;
 }
 
-// How the whole tiles of a run reach memory (a ragged last tile always takes the guarded path).
+// How the whole tiles of a run reach memory (a ragged last tile always takes the range-checked path).
 enum TilePath : uint32_t {
-    kPathGuarded = 0,   // element by element: some message array is not 16-byte aligned
     kPathBuffer = 1,    // every array of the call is 16-byte aligned at the run's first element
-    kPathVector = 2,    // the message arrays are, the model arrays start at some other element
+    kPathVector = 2,    // some array starts at some other element (or, messages of 4 and 8 bits, byte)
 };
 
 // A run of a launch.  32-bit numbers relative to the launch's bases, so that many runs fit the kernel arguments.
@@ -331,11 +330,14 @@ __device__ __forceinline__ void decode_e4m3(uint32_t c0, float scale, float (&dq
 // of row `row` of each array.
 //   TileIO     a whole, 16-byte aligned tile: buffer loads / stores through one resource
 //              per array (scalar base, 32-bit lane offset) with explicit cache policy
-//   TileIOT<false>  a whole tile whose model arrays start at any element (a run behind a
-//              parameter group of odd length): the same lane layout through plain vector
-//              loads / stores of element alignment; the message arrays as in TileIO
-//   GuardedIO  any alignment, any tail: per-element global loads / stores under a
-//              per-row count of valid elements
+//   TileIOT<false>  a whole tile of arrays that start at any element (a run behind a parameter
+//              group of odd length, messages packed back to back): the same lane layout through
+//              plain vector loads / stores of element alignment (byte alignment for the 4- and
+//              8-bit codes)
+//   TailIO     the ragged last tile of a run, any alignment: one buffer access per element (per
+//              byte of 4- and 8-bit codes) under the range check of the buffer instructions,
+//              which returns 0 past the end and drops stores there -- no branches, so that all
+//              of a tile's loads are in flight at once
 
 template <bool ALIGNED, int ROWS>
 struct TileIOT {
@@ -446,6 +448,13 @@ struct TileIOT {
     __device__ __forceinline__ void load_wn(uint32_t m, int row, uint32_t (&u)[2]) const { model_ld_bf16(a.w_now[m] + t0, row, u); }
     __device__ __forceinline__ void store_wn(uint32_t m, int row, const uint32_t (&u)[2]) const { model_st_bf16(a.w_now[m] + t0, row, u); }
 
+    // Where the lane's four codes of a row lie in a message array of NUM / DEN bytes per element.  Accesses at this address
+    // (not ALIGNED) use the normal cache policy: lanes and tiles share lines, which L2 puts together.
+    template <int NUM, int DEN> __device__ __forceinline__ uint64_t msg_byte(int row) const
+    {
+        return tb * NUM / DEN + (uint32_t)((row * kRow + (int)(lane * kVec)) * NUM / DEN);
+    }
+
     // E4M3 only: with EXACT = false the two byte values the encoder never writes decode to NaN
     static constexpr bool kHasInexactDecode = true;
     // whole tiles: a run-time replica count is taken in groups whose loads are issued together
@@ -455,11 +464,25 @@ struct TileIOT {
     {
         const uint8_t* codes = a.codes[m];
         if constexpr (FMT == SDL_FMT_FP32) {
-            ld_f32(reinterpret_cast<const float*>(codes) + tb, row, dq);
+            if constexpr (ALIGNED) {
+                ld_f32(reinterpret_cast<const float*>(codes) + tb, row, dq);
+            } else {
+                const f32x4_elem x = *(reinterpret_cast<const f32x4_elem*>(codes + msg_byte<4, 1>(row)));
+                dq[0] = x.x; dq[1] = x.y; dq[2] = x.z; dq[3] = x.w;
+            }
         } else if constexpr (FMT == SDL_FMT_BF16) {
             uint32_t u[2];
-            ld_bf16(reinterpret_cast<const uint16_t*>(codes) + tb, row, u);
+            if constexpr (ALIGNED) {
+                ld_bf16(reinterpret_cast<const uint16_t*>(codes) + tb, row, u);
+            } else {
+                const u32x2_elem x = *(reinterpret_cast<const u32x2_elem*>(codes + msg_byte<2, 1>(row)));
+                u[0] = x.x; u[1] = x.y;
+            }
             unpack_bf16(u, dq);
+        } else if constexpr (!ALIGNED) {
+            const float scale = load_scale<FMT>(m, row);
+            if constexpr (is_e3m0(FMT)) decode_e3m0(*reinterpret_cast<const u16_byte*>(codes + msg_byte<1, 2>(row)), scale, dq);
+            else decode_e4m3<EXACT>(*reinterpret_cast<const u32_byte*>(codes + msg_byte<1, 1>(row)), scale, dq);
         } else {
             const float scale = load_scale<FMT>(m, row);
             if constexpr (is_e3m0(FMT)) {
@@ -478,7 +501,17 @@ struct TileIOT {
     __device__ __forceinline__ void store_message(uint32_t m, int row, const uint32_t (&c)[kVec], uint32_t sb) const
     {
         uint8_t* codes = a.codes[m];
-        if constexpr (FMT == SDL_FMT_FP32) {
+        if constexpr (!ALIGNED) {
+            if constexpr (FMT == SDL_FMT_FP32) {
+                *reinterpret_cast<u32x4_f32elem*>(codes + msg_byte<4, 1>(row)) = u32x4_f32elem{c[0], c[1], c[2], c[3]};
+            } else if constexpr (FMT == SDL_FMT_BF16) {
+                *reinterpret_cast<u32x2_elem*>(codes + msg_byte<2, 1>(row)) = u32x2_elem{c[0], c[1]};
+            } else {
+                store_scale<FMT>(m, row, sb);
+                if constexpr (is_e3m0(FMT)) *reinterpret_cast<u16_byte*>(codes + msg_byte<1, 2>(row)) = (uint16_t)c[0];
+                else *reinterpret_cast<u32_byte*>(codes + msg_byte<1, 1>(row)) = c[0];
+            }
+        } else if constexpr (FMT == SDL_FMT_FP32) {
             const u32x4 x = {c[0], c[1], c[2], c[3]};
             __builtin_amdgcn_raw_buffer_store_b128(x, rsrc(codes + tb * 4, kTile * 4),
                                                    (int)(row * kRow * 4 + lane * 16), 0, kAuxStore);
@@ -499,130 +532,127 @@ struct TileIOT {
     }
 };
 
-struct GuardedIO {
+struct TailIO {
     const Args& a;
     uint64_t t0;           // tile's first element in the flat arrays
-    uint64_t tb;           // tile's first element counted from the run start
     uint64_t mb;           // tile's first element in the message arrays
-    uint64_t run_n;        // elements of the run
+    uint64_t s0;           // tile's first element in g / mom (= t0 unless the state is staged)
+    uint32_t left;         // elements of the run from the tile's first on
     uint32_t lane;
     uint32_t sidx;         // whole-span scale: index of the run's scale word
-    uint64_t s0;           // tile's first element in g / mom (= t0 unless the state is staged)
 
     __device__ __forceinline__ uint32_t span_amax(uint32_t m) const
     {
         return reinterpret_cast<const uint32_t*>(a.scales[m])[sidx];
     }
-
-    // lane's first element of a row, counted from the run start, and how many of its 4 exist
-    __device__ __forceinline__ uint64_t first(int row) const { return tb + (uint64_t)(row * kRow) + lane * kVec; }
-    __device__ __forceinline__ int valid(int row) const
+    // elements of a row that exist
+    __device__ __forceinline__ uint32_t valid(int row) const
     {
-        const uint64_t b = first(row);
-        return b >= run_n ? 0 : (run_n - b >= (uint64_t)kVec ? kVec : (int)(run_n - b));
+        const uint32_t at = (uint32_t)(row * kRow);
+        return left <= at ? 0u : left - at < (uint32_t)kRow ? left - at : (uint32_t)kRow;
     }
-    __device__ __forceinline__ uint64_t flat(int row) const { return t0 + (uint64_t)(row * kRow) + lane * kVec; }
-    __device__ __forceinline__ uint64_t msg(int row) const { return mb + (uint64_t)(row * kRow) + lane * kVec; }
-    __device__ __forceinline__ uint64_t state(int row) const { return s0 + (uint64_t)(row * kRow) + lane * kVec; }
-
-    __device__ __forceinline__ void ld_f32(const float* p, int n, float (&v)[kVec]) const
+    // p = address of the tile's first element in the array
+    __device__ __forceinline__ void ld_f32(const float* p, int row, float (&v)[kVec]) const
     {
+        const __amdgpu_buffer_rsrc_t r = rsrc(p + row * kRow, valid(row) * 4);
 #pragma unroll
-        for (int j = 0; j < kVec; ++j) v[j] = j < n ? p[j] : 0.0f;
+        for (int j = 0; j < kVec; ++j) v[j] = u2f(__builtin_amdgcn_raw_buffer_load_b32(r, (int)(lane * 16 + 4 * j), 0, 0));
     }
-    __device__ __forceinline__ void st_f32(float* p, int n, const float (&v)[kVec]) const
+    __device__ __forceinline__ void st_f32(float* p, int row, const float (&v)[kVec]) const
     {
+        const __amdgpu_buffer_rsrc_t r = rsrc(p + row * kRow, valid(row) * 4);
+#pragma unroll
+        for (int j = 0; j < kVec; ++j) __builtin_amdgcn_raw_buffer_store_b32(f2u(v[j]), r, (int)(lane * 16 + 4 * j), 0, 0);
+    }
+    __device__ __forceinline__ void ld_bf16(const uint16_t* p, int row, uint32_t (&u)[2]) const
+    {
+        const __amdgpu_buffer_rsrc_t r = rsrc(p + row * kRow, valid(row) * 2);
+        uint32_t h[kVec];
 #pragma unroll
         for (int j = 0; j < kVec; ++j)
-            if (j < n) p[j] = v[j];
+            h[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)(lane * 8 + 2 * j), 0, 0) & 0xffffu;
+        u[0] = h[0] | (h[1] << 16);
+        u[1] = h[2] | (h[3] << 16);
     }
-    __device__ __forceinline__ void ld_bf16(const uint16_t* p, int n, uint32_t (&u)[2]) const
+    __device__ __forceinline__ void st_bf16(uint16_t* p, int row, const uint32_t (&u)[2]) const
     {
+        const __amdgpu_buffer_rsrc_t r = rsrc(p + row * kRow, valid(row) * 2);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const uint32_t lo = 2 * k < n ? p[2 * k] : 0u;
-            const uint32_t hi = 2 * k + 1 < n ? p[2 * k + 1] : 0u;
-            u[k] = lo | (hi << 16);
-        }
+        for (int j = 0; j < kVec; ++j)
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(u[j / 2] >> (16 * (j % 2))), r, (int)(lane * 8 + 2 * j), 0, 0);
     }
-    __device__ __forceinline__ void st_bf16(uint16_t* p, int n, const uint32_t (&u)[2]) const
+    // N codes of one byte each per lane (E4M3: 4; E3M0: 2, of two elements)
+    template <int N> __device__ __forceinline__ __amdgpu_buffer_rsrc_t code_rsrc(uint8_t* codes, int row) const
     {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            if (2 * k < n) p[2 * k] = (uint16_t)(u[k] & 0xffffu);
-            if (2 * k + 1 < n) p[2 * k + 1] = (uint16_t)(u[k] >> 16);
-        }
+        return rsrc(codes + (mb + (uint32_t)(row * kRow)) * N / kVec, (valid(row) * N + kVec - 1) / kVec);
     }
 
-    __device__ __forceinline__ void load_g(int row, float (&v)[kVec]) const { ld_f32(a.g + state(row), valid(row), v); }
-    __device__ __forceinline__ void load_mom(int row, float (&v)[kVec]) const { ld_f32(a.mom + state(row), valid(row), v); }
-    __device__ __forceinline__ void store_g(int row, const float (&v)[kVec]) const { st_f32(a.g + state(row), valid(row), v); }
-    __device__ __forceinline__ void store_mom(int row, const float (&v)[kVec]) const { st_f32(a.mom + state(row), valid(row), v); }
-    __device__ __forceinline__ void load_ws(uint32_t m, int row, uint32_t (&u)[2]) const { ld_bf16(a.w_send[m] + flat(row), valid(row), u); }
-    __device__ __forceinline__ void load_wn(uint32_t m, int row, uint32_t (&u)[2]) const { ld_bf16(a.w_now[m] + flat(row), valid(row), u); }
-    __device__ __forceinline__ void store_wn(uint32_t m, int row, const uint32_t (&u)[2]) const { st_bf16(a.w_now[m] + flat(row), valid(row), u); }
+    __device__ __forceinline__ void load_g(int row, float (&v)[kVec]) const { ld_f32(a.g + s0, row, v); }
+    __device__ __forceinline__ void load_mom(int row, float (&v)[kVec]) const { ld_f32(a.mom + s0, row, v); }
+    __device__ __forceinline__ void store_g(int row, const float (&v)[kVec]) const { st_f32(a.g + s0, row, v); }
+    __device__ __forceinline__ void store_mom(int row, const float (&v)[kVec]) const { st_f32(a.mom + s0, row, v); }
+    __device__ __forceinline__ void load_ws(uint32_t m, int row, uint32_t (&u)[2]) const { ld_bf16(a.w_send[m] + t0, row, u); }
+    __device__ __forceinline__ void load_wn(uint32_t m, int row, uint32_t (&u)[2]) const { ld_bf16(a.w_now[m] + t0, row, u); }
+    __device__ __forceinline__ void store_wn(uint32_t m, int row, const uint32_t (&u)[2]) const { st_bf16(a.w_now[m] + t0, row, u); }
 
     static constexpr bool kHasInexactDecode = false;
-    static constexpr bool kGroupReplicas = false;    // ragged tails: one replica at a time, small code
+    static constexpr bool kGroupReplicas = true;
     template <int FMT, bool EXACT = true>
     __device__ __forceinline__ void load_message(uint32_t m, int row, float (&dq)[kVec]) const
     {
-        const uint8_t* codes = a.codes[m];
-        const uint64_t b = msg(row);
-        const int n = valid(row);
+        uint8_t* codes = a.codes[m];
         if constexpr (FMT == SDL_FMT_FP32) {
-            ld_f32(reinterpret_cast<const float*>(codes) + b, n, dq);
+            ld_f32(reinterpret_cast<const float*>(codes) + mb, row, dq);
         } else if constexpr (FMT == SDL_FMT_BF16) {
             uint32_t u[2];
-            ld_bf16(reinterpret_cast<const uint16_t*>(codes) + b, n, u);
+            ld_bf16(reinterpret_cast<const uint16_t*>(codes) + mb, row, u);
             unpack_bf16(u, dq);
         } else {
             float scale;
-            if constexpr (is_span_scaled(FMT)) scale = block_scale_from_exponent<FMT>(span_amax(m) >> 23).scale;
-            else scale = scale_from_byte(n > 0 ? a.scales[m][b / block_elems(FMT)] : 127u);
-            uint32_t c0 = 0;
-            if constexpr (is_e3m0(FMT)) {
-#pragma unroll
-                for (int k = 0; k < 2; ++k)
-                    if (2 * k < n) c0 |= (uint32_t)codes[b / 2 + k] << (8 * k);
-                decode_e3m0(c0, scale, dq);
+            if constexpr (is_span_scaled(FMT)) {
+                scale = block_scale_from_exponent<FMT>(span_amax(m) >> 23).scale;
             } else {
-#pragma unroll
-                for (int j = 0; j < kVec; ++j)
-                    if (j < n) c0 |= (uint32_t)codes[b + j] << (8 * j);
-                decode_e4m3<true>(c0, scale, dq);
+                constexpr int B = block_elems(FMT);
+                const __amdgpu_buffer_rsrc_t r = rsrc(a.scales[m] + (mb + (uint32_t)(row * kRow)) / B, (valid(row) + B - 1) / B);
+                scale = scale_from_byte(__builtin_amdgcn_raw_buffer_load_b8(r, (int)(lane / (B / kVec)), 0, kAuxScale));
             }
+            constexpr int N = is_e3m0(FMT) ? 2 : 4;
+            const __amdgpu_buffer_rsrc_t r = code_rsrc<N>(codes, row);
+            uint32_t c0 = 0;
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                c0 |= ((uint32_t)__builtin_amdgcn_raw_buffer_load_b8(r, (int)(lane * N + k), 0, 0) & 255u) << (8 * k);
+            if constexpr (is_e3m0(FMT)) decode_e3m0(c0, scale, dq);
+            else decode_e4m3<true>(c0, scale, dq);
         }
     }
+    // elements beyond the end are zero outer gradients: they add nothing to a block maximum, and the unused nibble of a
+    // last E3M0 byte is 0
     template <int FMT>
     __device__ __forceinline__ void store_message(uint32_t m, int row, const uint32_t (&c)[kVec], uint32_t sb) const
     {
         uint8_t* codes = a.codes[m];
-        const uint64_t b = msg(row);
-        const int n = valid(row);
         if constexpr (FMT == SDL_FMT_FP32) {
             float v[kVec];
 #pragma unroll
             for (int j = 0; j < kVec; ++j) v[j] = u2f(c[j]);
-            st_f32(reinterpret_cast<float*>(codes) + b, n, v);
+            st_f32(reinterpret_cast<float*>(codes) + mb, row, v);
         } else if constexpr (FMT == SDL_FMT_BF16) {
             const uint32_t u[2] = {c[0], c[1]};
-            st_bf16(reinterpret_cast<uint16_t*>(codes) + b, n, u);
+            st_bf16(reinterpret_cast<uint16_t*>(codes) + mb, row, u);
         } else {
             if constexpr (!is_span_scaled(FMT)) {
                 constexpr int B = block_elems(FMT);
-                if ((lane % (B / kVec)) == 0u && n > 0) a.scales[m][b / B] = (uint8_t)sb;
+                if ((lane % (B / kVec)) == 0u)
+                    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)sb, rsrc(a.scales[m] + (mb + (uint32_t)(row * kRow)) / B,
+                                                                           (valid(row) + B - 1) / B),
+                                                         (int)(lane / (B / kVec)), 0, kAuxScale);
             }
-            if constexpr (is_e3m0(FMT)) {
-                // elements beyond the end are zero outer gradients: their nibbles are 0
+            constexpr int N = is_e3m0(FMT) ? 2 : 4;
+            const __amdgpu_buffer_rsrc_t r = code_rsrc<N>(codes, row);
 #pragma unroll
-                for (int k = 0; k < 2; ++k)
-                    if (2 * k < n) codes[b / 2 + k] = (uint8_t)(c[0] >> (8 * k));
-            } else {
-#pragma unroll
-                for (int j = 0; j < kVec; ++j)
-                    if (j < n) codes[b + j] = (uint8_t)(c[0] >> (8 * j));
-            }
+            for (int k = 0; k < N; ++k)
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(c[0] >> (8 * k)), r, (int)(lane * N + k), 0, 0);
         }
     }
 };
@@ -882,15 +912,15 @@ void sdl_kernel(const Args a)
     const uint64_t tb = (uint64_t)run.msg * kPad + tile;
     const uint64_t s0 = a.soff0 + run.soff + tile;
     const bool whole = run.numel - tile >= kTile;
-    if (whole && path == kPathBuffer) {
+    if (!whole) {
+        const TailIO io{a, t0, tb, s0, run.numel - tile, threadIdx.x, sidx};
+        process<MODE, FMT, 0, ALIASED, EMIT, ROWS>(a, io);
+    } else if (path == kPathBuffer) {
         const TileIOT<true, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0};
         process<MODE, FMT, MT, ALIASED, EMIT, ROWS>(a, io);
-    } else if (whole && path == kPathVector) {
+    } else {
         const TileIOT<false, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0};
         process<MODE, FMT, MT, ALIASED, EMIT, ROWS>(a, io);
-    } else {
-        const GuardedIO io{a, t0, tile, tb, run.numel, threadIdx.x, sidx, s0};
-        process<MODE, FMT, 0, ALIASED, EMIT, ROWS>(a, io);
     }
 }
 
@@ -1222,7 +1252,7 @@ bool valid_format(sdl_format_t fmt) { return fmt >= SDL_FMT_FP32 && fmt <= SDL_F
 // bytes need none).
 struct Align16 {
     bool model = true, msg = true;
-    TilePath path() const { return !msg ? kPathGuarded : model ? kPathBuffer : kPathVector; }
+    TilePath path() const { return model && msg ? kPathBuffer : kPathVector; }
     Align16 at(bool run_start_aligned) const { return Align16{model && run_start_aligned, msg}; }
 };
 
