@@ -122,6 +122,7 @@ struct Args {
     uint32_t aliased;    // w_send[m] == w_now[m]
     uint32_t emit;       // fused kernel: also write the messages
     uint32_t staged;     // g / mom point at a staging buffer that holds only this fragment
+    uint32_t chunked;    // each XCD takes kChunkRows consecutive rows (see chunked_tile)
     uint32_t group_wg[kMaxRuns / kRunGroup];   // first workgroup of every 16th run
     uint32_t first_wg[kMaxRuns];               // first workgroup of each run, ascending; 0xffffffff behind the last
     Run runs[kMaxRuns];
@@ -864,12 +865,27 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
 
 // ------------------------------------------------------------------ the kernel
 
+// Workgroup -> tile.  The dispatcher deals workgroups round robin to the 8 XCDs.  Tiles in that order spread best over the
+// memory channels, and it is what aligned arrays get.  Where the arrays start somewhere inside a cache line, every row
+// shares its first and last line with its neighbours; on another XCD that line is fetched into a second L2 and written in
+// two parts, so consecutive tiles go to one XCD, kChunkRows rows at a time (72 M parameters of odd groups, fused: M = 2
+// 388 -> 329 us, M = 4 572 -> 483, M = 8 892 -> 869; half or twice the chunk is up to 2 % slower, and aligned arrays lose
+// 3-8 % with it).
+constexpr int kXcds = 8;
+constexpr int kChunkRows = 8;
+template <int ROWS>
+__device__ __forceinline__ uint32_t chunked_tile(uint32_t wg)
+{
+    constexpr uint32_t C = kChunkRows / ROWS, whole = kXcds * C;
+    return wg < gridDim.x / whole * whole ? wg / whole * whole + (wg % kXcds) * C + (wg / kXcds) % C : wg;
+}
+
 // Has the addresses that a call's loads need in scalar registers from here on (the compiler would ask for each where it is
 // first used, one wait after the other).
 template <int MODE, int MT, bool ALIASED>
 __device__ __forceinline__ void touch_arguments(const Args& a)
 {
-    asm volatile("" :: "s"(a.g), "s"(a.n_runs), "s"(a.first_wg[1]));
+    asm volatile("" :: "s"(a.g), "s"(a.n_runs), "s"(a.chunked), "s"(a.first_wg[1]));
     if constexpr (MODE == kReduce || MODE == kFused || MODE == kReceive) asm volatile("" :: "s"(a.mom));
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
@@ -890,7 +906,8 @@ void sdl_kernel(const Args a)
     // with more runs than that, those of every 16th run come first.  (Entry by entry it was a chain of scalar loads as long
     // as the list: 8.5 us for a launch of 16 small runs.  One vector load and a ballot are two dependent loads as well, but
     // the streams push the arguments out of the vector caches: 7 % slower on a fragment of 6 large runs.)
-    const uint32_t wg = blockIdx.x;
+    constexpr int ROWS = tile_rows(MODE, MT, FMT);
+    const uint32_t wg = a.chunked ? chunked_tile<ROWS>(blockIdx.x) : blockIdx.x;
     uint32_t base = 0;
     if (a.n_runs > (uint32_t)kRunGroup) {
 #pragma unroll
@@ -905,7 +922,6 @@ void sdl_kernel(const Args a)
     asm volatile("" :: "s"(run.first_wg), "s"(run.offset), "s"(run.numel), "s"(run.msg), "s"(run.soff), "s"(run.sidx_path),
                  "s"(a.offset0), "s"(a.soff0));
     const uint32_t path = run.sidx_path & 3u, sidx = run.sidx_path >> 2;
-    constexpr int ROWS = tile_rows(MODE, MT, FMT);
     constexpr uint32_t kTile = ROWS * kRow;
     const uint32_t tile = (wg - run.first_wg) * kTile;   // first element of the tile in the run
     const uint64_t t0 = a.offset0 + run.offset + tile;
@@ -1267,12 +1283,12 @@ uint32_t tile_elems(int mode, const Args& a, sdl_format_t fmt)
 struct RunBuilder {
     Args* a;
     uint64_t tile;       // parameters per workgroup
-    uint64_t n_wg = 0;
+    uint64_t n_wg = 0, n_unaligned = 0;
     RunBuilder(Args* args, uint32_t tile_elems) : a(args), tile(tile_elems) { reset(); }
     void reset()
     {
         a->n_runs = 0;
-        n_wg = 0;
+        n_wg = n_unaligned = 0;
         std::memset(a->first_wg, 0xff, sizeof(a->first_wg));
         std::memset(a->group_wg, 0xff, sizeof(a->group_wg));
     }
@@ -1285,15 +1301,16 @@ struct RunBuilder {
                && (!a->staged || (soff >= a->soff0 && soff - a->soff0 <= 0xffffffffull)) && n_wg + (n + tile - 1) / tile <= 0x7fffffffull
                && msg / kPad <= 0xffffffffull;
     }
-    void add(uint64_t offset, uint64_t n, TilePath path, uint64_t msg, uint32_t sidx, uint64_t soff)
+    void add(uint64_t offset, uint64_t n, Align16 al, uint64_t msg, uint32_t sidx, uint64_t soff)
     {
         if (!a->staged) soff = offset;
         if (a->n_runs == 0) { a->offset0 = offset; a->soff0 = soff; }
         a->first_wg[a->n_runs] = (uint32_t)n_wg;
         if (a->n_runs % kRunGroup == 0) a->group_wg[a->n_runs / kRunGroup] = (uint32_t)n_wg;
         a->runs[a->n_runs++] = Run{(uint32_t)n_wg, (uint32_t)(offset - a->offset0), (uint32_t)n, (uint32_t)(msg / kPad),
-                                   (uint32_t)(soff - a->soff0), (sidx << 2) | (uint32_t)path};
+                                   (uint32_t)(soff - a->soff0), (sidx << 2) | (uint32_t)al.path()};
         n_wg += (n + tile - 1) / tile;
+        if (!al.model) n_unaligned += (n + tile - 1) / tile;
     }
 };
 
@@ -1333,6 +1350,7 @@ template <int MODE>
 bool flush(RunBuilder& rb, sdl_format_t fmt, void* stream)
 {
     if (rb.a->n_runs == 0) return true;
+    rb.a->chunked = 2 * rb.n_unaligned > rb.n_wg ? 1u : 0u;   // what most of the launch's tiles want
     const hipError_t e = launch<MODE>(*rb.a, fmt, (uint32_t)rb.n_wg, (hipStream_t)stream);
     rb.reset();
     return e == hipSuccess;
@@ -1340,13 +1358,13 @@ bool flush(RunBuilder& rb, sdl_format_t fmt, void* stream)
 
 // Adds one piece, cut to kMaxRunElems, launching whenever the launch is full.
 template <int MODE>
-bool add_piece(RunBuilder& rb, sdl_format_t fmt, uint64_t offset, uint64_t numel, TilePath path, uint64_t msg, uint32_t sidx,
+bool add_piece(RunBuilder& rb, sdl_format_t fmt, uint64_t offset, uint64_t numel, Align16 al, uint64_t msg, uint32_t sidx,
                uint64_t soff, void* stream)
 {
     for (uint64_t at = 0; at < numel; at += kMaxRunElems) {
         const uint64_t n = numel - at < kMaxRunElems ? numel - at : kMaxRunElems;
         if (!rb.fits(offset + at, n, msg + at, soff + at) && !flush<MODE>(rb, fmt, stream)) return false;
-        rb.add(offset + at, n, path, msg + at, sidx, soff + at);
+        rb.add(offset + at, n, al, msg + at, sidx, soff + at);
     }
     return true;
 }
@@ -1371,7 +1389,7 @@ int run_single_span(Args& a, uint64_t n, sdl_format_t fmt, Align16 al, void* str
         }
     }
     RunBuilder rb(&a, tile);
-    return add_piece<MODE>(rb, fmt, 0, n, al.path(), 0, 0, 0, stream) && flush<MODE>(rb, fmt, stream) ? SDL_OK : SDL_ERR_DEVICE;
+    return add_piece<MODE>(rb, fmt, 0, n, al, 0, 0, 0, stream) && flush<MODE>(rb, fmt, stream) ? SDL_OK : SDL_ERR_DEVICE;
 }
 
 }  // namespace
@@ -1648,7 +1666,7 @@ static int launch_fragment(Args& a, const sdl_plan_t* plan, uint32_t p, Align16 
     RunBuilder rb(&a, tile);
     PieceWalk walk = start;
     while (walk.next(&pc))
-        if (!add_piece<MODE>(rb, fmt, pc.offset, pc.numel, pc.al.path(), pc.msg, pc.sidx, pc.soff, stream)) return SDL_ERR_DEVICE;
+        if (!add_piece<MODE>(rb, fmt, pc.offset, pc.numel, pc.al, pc.msg, pc.sidx, pc.soff, stream)) return SDL_ERR_DEVICE;
     if (!flush<MODE>(rb, fmt, stream)) return SDL_ERR_DEVICE;
     return SDL_OK;
 }
