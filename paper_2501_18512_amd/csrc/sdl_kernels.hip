@@ -1145,32 +1145,48 @@ size_t code_bytes_at(sdl_format_t fmt, uint64_t elem)
     }
 }
 
-// Dynamic LDS requested per workgroup.  The kernels use no LDS; the request only caps how
-// many wavefronts share a CU (160 KiB of LDS per CU: 20480 B -> 8, 13653 B -> 12, 10240 B -> 16),
-// which is the knob that matters for a streaming kernel: enough loads in flight, not so many
-// that the access window in each array grows and DRAM page locality is lost.  Measured on
-// MI355X (medians of three runs over 302 M parameters, replica counts 2 / 4 / 8): the kernels
-// that write the replicas back want few wavefronts -- fused 12 / 8 / 8 (12 when w_send aliases
-// w_now), one-pass receive 12 / 8 / 8, merge 16 / 12 / 8 --, the receive side without the merge
-// all / 16 / all (measured again with the arrays in one allocation: 16 cost it 3 % at two replicas),
-// and the send side every wavefront it can get.  A single replica: 16 for the fused
-// kernel and the one-pass receive, no cap otherwise.
-uint32_t lds_cap_bytes(int mode, uint32_t mt, bool aliased)
+// Wavefronts that share a CU (0: as many as fit).  Enough loads in flight, not so many that the access window in each array
+// grows and DRAM page locality is lost: the knob that matters for a streaming kernel.  Measured on MI355X (medians of three
+// runs over 302 M parameters, replica counts 2 / 4 / 8): the kernels that write the replicas back want few wavefronts --
+// fused 12 / 8 / 8 (12 when w_send aliases w_now), one-pass receive 12 / 8 / 8, merge 16 / 12 / 8 --, the receive side
+// without the merge all / 16 / all (measured again with the arrays in one allocation: 16 cost it 3 % at two replicas), and
+// the send side every wavefront it can get.  A single replica: 16 for the fused kernel and the one-pass receive, no cap
+// otherwise.  The any-M variant (two rows), swept over none, 24, 16, 12, 8, 6 and 4: fewer with more arrays, never below 8
+// (6 costs 15-20 %).  us without a cap -> with it, 105 M parameters: fused M = 3 701 -> 669, 6 1143 -> 1037, 12 2002 -> 1830;
+// one-pass receive 3 656 -> 600, 6 985 -> 879, 12 1657 -> 1476; 67 M parameters: receive side 3 194 -> 182, 12 250 -> 245;
+// merge 3 169 -> 164, 6 316 -> 286, 16 814 -> 724; 53 M parameters, messages written: bf16 M = 2 293 -> 277, 4 459 -> 422,
+// 8 784 -> 733, e3m0 M = 4 386 -> 365.  Formats that run the codec want more of them than those that only round.
+uint32_t waves_per_cu(int mode, uint32_t mt, uint32_t M, int fmt, bool aliased, bool emit)
 {
-    if (mt == 0) return 0u;
-    if (mode == kFused) return mt == 1 ? 10240u : ((aliased || mt == 2) ? 13653u : 20480u);
-    if (mode == kReceive) return mt == 1 ? 10240u : (mt == 2 ? 13653u : 20480u);
-    if (mode == kMerge) return mt == 1 ? 0u : (mt == 2 ? 10240u : (mt == 4 ? 13653u : 20480u));
-    if (mode == kReduce) return mt == 4 ? 10240u : 0u;
-    return 0u;
+    switch (mode) {
+    case kFused:
+        if (emit && is_scaled(fmt)) return M <= 4 ? 16 : 12;
+        if (emit) return M <= 2 ? 16 : (M == 3 ? 12 : 8);
+        if (mt == 0) return M == 3 ? 12 : 8;
+        return mt == 1 ? 16 : ((aliased || mt == 2) ? 12 : 8);
+    case kReceive:
+        if (mt == 0) return M <= 5 ? 12 : 8;
+        return mt == 1 ? 16 : (mt == 2 ? 12 : 8);
+    case kMerge:
+        if (mt == 0) return M == 3 ? 24 : (M == 5 ? 16 : (M <= 7 ? 12 : 8));
+        return mt == 1 ? 0 : (mt == 2 ? 16 : (mt == 4 ? 12 : 8));
+    case kReduce:
+        if (mt == 0) return M <= 9 ? 16 : 24;
+        return mt == 4 ? 16 : 0;
+    default:
+        return 0;
+    }
 }
+
+// The cap takes the form of dynamic LDS that nothing uses: 160 KiB per CU, shared out among the wavefronts.
+uint32_t lds_cap_bytes(uint32_t waves) { return waves ? 163840u / waves : 0u; }
 
 template <int MODE, int FMT, bool ALIASED, bool EMIT>
 hipError_t launch_m(const Args& a, uint32_t n_wg, hipStream_t s)
 {
     const dim3 grid(n_wg), block(kWave);
     const uint32_t mt = variant_mt(MODE, a.M, EMIT);   // the grid was sized for this variant's tile
-    const uint32_t lds = lds_cap_bytes(MODE, mt, ALIASED);
+    const uint32_t lds = lds_cap_bytes(waves_per_cu(MODE, mt, a.M, FMT, ALIASED, EMIT));
     switch (mt) {
     case 1: if constexpr (!EMIT) hipLaunchKernelGGL((sdl_kernel<MODE, FMT, 1, ALIASED, EMIT>), grid, block, lds, s, a); break;
     case 2: if constexpr (!EMIT) hipLaunchKernelGGL((sdl_kernel<MODE, FMT, 2, ALIASED, EMIT>), grid, block, lds, s, a); break;
