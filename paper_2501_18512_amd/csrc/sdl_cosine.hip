@@ -15,13 +15,13 @@
 //                     the end the wavefront folds them with a butterfly of lane exchanges and
 //                     lane 0 writes one partial Gram matrix.  The next tile's loads are issued
 //                     before the current tile is consumed.
-//   sdl_gram_finalize adds the partial matrices of a set in a fixed order (lane-strided, then
-//                     the same butterfly; a set with more than 128 partial matrices in two
-//                     launches, chunks of 64 first) and derives cos and the mean over pairs.
-//                     The same kernel adds the Gram matrices of several sets (fragment from
-//                     spans, unions of fragments).
+//   sdl_gram_pair_kernel  the same for 9 to 12 replicas, two wavefronts with half of the matrix each.
+//   sdl_gram_mfma_kernel  the same for 13 to 16 replicas, on the matrix cores.
+//   sdl_gram_finalize adds the partial matrices of a set in a fixed order (one thread per entry and
+//                     slice of the matrices, then the slices as a tree; a set with many partial matrices in
+//                     two launches) and derives cos and the mean over pairs.  The same kernel adds
+//                     the Gram matrices of several sets (fragment from spans, unions of fragments).
 // No atomics: the order of every sum depends on the sizes alone, so results are reproducible.
-// More than 8 replicas are handled as 8 x 8 blocks of the matrix, one launch per block.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -35,11 +35,13 @@ using namespace sdl_device;
 
 constexpr int kLaneElems = 8;                   // consecutive parameters a lane owns in a tile
 constexpr int kTile = kLaneElems * kWave;       // 512
-constexpr int kBlockM = 8;                      // replicas per side of one launch's block of the matrix
+constexpr int kOneWaveM = 8;                    // most replicas whose whole matrix one lane holds
 constexpr int kMaxSets = 48;                    // parameter sets per launch
 constexpr int kWindows = 48;                    // windows per launch: a set holding a share of 4/48 or more is cut
 constexpr int kMaxPieces = kMaxSets + kWindows;
 constexpr uint32_t kGroups = 8192;              // workgroups per launch, shared out among the sets (32 per compute unit)
+constexpr uint32_t kWideGroups = 4096;          // the same for more than 8 replicas (1024: 15-20 % slower, the last round of
+                                                // workgroups is nearly empty; 8192: up to 5 %, twice the partial matrices)
 constexpr uint32_t kMaxGroups = 8192;           // what the workspace is sized for
 
 
@@ -63,14 +65,13 @@ struct Piece {
 
 struct GramArgs {
     const float* g;
-    const uint16_t* wr[kBlockM];   // replicas of the block's rows
-    const uint16_t* wc[kBlockM];   // replicas of the block's columns (unused for a diagonal block)
+    const uint16_t* w[SDL_MAX_WORKERS];
     double* partial;               // [workgroup of the launch][M*M]
-    uint32_t M;                    // side of the whole matrix
-    uint32_t r0, c0;               // first row / column of this block
+    uint32_t M;                    // side of the matrix
     uint32_t n_pieces;
     Piece pieces[kMaxPieces];
 };
+static_assert(sizeof(GramArgs) <= 4096, "kernel arguments");
 
 // Raw bits of one tile as a lane holds them: 8 fp32 of g, 8 bf16 of each replica.
 template <int NW>
@@ -141,12 +142,10 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// MR x MC block of the Gram matrix; DIAG: rows and columns are the same replicas (upper
-// triangle only, MC == MR).
-template <int MR, int MC, bool DIAG>
+// Up to 8 replicas: every lane holds the whole upper triangle.
+template <int M>
 __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
 {
-    constexpr int NW = DIAG ? MR : MR + MC;
     const uint32_t lane = threadIdx.x;
     uint32_t s = 0;
     while (s + 1 < a.n_pieces && blockIdx.x >= a.pieces[s + 1].first_wg) ++s;
@@ -155,72 +154,316 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
     const bool fast = set.fast != 0u;
     const uint64_t n_tiles = (set.numel + kTile - 1) / kTile;
 
-    const uint16_t* w[NW];
+    const uint16_t* w[M];
 #pragma unroll
-    for (int m = 0; m < MR; ++m) w[m] = a.wr[m];
-    if constexpr (!DIAG) {
-#pragma unroll
-        for (int m = 0; m < MC; ++m) w[MR + m] = a.wc[m];
-    }
+    for (int m = 0; m < M; ++m) w[m] = a.w[m];
 
-    double acc[MR][MC];
+    double acc[M][M];
 #pragma unroll
-    for (int r = 0; r < MR; ++r)
+    for (int r = 0; r < M; ++r)
 #pragma unroll
-        for (int c = 0; c < MC; ++c) acc[r][c] = 0.0;
+        for (int c = 0; c < M; ++c) acc[r][c] = 0.0;
 
     auto valid_of = [&](uint64_t t) -> uint32_t {
         const uint64_t rem = set.numel - t * kTile;
         return rem < (uint64_t)kTile ? (uint32_t)rem : (uint32_t)kTile;
     };
 
-    auto consume = [&](const TileRegs<NW>& t) {
-        float f[NW][kLaneElems];
+    auto consume = [&](const TileRegs<M>& t) {
+        float f[M][kLaneElems];
 #pragma unroll
-        for (int m = 0; m < NW; ++m) deltas(t.g0, t.g1, t.w[m], f[m]);
+        for (int m = 0; m < M; ++m) deltas(t.g0, t.g1, t.w[m], f[m]);
 #pragma unroll
         for (int j = 0; j < kLaneElems; ++j) {
-            double d[NW];
+            double d[M];
 #pragma unroll
-            for (int m = 0; m < NW; ++m) d[m] = (double)f[m][j];
+            for (int m = 0; m < M; ++m) d[m] = (double)f[m][j];
 #pragma unroll
-            for (int r = 0; r < MR; ++r)
+            for (int r = 0; r < M; ++r)
 #pragma unroll
-                for (int c = DIAG ? r : 0; c < MC; ++c)
-                    acc[r][c] = __builtin_fma(d[r], d[DIAG ? c : MR + c], acc[r][c]);
+                for (int c = r; c < M; ++c) acc[r][c] = __builtin_fma(d[r], d[c], acc[r][c]);
         }
     };
 
     // workgroup k's tiles: first, first + step, ... below end; the next tile's loads are issued before the
     // current tile is consumed
     const uint64_t first = k, step = set.G, end = n_tiles;
-    TileRegs<NW> cur;
-    if (first < end) load_tile<NW>(cur, a.g, w, set.offset + first * kTile, valid_of(first), fast, lane);
+    TileRegs<M> cur;
+    if (first < end) load_tile<M>(cur, a.g, w, set.offset + first * kTile, valid_of(first), fast, lane);
     for (uint64_t t = first; t < end; t += step) {
-        TileRegs<NW> nxt = cur;
+        TileRegs<M> nxt = cur;
         const uint64_t tn = t + step;
-        if (tn < end) load_tile<NW>(nxt, a.g, w, set.offset + tn * kTile, valid_of(tn), fast, lane);
+        if (tn < end) load_tile<M>(nxt, a.g, w, set.offset + tn * kTile, valid_of(tn), fast, lane);
         consume(cur);
         cur = nxt;
     }
 
-    double* out = a.partial + (uint64_t)blockIdx.x * a.M * a.M;
+    double* out = a.partial + (uint64_t)blockIdx.x * M * M;
 #pragma unroll
-    for (int r = 0; r < MR; ++r)
+    for (int r = 0; r < M; ++r)
 #pragma unroll
-        for (int c = DIAG ? r : 0; c < MC; ++c) {
+        for (int c = r; c < M; ++c) {
             const double v = wave_sum(acc[r][c]);
-            if (lane == 0) out[(a.r0 + r) * a.M + (a.c0 + c)] = v;
+            if (lane == 0) out[r * M + c] = v;
         }
 }
 
+// 9 to 12 replicas, H = ceil(M / 2) per half.  Bound: 78 fp64 FMAs and 36 other operations per parameter at M = 12, about
+// the time that HBM needs for its 28 bytes, so the matrix has to be formed in one pass.  One lane cannot hold 78 sums, the
+// tile and the next one; the two wavefronts of a workgroup run the same code on the same tiles (the second finds them in L1
+// / L2) and differ in which replicas they call "rows" and "columns":
+//   wavefront 0   rows i = replicas 0..H-1,       columns j = replicas H..2H-1
+//   wavefront 1   rows i = replicas H..2H-1,      columns j = replicas 1, 2, ... H-1, 0
+// Each forms its rows' triangle and, of the block rows x columns, the entries with (j - i) mod H < ceil(H / 2): in the first
+// wavefront's terms the second one forms those with (j - i) mod H >= H - ceil(H / 2), so all are there (for odd H one
+// diagonal twice).  With odd M the replica 2H-1 does not exist: the lanes work on replica 0 in its place and nothing of it
+// is stored.  52.9 M parameters, M = 9 / 10 / 12, whole call: 465 / 511 / 632 us as 8 x 8 blocks in three launches, 306 /
+// 315 / 402 now (the matrix cores: 475).  At 14 two wavefronts of 249 registers on a SIMD no longer cover the loads (494).
+template <int H>
+struct PairTile {
+    f32x4_elem g;
+    u32x2 w[2 * H];
+};
+constexpr int kPairTile = 4 * kWave;      // parameters a wavefront takes at a time
+
+template <int H>
+__device__ __forceinline__ void load_pair_tile(PairTile<H>& t, const float* g, const uint16_t* (&w)[2 * H], uint64_t e0,
+                                               uint64_t left, bool fast, uint32_t lane)
+{
+    if (fast && left >= (uint64_t)kPairTile) {
+        // normal cache policy: the other wavefront reads the same lines
+        t.g = __builtin_bit_cast(f32x4_elem, __builtin_amdgcn_raw_buffer_load_b128(rsrc(g + e0, kPairTile * 4), (int)(lane * 16), 0, 0));
+#pragma unroll
+        for (int m = 0; m < 2 * H; ++m)
+            t.w[m] = __builtin_amdgcn_raw_buffer_load_b64(rsrc(w[m] + e0, kPairTile * 2), (int)(lane * 8), 0, 0);
+    } else if (left >= (uint64_t)kPairTile) {
+        t.g = *reinterpret_cast<const f32x4_elem*>(g + e0 + lane * 4);
+#pragma unroll
+        for (int m = 0; m < 2 * H; ++m) {
+            const u32x2_elem x = *reinterpret_cast<const u32x2_elem*>(w[m] + e0 + lane * 4);
+            t.w[m] = u32x2{x.x, x.y};
+        }
+    } else {
+        // ragged tail: 0 past the end of g and of every replica
+        const uint32_t valid = (uint32_t)left;
+        const __amdgpu_buffer_rsrc_t rg = rsrc(g + e0, valid * 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) t.g[j] = u2f(__builtin_amdgcn_raw_buffer_load_b32(rg, (int)((lane * 4 + j) * 4), 0, 0));
+#pragma unroll
+        for (int m = 0; m < 2 * H; ++m) {
+            const __amdgpu_buffer_rsrc_t rw = rsrc(w[m] + e0, valid * 2);
+            uint32_t h[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                h[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (int)((lane * 4 + j) * 2), 0, 0) & 0xffffu;
+            t.w[m] = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+        }
+    }
+}
+
+template <int H>
+__global__ void __launch_bounds__(2 * kWave, 2) sdl_gram_pair_kernel(const GramArgs a)
+{
+    constexpr int kOff = (H + 1) / 2;     // entries of the block rows x columns per row
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    uint32_t s = 0;
+    while (s + 1 < a.n_pieces && blockIdx.x >= a.pieces[s + 1].first_wg) ++s;
+    const Piece set = a.pieces[s];
+    const bool fast = set.fast != 0u;
+    const uint32_t M = a.M;
+
+    auto row = [&](int i) -> uint32_t { return wave ? (uint32_t)(H + i) : (uint32_t)i; };
+    auto col = [&](int j) -> uint32_t { return wave ? (uint32_t)((j + 1) % H) : (uint32_t)(H + j); };
+    const uint16_t* w[2 * H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        w[i] = a.w[row(i) < M ? row(i) : 0u];
+        w[H + i] = a.w[col(i) < M ? col(i) : 0u];
+    }
+
+    double tri[H][H], off[H][kOff];
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+#pragma unroll
+        for (int j = 0; j < H; ++j) tri[i][j] = 0.0;
+#pragma unroll
+        for (int j = 0; j < kOff; ++j) off[i][j] = 0.0;
+    }
+
+    auto consume = [&](const PairTile<H>& t) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            double d[2 * H];
+#pragma unroll
+            for (int m = 0; m < 2 * H; ++m) {
+                const uint32_t u = t.w[m][e / 2];
+                d[m] = (double)(t.g[e] - u2f((e & 1) ? (u & 0xffff0000u) : (u << 16)));   // one fp32 subtraction
+            }
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+#pragma unroll
+                for (int j = i; j < H; ++j) tri[i][j] = __builtin_fma(d[i], d[j], tri[i][j]);
+#pragma unroll
+                for (int j = 0; j < kOff; ++j) off[i][j] = __builtin_fma(d[i], d[H + (i + j) % H], off[i][j]);
+            }
+        }
+    };
+
+    const uint64_t step = (uint64_t)set.G * kPairTile;
+    uint64_t at = (uint64_t)(blockIdx.x - set.first_wg) * kPairTile;
+    PairTile<H> cur;
+    if (at < set.numel) load_pair_tile<H>(cur, a.g, w, set.offset + at, set.numel - at, fast, lane);
+    for (; at < set.numel; at += step) {
+        PairTile<H> nxt = cur;
+        const uint64_t an = at + step;
+        if (an < set.numel) load_pair_tile<H>(nxt, a.g, w, set.offset + an, set.numel - an, fast, lane);
+        __builtin_amdgcn_sched_barrier(0);   // the loads stay ahead of the arithmetic
+        consume(cur);
+        cur = nxt;
+    }
+
+    double* out = a.partial + (uint64_t)blockIdx.x * M * M;
+    auto store = [&](uint32_t x, uint32_t y, double v) {
+        v = wave_sum(v);
+        if (lane == 0 && x < M && y < M) out[x < y ? x * M + y : y * M + x] = v;
+    };
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+#pragma unroll
+        for (int j = i; j < H; ++j) store(row(i), row(j), tri[i][j]);
+#pragma unroll
+        for (int j = 0; j < kOff; ++j)
+            if (!(H % 2 == 1 && j == kOff - 1 && wave == 1u))    // the diagonal that both formed: once is enough
+                store(row(i), col((i + j) % H), off[i][j]);
+    }
+}
+
+// 13 to 16 replicas: the matrix cores form the whole matrix, v_mfma_f64_16x16x4_f64 taking four parameters of up to 16
+// replicas at a time.  Lane l holds replica l % 16's value of parameter l / 16, which is the instruction's layout of the left
+// operand and of the right one alike.  Bound: the matrix pipe, 256 fp64 FMAs per parameter (half of them for the lower
+// triangle; rows behind the last replica repeat replica 0 and are not stored): 52.9 M parameters at the 77 TFLOP/s that a
+// chain of this instruction reaches take 350 us, HBM 268 us at 16 replicas; the loads alone take 370 us in this layout, the
+// arithmetic alone 395.  Whole call at 13 / 16 replicas: 698 / 935 us as 8 x 8 blocks in three launches, 488 / 503 now.
+// A load covers 64 bytes of 16 arrays; the chunk of 64 parameters that a wavefront takes at a time is a whole line of each.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kMfmaWaves = 4;             // wavefronts per workgroup, which adds their matrices up before it writes one
+constexpr int kMfmaChunk = 64;            // parameters: 16 per lane, as two pieces of 8
+
+struct MfmaChunk {
+    u32x4 g[2][2], w[2];
+};
+
+// g and w: the lane's first parameter of the chunk (w in the lane's replica).
+__device__ __forceinline__ void load_chunk(MfmaChunk& c, const float* g, const uint16_t* w)
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const u32x4_f32elem* pg = reinterpret_cast<const u32x4_f32elem*>(g + 32 * h);
+        c.g[h][0] = pg[0];
+        c.g[h][1] = pg[1];
+        c.w[h] = *reinterpret_cast<const u32x4_bf16elem*>(w + 32 * h);
+    }
+}
+
+__device__ __forceinline__ f64x4 chunk_sums(const MfmaChunk& c)
+{
+    f64x4 acc = {};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        float f[kLaneElems];
+        deltas(c.g[h][0], c.g[h][1], c.w[h], f);
+#pragma unroll
+        for (int j = 0; j < kLaneElems; ++j) {
+            const double d = (double)f[j];
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(d, d, acc, 0, 0, 0);
+        }
+    }
+    return acc;
+}
+
+// (four wavefronts per SIMD: the compiler's own choice of registers leaves two, 540 us against 503)
+__global__ void __launch_bounds__(kMfmaWaves * kWave) __attribute__((amdgpu_waves_per_eu(4)))
+sdl_gram_mfma_kernel(const GramArgs a)
+{
+    __shared__ double mats[kMfmaWaves][16 * 16];
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    uint32_t s = 0;
+    while (s + 1 < a.n_pieces && blockIdx.x >= a.pieces[s + 1].first_wg) ++s;
+    const Piece set = a.pieces[s];
+    const uint32_t M = a.M, replica = lane % 16, quarter = lane / 16;
+    const float* g = a.g + set.offset + quarter * kLaneElems;
+    const uint16_t* w = a.w[replica < M ? replica : 0u] + set.offset + quarter * kLaneElems;
+
+    // The instruction rounds its sums towards zero, so chains are kept to the sixteen of one chunk, whose sums are added to
+    // the total by plain additions while the next chunk's instructions run.  In one chain over all tiles the error against
+    // exact sums is 1.4e-15 to 5e-15 of the matrix, with chains of 64 2e-16 to 9e-16, like this 2e-16 to 3e-16, as with
+    // plain FMAs.
+    f64x4 last = {}, total = {};
+    const uint64_t n_whole = set.numel / kTile, step = (uint64_t)set.G * kMfmaWaves;
+    uint64_t t = (uint64_t)wave * set.G + (blockIdx.x - set.first_wg);
+    MfmaChunk c[2];
+    if (t < n_whole) load_chunk(c[0], g + t * kTile, w + t * kTile);
+    for (; t < n_whole; t += step) {
+#pragma unroll
+        for (int k = 0; k < kTile / kMfmaChunk; ++k) {
+            // the next chunk's loads go out before this one is consumed, and stay there (the compiler would move each down
+            // to its first use)
+            if (k + 1 < kTile / kMfmaChunk) {
+                const uint64_t e = t * kTile + (k + 1) * kMfmaChunk;
+                load_chunk(c[(k + 1) % 2], g + e, w + e);
+            } else if (t + step < n_whole) {
+                load_chunk(c[0], g + (t + step) * kTile, w + (t + step) * kTile);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            const f64x4 sums = chunk_sums(c[k % 2]);
+            __builtin_amdgcn_sched_barrier(0);
+            total += last;
+            last = sums;
+        }
+    }
+    if (t == n_whole && t * kTile < set.numel) {
+        // ragged tail: g = 0 and w = 0 past the end give an outer gradient of 0
+        const uint32_t left = (uint32_t)(set.numel - t * kTile);
+        for (uint32_t at = 0; at < left; at += kMfmaChunk) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < kLaneElems; ++j) {
+                    const bool there = at + 32 * h + quarter * kLaneElems + j < left;
+                    const uint64_t e = t * kTile + at + 32 * h + j;
+                    c[0].g[h][j / 4][j % 4] = there ? f2u(g[e]) : 0u;
+                    const uint32_t x = there ? (uint32_t)w[e] : 0u;
+                    c[0].w[h][j / 2] = j % 2 ? c[0].w[h][j / 2] | (x << 16) : x;
+                }
+            total += chunk_sums(c[0]);
+        }
+    }
+    total += last;
+    // register i of lane l: row 4 i + l / 16, column l % 16
+#pragma unroll
+    for (int i = 0; i < 4; ++i) mats[wave][(4 * i + quarter) * 16 + replica] = total[i];
+    __syncthreads();
+    static_assert(kMfmaWaves * kWave == 16 * 16, "one thread per entry");
+    const uint32_t row = threadIdx.x / 16, col = threadIdx.x % 16;
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < kMfmaWaves; ++k) v += mats[k][threadIdx.x];
+    if (row <= col && col < M) a.partial[(uint64_t)blockIdx.x * M * M + row * M + col] = v;
+}
+
 // What each output of the finalize kernel adds up.
-constexpr uint32_t kFinChunk = 64;                                        // matrices one first-level output adds
-constexpr int kMaxFin = kMaxGroups / kFinChunk + 2 * kMaxSets + 2;        // outputs per finalize launch
+constexpr uint32_t kFinThreads = 1024;
+constexpr int kMaxFin = kMaxGroups / 64 + 2 * kMaxSets + 2;               // outputs per finalize launch
+
+// Matrices that one first-level output adds: 8 for each of the threads that share an entry.
+uint32_t fin_chunk(uint32_t M) { return 8u * (kFinThreads / (M * (M + 1u) / 2u)); }
 
 struct FinArgs {
     const double* in;              // matrices of M*M doubles (only a <= b is read), stride_k doubles apart
     double* out;                   // output o at out + o * out_stride
+    double* last_out;              // if not null, where the last output goes instead
     uint64_t stride_k;
     uint64_t out_stride;
     uint32_t M;
@@ -229,31 +472,46 @@ struct FinArgs {
     uint32_t count[kMaxFin];
 };
 
-// One workgroup per output.  A lane adds every 64th matrix of its output's range, so a range
-// should be short: long ranges go through a first level of kFinChunk matrices per output.
-__global__ void __launch_bounds__(256) sdl_gram_finalize(const FinArgs f)
+// One workgroup per output.  A thread adds every S-th matrix's value of one entry a <= b (neighbouring threads read
+// neighbouring entries), then the S sums of an entry are added as a tree.  Latency bound: a range should give a thread a
+// handful of matrices, so long ranges go through a first level of fin_chunk matrices per output.  (One wavefront per entry
+// and a butterfly of lane exchanges took 5 us at 4 replicas and 25 us at 16, entry after entry.)
+__global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f)
 {
     __shared__ double G[SDL_MAX_WORKERS * SDL_MAX_WORKERS];
     __shared__ double C[SDL_MAX_WORKERS * SDL_MAX_WORKERS];
-    const uint32_t M = f.M, count = f.count[blockIdx.x];
+    __shared__ double part[kFinThreads];
+    const uint32_t M = f.M, count = f.count[blockIdx.x], entries = M * (M + 1u) / 2u, S = kFinThreads / entries;
     const double* base = f.in + (uint64_t)f.first[blockIdx.x] * f.stride_k;
-    const uint32_t wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    uint32_t pair = 0;
-    for (uint32_t a = 0; a < M; ++a)
-        for (uint32_t b = a; b < M; ++b, ++pair) {
-            if (pair % 4u != wave) continue;
-            double s = 0.0;
-            for (uint32_t k = lane; k < count; k += kWave) s += base[(uint64_t)k * f.stride_k + a * M + b];
-            s = wave_sum(s);
-            if (lane == 0) { G[a * M + b] = s; G[b * M + a] = s; }
-        }
+    const uint32_t entry = threadIdx.x % entries, slice = threadIdx.x / entries;
+    uint32_t a = 0, b = entry;             // entry number -> (a, b), row by row of the upper triangle
+    while (b >= M - a) { b -= M - a; ++a; }
+    b += a;
+    if (slice < S) {
+        double s = 0.0;
+#pragma unroll 8
+        for (uint32_t k = slice; k < count; k += S) s += base[(uint64_t)k * f.stride_k + a * M + b];
+        part[threadIdx.x] = s;
+    }
     __syncthreads();
-    double* o = f.out + (uint64_t)blockIdx.x * f.out_stride;
+    // the slices, pair by pair (a sum in sequence would lose a digit that the partial matrices still have)
+    for (uint32_t n = S; n > 1u;) {
+        const uint32_t half = (n + 1u) / 2u;
+        if (slice + half < n) part[threadIdx.x] += part[threadIdx.x + half * entries];
+        n = half;
+        __syncthreads();
+    }
+    if (threadIdx.x < entries) {
+        G[a * M + b] = part[threadIdx.x];
+        G[b * M + a] = part[threadIdx.x];
+    }
+    __syncthreads();
+    double* o = f.last_out && blockIdx.x + 1u == gridDim.x ? f.last_out : f.out + (uint64_t)blockIdx.x * f.out_stride;
     if (!f.emit) {
-        for (uint32_t i = threadIdx.x; i < M * M; i += 256) o[i] = G[i];
+        for (uint32_t i = threadIdx.x; i < M * M; i += kFinThreads) o[i] = G[i];
         return;
     }
-    for (uint32_t i = threadIdx.x; i < M * M; i += 256) {
+    for (uint32_t i = threadIdx.x; i < M * M; i += kFinThreads) {
         const uint32_t a = i / M, b = i % M;
         const double den = __builtin_sqrt(G[a * M + a]) * __builtin_sqrt(G[b * M + b]);
         const double c = den > 0.0 ? G[i] / den : 0.0;
@@ -273,45 +531,26 @@ __global__ void __launch_bounds__(256) sdl_gram_finalize(const FinArgs f)
 
 // ------------------------------------------------------------------ host side
 
-uint32_t windows_per_launch() { return kWindows; }
-uint32_t groups_per_launch() { return kGroups; }
-
-template <int MR, bool DIAG>
-int launch_block_c(int mc, const GramArgs& a, hipStream_t st)
+int launch_kernel(uint32_t M, const GramArgs& a, hipStream_t st)
 {
-    const dim3 grid(a.pieces[a.n_pieces - 1].first_wg + a.pieces[a.n_pieces - 1].G), block(kWave);
-    if constexpr (DIAG) {
-        hipLaunchKernelGGL((sdl_gram_kernel<MR, MR, true>), grid, block, 0, st, a);
-    } else {
-        switch (mc) {
-        case 1: hipLaunchKernelGGL((sdl_gram_kernel<MR, 1, false>), grid, block, 0, st, a); break;
-        case 2: hipLaunchKernelGGL((sdl_gram_kernel<MR, 2, false>), grid, block, 0, st, a); break;
-        case 3: hipLaunchKernelGGL((sdl_gram_kernel<MR, 3, false>), grid, block, 0, st, a); break;
-        case 4: hipLaunchKernelGGL((sdl_gram_kernel<MR, 4, false>), grid, block, 0, st, a); break;
-        case 5: hipLaunchKernelGGL((sdl_gram_kernel<MR, 5, false>), grid, block, 0, st, a); break;
-        case 6: hipLaunchKernelGGL((sdl_gram_kernel<MR, 6, false>), grid, block, 0, st, a); break;
-        case 7: hipLaunchKernelGGL((sdl_gram_kernel<MR, 7, false>), grid, block, 0, st, a); break;
-        case 8: hipLaunchKernelGGL((sdl_gram_kernel<MR, 8, false>), grid, block, 0, st, a); break;
-        default: return SDL_ERR_INVALID_ARG;
-        }
+    const dim3 grid(a.pieces[a.n_pieces - 1].first_wg + a.pieces[a.n_pieces - 1].G), one(kWave);
+    switch (M) {
+    case 1: hipLaunchKernelGGL((sdl_gram_kernel<1>), grid, one, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((sdl_gram_kernel<2>), grid, one, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((sdl_gram_kernel<3>), grid, one, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((sdl_gram_kernel<4>), grid, one, 0, st, a); break;
+    case 5: hipLaunchKernelGGL((sdl_gram_kernel<5>), grid, one, 0, st, a); break;
+    case 6: hipLaunchKernelGGL((sdl_gram_kernel<6>), grid, one, 0, st, a); break;
+    case 7: hipLaunchKernelGGL((sdl_gram_kernel<7>), grid, one, 0, st, a); break;
+    case 8: hipLaunchKernelGGL((sdl_gram_kernel<8>), grid, one, 0, st, a); break;
+    case 9: case 10: hipLaunchKernelGGL((sdl_gram_pair_kernel<5>), grid, dim3(2 * kWave), 0, st, a); break;
+    case 11: case 12: hipLaunchKernelGGL((sdl_gram_pair_kernel<6>), grid, dim3(2 * kWave), 0, st, a); break;
+    default: hipLaunchKernelGGL(sdl_gram_mfma_kernel, grid, dim3(kMfmaWaves * kWave), 0, st, a); break;
     }
     return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
 }
 
-int launch_diag(int m, const GramArgs& a, hipStream_t st)
-{
-    switch (m) {
-    case 1: return launch_block_c<1, true>(1, a, st);
-    case 2: return launch_block_c<2, true>(2, a, st);
-    case 3: return launch_block_c<3, true>(3, a, st);
-    case 4: return launch_block_c<4, true>(4, a, st);
-    case 5: return launch_block_c<5, true>(5, a, st);
-    case 6: return launch_block_c<6, true>(6, a, st);
-    case 7: return launch_block_c<7, true>(7, a, st);
-    case 8: return launch_block_c<8, true>(8, a, st);
-    default: return SDL_ERR_INVALID_ARG;
-    }
-}
+uint32_t groups_per_launch(uint32_t M) { return M > (uint32_t)kOneWaveM ? kWideGroups : kGroups; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -344,7 +583,7 @@ int launch_gram(const float* g, const void* const* w, uint32_t M, const Set* set
     a.partial = partial;
     a.M = M;
     // cut the sets into windows: about `windows` pieces per launch, shared out like the workgroups
-    const uint32_t windows = windows_per_launch();
+    const uint32_t windows = kWindows;
     uint64_t total_G = 0;
     for (uint32_t s = 0; s < n_sets; ++s) total_G += sets[s].G;
     for (uint32_t s = 0; s < n_sets; ++s) {
@@ -372,71 +611,64 @@ int launch_gram(const float* g, const void* const* w, uint32_t M, const Set* set
             pc.fast = fast ? 1u : 0u;
         }
     }
-    // the matrix in blocks of up to 8 x 8 replicas: diagonal blocks, then the blocks above them
-    for (uint32_t r0 = 0; r0 < M; r0 += kBlockM) {
-        const uint32_t mr = M - r0 < (uint32_t)kBlockM ? M - r0 : (uint32_t)kBlockM;
-        for (uint32_t c0 = r0; c0 < M; c0 += kBlockM) {
-            const uint32_t mc = M - c0 < (uint32_t)kBlockM ? M - c0 : (uint32_t)kBlockM;
-            a.r0 = r0;
-            a.c0 = c0;
-            for (uint32_t m = 0; m < mr; ++m) a.wr[m] = static_cast<const uint16_t*>(w[r0 + m]);
-            for (uint32_t m = 0; m < mc; ++m) a.wc[m] = static_cast<const uint16_t*>(w[c0 + m]);
-            int rc;
-            if (c0 == r0) rc = launch_diag((int)mr, a, st);
-            else rc = launch_block_c<kBlockM, false>((int)mc, a, st);   // rows of an off-diagonal block are always full
-            if (rc != SDL_OK) return rc;
-        }
-    }
-    return SDL_OK;
+    for (uint32_t m = 0; m < M; ++m) a.w[m] = static_cast<const uint16_t*>(w[m]);
+    return launch_kernel(M, a, st);
 }
 
 int launch_finalize(const FinArgs& f, uint32_t n_out, hipStream_t st)
 {
-    hipLaunchKernelGGL(sdl_gram_finalize, dim3(n_out), dim3(256), 0, st, f);
+    hipLaunchKernelGGL(sdl_gram_finalize, dim3(n_out), dim3(kFinThreads), 0, st, f);
     return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
 }
 
-// One result per set from the partial matrices of its workgroups.  Sets with many workgroups
-// are first added up in chunks of kFinChunk matrices (into tmp), so that no lane of the
-// finalize kernel walks a long range.
-int finalize_sets(const double* partial, const Set* sets, uint32_t n_sets, uint32_t M, double* out, double* tmp,
-                  hipStream_t st)
+// One result per set from the partial matrices of its workgroups (the sets' workgroups lie one behind the other) and, if
+// union_out is not null, the result of all of them together.  Sets with many workgroups are first added up in chunks (into
+// tmp), so that no thread of the finalize kernel walks a long range.
+int finalize_sets(const double* partial, const Set* sets, uint32_t n_sets, uint32_t M, double* out, double* union_out,
+                  double* tmp, hipStream_t st)
 {
     const uint64_t mm = (uint64_t)M * M;
+    const uint32_t chunk = fin_chunk(M);
+    uint32_t total = 0;
     bool two_level = false;
-    for (uint32_t s = 0; s < n_sets; ++s) two_level = two_level || sets[s].G > 2 * kFinChunk;
+    for (uint32_t s = 0; s < n_sets; ++s) {
+        two_level = two_level || sets[s].G > 2 * chunk;
+        total += sets[s].G;
+    }
+    two_level = two_level || (union_out && total > 2 * chunk);
     FinArgs last{};
     last.out = out;
+    last.last_out = union_out;
     last.stride_k = mm;
     last.out_stride = SDL_COSINE_RESULT_DOUBLES(M);
     last.M = M;
     last.emit = 1;
-    if (!two_level) {
-        last.in = partial;
-        for (uint32_t s = 0; s < n_sets; ++s) { last.first[s] = sets[s].first_wg; last.count[s] = sets[s].G; }
-        return launch_finalize(last, n_sets, st);
-    }
-    FinArgs lvl1{};
-    lvl1.in = partial;
-    lvl1.out = tmp;
-    lvl1.stride_k = mm;
-    lvl1.out_stride = mm;
-    lvl1.M = M;
-    lvl1.emit = 0;
-    uint32_t n = 0;
-    for (uint32_t s = 0; s < n_sets; ++s) {
-        last.first[s] = n;
-        for (uint32_t c = 0; c < sets[s].G; c += kFinChunk) {
-            lvl1.first[n] = sets[s].first_wg + c;
-            lvl1.count[n] = sets[s].G - c < kFinChunk ? sets[s].G - c : kFinChunk;
-            ++n;
+    last.in = partial;
+    for (uint32_t s = 0; s < n_sets; ++s) { last.first[s] = sets[s].first_wg; last.count[s] = sets[s].G; }
+    if (two_level) {
+        FinArgs lvl1{};
+        lvl1.in = partial;
+        lvl1.out = tmp;
+        lvl1.stride_k = mm;
+        lvl1.out_stride = mm;
+        lvl1.M = M;
+        uint32_t n = 0;
+        for (uint32_t s = 0; s < n_sets; ++s) {
+            last.first[s] = n;
+            for (uint32_t c = 0; c < sets[s].G; c += chunk) {
+                lvl1.first[n] = sets[s].first_wg + c;
+                lvl1.count[n] = sets[s].G - c < chunk ? sets[s].G - c : chunk;
+                ++n;
+            }
+            last.count[s] = n - last.first[s];
         }
-        last.count[s] = n - last.first[s];
+        const int rc = launch_finalize(lvl1, n, st);
+        if (rc != SDL_OK) return rc;
+        last.in = tmp;
+        total = n;
     }
-    int rc = launch_finalize(lvl1, n, st);
-    if (rc != SDL_OK) return rc;
-    last.in = tmp;
-    return launch_finalize(last, n_sets, st);
+    if (union_out) { last.first[n_sets] = last.first[0]; last.count[n_sets] = total; }
+    return launch_finalize(last, n_sets + (union_out ? 1u : 0u), st);
 }
 
 // One result from the Gram matrices of `count` results that lie stride doubles apart.
@@ -465,7 +697,7 @@ size_t partial_mats(size_t n_sets)
 size_t tmp_mats(size_t n_sets)
 {
     const size_t launches = (n_sets + kMaxSets - 1) / kMaxSets;
-    return launches * (kMaxGroups / kFinChunk + 2) + 2 * n_sets;
+    return launches * (kMaxGroups / 64 + 2) + 2 * n_sets;
 }
 
 int check_common(const void* g, const void* const* w, uint32_t M, const void* workspace)
@@ -498,12 +730,12 @@ int sdl_outer_grad_cosine(const float* g, const void* const* w, uint32_t M, uint
     if (workspace_bytes < sdl_cosine_workspace_bytes(M, 1)) return SDL_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     Set set{0, numel, 0, 0};
-    share_groups(&set, 1, groups_per_launch());
+    share_groups(&set, 1, groups_per_launch(M));
     double* partial = static_cast<double*>(workspace);
     double* tmp = partial + partial_mats(1) * M * M;
     rc = launch_gram(g, w, M, &set, 1, partial, st);
     if (rc != SDL_OK) return rc;
-    return finalize_sets(partial, &set, 1, M, result, tmp, st);
+    return finalize_sets(partial, &set, 1, M, result, nullptr, tmp, st);
 }
 
 int sdl_outer_grad_cosine_plan(const sdl_plan_t* plan, uint32_t p, const float* g_base, const void* const* w_base,
@@ -521,7 +753,7 @@ int sdl_outer_grad_cosine_plan(const sdl_plan_t* plan, uint32_t p, const float* 
     if (rc != SDL_OK) return rc;
     if (workspace_bytes < sdl_cosine_workspace_bytes(M, n_spans)) return SDL_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const uint32_t groups = groups_per_launch();
+    const uint32_t groups = groups_per_launch(M);
     const uint64_t mm = (uint64_t)M * M, R = SDL_COSINE_RESULT_DOUBLES(M);
     double* partial = static_cast<double*>(workspace);
     double* tmp = partial + partial_mats(n_spans) * mm;
@@ -535,11 +767,14 @@ int sdl_outer_grad_cosine_plan(const sdl_plan_t* plan, uint32_t p, const float* 
         double* part = partial + used * mm;
         rc = launch_gram(g_base, w_base, M, sets, ns, part, st);
         if (rc != SDL_OK) return rc;
-        rc = finalize_sets(part, sets, ns, M, per_span + (uint64_t)s0 * R, tmp + used_tmp * mm, st);
+        // the spans of one launch give the fragment's result as well
+        rc = finalize_sets(part, sets, ns, M, per_span + (uint64_t)s0 * R, ns == n_spans ? fragment_result : nullptr,
+                           tmp + used_tmp * mm, st);
         if (rc != SDL_OK) return rc;
         used += n_wg;
-        used_tmp += n_wg / kFinChunk + ns;
+        used_tmp += n_wg / fin_chunk(M) + ns;
     }
+    if (n_spans && n_spans <= (uint32_t)kMaxSets) return SDL_OK;
     // the fragment: Gram matrices of its spans added in span order
     return finalize_union(per_span, R, n_spans, M, fragment_result, st);
 }
