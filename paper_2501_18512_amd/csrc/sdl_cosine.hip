@@ -457,8 +457,14 @@ sdl_gram_mfma_kernel(const GramArgs a)
 constexpr uint32_t kFinThreads = 1024;
 constexpr int kMaxFin = kMaxGroups / 64 + 2 * kMaxSets + 2;               // outputs per finalize launch
 
-// Matrices that one first-level output adds: 8 for each of the threads that share an entry.
-uint32_t fin_chunk(uint32_t M) { return 8u * (kFinThreads / (M * (M + 1u) / 2u)); }
+// Threads that share an entry (beyond 64 the tree over them costs more than it saves), and the matrices that one first-level
+// output adds: 8 for each of them.
+__host__ __device__ inline uint32_t fin_slices(uint32_t M)
+{
+    const uint32_t s = kFinThreads / (M * (M + 1u) / 2u);
+    return s < 64u ? s : 64u;
+}
+uint32_t fin_chunk(uint32_t M) { return 8u * fin_slices(M); }
 
 struct FinArgs {
     const double* in;              // matrices of M*M doubles (only a <= b is read), stride_k doubles apart
@@ -481,7 +487,7 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
     __shared__ double G[SDL_MAX_WORKERS * SDL_MAX_WORKERS];
     __shared__ double C[SDL_MAX_WORKERS * SDL_MAX_WORKERS];
     __shared__ double part[kFinThreads];
-    const uint32_t M = f.M, count = f.count[blockIdx.x], entries = M * (M + 1u) / 2u, S = kFinThreads / entries;
+    const uint32_t M = f.M, count = f.count[blockIdx.x], entries = M * (M + 1u) / 2u, S = fin_slices(M);
     const double* base = f.in + (uint64_t)f.first[blockIdx.x] * f.stride_k;
     const uint32_t entry = threadIdx.x % entries, slice = threadIdx.x / entries;
     uint32_t a = 0, b = entry;             // entry number -> (a, b), row by row of the upper triangle
