@@ -943,8 +943,8 @@ void sdl_kernel(const Args a)
 // Pre-pass of the whole-span scale: the absolute maximum of every replica's outer gradient over
 // each run, folded into the run's scale word with an integer atomic maximum (the words hold fp32
 // bit patterns of non-negative values, which order like the values).  It has an argument block of
-// its own, so that one launch covers up to 64 runs (a whole fragment as a rule).  A fixed number of
-// wavefronts is shared out among the runs; wavefront k of a run walks the run's tiles k, k + G, ...
+// its own, so that one launch covers up to 64 runs (a whole fragment as a rule).  The
+// wavefronts are shared out among the runs; wavefront k of a run walks the run's tiles k, k + G, ...
 // with 8 consecutive parameters per lane (128-bit loads, the next tile's loads issued before the
 // current tile is consumed), keeps the running maxima in registers, and the scale words are touched
 // once at the very end -- one atomic per workgroup (4 wavefronts) and replica instead of one per
@@ -972,8 +972,11 @@ struct AbsmaxArgs {
     uint32_t m0;         // first replica handled by this launch
     uint32_t staged;
     uint32_t n_runs;
+    uint32_t look;       // a long launch: workgroups look at a word before the atomic on it
+    uint32_t first[kAbsmaxMaxRuns];   // first workgroup of each run, ascending; 0xffffffff behind the last
     AbsmaxRun runs[kAbsmaxMaxRuns];
 };
+static_assert(sizeof(AbsmaxArgs) <= 4096, "kernel arguments");
 
 template <int MB>
 struct AbsmaxTile {
@@ -981,27 +984,29 @@ struct AbsmaxTile {
     u32x4 w[MB];
 };
 
-template <int MB>
+template <int MB, bool KEEP>
 __device__ __forceinline__ void absmax_load(AbsmaxTile<MB>& t, const AbsmaxArgs& a, uint64_t ge, uint64_t we,
                                             uint32_t valid, bool fast, uint32_t lane)
 {
+    constexpr int kAux = KEEP ? 0 : kAuxLoad;
     if (fast && valid == (uint32_t)kAbsmaxTile) {
         const __amdgpu_buffer_rsrc_t rg = rsrc(a.g + ge, kAbsmaxTile * 4);
-        t.g0 = __builtin_amdgcn_raw_buffer_load_b128(rg, (int)(lane * 32), 0, kAuxLoad);
-        t.g1 = __builtin_amdgcn_raw_buffer_load_b128(rg, (int)(lane * 32 + 16), 0, kAuxLoad);
+        t.g0 = __builtin_amdgcn_raw_buffer_load_b128(rg, (int)(lane * 32), 0, kAux);
+        t.g1 = __builtin_amdgcn_raw_buffer_load_b128(rg, (int)(lane * 32 + 16), 0, kAux);
 #pragma unroll
         for (int m = 0; m < MB; ++m)
             t.w[m] = __builtin_amdgcn_raw_buffer_load_b128(rsrc(a.w_send[a.m0 + m] + we, kAbsmaxTile * 2),
-                                                           (int)(lane * 16), 0, kAuxLoad);
+                                                           (int)(lane * 16), 0, kAux);
     } else if (valid == (uint32_t)kAbsmaxTile) {
         // a whole tile of a run that starts at some other element: vectors of element alignment
         const u32x4_f32elem* pg = reinterpret_cast<const u32x4_f32elem*>(a.g + ge + lane * 8);
-        t.g0 = __builtin_nontemporal_load(pg);
-        t.g1 = __builtin_nontemporal_load(pg + 1);
+        t.g0 = KEEP ? pg[0] : __builtin_nontemporal_load(pg);
+        t.g1 = KEEP ? pg[1] : __builtin_nontemporal_load(pg + 1);
 #pragma unroll
-        for (int m = 0; m < MB; ++m)
-            t.w[m] = __builtin_nontemporal_load(
-                reinterpret_cast<const u32x4_bf16elem*>(a.w_send[a.m0 + m] + we + lane * 8));
+        for (int m = 0; m < MB; ++m) {
+            const u32x4_bf16elem* pw = reinterpret_cast<const u32x4_bf16elem*>(a.w_send[a.m0 + m] + we + lane * 8);
+            t.w[m] = KEEP ? *pw : __builtin_nontemporal_load(pw);
+        }
     } else {
         // ragged tail: element by element under the buffer range check, which returns 0 past the
         // end (g = 0 and w = 0 give an outer gradient of 0: no effect on a maximum)
@@ -1023,7 +1028,8 @@ __device__ __forceinline__ void absmax_load(AbsmaxTile<MB>& t, const AbsmaxArgs&
     }
 }
 
-template <int MB>
+// KEEP: normal cache policy, where the fused pass behind this one finds some of g and w_send in the memory-side cache.
+template <int MB, bool KEEP>
 __global__ __launch_bounds__(kWave * kAbsmaxWaves) void sdl_span_absmax_kernel(const AbsmaxArgs a)
 {
     __shared__ uint32_t wave_max[kAbsmaxWaves][MB];
@@ -1032,8 +1038,9 @@ __global__ __launch_bounds__(kWave * kAbsmaxWaves) void sdl_span_absmax_kernel(c
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     uint32_t r = 0;
-    for (uint32_t i = 1; i < a.n_runs; ++i)
-        if (blockIdx.x >= a.runs[i].first) r = i;
+#pragma unroll
+    for (int i = 1; i < kAbsmaxMaxRuns; ++i)       // four scalar loads, compared at once
+        if (blockIdx.x >= a.first[i]) r = (uint32_t)i;
     const AbsmaxRun run = a.runs[r];
     // every wavefront of the run's workgroups walks its own tiles: k, k + G, ...; neighbouring
     // tiles go to neighbouring workgroups (which the dispatcher deals to different XCDs), not to
@@ -1047,16 +1054,17 @@ __global__ __launch_bounds__(kWave * kAbsmaxWaves) void sdl_span_absmax_kernel(c
     };
     auto g_elem = [&](uint64_t t) -> uint64_t { return (a.staged ? run.soff : run.offset) + t * kAbsmaxTile; };
 
+    auto word = [&](uint32_t m) { return reinterpret_cast<uint32_t*>(a.scales[a.m0 + m]) + run.sidx; };
     uint32_t amax[MB];
 #pragma unroll
     for (int m = 0; m < MB; ++m) amax[m] = 0u;
 
     AbsmaxTile<MB> cur;
-    if (k < n_tiles) absmax_load<MB>(cur, a, g_elem(k), run.offset + (uint64_t)k * kAbsmaxTile, valid_of(k), fast, lane);
+    if (k < n_tiles) absmax_load<MB, KEEP>(cur, a, g_elem(k), run.offset + (uint64_t)k * kAbsmaxTile, valid_of(k), fast, lane);
     for (uint64_t t = k; t < n_tiles; t += G) {
         AbsmaxTile<MB> nxt = cur;
         const uint64_t tn = t + G;
-        if (tn < n_tiles) absmax_load<MB>(nxt, a, g_elem(tn), run.offset + tn * kAbsmaxTile, valid_of(tn), fast, lane);
+        if (tn < n_tiles) absmax_load<MB, KEEP>(nxt, a, g_elem(tn), run.offset + tn * kAbsmaxTile, valid_of(tn), fast, lane);
         const uint32_t gb[8] = {cur.g0.x, cur.g0.y, cur.g0.z, cur.g0.w, cur.g1.x, cur.g1.y, cur.g1.z, cur.g1.w};
 #pragma unroll
         for (int m = 0; m < MB; ++m) {
@@ -1081,11 +1089,13 @@ __global__ __launch_bounds__(kWave * kAbsmaxWaves) void sdl_span_absmax_kernel(c
     if (threadIdx.x < (uint32_t)MB) {
         uint32_t v = 0u;
         for (int w = 0; w < kAbsmaxWaves; ++w) v = wave_max[w][threadIdx.x] > v ? wave_max[w][threadIdx.x] : v;
-        // look before the atomic: reads of one cache line are served in parallel, atomics on it one
-        // after the other, and by the time most workgroups finish the word already holds a larger value
-        uint32_t* word = reinterpret_cast<uint32_t*>(a.scales[a.m0 + threadIdx.x]) + run.sidx;
-        if (v > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            __hip_atomic_fetch_max(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // A look at the word first spares the atomic where the word already holds more, but it is itself served one after
+        // the other, at memory that every XCD shares, and finds nothing while all workgroups end at once.  It pays only in
+        // long launches, whose workgroups drift apart (28 M parameters, M = 2, 2048 workgroups: the whole call 197 us with
+        // it, 167 without; 53 M 328 and 316; 302 M, M = 4, 2532 and 2539).
+        uint32_t* const to = word(threadIdx.x);
+        if (!a.look || v > __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            __hip_atomic_fetch_max(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -1209,9 +1219,31 @@ hipError_t launch_f(const Args& a, uint32_t n_wg, hipStream_t s)
 }
 
 // Whole-span scale words of a list of runs: cleared, then the maximum of every replica's outer
-// gradient over each run.  kAbsmaxGroups wavefronts per launch are shared out among the runs in
-// proportion to their tiles (whole workgroups, at least one each); up to 8 replicas per pass over g.
-constexpr uint32_t kAbsmaxGroups = 8192;
+// gradient over each run.  A launch's wavefronts are shared out among the runs in proportion to their tiles (whole
+// workgroups, at least one each); up to 8 replicas per pass over g.  One wavefront for 16 tiles, 1024 to 8192 of them: the
+// atomics at the end cost 8 ns for each workgroup and replica whatever the size (28 M parameters, M = 2: 160 us the whole
+// call, 167 with 8192; 8 M parameters 50 and 60; 302 M the same).
+constexpr uint32_t kAbsmaxMinGroups = 1024, kAbsmaxGroups = 8192, kAbsmaxTilesPerWave = 16;
+
+// What the pre-pass reads stays in the 256 MiB memory-side cache for the pass behind it if it fits there (28 M parameters,
+// 227 MB: the whole call 170 us with the normal cache policy, 183 non-temporal; 302 M, 3.6 GB: 2621 and 2604).
+constexpr uint64_t kKeepBytes = 256ull << 20;
+
+template <bool KEEP>
+void launch_absmax(uint32_t mb, dim3 grid, hipStream_t s, const AbsmaxArgs& b)
+{
+    const dim3 block(kWave * kAbsmaxWaves);
+    switch (mb) {
+    case 8: hipLaunchKernelGGL((sdl_span_absmax_kernel<8, KEEP>), grid, block, 0, s, b); break;
+    case 7: hipLaunchKernelGGL((sdl_span_absmax_kernel<7, KEEP>), grid, block, 0, s, b); break;
+    case 6: hipLaunchKernelGGL((sdl_span_absmax_kernel<6, KEEP>), grid, block, 0, s, b); break;
+    case 5: hipLaunchKernelGGL((sdl_span_absmax_kernel<5, KEEP>), grid, block, 0, s, b); break;
+    case 4: hipLaunchKernelGGL((sdl_span_absmax_kernel<4, KEEP>), grid, block, 0, s, b); break;
+    case 3: hipLaunchKernelGGL((sdl_span_absmax_kernel<3, KEEP>), grid, block, 0, s, b); break;
+    case 2: hipLaunchKernelGGL((sdl_span_absmax_kernel<2, KEEP>), grid, block, 0, s, b); break;
+    default: hipLaunchKernelGGL((sdl_span_absmax_kernel<1, KEEP>), grid, block, 0, s, b); break;
+    }
+}
 
 struct SpanRun { uint64_t offset, numel, soff; bool vec; uint32_t sidx; };
 
@@ -1219,6 +1251,7 @@ hipError_t launch_span_prepass(const Args& a, const SpanRun* runs, uint32_t n_ru
 {
     for (uint32_t r0 = 0; r0 < n_runs; r0 += kAbsmaxMaxRuns) {
         AbsmaxArgs b{};
+        std::memset(b.first, 0xff, sizeof(b.first));
         b.g = a.g;
         b.M = a.M;
         b.staged = a.staged;
@@ -1226,34 +1259,32 @@ hipError_t launch_span_prepass(const Args& a, const SpanRun* runs, uint32_t n_ru
         const uint32_t n = n_runs - r0 < (uint32_t)kAbsmaxMaxRuns ? n_runs - r0 : (uint32_t)kAbsmaxMaxRuns;
         uint64_t total_tiles = 0;
         for (uint32_t r = 0; r < n; ++r) total_tiles += (runs[r0 + r].numel + kAbsmaxTile - 1) / kAbsmaxTile;
+        uint64_t groups = total_tiles / kAbsmaxTilesPerWave;
+        if (groups < kAbsmaxMinGroups) groups = kAbsmaxMinGroups;
+        if (groups > kAbsmaxGroups) groups = kAbsmaxGroups;
+        b.look = total_tiles > 2u * kAbsmaxTilesPerWave * kAbsmaxGroups ? 1u : 0u;   // 134 M parameters
         uint32_t next = 0;
         for (uint32_t r = 0; r < n; ++r) {
             const SpanRun& in = runs[r0 + r];
             const uint64_t tiles = (in.numel + kAbsmaxTile - 1) / kAbsmaxTile;
-            uint64_t waves = total_tiles ? (tiles * kAbsmaxGroups + total_tiles - 1) / total_tiles : 1;
+            uint64_t waves = total_tiles ? (tiles * groups + total_tiles - 1) / total_tiles : 1;
             if (waves > tiles) waves = tiles;
             uint64_t G = (waves + kAbsmaxWaves - 1) / kAbsmaxWaves;
             if (G < 1) G = 1;
+            b.first[r] = next;
             b.runs[r] = AbsmaxRun{in.offset, in.numel, in.soff, in.vec ? 1u : 0u, in.sidx, next, (uint32_t)G};
             next += (uint32_t)G;
         }
         b.n_runs = n;
         hipLaunchKernelGGL(sdl_zero_span_scales, dim3(1), dim3(SDL_MAX_WORKERS * kAbsmaxMaxRuns), 0, s, b);
-        const dim3 grid(next), block(kWave * kAbsmaxWaves);
+        const dim3 grid(next);
+        const bool keep = total_tiles * kAbsmaxTile * (4u + 2u * a.M) <= kKeepBytes;
         for (uint32_t m0 = 0; m0 < a.M;) {
             const uint32_t left = a.M - m0;
             const uint32_t mb = left < 8u ? left : 8u;
             b.m0 = m0;
-            switch (mb) {
-            case 8: hipLaunchKernelGGL((sdl_span_absmax_kernel<8>), grid, block, 0, s, b); break;
-            case 7: hipLaunchKernelGGL((sdl_span_absmax_kernel<7>), grid, block, 0, s, b); break;
-            case 6: hipLaunchKernelGGL((sdl_span_absmax_kernel<6>), grid, block, 0, s, b); break;
-            case 5: hipLaunchKernelGGL((sdl_span_absmax_kernel<5>), grid, block, 0, s, b); break;
-            case 4: hipLaunchKernelGGL((sdl_span_absmax_kernel<4>), grid, block, 0, s, b); break;
-            case 3: hipLaunchKernelGGL((sdl_span_absmax_kernel<3>), grid, block, 0, s, b); break;
-            case 2: hipLaunchKernelGGL((sdl_span_absmax_kernel<2>), grid, block, 0, s, b); break;
-            default: hipLaunchKernelGGL((sdl_span_absmax_kernel<1>), grid, block, 0, s, b); break;
-            }
+            if (keep) launch_absmax<true>(mb, grid, s, b);
+            else launch_absmax<false>(mb, grid, s, b);
             m0 += mb;
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
