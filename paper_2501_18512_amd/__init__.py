@@ -147,9 +147,16 @@ def _ptr_array(ts: Optional[Sequence]):
     return (ctypes.c_void_p * len(ts))(*[_ptr(t) for t in ts])
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the same handle as torch.cuda.current_stream().cuda_stream, without the Stream object around it, which
+        # takes 2.8 us to build: a call on 2^20 parameters, whose kernel runs 6 us, took 9.4 us and takes 7
+        if _raw_stream is None or not torch.cuda.is_initialized():
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
