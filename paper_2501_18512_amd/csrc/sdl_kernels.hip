@@ -1158,7 +1158,8 @@ size_t code_bytes_at(sdl_format_t fmt, uint64_t elem)
 // Wavefronts that share a CU (0: as many as fit).  Enough loads in flight, not so many that the access window in each array
 // grows and DRAM page locality is lost: the knob that matters for a streaming kernel.  Measured on MI355X (medians of three
 // runs over 302 M parameters, replica counts 2 / 4 / 8): the kernels that write the replicas back want few wavefronts --
-// fused 12 / 8 / 8 (12 when w_send aliases w_now), one-pass receive 12 / 8 / 8, merge 16 / 12 / 8 --, the receive side
+// fused 12 / 8 / 8 (12 / 12 / 8 when w_send aliases w_now), one-pass receive 16 / 8 / 8 (12 cost it 4-9 % at two replicas:
+// 53 M parameters 227 us, 208 with 16; 302 M 1233 and 1180), merge 16 / 12 / 8 --, the receive side
 // without the merge all / 16 / all (measured again with the arrays in one allocation: 16 cost it 3 % at two replicas), and
 // the send side every wavefront it can get.  A single replica: 16 for the fused kernel and the one-pass receive, no cap
 // otherwise.  The any-M variant (two rows), swept over none, 24, 16, 12, 8, 6 and 4: fewer with more arrays, never below 8
@@ -1173,10 +1174,10 @@ uint32_t waves_per_cu(int mode, uint32_t mt, uint32_t M, int fmt, bool aliased, 
         if (emit && is_scaled(fmt)) return M <= 4 ? 16 : 12;
         if (emit) return M <= 2 ? 16 : (M == 3 ? 12 : 8);
         if (mt == 0) return M == 3 ? 12 : 8;
-        return mt == 1 ? 16 : ((aliased || mt == 2) ? 12 : 8);
+        return mt == 1 ? 16 : (mt == 2 || (aliased && mt == 4) ? 12 : 8);
     case kReceive:
         if (mt == 0) return M <= 5 ? 12 : 8;
-        return mt == 1 ? 16 : (mt == 2 ? 12 : 8);
+        return mt <= 2 ? 16 : 8;
     case kMerge:
         if (mt == 0) return M == 3 ? 24 : (M == 5 ? 16 : (M <= 7 ? 12 : 8));
         return mt == 1 ? 0 : (mt == 2 ? 16 : (mt == 4 ? 12 : 8));
