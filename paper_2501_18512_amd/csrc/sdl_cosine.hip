@@ -344,7 +344,8 @@ __global__ void __launch_bounds__(2 * kWave, 2) sdl_gram_pair_kernel(const GramA
 // operand and of the right one alike.  Bound: the matrix pipe, 256 fp64 FMAs per parameter (half of them for the lower
 // triangle; rows behind the last replica repeat replica 0 and are not stored): 52.9 M parameters at the 77 TFLOP/s that a
 // chain of this instruction reaches take 350 us, HBM 268 us at 16 replicas; the loads alone take 370 us in this layout, the
-// arithmetic alone 395.  Whole call at 13 / 16 replicas: 698 / 935 us as 8 x 8 blocks in three launches, 488 / 503 now.
+// arithmetic alone 395 (in chains of 16).  Whole call at 13 / 16 replicas: 698 / 935 us as 8 x 8 blocks in three launches,
+// 502 / 510 now.
 // A load covers 64 bytes of 16 arrays; the chunk of 64 parameters that a wavefront takes at a time is a whole line of each.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kMfmaWaves = 4;             // wavefronts per workgroup, which adds their matrices up before it writes one
@@ -366,7 +367,22 @@ __device__ __forceinline__ void load_chunk(MfmaChunk& c, const float* g, const u
     }
 }
 
-__device__ __forceinline__ f64x4 chunk_sums(const MfmaChunk& c)
+// The instruction rounds its sums towards zero, so a chain of it is kept to 4 (16 parameters); a chunk's four chains and the
+// chunks are added by plain additions, which round to nearest, at two levels so that neither is long.  Root mean square of the
+// error of G[m][m] against exact sums, M = 16, in units of 1e-16, for the recipes normal / student_t3 / outliers / an outer
+// gradient with full mantissas: 0.26 M parameters 0.9 / 0.8 / 0.9 / 0.8, 8.4 M 1.0 / 0.9 / 0.9 / 0.8, 52.9 M 1.0 / 0.6 / 1.2 / 1.1;
+// the plain FMAs of sdl_gram_kernel at M = 8 give 0.8 / 0.8 / 0.8 / 0.8, 1.0 / 0.8 / 0.9 / 0.5 and 0.9 / 0.4 / 3.5 / 3.7.  One
+// chain for a chunk: outliers 2.4, full mantissas 1.8 at every size.  Chains of 8: 1.4 and 1.3, of 2: 0.7 and 0.8.  The whole
+// call at 52.9 M parameters: 488 us with chains of 16, 495 with 8, 510 with 4, 550 with 2.
+constexpr int kMfmaChain = 4;
+
+struct MfmaSums {
+    f64x4 total = {};     // whole chunks
+    f64x4 part = {};      // the chains of a chunk
+    f64x4 last = {};      // the latest chain, added one chain later, when its instructions have ended
+};
+
+__device__ __forceinline__ void add_chunk(const MfmaChunk& c, MfmaSums& s)
 {
     f64x4 acc = {};
 #pragma unroll
@@ -375,11 +391,26 @@ __device__ __forceinline__ f64x4 chunk_sums(const MfmaChunk& c)
         deltas(c.g[h][0], c.g[h][1], c.w[h], f);
 #pragma unroll
         for (int j = 0; j < kLaneElems; ++j) {
+            const int k = h * kLaneElems + j;
             const double d = (double)f[j];
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(d, d, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(d, d, k % kMfmaChain ? acc : f64x4{}, 0, 0, 0);
+            if (k % kMfmaChain != kMfmaChain - 1) continue;
+            if (k / kMfmaChain == 0) {                // ends the chunk before this one
+                s.part += s.last;
+                s.total += s.part;
+                asm volatile("" : "+v"(s.total));
+            } else if (k / kMfmaChain == 1) {
+                s.part = s.last;
+            } else {
+                s.part += s.last;
+                asm volatile("" : "+v"(s.part));
+            }
+            s.last = acc;
+            // Additions stay with their half of the chunk: moved to the end of the tile, they would keep every chain's sums
+            // alive, more than the registers hold (spilled ones are read back behind the next chunk's loads).
+            if (j == kLaneElems - 1) __builtin_amdgcn_sched_barrier(0);
         }
     }
-    return acc;
 }
 
 // (four wavefronts per SIMD: the compiler's own choice of registers leaves two, 540 us against 503)
@@ -396,11 +427,7 @@ sdl_gram_mfma_kernel(const GramArgs a)
     const float* g = a.g + set.offset + quarter * kLaneElems;
     const uint16_t* w = a.w[replica < M ? replica : 0u] + set.offset + quarter * kLaneElems;
 
-    // The instruction rounds its sums towards zero, so chains are kept to the sixteen of one chunk, whose sums are added to
-    // the total by plain additions while the next chunk's instructions run.  In one chain over all tiles the error against
-    // exact sums is 1.4e-15 to 5e-15 of the matrix, with chains of 64 2e-16 to 9e-16, like this 2e-16 to 3e-16, as with
-    // plain FMAs.
-    f64x4 last = {}, total = {};
+    MfmaSums sums;
     const uint64_t n_whole = set.numel / kTile, step = (uint64_t)set.G * kMfmaWaves;
     uint64_t t = (uint64_t)wave * set.G + (blockIdx.x - set.first_wg);
     MfmaChunk c[2];
@@ -417,13 +444,7 @@ sdl_gram_mfma_kernel(const GramArgs a)
                 load_chunk(c[0], g + (t + step) * kTile, w + (t + step) * kTile);
             }
             __builtin_amdgcn_sched_barrier(0);
-            const f64x4 sums = chunk_sums(c[k % 2]);
-            __builtin_amdgcn_sched_barrier(0);
-            // The compiler would move the eight additions of a tile behind its last chunk, which keeps eight chunks' sums alive:
-            // 12 registers spilled, read back behind the next chunk's loads (M = 16, 52.9 M parameters: 502 us, 488 without).
-            total += last;
-            asm volatile("" : "+v"(total));
-            last = sums;
+            add_chunk(c[k % 2], sums);
         }
     }
     if (t == n_whole && t * kTile < set.numel) {
@@ -440,10 +461,10 @@ sdl_gram_mfma_kernel(const GramArgs a)
                     const uint32_t x = there ? (uint32_t)w[e] : 0u;
                     c[0].w[h][j / 2] = j % 2 ? c[0].w[h][j / 2] | (x << 16) : x;
                 }
-            total += chunk_sums(c[0]);
+            add_chunk(c[0], sums);
         }
     }
-    total += last;
+    const f64x4 total = sums.total + (sums.part + sums.last);
     // register i of lane l: row 4 i + l / 16, column l % 16
 #pragma unroll
     for (int i = 0; i < 4; ++i) mats[wave][(4 * i + quarter) * 16 + replica] = total[i];
