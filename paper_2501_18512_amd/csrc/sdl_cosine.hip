@@ -35,13 +35,14 @@ using namespace sdl_device;
 
 constexpr int kLaneElems = 8;                   // consecutive parameters a lane owns in a tile
 constexpr int kTile = kLaneElems * kWave;       // 512
-constexpr int kOneWaveM = 8;                    // most replicas whose whole matrix one lane holds
 constexpr int kMaxSets = 48;                    // parameter sets per launch
 constexpr int kWindows = 48;                    // windows per launch: a set holding a share of 4/48 or more is cut
 constexpr int kMaxPieces = kMaxSets + kWindows;
+constexpr int kPairM = 12;                      // most replicas whose matrix two wavefronts share
 constexpr uint32_t kGroups = 8192;              // workgroups per launch, shared out among the sets (32 per compute unit)
-constexpr uint32_t kWideGroups = 4096;          // the same for more than 8 replicas (1024: 15-20 % slower, the last round of
-                                                // workgroups is nearly empty; 8192: up to 5 %, twice the partial matrices)
+constexpr uint32_t kWideGroups = 4096;          // the same for the matrix cores, 4 wavefronts each (1024: 15-20 % slower, the
+                                                // last round of workgroups is nearly empty; 8192: up to 5 %, twice the
+                                                // partial matrices)
 constexpr uint32_t kMaxGroups = 8192;           // what the workspace is sized for
 
 
@@ -208,8 +209,7 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
         }
 }
 
-// 9 to 12 replicas, H = ceil(M / 2) per half.  Bound: 78 fp64 FMAs and 36 other operations per parameter at M = 12, about
-// the time that HBM needs for its 28 bytes, so the matrix has to be formed in one pass.  One lane cannot hold 78 sums, the
+// 9 to 12 replicas, H = ceil(M / 2) per half, in one pass over memory (blocks of 8 x 8 need three).  One lane cannot hold 78 sums, the
 // tile and the next one; the two wavefronts of a workgroup run the same code on the same tiles (the second finds them in L1
 // / L2) and differ in which replicas they call "rows" and "columns":
 //   wavefront 0   rows i = replicas 0..H-1,       columns j = replicas H..2H-1
@@ -217,8 +217,13 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
 // Each forms its rows' triangle and, of the block rows x columns, the entries with (j - i) mod H < ceil(H / 2): in the first
 // wavefront's terms the second one forms those with (j - i) mod H >= H - ceil(H / 2), so all are there (for odd H one
 // diagonal twice).  With odd M the replica 2H-1 does not exist: the lanes work on replica 0 in its place and nothing of it
-// is stored.  52.9 M parameters, M = 9 / 10 / 12, whole call: 465 / 511 / 632 us as 8 x 8 blocks in three launches, 306 /
-// 315 / 402 now (the matrix cores: 475).  At 14 two wavefronts of 249 registers on a SIMD no longer cover the loads (494).
+// is stored.  Bound: both wavefronts form all 2H differences, and 166 / 198 registers leave 3 / 2 wavefronts on a SIMD to cover
+// the loads.  52.9 M parameters, M = 9 / 10 / 12, whole call: 467 / 511 / 629 us as 8 x 8 blocks, 291 / 302 / 385 now (HBM 164 /
+// 179 / 209, the matrix cores 475).  At 14 two wavefronts of 249 registers on a SIMD no longer cover
+// the loads (494).
+// Workgroups: as many as sdl_gram_kernel has, so that a lane's chain of additions is no longer than there.  With half as many
+// M = 11 and 12 took 367 and 374 us (302 M parameters, M = 12: 2070, 1961 now), but the error of G[m][m] doubled: outliers
+// 7.0e-16 where one wavefront at M = 8 has 3.4e-16, 3.7e-16 to 4.2e-16 now.
 template <int H>
 struct PairTile {
     f32x4_elem g;
@@ -580,7 +585,7 @@ int launch_kernel(uint32_t M, const GramArgs& a, hipStream_t st)
     return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
 }
 
-uint32_t groups_per_launch(uint32_t M) { return M > (uint32_t)kOneWaveM ? kWideGroups : kGroups; }
+uint32_t groups_per_launch(uint32_t M) { return M > (uint32_t)kPairM ? kWideGroups : kGroups; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 

@@ -1,5 +1,5 @@
-"""The sums of 13 to 16 replicas come from the matrix cores, which round towards zero, and must be no further from the exact ones
-than those of up to 8.
+"""The sums of 9 to 16 replicas come from other kernels than those of up to 8 (two wavefronts; matrix cores, which round towards
+zero) and must be no further from the exact ones.
 
 Exact: the fp64 products of fp32 differences are exact; they are folded in halves with the error of every addition kept
 (two-sum), which leaves about 1e-30.  Measure: root mean square of the relative error of the diagonal entries, over seeds.  The
@@ -7,7 +7,8 @@ same entries from a call with the first 8 replicas alone are the yardstick, but 
 a rounding to nearest errs by u / sqrt(3) of the binade, u = 2^-53, 0.43 u of the value on average over mantissas, and the
 levels of a tree, 2^k operands of 2^-k of the size, add up to 0.43 u * sqrt(1 + 1/2 + 1/4 + ...) = 0.6 u.  The entries of a seed
 share g, so a ratio of two measures scatters by a fifth: the bound is 1.6.  Sums of the matrix cores in chains of 64
-parameters are at 1.5 to 3 times the yardstick."""
+parameters are at 1.5 to 3 times the yardstick, those of two wavefronts with half as many workgroups at twice of it for
+52.9 M parameters."""
 import pytest
 import torch
 
@@ -52,7 +53,7 @@ def _rms_error(g, w, M, entries, exact):
 @pytest.mark.parametrize("n,seeds", [((1 << 18), 8), ((1 << 23) + 333, 4), (52_900_001, 1)])
 @pytest.mark.parametrize("recipe", ["outliers", "full"])
 def test_wide_sums_are_as_exact_as_those_of_8_replicas(recipe, n, seeds):
-    errors = {M: [] for M in (8, 13, 16)}
+    errors = {M: [] for M in (8, 9, 12, 13, 16)}
     for seed in range(seeds):
         g, w = _inputs(recipe, n, 16, seed)
         exact = [_exact((g - x.float()).double().square_()) for x in w[:8]]
