@@ -484,16 +484,29 @@ sdl_gram_mfma_kernel(const GramArgs a)
 
 // What each output of the finalize kernel adds up.
 constexpr uint32_t kFinThreads = 1024;
-constexpr int kMaxFin = kMaxGroups / 64 + 2 * kMaxSets + 2;               // outputs per finalize launch
 
 // Threads that share an entry (beyond 64 the tree over them costs more than it saves), and the matrices that one first-level
 // output adds: 8 for each of them.
-__host__ __device__ inline uint32_t fin_slices(uint32_t M)
+__host__ __device__ constexpr uint32_t fin_slices(uint32_t M)
 {
     const uint32_t s = kFinThreads / (M * (M + 1u) / 2u);
     return s < 64u ? s : 64u;
 }
-uint32_t fin_chunk(uint32_t M) { return 8u * fin_slices(M); }
+constexpr uint32_t fin_chunk(uint32_t M) { return 8u * fin_slices(M); }
+
+constexpr uint32_t groups_per_launch(uint32_t M) { return M > (uint32_t)kPairM ? kWideGroups : kGroups; }
+
+// A launch over n sets has at most groups_per_launch + n workgroups, so at most (groups_per_launch + n) / fin_chunk + n
+// first-level outputs: kFirstLevel and one for each set, of which the workspace and the arguments have room.
+constexpr uint32_t kFirstLevel = kMaxGroups / 64 + 2;
+constexpr int kMaxFin = kFirstLevel + 2 * kMaxSets;                       // outputs per finalize launch
+constexpr bool sums_fit()
+{
+    for (uint32_t M = 1; M <= SDL_MAX_WORKERS; ++M)
+        if (groups_per_launch(M) > kMaxGroups || (groups_per_launch(M) + kMaxSets) / fin_chunk(M) > kFirstLevel) return false;
+    return true;
+}
+static_assert(sums_fit(), "workgroups per launch, matrices per first-level output and the workspace go together");
 
 struct FinArgs {
     const double* in;              // matrices of M*M doubles (only a <= b is read), stride_k doubles apart
@@ -584,8 +597,6 @@ int launch_kernel(uint32_t M, const GramArgs& a, hipStream_t st)
     }
     return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
 }
-
-uint32_t groups_per_launch(uint32_t M) { return M > (uint32_t)kPairM ? kWideGroups : kGroups; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -732,7 +743,7 @@ size_t partial_mats(size_t n_sets)
 size_t tmp_mats(size_t n_sets)
 {
     const size_t launches = (n_sets + kMaxSets - 1) / kMaxSets;
-    return launches * (kMaxGroups / 64 + 2) + 2 * n_sets;
+    return launches * kFirstLevel + 2 * n_sets;
 }
 
 int check_common(const void* g, const void* const* w, uint32_t M, const void* workspace)
