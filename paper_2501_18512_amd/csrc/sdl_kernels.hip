@@ -1155,42 +1155,75 @@ size_t code_bytes_at(sdl_format_t fmt, uint64_t elem)
     }
 }
 
-// Wavefronts that share a CU (0: as many as fit).  Enough loads in flight, not so many that the access window in each array
-// grows and DRAM page locality is lost: the knob that matters for a streaming kernel.  Measured on MI355X (medians of three
-// runs over 302 M parameters, replica counts 2 / 4 / 8): the kernels that write the replicas back want few wavefronts --
-// fused 12 / 8 / 8 (12 / 12 / 8 when w_send aliases w_now), one-pass receive 16 / 8 / 8 (12 cost it 4-9 % at two replicas:
-// 53 M parameters 227 us, 208 with 16; 302 M 1233 and 1180), merge 16 / 12 / 8 --, the receive side
-// without the merge all / 16 / all (measured again with the arrays in one allocation: 16 cost it 3 % at two replicas), and
-// the send side every wavefront it can get.  A single replica: 16 for the fused kernel and the one-pass receive, no cap
-// otherwise.  The any-M variant (two rows), swept over none, 24, 16, 12, 8, 6 and 4: fewer with more arrays, never below 8
-// (6 costs 15-20 %).  us without a cap -> with it, 105 M parameters: fused M = 3 701 -> 669, 6 1143 -> 1037, 12 2002 -> 1830;
-// one-pass receive 3 656 -> 600, 6 985 -> 879, 12 1657 -> 1476; 67 M parameters: receive side 3 194 -> 182, 12 250 -> 245;
-// merge 3 169 -> 164, 6 316 -> 286, 16 814 -> 724; 53 M parameters, messages written: bf16 M = 2 293 -> 277, 4 459 -> 422,
-// 8 784 -> 733, e3m0 M = 4 386 -> 365.  Formats that run the codec want more of them than those that only round.
+// Wavefronts that share a CU (0: as many as fit, 32).  Enough loads in flight, not so many that the access window in each array
+// grows and DRAM page locality is lost: the knob that matters for a streaming kernel.  The kernels that write the replicas
+// back want few, and fewer the more arrays they walk, but never less than 8 (6 cost 15-20 %); the receive side without the
+// merge reads many small messages and writes two arrays, and wants more as decoding grows with the replicas; the send side
+// wants all it can get.  Formats that run the codec want more than those that only round.  us in one process, the caps in turn
+// on the same arrays, E3M0 unless named (between processes all of a row move by up to 4 %, with where the arrays lie; within one
+// a figure repeats to 1 %):
+//                                         M    none   21   16   11    8
+//   fused, 105 M parameters               2     489  485  476  469  495
+//                                         3     609  609  600  589  629
+//                                         4     734  743  729  707  682
+//                                         6     984  984  973  940  905
+//                                         8    1228 1227 1250 1228 1190
+//                                        12    1765 1765 1753 1682 1624
+//   fused, w_send aliases w_now           2     417  412  406  404  471
+//                                         4     582  577  565  552  596
+//                                         8     914  912  914  882  866
+//   one-pass receive, 53 M                2     216  214  209  227  240
+//                                         3     268  261  258  262  290
+//                                         5     365  364  350  342  356
+//                                         6     409  412  399  384  389
+//                                        12     708  716  696  668  650
+//   merge, 67 M                           2     123  121  120  135  163
+//                                         3     170  164  169  181  205
+//                                         4     219  217  211  205  226
+//                                         5     267  257  251  254  279
+//                                         7     373  362  345  338  364
+//                                        10     518  519  502  464  460
+//                                        16     837  849  829  770  727
+//   receive side without the merge, 67 M  3     200  190  183  189  217
+//                                         9     230  225  224  250  304
+//                                        10     236  232  228  258  316
+//                                        12     253  247  254  297  366
+//                                        16     280  277  302  362  444
+//   messages written, BF16, 53 M          2     295  289  278  273  279
+//                                         4     454  456  448  430  415
+//                                         8     785  793  785  753  731
+//   messages written, E3M0                3     318  318  318  344  398
+//                                         6     517  517  517  508  538
+//   messages written, E4M3                4     413  414  404  392  393
+//                                         8     702  703  688  670  655
 uint32_t waves_per_cu(int mode, uint32_t mt, uint32_t M, int fmt, bool aliased, bool emit)
 {
     switch (mode) {
     case kFused:
-        if (emit && is_scaled(fmt)) return M <= 4 ? 16 : 12;
-        if (emit) return M <= 2 ? 16 : (M == 3 ? 12 : 8);
-        if (mt == 0) return M == 3 ? 12 : 8;
-        return mt == 1 ? 16 : (mt == 2 || (aliased && mt == 4) ? 12 : 8);
+        if (emit && is_scaled(fmt)) return M <= 4 ? 16 : 11;
+        if (emit) return M <= 2 ? 16 : (M == 3 ? 11 : 8);
+        if (mt == 0) return M == 3 ? 11 : 8;
+        return mt == 1 ? 16 : (mt == 2 || (aliased && mt == 4) ? 11 : 8);
     case kReceive:
-        if (mt == 0) return M <= 5 ? 12 : 8;
+        if (mt == 0) return M <= 5 ? 11 : 8;
         return mt <= 2 ? 16 : 8;
     case kMerge:
-        if (mt == 0) return M == 3 ? 24 : (M == 5 ? 16 : (M <= 7 ? 12 : 8));
-        return mt == 1 ? 0 : (mt == 2 ? 16 : (mt == 4 ? 12 : 8));
+        if (mt == 0) return M == 3 ? 21 : (M == 5 ? 16 : (M <= 7 ? 11 : 8));
+        return mt == 1 ? 0 : (mt == 2 ? 16 : (mt == 4 ? 11 : 8));
     case kReduce:
-        if (mt == 0) return M <= 9 ? 16 : 24;
+        if (mt == 0) return M <= 10 ? 16 : 21;
         return mt == 4 ? 16 : 0;
     default:
         return 0;
     }
 }
 
-// The cap takes the form of dynamic LDS that nothing uses: 160 KiB per CU, shared out among the wavefronts.
-uint32_t lds_cap_bytes(uint32_t waves) { return waves ? 163840u / waves : 0u; }
+// The cap takes the form of dynamic LDS that nothing uses: 160 KiB per CU, given out in units of 1280 bytes (measured: 6826
+// and 7680 bytes leave 21 wavefronts on a CU, 7681 leave 18, 12800 12, 13653 and 14080 11, 14081 10).
+constexpr uint32_t kLdsPerCu = 163840, kLdsUnit = 1280;
+constexpr uint32_t lds_cap_bytes(uint32_t waves) { return waves ? kLdsPerCu / waves / kLdsUnit * kLdsUnit : 0u; }
+constexpr bool cap_is_kept(uint32_t waves) { return kLdsPerCu / lds_cap_bytes(waves) == waves; }
+static_assert(cap_is_kept(8) && cap_is_kept(11) && cap_is_kept(16) && cap_is_kept(21), "the caps of waves_per_cu");
 
 template <int MODE, int FMT, bool ALIASED, bool EMIT>
 hipError_t launch_m(const Args& a, uint32_t n_wg, hipStream_t s)
