@@ -1,8 +1,8 @@
 // Cosine similarity between the replicas' outer gradients (Appendix of the paper, paragraph on
 // the outer gradients' cosine similarity) for gfx950 (MI355X).
 //
-// Two kernels.
-//   sdl_gram_kernel   streams g and the M replicas once and accumulates the Gram matrix of
+// Four kernels.
+//   sdl_gram_kernel   up to 8 replicas: streams g and the M replicas once and accumulates the Gram matrix of
 //                     the outer gradients Delta_m = g - float(w_m).  A workgroup is one
 //                     64-lane wavefront; a set of parameters gets a share G of the launch's
 //                     workgroups in proportion to its size, and workgroup k of the set walks

@@ -458,8 +458,6 @@ struct TileIOT {
 
     // E4M3 only: with EXACT = false the two byte values the encoder never writes decode to NaN
     static constexpr bool kHasInexactDecode = true;
-    // whole tiles: a run-time replica count is taken in groups whose loads are issued together
-    static constexpr bool kGroupReplicas = true;
     template <int FMT, bool EXACT = true>
     __device__ __forceinline__ void load_message(uint32_t m, int row, float (&dq)[kVec]) const
     {
@@ -597,7 +595,6 @@ struct TailIO {
     __device__ __forceinline__ void store_wn(uint32_t m, int row, const uint32_t (&u)[2]) const { st_bf16(a.w_now[m] + t0, row, u); }
 
     static constexpr bool kHasInexactDecode = false;
-    static constexpr bool kGroupReplicas = true;
     template <int FMT, bool EXACT = true>
     __device__ __forceinline__ void load_message(uint32_t m, int row, float (&dq)[kVec]) const
     {
@@ -786,10 +783,8 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
                 for (int r = 0; r < kRows; ++r) add_replica<MODE, FMT, EMIT>(io, (uint32_t)m, r, ws[m][r], g[r], acc[r]);
         } else {
             uint32_t m = 0;
-            if constexpr (IO::kGroupReplicas) {
-                for (; m + 4u <= M; m += 4u) add_replica_group<MODE, FMT, EMIT, kRows, 4>(io, m, g, acc);
-                if (M - m >= 2u) { add_replica_group<MODE, FMT, EMIT, kRows, 2>(io, m, g, acc); m += 2u; }
-            }
+            for (; m + 4u <= M; m += 4u) add_replica_group<MODE, FMT, EMIT, kRows, 4>(io, m, g, acc);
+            if (M - m >= 2u) { add_replica_group<MODE, FMT, EMIT, kRows, 2>(io, m, g, acc); m += 2u; }
             for (; m < M; ++m) add_replica_group<MODE, FMT, EMIT, kRows, 1>(io, m, g, acc);
         }
     }
@@ -854,10 +849,8 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
         } else {
             // (with w_send aliasing w_now these are the same words as at the send step, read again)
             uint32_t m = 0;
-            if constexpr (IO::kGroupReplicas) {
-                for (; m + 4u <= M; m += 4u) merge_replica_group<kRows, 4>(a, io, m, g);
-                if (M - m >= 2u) { merge_replica_group<kRows, 2>(a, io, m, g); m += 2u; }
-            }
+            for (; m + 4u <= M; m += 4u) merge_replica_group<kRows, 4>(a, io, m, g);
+            if (M - m >= 2u) { merge_replica_group<kRows, 2>(a, io, m, g); m += 2u; }
             for (; m < M; ++m) merge_replica_group<kRows, 1>(a, io, m, g);
         }
     }
@@ -869,8 +862,10 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
 // memory channels, and it is what aligned arrays get.  Where the arrays start somewhere inside a cache line, every row
 // shares its first and last line with its neighbours; on another XCD that line is fetched into a second L2 and written in
 // two parts, so consecutive tiles go to one XCD, kChunkRows rows at a time (72 M parameters of odd groups, fused: M = 2
-// 388 -> 329 us, M = 4 572 -> 483, M = 8 892 -> 869; half or twice the chunk is up to 2 % slower, and aligned arrays lose
-// 3-8 % with it).
+// 388 -> 329 us, M = 4 572 -> 483, M = 8 892 -> 869; half or twice the chunk is up to 2 % slower, and arrays that start on a
+// line lose 3-8 % with it).  The rule (RunBuilder, flush) asks for 16 bytes and not for a line: it was measured on arrays that
+// start at any element and on arrays that start on a line.  Those in between, where every group is a multiple of 8 elements
+// but not of 64, take the buffer path in the order of the grid, at about the rate that unaligned arrays have without chunks.
 constexpr int kXcds = 8;
 constexpr int kChunkRows = 8;
 template <int ROWS>
@@ -1431,7 +1426,7 @@ template <int MODE>
 bool flush(RunBuilder& rb, sdl_format_t fmt, void* stream)
 {
     if (rb.a->n_runs == 0) return true;
-    rb.a->chunked = 2 * rb.n_unaligned > rb.n_wg ? 1u : 0u;   // what most of the launch's tiles want
+    rb.a->chunked = 2 * rb.n_unaligned > rb.n_wg ? 1u : 0u;   // what most of the launch's tiles want (see chunked_tile)
     const hipError_t e = launch<MODE>(*rb.a, fmt, (uint32_t)rb.n_wg, (hipStream_t)stream);
     rb.reset();
     return e == hipSuccess;
