@@ -483,7 +483,7 @@ sdl_gram_mfma_kernel(const GramArgs a)
 }
 
 // What each output of the finalize kernel adds up.
-constexpr uint32_t kFinThreads = 1024;
+constexpr uint32_t kFinThreads = 1024;                                     // most threads of a workgroup
 
 // Threads that share an entry (beyond 64 the tree over them costs more than it saves), and the matrices that one first-level
 // output adds: 8 for each of them.
@@ -556,10 +556,10 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
     __syncthreads();
     double* o = f.last_out && blockIdx.x + 1u == gridDim.x ? f.last_out : f.out + (uint64_t)blockIdx.x * f.out_stride;
     if (!f.emit) {
-        for (uint32_t i = threadIdx.x; i < M * M; i += kFinThreads) o[i] = G[i];
+        for (uint32_t i = threadIdx.x; i < M * M; i += blockDim.x) o[i] = G[i];
         return;
     }
-    for (uint32_t i = threadIdx.x; i < M * M; i += kFinThreads) {
+    for (uint32_t i = threadIdx.x; i < M * M; i += blockDim.x) {
         const uint32_t a = i / M, b = i % M;
         const double den = __builtin_sqrt(G[a * M + a]) * __builtin_sqrt(G[b * M + b]);
         const double c = den > 0.0 ? G[i] / den : 0.0;
@@ -663,7 +663,9 @@ int launch_gram(const float* g, const void* const* w, uint32_t M, const Set* set
 
 int launch_finalize(const FinArgs& f, uint32_t n_out, hipStream_t st)
 {
-    hipLaunchKernelGGL(sdl_gram_finalize, dim3(n_out), dim3(kFinThreads), 0, st, f);
+    // whole wavefronts for the entries and their slices: 64 threads at one replica, 192 at two (idle ones cost their barriers)
+    const uint32_t threads = (f.M * (f.M + 1u) / 2u * fin_slices(f.M) + kWave - 1u) / kWave * kWave;
+    hipLaunchKernelGGL(sdl_gram_finalize, dim3(n_out), dim3(threads), 0, st, f);
     return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
 }
 
