@@ -121,8 +121,8 @@ def test_config_stress_m8_variations_sampled(fmt):
 
 
 def test_plan_call_with_many_ragged_runs():
-    """More runs than one launch holds (16), ragged and partly unaligned: spans whose lengths are
-    not multiples of 128 end their run, so nearly every span is its own run, with its own block grid."""
+    """More runs than a workgroup compares at once (16), ragged and partly unaligned: spans whose lengths
+    are not multiples of 128 end their run, so nearly every span is its own run, with its own block grid."""
     rng = np.random.default_rng(3)
     numel = [int(x) for x in rng.integers(1, 5000, 45)] + [4096, 512, 33, 2048 * 3]
     block = [i % 7 for i in range(len(numel))]

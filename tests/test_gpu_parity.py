@@ -63,7 +63,8 @@ def test_dequant_reduce_nesterov(fmt, M):
 
 @pytest.mark.parametrize("fmt", [sdl.FMT_E3M0, sdl.FMT_E4M3, sdl.FMT_E3M0_B64, sdl.FMT_E3M0_B128, sdl.FMT_E3M0_RN])
 @pytest.mark.parametrize("M", [1, 3])
-def test_receive_side_decodes_every_code_and_scale(fmt, M):
+@pytest.mark.parametrize("shift", [0, 1])          # code arrays on 16 bytes, and one byte behind
+def test_receive_side_decodes_every_code_and_scale(fmt, M, shift):
     """Messages are plain bytes: whatever a peer sends is decoded like the oracle decodes it,
     including the codes the encoder never produces and the extreme scale bytes."""
     n = 4 * 2048 + 96
@@ -79,7 +80,9 @@ def test_receive_side_decodes_every_code_and_scale(fmt, M):
     hg = rng.standard_normal(n).astype(np.float32)
     hmom = (rng.standard_normal(n) * 1e-3).astype(np.float32)
     g, mom = torch.from_numpy(hg).to(DEV), torch.from_numpy(hmom).to(DEV)
-    codes, scales = sdl.alloc_exchange(fmt, n, M)
+    scales = sdl.alloc_exchange(fmt, n, M)[1]
+    codes = [torch.zeros(cb + 16, dtype=torch.uint8, device=DEV)[shift:] for _ in range(M)]
+    assert codes[0].data_ptr() % 16 == shift
     for m in range(M):
         codes[m][:cb].copy_(torch.from_numpy(rc[m]))
         scales[m][:sb].copy_(torch.from_numpy(rs[m]))
@@ -164,7 +167,7 @@ def test_fused_equals_three_calls_on_gpu(fmt):
 @pytest.mark.parametrize("fmt", FMTS)
 def test_unaligned_model_arrays(fmt):
     """Model arrays that start at odd element offsets (4-byte / 2-byte aligned only): whole tiles
-    go through element-aligned vectors, the ragged last tile element by element."""
+    go through element-aligned vectors, the ragged last tile through range-checked accesses of one element."""
     n, M = 2 * 2048 + 5, 2
     g, mom, w_send, w_now = _span(n + 3, M, tau=1)
     views = (g[1:1 + n], mom[3:3 + n], [w[1:1 + n] for w in w_send], [w[3:3 + n] for w in w_now])
@@ -176,7 +179,7 @@ def test_unaligned_model_arrays(fmt):
 @pytest.mark.parametrize("model_offset", [0, 1])
 def test_unaligned_message_arrays(fmt, model_offset):
     """Message arrays at the smallest alignment their element type allows (1 byte for the 4- and
-    8-bit codes, 2 / 4 bytes for bf16 / fp32): every tile goes element by element."""
+    8-bit codes, 2 / 4 bytes for bf16 / fp32): whole tiles go through vectors of that alignment."""
     n, M = 3 * 512 + 77, 2
     g0, mom0, ws0, wn0 = _span(n + 1, M, tau=1, delta="student_t3")
     o = model_offset
