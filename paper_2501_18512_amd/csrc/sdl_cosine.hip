@@ -349,8 +349,8 @@ __global__ void __launch_bounds__(2 * kWave, 2) sdl_gram_pair_kernel(const GramA
 // operand and of the right one alike.  Bound: the matrix pipe, 256 fp64 FMAs per parameter (half of them for the lower
 // triangle; rows behind the last replica repeat replica 0 and are not stored): 52.9 M parameters at the 77 TFLOP/s that a
 // chain of this instruction reaches take 350 us, HBM 268 us at 16 replicas; the loads alone take 370 us in this layout, the
-// arithmetic alone 395 (in chains of 16).  Whole call at 13 / 16 replicas: 698 / 935 us as 8 x 8 blocks in three launches,
-// 502 / 510 now.
+// arithmetic alone (the same few lines loaded again and again) 494: the conversions and additions between the chains are
+// fp64 operations as well.  Whole call at 13 / 16 replicas: 698 / 935 us as 8 x 8 blocks in three launches, 502 / 510 now.
 // A load covers 64 bytes of 16 arrays; the chunk of 64 parameters that a wavefront takes at a time is a whole line of each.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kMfmaWaves = 4;             // wavefronts per workgroup, which adds their matrices up before it writes one
@@ -418,7 +418,7 @@ __device__ __forceinline__ void add_chunk(const MfmaChunk& c, MfmaSums& s)
     }
 }
 
-// (four wavefronts per SIMD: the compiler's own choice of registers leaves two, 540 us against 503)
+// (four wavefronts per SIMD: left to itself the compiler takes registers for three, 539 us against 504)
 __global__ void __launch_bounds__(kMfmaWaves * kWave) __attribute__((amdgpu_waves_per_eu(4)))
 sdl_gram_mfma_kernel(const GramArgs a)
 {
