@@ -1,7 +1,7 @@
 // Cosine similarity between the replicas' outer gradients (Appendix of the paper, paragraph on
 // the outer gradients' cosine similarity) for gfx950 (MI355X).
 //
-// Four kernels.
+// Three kernels.
 //   sdl_gram_kernel   up to 8 replicas: streams g and the M replicas once and accumulates the Gram matrix of
 //                     the outer gradients Delta_m = g - float(w_m).  A workgroup is one
 //                     64-lane wavefront; a set of parameters gets a share G of the launch's
@@ -15,8 +15,8 @@
 //                     the end the wavefront folds them with a butterfly of lane exchanges and
 //                     lane 0 writes one partial Gram matrix.  The next tile's loads are issued
 //                     before the current tile is consumed.
-//   sdl_gram_pair_kernel  the same for 9 to 12 replicas, two wavefronts with half of the matrix each.
-//   sdl_gram_mfma_kernel  the same for 13 to 16 replicas, on the matrix cores.
+//   sdl_gramfma_pair_kernel  the same for 9 to 16 replicas: two wavefronts with half of the matrix each, which
+//                     exchange the outer gradients through LDS.
 //   sdl_gram_finalize adds the partial matrices of a set in a fixed order (one thread per entry and
 //                     slice of the matrices, then the slices as a tree; a set with many partial matrices in
 //                     two launches) and derives cos and the mean over pairs.  The same kernel adds
@@ -25,6 +25,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "sdl.h"
 #include "sdl_device.h"
@@ -38,11 +39,7 @@ constexpr int kTile = kLaneElems * kWave;       // 512
 constexpr int kMaxSets = 48;                    // parameter sets per launch
 constexpr int kWindows = 48;                    // windows per launch: a set holding a share of 4/48 or more is cut
 constexpr int kMaxPieces = kMaxSets + kWindows;
-constexpr int kPairM = 12;                      // most replicas whose matrix two wavefronts share
-constexpr uint32_t kGroups = 8192;              // workgroups per launch, shared out among the sets (32 per compute unit)
-constexpr uint32_t kWideGroups = 4096;          // the same for the matrix cores, 4 wavefronts each (1024: 15-20 % slower, the
-                                                // last round of workgroups is nearly empty; 8192: up to 5 %, twice the
-                                                // partial matrices)
+constexpr uint32_t kGroups = 8192;              // workgroups per launch up to 8 replicas, shared out among the sets (32 per compute unit)
 constexpr uint32_t kMaxGroups = 8192;           // what the workspace is sized for
 
 
@@ -209,277 +206,317 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
         }
 }
 
-// 9 to 12 replicas, H = ceil(M / 2) per half, in one pass over memory (blocks of 8 x 8 need three).  One lane cannot hold 78 sums, the
-// tile and the next one; the two wavefronts of a workgroup run the same code on the same tiles (the second finds them in L1
-// / L2) and differ in which replicas they call "rows" and "columns":
-//   wavefront 0   rows i = replicas 0..H-1,       columns j = replicas H..2H-1
-//   wavefront 1   rows i = replicas H..2H-1,      columns j = replicas 1, 2, ... H-1, 0
-// Each forms its rows' triangle and, of the block rows x columns, the entries with (j - i) mod H < ceil(H / 2): in the first
-// wavefront's terms the second one forms those with (j - i) mod H >= H - ceil(H / 2), so all are there (for odd H one
-// diagonal twice).  With odd M the replica 2H-1 does not exist: the lanes work on replica 0 in its place and nothing of it
-// is stored.  Bound: both wavefronts form all 2H differences, and 166 / 198 registers leave 3 / 2 wavefronts on a SIMD to cover
-// the loads.  52.9 M parameters, M = 9 / 10 / 12, whole call: 467 / 511 / 629 us as 8 x 8 blocks, 291 / 302 / 385 now (HBM 164 /
-// 179 / 209, the matrix cores 475).  At 14 two wavefronts of 249 registers on a SIMD no longer cover
-// the loads (494).
-// Workgroups: as many as sdl_gram_kernel has, so that a lane's chain of additions is no longer than there.  With half as many
-// M = 11 and 12 took 367 and 374 us (302 M parameters, M = 12: 2070, 1961 now), but the error of G[m][m] doubled: outliers
-// 7.0e-16 where one wavefront at M = 8 has 3.4e-16, 3.7e-16 to 4.2e-16 now.
+// 9 to 16 replicas, H = ceil(M / 2) of them to each of the two wavefronts of a workgroup.  One lane cannot hold up to 136 sums.
+// Wavefront 0 has the rows i = replicas 0..H-1 and the columns j = replicas H..2H-1, wavefront 1 the rows H..2H-1 and the columns
+// 1, 2, ... H-1, 0.  Each forms its rows' triangle and, of the block rows x columns, the entries with (j - i) mod H <
+// ceil(H / 2): in the first wavefront's terms the second one forms those with (j - i) mod H >= H - ceil(H / 2), so all are there
+// (for odd H one diagonal twice).  With odd M the replica 2H-1 does not exist: replica 0 is read in its place and nothing of it is
+// stored.
+//
+// A wavefront loads its own replicas, forms their outer gradients and puts them into LDS, where both find what they need as
+// fp32: each difference is formed once, and the tile on its way takes 2H + 4 registers.  Bound: fp64 FMAs, 136 for a parameter at
+// 16 replicas where a matrix instruction forms all 256 entries (both run at 16 a cycle and SIMD, and neither overlaps with the
+// other).  On real differences an FMA takes 2.4 ns, not the 1.7 of 2.4 GHz: 52.9 M parameters at 16 replicas are 263 us of FMAs and
+// 110 of conversions and subtractions; 300 us measured with the loads and the staging left out.  Whole call at 52.9 M parameters, M = 9 / 12 /
+// 13 / 16: 299 / 402 / 503 / 508 us as two wavefronts that each load everything (M <= 12) or on the matrix
+// cores, 246 / 324 / 400 /
+// 466 now (HBM 164 / 209 / 223 / 268); arrays at odd elements, M = 13 / 16: 541 / 584 and 416 / 490; 2.1 M parameters at 13 / 16: 54 / 57 and 37 / 43.
+// Four wavefronts with a quarter of the matrix each (more of them in flight, 48 conversions instead of 32): 503.  The tile copied
+// to LDS past the registers, up to three tiles ahead: 478.
 template <int H>
-struct PairTile {
+struct PairRaw {
     f32x4_elem g;
-    u32x2 w[2 * H];
+    u32x2 w[H];
 };
-constexpr int kPairTile = 4 * kWave;      // parameters a wavefront takes at a time
+constexpr int kPairTile = 4 * kWave;      // parameters a workgroup takes at a time
+constexpr int kPairChain = 4;             // tiles after which the diagonal entries start a new chain (16 parameters of a lane)
 
-template <int H>
-__device__ __forceinline__ void load_pair_tile(PairTile<H>& t, const float* g, const uint16_t* (&w)[2 * H], uint64_t e0,
-                                               uint64_t left, bool fast, uint32_t lane)
+// A whole tile of sets whose arrays are all 16-byte aligned (FAST) or start at any element.
+template <int H, bool FAST>
+__device__ __forceinline__ void load_pair_raw(PairRaw<H>& t, const float* g, const uint16_t* const (&w)[H], uint64_t e0, uint32_t lane)
 {
-    if (fast && left >= (uint64_t)kPairTile) {
-        // normal cache policy: the other wavefront reads the same lines
+    if constexpr (FAST) {
         t.g = __builtin_bit_cast(f32x4_elem, __builtin_amdgcn_raw_buffer_load_b128(rsrc(g + e0, kPairTile * 4), (int)(lane * 16), 0, 0));
 #pragma unroll
-        for (int m = 0; m < 2 * H; ++m)
-            t.w[m] = __builtin_amdgcn_raw_buffer_load_b64(rsrc(w[m] + e0, kPairTile * 2), (int)(lane * 8), 0, 0);
-    } else if (left >= (uint64_t)kPairTile) {
+        for (int m = 0; m < H; ++m)
+            t.w[m] = __builtin_amdgcn_raw_buffer_load_b64(rsrc(w[m] + e0, kPairTile * 2), (int)(lane * 8), 0, 2);
+    } else {
         t.g = *reinterpret_cast<const f32x4_elem*>(g + e0 + lane * 4);
 #pragma unroll
-        for (int m = 0; m < 2 * H; ++m) {
+        for (int m = 0; m < H; ++m) {
             const u32x2_elem x = *reinterpret_cast<const u32x2_elem*>(w[m] + e0 + lane * 4);
             t.w[m] = u32x2{x.x, x.y};
         }
-    } else {
-        // ragged tail: 0 past the end of g and of every replica
-        const uint32_t valid = (uint32_t)left;
-        const __amdgpu_buffer_rsrc_t rg = rsrc(g + e0, valid * 4);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) t.g[j] = u2f(__builtin_amdgcn_raw_buffer_load_b32(rg, (int)((lane * 4 + j) * 4), 0, 0));
-#pragma unroll
-        for (int m = 0; m < 2 * H; ++m) {
-            const __amdgpu_buffer_rsrc_t rw = rsrc(w[m] + e0, valid * 2);
-            uint32_t h[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                h[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (int)((lane * 4 + j) * 2), 0, 0) & 0xffffu;
-            t.w[m] = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-        }
     }
 }
+// A set's ragged last tile: 0 past the end of g and of every replica.
+template <int H>
+__device__ __forceinline__ void load_pair_tail(PairRaw<H>& t, const float* g, const uint16_t* const (&w)[H], uint64_t e0, uint32_t valid,
+                                               uint32_t lane)
+{
+    const __amdgpu_buffer_rsrc_t rg = rsrc(g + e0, valid * 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t.g[j] = u2f(__builtin_amdgcn_raw_buffer_load_b32(rg, (int)((lane * 4 + j) * 4), 0, 0));
+#pragma unroll
+    for (int m = 0; m < H; ++m) {
+        const __amdgpu_buffer_rsrc_t rw = rsrc(w[m] + e0, valid * 2);
+        uint32_t h[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            h[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (int)((lane * 4 + j) * 2), 0, 0) & 0xffffu;
+        t.w[m] = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+    }
+}
+
+// The wavefront's totals of the N sums that each lane holds in v, lane by lane fewer of them: at each of the six levels two
+// lanes split the sums they both hold, so that N / 2 exchanges take the place of N.  Afterwards a lane holds halved(N) totals.
+constexpr int halved(int n) { for (int l = 0; l < 6; ++l) n = (n + 1) / 2; return n; }
+
+template <int LEVEL> __device__ __forceinline__ double from_partner(double x)
+{
+    constexpr int kCtrl = LEVEL == 2 ? 0x140 : LEVEL == 3 ? 0x141 : LEVEL == 4 ? 0x4E : 0xB1;   // mirrors of 16 and 8, quad_perm
+    const u32x2 u = __builtin_bit_cast(u32x2, x);
+    const u32x2 r = {(uint32_t)__builtin_amdgcn_mov_dpp((int)u.x, kCtrl, 0xF, 0xF, true),
+                     (uint32_t)__builtin_amdgcn_mov_dpp((int)u.y, kCtrl, 0xF, 0xF, true)};
+    return __builtin_bit_cast(double, r);
+}
+
+template <int N, int LEVEL, int MAX>
+__device__ __forceinline__ void halve(double (&v)[MAX], uint32_t lane)
+{
+    if constexpr (LEVEL < 6) {
+        constexpr int half = (N + 1) / 2;
+        const bool upper = (lane >> (5 - LEVEL)) & 1u;
+#pragma unroll
+        for (int i = 0; i < half; ++i) {
+            double lo = v[i], hi = half + i < N ? v[half + i] : 0.0;
+            if constexpr (LEVEL < 2) {
+                const u32x2 a = __builtin_bit_cast(u32x2, lo), b = __builtin_bit_cast(u32x2, hi);
+                u32x2 x, y;
+                if constexpr (LEVEL == 0) {
+                    x = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false);
+                    y = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
+                } else {
+                    x = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
+                    y = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
+                }
+                lo = __builtin_bit_cast(double, u32x2{x.x, y.x});
+                hi = __builtin_bit_cast(double, u32x2{x.y, y.y});
+                v[i] = lo + hi;
+            } else {
+                v[i] = (upper ? hi : lo) + from_partner<LEVEL>(upper ? lo : hi);
+            }
+        }
+        halve<half, LEVEL + 1>(v, lane);
+    }
+}
+
+// Everything but the LDS accesses of the workgroup may be moved across, and loads stay in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// What the kernel works on: the tiles of all sets one behind the other, shared out among the workgroups in order.  A workgroup
+// writes one matrix for each set that it has tiles of.  Three shares of the launch, each with as many workgroups as there is
+// room for on the chip at once: 85 % of the tiles, then 10.5 % and 4.5 % in smaller parts, which fill what the first ones leave
+// free when they end (16 replicas: 492 us with equal parts for one round of workgroups, 478 so).
+constexpr int kShares = 3;
+struct Share {
+    uint32_t first_wg, first_tile, per_wg, extra;     // workgroup first_wg + i takes per_wg tiles, one more if i < extra
+};
+// Workgroups of a launch that are on the chip at once: 12 wavefronts on a compute unit with up to 168 registers, else 8.
+constexpr uint32_t pair_resident(uint32_t M) { return 256u * (M <= 10u ? 6u : 4u); }
+struct PairArgs {
+    const float* g;
+    const uint16_t* w[SDL_MAX_WORKERS];
+    double* partial;
+    uint32_t M;
+    uint32_t fast;                    // every array is 16-byte aligned at every set's start
+    uint32_t first_tile[kMaxSets + 1];   // of each set, then the number of tiles; 0xffffffff behind it
+    Share shares[kShares];
+    int32_t slot[kMaxSets];           // workgroup b's matrix of set s is partial[b + slot[s]]
+    uint64_t offset[kMaxSets];
+    uint64_t numel[kMaxSets];
+};
+static_assert(sizeof(PairArgs) <= 4096, "kernel arguments");
 
 template <int H>
-__global__ void __launch_bounds__(2 * kWave, 2) sdl_gram_pair_kernel(const GramArgs a)
+__global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(H <= 5 ? 3 : 2))) sdl_gramfma_pair_kernel(const PairArgs a)
 {
-    constexpr int kOff = (H + 1) / 2;     // entries of the block rows x columns per row
+    constexpr int kOff = (H + 1) / 2;                // entries of the block rows x columns per row
+    constexpr int kTri = H * (H + 1) / 2, kSums = kTri + H * kOff, kLeft = halved(kSums);
+    __shared__ float diff[2][2 * H][kPairTile];      // outer gradients of two tiles
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    uint32_t s = 0;
-    while (s + 1 < a.n_pieces && blockIdx.x >= a.pieces[s + 1].first_wg) ++s;
-    const Piece set = a.pieces[s];
-    const bool fast = set.fast != 0u;
     const uint32_t M = a.M;
 
-    auto row = [&](int i) -> uint32_t { return wave ? (uint32_t)(H + i) : (uint32_t)i; };
-    auto col = [&](int j) -> uint32_t { return wave ? (uint32_t)((j + 1) % H) : (uint32_t)(H + j); };
-    const uint16_t* w[2 * H];
+    auto row = [&](uint32_t i) -> uint32_t { return wave * H + i; };
+    auto col = [&](uint32_t j) -> uint32_t { return wave ? (j + 1u) % H : H + j; };
+    const uint16_t* w[H];
 #pragma unroll
-    for (int i = 0; i < H; ++i) {
-        w[i] = a.w[row(i) < M ? row(i) : 0u];
-        w[H + i] = a.w[col(i) < M ? col(i) : 0u];
-    }
+    for (int i = 0; i < H; ++i) w[i] = a.w[row(i) < M ? row(i) : 0u];
 
-    double tri[H][H], off[H][kOff];
+    auto stage = [&](uint32_t buf, const PairRaw<H>& t) {
 #pragma unroll
-    for (int i = 0; i < H; ++i) {
-#pragma unroll
-        for (int j = 0; j < H; ++j) tri[i][j] = 0.0;
-#pragma unroll
-        for (int j = 0; j < kOff; ++j) off[i][j] = 0.0;
-    }
-
-    auto consume = [&](const PairTile<H>& t) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            double d[2 * H];
-#pragma unroll
-            for (int m = 0; m < 2 * H; ++m) {
-                const uint32_t u = t.w[m][e / 2];
-                d[m] = (double)(t.g[e] - u2f((e & 1) ? (u & 0xffff0000u) : (u << 16)));   // one fp32 subtraction
-            }
-#pragma unroll
-            for (int i = 0; i < H; ++i) {
-#pragma unroll
-                for (int j = i; j < H; ++j) tri[i][j] = __builtin_fma(d[i], d[j], tri[i][j]);
-#pragma unroll
-                for (int j = 0; j < kOff; ++j) off[i][j] = __builtin_fma(d[i], d[H + (i + j) % H], off[i][j]);
-            }
+        for (int i = 0; i < H; ++i) {
+            const f32x4_elem d = {t.g.x - u2f(t.w[i].x << 16), t.g.y - u2f(t.w[i].x & 0xffff0000u), t.g.z - u2f(t.w[i].y << 16),
+                                  t.g.w - u2f(t.w[i].y & 0xffff0000u)};
+            *reinterpret_cast<f32x4_elem __attribute__((aligned(16)))*>(&diff[buf][row(i)][lane * 4]) = d;
         }
     };
-
-    const uint64_t step = (uint64_t)set.G * kPairTile;
-    uint64_t at = (uint64_t)(blockIdx.x - set.first_wg) * kPairTile;
-    PairTile<H> cur;
-    if (at < set.numel) load_pair_tile<H>(cur, a.g, w, set.offset + at, set.numel - at, fast, lane);
-    for (; at < set.numel; at += step) {
-        PairTile<H> nxt = cur;
-        const uint64_t an = at + step;
-        if (an < set.numel) load_pair_tile<H>(nxt, a.g, w, set.offset + an, set.numel - an, fast, lane);
-        __builtin_amdgcn_sched_barrier(0);   // the loads stay ahead of the arithmetic
-        consume(cur);
-        cur = nxt;
-    }
-
-    double* out = a.partial + (uint64_t)blockIdx.x * M * M;
-    auto store = [&](uint32_t x, uint32_t y, double v) {
-        v = wave_sum(v);
-        if (lane == 0 && x < M && y < M) out[x < y ? x * M + y : y * M + x] = v;
+    // every 64th parameter of the tile: lane l's part-th one is part * 64 + l
+    float f[2 * H];
+    auto read = [&](uint32_t buf, int part) {
+        const float* mine = &diff[buf][row(0)][part * kWave + lane];
+        const float* theirs = &diff[buf][col(0)][part * kWave + lane];
+#pragma unroll
+        for (int i = 0; i < H; ++i) f[i] = mine[i * kPairTile];
+#pragma unroll
+        for (int j = 0; j < H - 1; ++j) f[H + j] = theirs[j * kPairTile];
+        f[2 * H - 1] = diff[buf][col(H - 1)][part * kWave + lane];
+        __builtin_amdgcn_sched_barrier(0);
     };
+    double sum[kSums];                               // the rows' triangle, then the block's entries
+    // Whole chains of the diagonal entries.  Squares of short mantissas end alike, so where a sum has outgrown them the ties of its
+    // roundings all go one way, and the error grows with the chain: with chains of a lane's 800 parameters the entries G[m][m]
+    // err by 7.5e-16 for replicas with outliers (52.9 M parameters), with chains of 16 by 0.9e-16.  Products of different
+    // replicas do not.
+    double squares[H];
+    // the sums of one parameter; once it is converted, the next one is read into the same registers
+    auto consume = [&](auto read_next) {
+        double d[2 * H];
 #pragma unroll
-    for (int i = 0; i < H; ++i) {
+        for (int m = 0; m < 2 * H; ++m) d[m] = (double)f[m];
 #pragma unroll
-        for (int j = i; j < H; ++j) store(row(i), row(j), tri[i][j]);
+        for (int m = 0; m < 2 * H; ++m) asm volatile("" : "+v"(d[m]));    // converted here, not where it is first used
+        read_next();
+        int k = 0;
 #pragma unroll
-        for (int j = 0; j < kOff; ++j)
-            if (!(H % 2 == 1 && j == kOff - 1 && wave == 1u))    // the diagonal that both formed: once is enough
-                store(row(i), col((i + j) % H), off[i][j]);
-    }
-}
+        for (int i = 0; i < H; ++i)
+#pragma unroll
+            for (int j = i; j < H; ++j, ++k) sum[k] = __builtin_fma(d[i], d[j], sum[k]);
+#pragma unroll
+        for (int i = 0; i < H; ++i)
+#pragma unroll
+            for (int j = 0; j < kOff; ++j, ++k) sum[k] = __builtin_fma(d[i], d[H + (i + j) % H], sum[k]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto end_chain = [&]() {
+        int k = 0;
+#pragma unroll
+        for (int i = 0; i < H; k += H - i, ++i) { squares[i] += sum[k]; sum[k] = 0.0; }
+    };
 
-// 13 to 16 replicas: the matrix cores form the whole matrix, v_mfma_f64_16x16x4_f64 taking four parameters of up to 16
-// replicas at a time.  Lane l holds replica l % 16's value of parameter l / 16, which is the instruction's layout of the left
-// operand and of the right one alike.  Bound: the matrix pipe, 256 fp64 FMAs per parameter (half of them for the lower
-// triangle; rows behind the last replica repeat replica 0 and are not stored): 52.9 M parameters at the 77 TFLOP/s that a
-// chain of this instruction reaches take 350 us, HBM 268 us at 16 replicas; the loads alone take 370 us in this layout, the
-// arithmetic alone (the same few lines loaded again and again) 494: the conversions and additions between the chains are
-// fp64 operations as well.  Whole call at 13 / 16 replicas: 698 / 935 us as 8 x 8 blocks in three launches, 502 / 510 now.
-// A load covers 64 bytes of 16 arrays; the chunk of 64 parameters that a wavefront takes at a time is a whole line of each.
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-constexpr int kMfmaWaves = 4;             // wavefronts per workgroup, which adds their matrices up before it writes one
-constexpr int kMfmaChunk = 64;            // parameters: 16 per lane, as two pieces of 8
-
-struct MfmaChunk {
-    u32x4 g[2][2], w[2];
-};
-
-// g and w: the lane's first parameter of the chunk (w in the lane's replica).
-__device__ __forceinline__ void load_chunk(MfmaChunk& c, const float* g, const uint16_t* w)
-{
+    const uint32_t b = blockIdx.x;
+    Share share = a.shares[0];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const u32x4_f32elem* pg = reinterpret_cast<const u32x4_f32elem*>(g + 32 * h);
-        c.g[h][0] = pg[0];
-        c.g[h][1] = pg[1];
-        c.w[h] = *reinterpret_cast<const u32x4_bf16elem*>(w + 32 * h);
-    }
-}
-
-// The instruction rounds its sums towards zero, so a chain of it is kept to 4 (16 parameters); a chunk's four chains and the
-// chunks are added by plain additions, which round to nearest, at two levels so that neither is long.  Root mean square of the
-// error of G[m][m] against exact sums, M = 16, in units of 1e-16, for the recipes normal / student_t3 / outliers / an outer
-// gradient with full mantissas: 0.26 M parameters 0.9 / 0.8 / 0.9 / 0.8, 8.4 M 1.0 / 0.9 / 0.9 / 0.8, 52.9 M 1.0 / 0.6 / 1.2 / 1.1;
-// the plain FMAs of sdl_gram_kernel at M = 8 give 0.8 / 0.8 / 0.8 / 0.8, 1.0 / 0.8 / 0.9 / 0.5 and 0.9 / 0.4 / 3.5 / 3.7.  One
-// chain for a chunk: outliers 2.4, full mantissas 1.8 at every size.  Chains of 8: 1.4 and 1.3, of 2: 0.7 and 0.8.  The whole
-// call at 52.9 M parameters: 488 us with chains of 16, 495 with 8, 510 with 4, 550 with 2.
-constexpr int kMfmaChain = 4;
-
-struct MfmaSums {
-    f64x4 total = {};     // whole chunks
-    f64x4 part = {};      // the chains of a chunk
-    f64x4 last = {};      // the latest chain, added one chain later, when its instructions have ended
-};
-
-__device__ __forceinline__ void add_chunk(const MfmaChunk& c, MfmaSums& s)
-{
-    f64x4 acc = {};
+    for (int i = 1; i < kShares; ++i)
+        if (b >= a.shares[i].first_wg) share = a.shares[i];
+    const uint32_t nth = b - share.first_wg;
+    uint32_t t = share.first_tile + nth * share.per_wg + (nth < share.extra ? nth : share.extra);
+    const uint32_t end = t + share.per_wg + (nth < share.extra ? 1u : 0u);
+    while (t < end) {
+        uint32_t group = 0;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        float f[kLaneElems];
-        deltas(c.g[h][0], c.g[h][1], c.w[h], f);
+        for (int i = 16; i < kMaxSets; i += 16)
+            if (t >= a.first_tile[i]) group = (uint32_t)i;
+        uint32_t s = group;
 #pragma unroll
-        for (int j = 0; j < kLaneElems; ++j) {
-            const int k = h * kLaneElems + j;
-            const double d = (double)f[j];
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(d, d, k % kMfmaChain ? acc : f64x4{}, 0, 0, 0);
-            if (k % kMfmaChain != kMfmaChain - 1) continue;
-            if (k / kMfmaChain == 0) {                // ends the chunk before this one
-                s.part += s.last;
-                s.total += s.part;
-                asm volatile("" : "+v"(s.total));
-            } else if (k / kMfmaChain == 1) {
-                s.part = s.last;
-            } else {
-                s.part += s.last;
-                asm volatile("" : "+v"(s.part));
-            }
-            s.last = acc;
-            // Additions stay with their half of the chunk: moved to the end of the tile, they would keep every chain's sums
-            // alive, more than the registers hold (spilled ones are read back behind the next chunk's loads).
-            if (j == kLaneElems - 1) __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-}
+        for (int i = 1; i < 16; ++i)
+            if (t >= a.first_tile[group + i]) s = group + (uint32_t)i;
+        const uint32_t set_first = a.first_tile[s], set_end = a.first_tile[s + 1], stop = end < set_end ? end : set_end;
+        const uint64_t offset = a.offset[s], numel = a.numel[s];
+        const uint32_t whole = (uint32_t)(numel / kPairTile), last = stop - set_first < whole ? stop - set_first : whole;
+        uint32_t k = t - set_first;
+#pragma unroll
+        for (int i = 0; i < kSums; ++i) sum[i] = 0.0;
+#pragma unroll
+        for (int i = 0; i < H; ++i) squares[i] = 0.0;
 
-// (four wavefronts per SIMD: left to itself the compiler takes registers for three, 539 us against 504)
-__global__ void __launch_bounds__(kMfmaWaves * kWave) __attribute__((amdgpu_waves_per_eu(4)))
-sdl_gram_mfma_kernel(const GramArgs a)
-{
-    __shared__ double mats[kMfmaWaves][16 * 16];
-    const uint32_t lane = threadIdx.x & (kWave - 1);
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    uint32_t s = 0;
-    while (s + 1 < a.n_pieces && blockIdx.x >= a.pieces[s + 1].first_wg) ++s;
-    const Piece set = a.pieces[s];
-    const uint32_t M = a.M, replica = lane % 16, quarter = lane / 16;
-    const float* g = a.g + set.offset + quarter * kLaneElems;
-    const uint16_t* w = a.w[replica < M ? replica : 0u] + set.offset + quarter * kLaneElems;
-
-    MfmaSums sums;
-    const uint64_t n_whole = set.numel / kTile, step = (uint64_t)set.G * kMfmaWaves;
-    uint64_t t = (uint64_t)wave * set.G + (blockIdx.x - set.first_wg);
-    MfmaChunk c[2];
-    if (t < n_whole) load_chunk(c[0], g + t * kTile, w + t * kTile);
-    for (; t < n_whole; t += step) {
-#pragma unroll
-        for (int k = 0; k < kTile / kMfmaChunk; ++k) {
-            // the next chunk's loads go out before this one is consumed, and stay there (the compiler would move each down
-            // to its first use)
-            if (k + 1 < kTile / kMfmaChunk) {
-                const uint64_t e = t * kTile + (k + 1) * kMfmaChunk;
-                load_chunk(c[(k + 1) % 2], g + e, w + e);
-            } else if (t + step < n_whole) {
-                load_chunk(c[0], g + (t + step) * kTile, w + (t + step) * kTile);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            add_chunk(c[k % 2], sums);
-        }
-    }
-    if (t == n_whole && t * kTile < set.numel) {
-        // ragged tail: g = 0 and w = 0 past the end give an outer gradient of 0
-        const uint32_t left = (uint32_t)(set.numel - t * kTile);
-        for (uint32_t at = 0; at < left; at += kMfmaChunk) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int j = 0; j < kLaneElems; ++j) {
-                    const bool there = at + 32 * h + quarter * kLaneElems + j < left;
-                    const uint64_t e = t * kTile + at + 32 * h + j;
-                    c[0].g[h][j / 4][j % 4] = there ? f2u(g[e]) : 0u;
-                    const uint32_t x = there ? (uint32_t)w[e] : 0u;
-                    c[0].w[h][j / 2] = j % 2 ? c[0].w[h][j / 2] | (x << 16) : x;
+        // whole tiles k, k + 1, ...: while one is consumed the next one lies in the other half of diff, or will by the time of
+        // the barrier, and the one after it is on its way into registers (behind the last tile: that tile again)
+        auto walk = [&](auto is_fast) {
+            constexpr bool FAST = decltype(is_fast)::value;
+            PairRaw<H> raw;
+            auto load = [&](uint32_t n) {
+                load_pair_raw<H, FAST>(raw, a.g, w, offset + (uint64_t)(n < last ? n : last - 1u) * kPairTile, lane);
+            };
+            uint32_t buf = 0;
+            load(k);
+            lds_barrier();       // the tile before this set has been read
+            stage(0, raw);
+            load(k + 1u);
+            lds_barrier();
+            read(0, 0);
+            while (k < last) {
+                const uint32_t chain = last - k < (uint32_t)kPairChain ? last : k + kPairChain;
+                for (; k < chain; ++k, buf ^= 1u) {
+                    consume([&]() { read(buf, 1); });
+                    consume([&]() { read(buf, 2); });
+                    stage(buf ^ 1u, raw);
+                    load(k + 2u);
+                    consume([&]() { read(buf, 3); });
+                    lds_barrier();
+                    consume([&]() { read(buf ^ 1u, 0); });
                 }
-            add_chunk(c[0], sums);
+                end_chain();
+            }
+        };
+        if (k < last) {
+            if (a.fast) walk(std::true_type{});
+            else walk(std::false_type{});
         }
+        if (stop - set_first > whole) {
+            PairRaw<H> raw;
+            load_pair_tail<H>(raw, a.g, w, offset + (uint64_t)whole * kPairTile, (uint32_t)(numel - (uint64_t)whole * kPairTile), lane);
+            lds_barrier();
+            stage(0, raw);
+            lds_barrier();
+#pragma unroll 1
+            for (int part = 0; part < kPairTile / kWave; ++part) {
+                read(0, part);
+                consume([]() {});
+            }
+        }
+        end_chain();
+        {
+            int d = 0;
+#pragma unroll
+            for (int i = 0; i < H; d += H - i, ++i) sum[d] = squares[i];
+        }
+        halve<kSums, 0>(sum, lane);
+
+        // which sums the lane ended up with: at each level the lower lane kept the first half of them
+        uint32_t first = 0, count = kSums, n = kSums, lane_here = lane;
+        asm volatile("" : "+v"(lane_here));      // (computed ahead of the loop, this would hold registers that it needs)
+        for (int level = 0; level < 6; ++level) {
+            const uint32_t half = (n + 1u) / 2u;
+            if ((lane_here >> (5 - level)) & 1u) { first += half; count = count > half ? count - half : 0u; }
+            else count = count < half ? count : half;
+            n = half;
+        }
+        double* out = a.partial + (uint64_t)(uint32_t)((int32_t)b + a.slot[s]) * M * M;
+#pragma unroll
+        for (uint32_t v = 0; v < (uint32_t)kLeft; ++v) {
+            if (v >= count) continue;
+            uint32_t i = 0, j = first + v;
+            if (j < (uint32_t)kTri) {
+                while (j >= H - i) { j -= H - i; ++i; }
+                j = row(i + j);
+            } else {
+                i = (j - kTri) / kOff;
+                const uint32_t o = (j - kTri) % kOff;
+                if (H % 2 == 1 && o == kOff - 1 && wave == 1u) continue;     // the diagonal that both formed: once is enough
+                j = col((i + o) % H);
+            }
+            i = row(i);
+            if (i < M && j < M) out[i < j ? i * M + j : j * M + i] = sum[v];
+        }
+        t = stop;
     }
-    const f64x4 total = sums.total + (sums.part + sums.last);
-    // register i of lane l: row 4 i + l / 16, column l % 16
-#pragma unroll
-    for (int i = 0; i < 4; ++i) mats[wave][(4 * i + quarter) * 16 + replica] = total[i];
-    __syncthreads();
-    static_assert(kMfmaWaves * kWave == 16 * 16, "one thread per entry");
-    const uint32_t row = threadIdx.x / 16, col = threadIdx.x % 16;
-    double v = 0.0;
-#pragma unroll
-    for (int k = 0; k < kMfmaWaves; ++k) v += mats[k][threadIdx.x];
-    if (row <= col && col < M) a.partial[(uint64_t)blockIdx.x * M * M + row * M + col] = v;
 }
 
 // What each output of the finalize kernel adds up.
@@ -494,19 +531,20 @@ __host__ __device__ constexpr uint32_t fin_slices(uint32_t M)
 }
 constexpr uint32_t fin_chunk(uint32_t M) { return 8u * fin_slices(M); }
 
-constexpr uint32_t groups_per_launch(uint32_t M) { return M > (uint32_t)kPairM ? kWideGroups : kGroups; }
+// matrices of a launch, without one for each set
+constexpr uint32_t mats_per_launch(uint32_t M) { return M > 8u ? kShares * pair_resident(M) : kGroups; }
 
-// A launch over n sets has at most groups_per_launch + n workgroups, so at most (groups_per_launch + n) / fin_chunk + n
+// A launch over n sets leaves at most mats_per_launch + n matrices, so at most (mats_per_launch + n) / fin_chunk + n
 // first-level outputs: kFirstLevel and one for each set, of which the workspace and the arguments have room.
 constexpr uint32_t kFirstLevel = kMaxGroups / 64 + 2;
 constexpr int kMaxFin = kFirstLevel + 2 * kMaxSets;                       // outputs per finalize launch
 constexpr bool sums_fit()
 {
     for (uint32_t M = 1; M <= SDL_MAX_WORKERS; ++M)
-        if (groups_per_launch(M) > kMaxGroups || (groups_per_launch(M) + kMaxSets) / fin_chunk(M) > kFirstLevel) return false;
+        if (mats_per_launch(M) > kMaxGroups || (mats_per_launch(M) + kMaxSets) / fin_chunk(M) > kFirstLevel) return false;
     return true;
 }
-static_assert(sums_fit(), "workgroups per launch, matrices per first-level output and the workspace go together");
+static_assert(sums_fit(), "matrices per launch, matrices per first-level output and the workspace go together");
 
 struct FinArgs {
     const double* in;              // matrices of M*M doubles (only a <= b is read), stride_k doubles apart
@@ -591,9 +629,7 @@ int launch_kernel(uint32_t M, const GramArgs& a, hipStream_t st)
     case 6: hipLaunchKernelGGL((sdl_gram_kernel<6>), grid, one, 0, st, a); break;
     case 7: hipLaunchKernelGGL((sdl_gram_kernel<7>), grid, one, 0, st, a); break;
     case 8: hipLaunchKernelGGL((sdl_gram_kernel<8>), grid, one, 0, st, a); break;
-    case 9: case 10: hipLaunchKernelGGL((sdl_gram_pair_kernel<5>), grid, dim3(2 * kWave), 0, st, a); break;
-    case 11: case 12: hipLaunchKernelGGL((sdl_gram_pair_kernel<6>), grid, dim3(2 * kWave), 0, st, a); break;
-    default: hipLaunchKernelGGL(sdl_gram_mfma_kernel, grid, dim3(kMfmaWaves * kWave), 0, st, a); break;
+    default: return SDL_ERR_INVALID_ARG;
     }
     return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
 }
@@ -661,12 +697,84 @@ int launch_gram(const float* g, const void* const* w, uint32_t M, const Set* set
     return launch_kernel(M, a, st);
 }
 
+// Partial Gram matrices of more than 8 replicas; sets[s].first_wg and .G become the numbers of set s's first matrix and of its
+// matrices.  n_mats = all of them.
+int launch_pair(const float* g, const void* const* w, uint32_t M, Set* sets, uint32_t n_sets, double* partial, uint32_t* n_mats,
+                hipStream_t st)
+{
+    const uint32_t H = (M + 1u) / 2u;
+    PairArgs a{};
+    a.g = g;
+    a.partial = partial;
+    a.M = M;
+    for (uint32_t m = 0; m < M; ++m) a.w[m] = static_cast<const uint16_t*>(w[m]);
+    uint64_t tiles = 0;
+    bool fast = true;
+    for (uint32_t s = 0; s < n_sets; ++s) {
+        a.first_tile[s] = (uint32_t)tiles;
+        a.offset[s] = sets[s].offset;
+        a.numel[s] = sets[s].numel;
+        tiles += (sets[s].numel + kPairTile - 1) / kPairTile;
+        if (tiles >= 0xffffffffull) return SDL_ERR_UNSUPPORTED;
+        fast = fast && aligned16(g + sets[s].offset);
+        for (uint32_t m = 0; m < M; ++m) fast = fast && aligned16(static_cast<const uint16_t*>(w[m]) + sets[s].offset);
+    }
+    a.fast = fast ? 1u : 0u;
+    a.first_tile[n_sets] = (uint32_t)tiles;
+    for (uint32_t s = n_sets + 1u; s <= (uint32_t)kMaxSets; ++s) a.first_tile[s] = 0xffffffffu;
+    const uint32_t resident = pair_resident(M);
+    uint32_t mats = 0, n_wg = 0, at = 0;
+    constexpr uint32_t kPercent[kShares] = {85, 70, 100};      // of what is left
+    for (int i = 0; i < kShares; ++i) {
+        const uint32_t left = (uint32_t)tiles - at, n = (uint32_t)((uint64_t)left * kPercent[i] / 100u);
+        const uint32_t wgs = n < resident ? n : resident;
+        a.shares[i] = Share{n_wg, at, wgs ? n / wgs : 0u, wgs ? n % wgs : 0u};
+        n_wg += wgs;
+        at += n;
+    }
+    auto wg_of = [&](uint32_t t) {
+        int i = kShares - 1;
+        while (i > 0 && t < a.shares[i].first_tile) --i;
+        const Share& sh = a.shares[i];
+        const uint32_t nth = t - sh.first_tile, longer = sh.extra * (sh.per_wg + 1u);
+        return sh.first_wg + (nth < longer ? nth / (sh.per_wg + 1u) : sh.extra + (nth - longer) / sh.per_wg);
+    };
+    for (uint32_t s = 0; s < n_sets; ++s) {
+        sets[s].first_wg = mats;
+        sets[s].G = 0;
+        if (a.first_tile[s + 1] == a.first_tile[s]) continue;
+        const uint32_t b0 = wg_of(a.first_tile[s]), b1 = wg_of(a.first_tile[s + 1] - 1u);
+        a.slot[s] = (int32_t)mats - (int32_t)b0;
+        sets[s].G = b1 - b0 + 1u;
+        mats += sets[s].G;
+    }
+    *n_mats = mats;
+    if (!n_wg) return SDL_OK;
+    const dim3 grid(n_wg), block(2 * kWave);
+    switch (H) {
+    case 5: hipLaunchKernelGGL((sdl_gramfma_pair_kernel<5>), grid, block, 0, st, a); break;
+    case 6: hipLaunchKernelGGL((sdl_gramfma_pair_kernel<6>), grid, block, 0, st, a); break;
+    case 7: hipLaunchKernelGGL((sdl_gramfma_pair_kernel<7>), grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL((sdl_gramfma_pair_kernel<8>), grid, block, 0, st, a); break;
+    }
+    return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
+}
+
 int launch_finalize(const FinArgs& f, uint32_t n_out, hipStream_t st)
 {
     // whole wavefronts for the entries and their slices: 64 threads at one replica, 192 at two (idle ones cost their barriers)
     const uint32_t threads = (f.M * (f.M + 1u) / 2u * fin_slices(f.M) + kWave - 1u) / kWave * kWave;
     hipLaunchKernelGGL(sdl_gram_finalize, dim3(n_out), dim3(threads), 0, st, f);
     return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
+}
+
+// Partial Gram matrices of up to kMaxSets sets into `partial`; where they lie goes into the sets.
+int launch_sums(const float* g, const void* const* w, uint32_t M, Set* sets, uint32_t n_sets, double* partial, uint32_t* n_mats,
+                hipStream_t st)
+{
+    if (M > 8u) return launch_pair(g, w, M, sets, n_sets, partial, n_mats, st);
+    *n_mats = share_groups(sets, n_sets, kGroups);
+    return launch_gram(g, w, M, sets, n_sets, partial, st);
 }
 
 // One result per set from the partial matrices of its workgroups (the sets' workgroups lie one behind the other) and, if
@@ -778,10 +886,10 @@ int sdl_outer_grad_cosine(const float* g, const void* const* w, uint32_t M, uint
     if (workspace_bytes < sdl_cosine_workspace_bytes(M, 1)) return SDL_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     Set set{0, numel, 0, 0};
-    share_groups(&set, 1, groups_per_launch(M));
     double* partial = static_cast<double*>(workspace);
     double* tmp = partial + partial_mats(1) * M * M;
-    rc = launch_gram(g, w, M, &set, 1, partial, st);
+    uint32_t n_mats = 0;
+    rc = launch_sums(g, w, M, &set, 1, partial, &n_mats, st);
     if (rc != SDL_OK) return rc;
     return finalize_sets(partial, &set, 1, M, result, nullptr, tmp, st);
 }
@@ -801,7 +909,6 @@ int sdl_outer_grad_cosine_plan(const sdl_plan_t* plan, uint32_t p, const float* 
     if (rc != SDL_OK) return rc;
     if (workspace_bytes < sdl_cosine_workspace_bytes(M, n_spans)) return SDL_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const uint32_t groups = groups_per_launch(M);
     const uint64_t mm = (uint64_t)M * M, R = SDL_COSINE_RESULT_DOUBLES(M);
     double* partial = static_cast<double*>(workspace);
     double* tmp = partial + partial_mats(n_spans) * mm;
@@ -811,16 +918,16 @@ int sdl_outer_grad_cosine_plan(const sdl_plan_t* plan, uint32_t p, const float* 
         const uint32_t ns = n_spans - s0 < (uint32_t)kMaxSets ? n_spans - s0 : (uint32_t)kMaxSets;
         Set sets[kMaxSets];
         for (uint32_t s = 0; s < ns; ++s) sets[s] = Set{spans[s0 + s].offset, spans[s0 + s].numel, 0, 0};
-        const uint32_t n_wg = share_groups(sets, ns, groups);
+        uint32_t n_mats = 0;
         double* part = partial + used * mm;
-        rc = launch_gram(g_base, w_base, M, sets, ns, part, st);
+        rc = launch_sums(g_base, w_base, M, sets, ns, part, &n_mats, st);
         if (rc != SDL_OK) return rc;
         // the spans of one launch give the fragment's result as well
         rc = finalize_sets(part, sets, ns, M, per_span + (uint64_t)s0 * R, ns == n_spans ? fragment_result : nullptr,
                            tmp + used_tmp * mm, st);
         if (rc != SDL_OK) return rc;
-        used += n_wg;
-        used_tmp += n_wg / fin_chunk(M) + ns;
+        used += n_mats;
+        used_tmp += n_mats / fin_chunk(M) + ns;
     }
     if (n_spans && n_spans <= (uint32_t)kMaxSets) return SDL_OK;
     // the fragment: Gram matrices of its spans added in span order
