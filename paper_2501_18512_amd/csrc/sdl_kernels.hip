@@ -17,7 +17,7 @@
 // Full, 16-byte aligned tiles use buffer instructions with non-temporal cache policy
 // (every byte is touched once); full tiles of runs in which some array starts at some other
 // element use vector accesses of element alignment in the same lane layout; ragged tails use
-// range-checked accesses of one element each.  A launch covers up to kMaxRuns contiguous runs of the flat
+// range-checked accesses of one element each.  A launch covers up to 272 contiguous runs of the flat
 // model; every workgroup belongs to exactly one run, so scale blocks never straddle
 // runs.
 //
@@ -51,9 +51,9 @@ constexpr int kRow = kVec * kWave;            // parameters per row (256); a wor
 constexpr int kPad = kRow * kMaxRows;          // message and staging layouts pad every piece to this many
                                               // parameters (512): a whole number of tiles of either height
 constexpr int kRunGroup = 16;                 // runs whose first workgroups a workgroup compares at once
-constexpr int kMaxRuns = 7 * kRunGroup;       // runs per launch (3.8 KB of kernel arguments)
+constexpr int kTableWords = 3 * 17 * kRunGroup;   // what a launch says about its runs (3.9 KB of kernel arguments in all)
 constexpr int kCheckedRuns = 16;              // pieces over which a fragment's workgroups are added up for the size check
-constexpr uint64_t kMaxRunElems = 1ull << 31;  // longest run of a launch (its numbers are 32-bit); longer ones are cut here
+constexpr uint64_t kMaxRunElems = 1ull << 30;  // longest run of a launch (its numbers are 32-bit); longer ones are cut here
 
 enum Mode { kQuantize = 0, kReduce = 1, kMerge = 2, kFused = 3, kReceive = 5 };   // kReceive = kReduce + kMerge
 
@@ -96,16 +96,18 @@ enum TilePath : uint32_t {
     kPathVector = 2,    // some array starts at some other element (or, messages of 4 and 8 bits, byte)
 };
 
-// A run of a launch.  32-bit numbers relative to the launch's bases, so that many runs fit the kernel arguments.
-struct Run {
-    uint32_t first_wg;   // first workgroup of the launch that works on this run
-    uint32_t offset;     // first element of the run in the flat arrays, from Args::offset0
-    uint32_t numel;
-    uint32_t msg;        // where the run starts in the message arrays, in units of 512 elements
-    uint32_t soff;       // where the run starts in g / mom, from Args::soff0 (the same as offset unless they are staged)
-    uint32_t sidx_path;  // TilePath of the run's whole tiles in the two low bits; above them, for the whole-span
-                         // scale, the index of the run's 4-byte scale word
-};
+// What a launch says about its runs, in 32-bit numbers relative to the launch's bases, three words a run so that as many as
+// possible fit the kernel arguments: 272 runs (a fragment of 193 groups of 100 to 30000 parameters, M = 2: 20.8 us as two launches
+// of 112 runs and 81, 17.5 as one).  Every run takes the workgroups of whole 512-element pieces, so the workgroup's number
+// alone says where its tile lies in the messages and in staged g / mom, which hold the runs back to back in such pieces;
+// where a tile has 256 parameters the last workgroup of a run may have nothing to do.  A whole-span format adds two words:
+// the index of the run's scale word, and, since its runs are parts of what is staged, where it starts there.
+constexpr int kRunWords = 3, kSpanRunWords = 5;
+constexpr int run_words(int fmt) { return is_span_scaled(fmt) ? kSpanRunWords : kRunWords; }
+constexpr int max_runs(int fmt) { return kTableWords / run_words(fmt) / kRunGroup * kRunGroup; }
+// words of the table: the first workgroup of each run, ascending, 0xffffffff behind the last; then the runs
+template <int FMT> constexpr uint32_t run_word(uint32_t r) { return (uint32_t)max_runs(FMT) + r * (uint32_t)(run_words(FMT) - 1); }
+constexpr uint32_t kVectorBit = 1u << 31;      // in a run's number of elements: its whole tiles take kPathVector
 
 struct Args {
     float* g;
@@ -115,17 +117,17 @@ struct Args {
     uint8_t* codes[SDL_MAX_WORKERS];
     uint8_t* scales[SDL_MAX_WORKERS];
     uint64_t offset0;    // what the runs' offsets count from, in the replicas and in g / mom
-    uint64_t soff0;
+    uint64_t msg0;       // where the first run starts in the message arrays
+    uint64_t soff0;      // and in staged g / mom
     uint32_t n_runs;
     uint32_t M;
     float lr, mu, alpha, one_minus_alpha;
     uint32_t aliased;    // w_send[m] == w_now[m]
     uint32_t emit;       // fused kernel: also write the messages
     uint32_t staged;     // g / mom point at a staging buffer that holds only this fragment
-    uint32_t chunked;    // each XCD takes kChunkRows consecutive rows (see chunked_tile)
-    uint32_t group_wg[kMaxRuns / kRunGroup];   // first workgroup of every 16th run
-    uint32_t first_wg[kMaxRuns];               // first workgroup of each run, ascending; 0xffffffff behind the last
-    Run runs[kMaxRuns];
+    uint32_t chunked;    // of the workgroups below this one each XCD takes kChunkRows consecutive rows (see chunked_tile)
+    uint32_t group_wg[kTableWords / kRunWords / kRunGroup - 1];   // first workgroup of the 16th, 32nd, ... run
+    uint32_t table[kTableWords];
 };
 static_assert(sizeof(Args) <= 4096, "kernel arguments");
 
@@ -349,7 +351,9 @@ struct TileIOT {
     uint32_t lane;
     uint32_t sidx;    // whole-span scale: index of the run's scale word
     uint64_t s0;      // tile's first element in g / mom (= t0 unless the state is staged)
+    uint32_t limit;   // ALIGNED: elements of the tile that exist (a multiple of 4, so that a lane has all four or none)
 
+    template <int B> __device__ __forceinline__ uint32_t scale_bytes() const { return ALIGNED ? (limit + B - 1) / B : kTile / B; }
     // bit pattern of the span's absolute maximum (whole-span scale)
     __device__ __forceinline__ uint32_t span_amax(uint32_t m) const
     {
@@ -362,7 +366,7 @@ struct TileIOT {
         } else {
             constexpr int B = block_elems(FMT);
             const uint32_t sb = __builtin_amdgcn_raw_buffer_load_b8(
-                rsrc(a.scales[m] + tb / B, kTile / B), (int)(row * (kRow / B) + lane / (B / kVec)), 0, kAuxScale);
+                rsrc(a.scales[m] + tb / B, scale_bytes<B>()), (int)(row * (kRow / B) + lane / (B / kVec)), 0, kAuxScale);
             return scale_from_byte(sb);
         }
     }
@@ -371,33 +375,33 @@ struct TileIOT {
         if constexpr (!is_span_scaled(FMT)) {
             constexpr int B = block_elems(FMT);
             if ((lane % (B / kVec)) == 0u)
-                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)sb, rsrc(a.scales[m] + tb / B, kTile / B),
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)sb, rsrc(a.scales[m] + tb / B, scale_bytes<B>()),
                                                      (int)(row * (kRow / B) + lane / (B / kVec)), 0, kAuxScale);
         }
     }
     // p = address of the tile's first element in the array
     __device__ __forceinline__ void ld_f32(const float* p, int row, float (&v)[kVec]) const
     {
-        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rsrc(p, kTile * 4),
+        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rsrc(p, limit * 4),
                                                               (int)(row * kRow * 4 + lane * 16), 0, kAuxLoad);
         v[0] = u2f(x.x); v[1] = u2f(x.y); v[2] = u2f(x.z); v[3] = u2f(x.w);
     }
     __device__ __forceinline__ void st_f32(float* p, int row, const float (&v)[kVec]) const
     {
         const u32x4 x = {f2u(v[0]), f2u(v[1]), f2u(v[2]), f2u(v[3])};
-        __builtin_amdgcn_raw_buffer_store_b128(x, rsrc(p, kTile * 4), (int)(row * kRow * 4 + lane * 16), 0,
+        __builtin_amdgcn_raw_buffer_store_b128(x, rsrc(p, limit * 4), (int)(row * kRow * 4 + lane * 16), 0,
                                                kAuxStore);
     }
     __device__ __forceinline__ void ld_bf16(const uint16_t* p, int row, uint32_t (&u)[2]) const
     {
-        const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(rsrc(p, kTile * 2),
+        const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(rsrc(p, limit * 2),
                                                              (int)(row * kRow * 2 + lane * 8), 0, kAuxLoad);
         u[0] = x.x; u[1] = x.y;
     }
     __device__ __forceinline__ void st_bf16(uint16_t* p, int row, const uint32_t (&u)[2]) const
     {
         const u32x2 x = {u[0], u[1]};
-        __builtin_amdgcn_raw_buffer_store_b64(x, rsrc(p, kTile * 2), (int)(row * kRow * 2 + lane * 8), 0,
+        __builtin_amdgcn_raw_buffer_store_b64(x, rsrc(p, limit * 2), (int)(row * kRow * 2 + lane * 8), 0,
                                               kAuxStore);
     }
 
@@ -485,12 +489,12 @@ struct TileIOT {
         } else {
             const float scale = load_scale<FMT>(m, row);
             if constexpr (is_e3m0(FMT)) {
-                const uint32_t c0 = __builtin_amdgcn_raw_buffer_load_b16(rsrc(codes + tb / 2, kTile / 2),
+                const uint32_t c0 = __builtin_amdgcn_raw_buffer_load_b16(rsrc(codes + tb / 2, limit / 2),
                                                                          (int)(row * (kRow / 2) + lane * 2), 0,
                                                                          kAuxLoad);
                 decode_e3m0(c0, scale, dq);
             } else {
-                const uint32_t c0 = __builtin_amdgcn_raw_buffer_load_b32(rsrc(codes + tb, kTile),
+                const uint32_t c0 = __builtin_amdgcn_raw_buffer_load_b32(rsrc(codes + tb, limit),
                                                                          (int)(row * kRow + lane * 4), 0, kAuxLoad);
                 decode_e4m3<EXACT>(c0, scale, dq);
             }
@@ -512,19 +516,19 @@ struct TileIOT {
             }
         } else if constexpr (FMT == SDL_FMT_FP32) {
             const u32x4 x = {c[0], c[1], c[2], c[3]};
-            __builtin_amdgcn_raw_buffer_store_b128(x, rsrc(codes + tb * 4, kTile * 4),
+            __builtin_amdgcn_raw_buffer_store_b128(x, rsrc(codes + tb * 4, limit * 4),
                                                    (int)(row * kRow * 4 + lane * 16), 0, kAuxStore);
         } else if constexpr (FMT == SDL_FMT_BF16) {
             const u32x2 x = {c[0], c[1]};
-            __builtin_amdgcn_raw_buffer_store_b64(x, rsrc(codes + tb * 2, kTile * 2),
+            __builtin_amdgcn_raw_buffer_store_b64(x, rsrc(codes + tb * 2, limit * 2),
                                                   (int)(row * kRow * 2 + lane * 8), 0, kAuxStore);
         } else {
             store_scale<FMT>(m, row, sb);
             if constexpr (is_e3m0(FMT)) {
-                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)c[0], rsrc(codes + tb / 2, kTile / 2),
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)c[0], rsrc(codes + tb / 2, limit / 2),
                                                       (int)(row * (kRow / 2) + lane * 2), 0, kAuxStore);
             } else {
-                __builtin_amdgcn_raw_buffer_store_b32(c[0], rsrc(codes + tb, kTile), (int)(row * kRow + lane * 4), 0,
+                __builtin_amdgcn_raw_buffer_store_b32(c[0], rsrc(codes + tb, limit), (int)(row * kRow + lane * 4), 0,
                                                       kAuxStore);
             }
         }
@@ -863,24 +867,25 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
 // shares its first and last line with its neighbours; on another XCD that line is fetched into a second L2 and written in
 // two parts, so consecutive tiles go to one XCD, kChunkRows rows at a time (72 M parameters of odd groups, fused: M = 2
 // 388 -> 329 us, M = 4 572 -> 483, M = 8 892 -> 869; half or twice the chunk is up to 2 % slower, and arrays that start on a
-// line lose 3-8 % with it).  The rule (RunBuilder, flush) asks for 16 bytes and not for a line: it was measured on arrays that
-// start at any element and on arrays that start on a line.  Those in between, where every group is a multiple of 8 elements
-// but not of 64, take the buffer path in the order of the grid, at about the rate that unaligned arrays have without chunks.
+// line lose 3-8 % with it).  The rule (RunBuilder, flush) asks whether a run starts on a line in every array: groups of 1000 and
+// 3 M parameters, which start on 16 bytes, without chunks and with: fused M = 2 374 and 342 us, M = 4 545 and 475, M = 8 856 and
+// 826, send M = 4 179 and 174, receive M = 4 475 and 420, M = 2 332 and 294.
 constexpr int kXcds = 8;
 constexpr int kChunkRows = 8;
 template <int ROWS>
 __device__ __forceinline__ uint32_t chunked_tile(uint32_t wg)
 {
     constexpr uint32_t C = kChunkRows / ROWS, whole = kXcds * C;
-    return wg < gridDim.x / whole * whole ? wg / whole * whole + (wg % kXcds) * C + (wg / kXcds) % C : wg;
+    return wg / whole * whole + (wg % kXcds) * C + (wg / kXcds) % C;
 }
 
-// Has the addresses that a call's loads need in scalar registers from here on (the compiler would ask for each where it is
-// first used, one wait after the other).
+// Has what a call's loads need in scalar registers from here on (the compiler would ask for each where it is first used, one
+// wait after the other).
 template <int MODE, int MT, bool ALIASED>
 __device__ __forceinline__ void touch_arguments(const Args& a)
 {
-    asm volatile("" :: "s"(a.g), "s"(a.n_runs), "s"(a.chunked), "s"(a.first_wg[1]));
+    asm volatile("" :: "s"(a.g), "s"(a.n_runs), "s"(a.chunked), "s"(a.staged), "s"(a.offset0), "s"(a.soff0));
+    if constexpr (MODE != kMerge) asm volatile("" :: "s"(a.msg0));
     if constexpr (MODE == kReduce || MODE == kFused || MODE == kReceive) asm volatile("" :: "s"(a.mom));
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
@@ -895,42 +900,67 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kWavesPer
 void sdl_kernel(const Args a)
 {
     // The start of a wavefront is a chain of dependent scalar loads, and with 8 wavefronts on a compute unit nothing
-    // hides it: what does not depend on the run (the arrays' addresses, the first 16 first workgroups) is asked for at once.
+    // hides it: what does not depend on the run (the arrays' addresses, the first 16 first workgroups, the first run) is asked for
+    // at once.
+    uint32_t behind[kRunGroup - 1];                  // first workgroups of the 15 runs behind the first of the group
+#pragma unroll
+    for (int i = 1; i < kRunGroup; ++i) behind[i - 1] = a.table[i];
+    uint32_t run = run_word<FMT>(0), first = 0, at = a.table[run], size = a.table[run + 1u], sidx = 0, soff = 0;
+    if constexpr (is_span_scaled(FMT)) { sidx = a.table[run + 2u]; soff = a.table[run + 3u]; }
     touch_arguments<MODE, MT, ALIASED>(a);
+    asm volatile("" :: "s"(at), "s"(size), "s"(sidx), "s"(soff), "s"(a.group_wg[0]), "s"(a.group_wg[1]), "s"(a.group_wg[2]), "s"(a.group_wg[3]),
+                 "s"(a.group_wg[4]), "s"(a.group_wg[5]));
+#pragma unroll
+    for (int i = 1; i < kRunGroup; ++i) asm volatile("" :: "s"(behind[i - 1]));
     // Which run does this workgroup work on.  The first workgroups of 16 runs are one scalar load, compared all at once;
     // with more runs than that, those of every 16th run come first.  (Entry by entry it was a chain of scalar loads as long
     // as the list: 8.5 us for a launch of 16 small runs.  One vector load and a ballot are two dependent loads as well, but
-    // the streams push the arguments out of the vector caches: 7 % slower on a fragment of 6 large runs.)
+    // the streams push the arguments out of the vector caches: 7 % slower on a fragment of 6 large runs.)  The scalar
+    // instructions count as well: 16 groups compared where 6 would do, and three instructions to an entry, cost 5-6 % on 97 runs
+    // with tiles of one row.
     constexpr int ROWS = tile_rows(MODE, MT, FMT);
-    const uint32_t wg = a.chunked ? chunked_tile<ROWS>(blockIdx.x) : blockIdx.x;
-    uint32_t base = 0;
-    if (a.n_runs > (uint32_t)kRunGroup) {
-#pragma unroll
-        for (int i = 1; i < kMaxRuns / kRunGroup; ++i)
-            if (wg >= a.group_wg[i]) base = (uint32_t)(i * kRunGroup);
-    }
-    uint32_t r = base;
-#pragma unroll
-    for (int i = 1; i < kRunGroup; ++i)
-        if (wg >= a.first_wg[base + i]) r = base + i;
-    const Run run = a.runs[r];
-    asm volatile("" :: "s"(run.first_wg), "s"(run.offset), "s"(run.numel), "s"(run.msg), "s"(run.soff), "s"(run.sidx_path),
-                 "s"(a.offset0), "s"(a.soff0));
-    const uint32_t path = run.sidx_path & 3u, sidx = run.sidx_path >> 2;
+    const uint32_t wg = blockIdx.x < a.chunked ? chunked_tile<ROWS>(blockIdx.x) : blockIdx.x;
     constexpr uint32_t kTile = ROWS * kRow;
-    const uint32_t tile = (wg - run.first_wg) * kTile;   // first element of the tile in the run
-    const uint64_t t0 = a.offset0 + run.offset + tile;
-    const uint64_t tb = (uint64_t)run.msg * kPad + tile;
-    const uint64_t s0 = a.soff0 + run.soff + tile;
-    const bool whole = run.numel - tile >= kTile;
-    if (!whole) {
-        const TailIO io{a, t0, tb, s0, run.numel - tile, threadIdx.x, sidx};
+    if (a.n_runs > 1u) {
+        uint32_t base = 0, r = kRunGroup - 1;
+        constexpr int kGroups = max_runs(FMT) / kRunGroup, kFew = kGroups < 7 ? kGroups : 7;
+        if (a.n_runs > (uint32_t)kRunGroup) {
+#pragma unroll
+            for (int i = 1; i < kFew; ++i)
+                if (wg >= a.group_wg[i - 1]) base = (uint32_t)(i * kRunGroup);
+            if (a.n_runs > (uint32_t)(kFew * kRunGroup)) {
+#pragma unroll
+                for (int i = kFew; i < kGroups; ++i)
+                    if (wg >= a.group_wg[i - 1]) base = (uint32_t)(i * kRunGroup);
+            }
+#pragma unroll
+            for (int i = 1; i < kRunGroup; ++i) behind[i - 1] = a.table[base + i];
+        }
+#pragma unroll
+        for (int i = kRunGroup - 1; i >= 1; --i)
+            if (wg < behind[i - 1]) r = (uint32_t)(i - 1);
+        r += base;
+        run = run_word<FMT>(r);
+        first = a.table[r];
+        at = a.table[run];
+        size = a.table[run + 1u];
+        if constexpr (is_span_scaled(FMT)) { sidx = a.table[run + 2u]; soff = a.table[run + 3u]; }
+        asm volatile("" :: "s"(first), "s"(at), "s"(size), "s"(sidx), "s"(soff));
+    }
+    const uint32_t numel = size & ~kVectorBit, tile = (wg - first) * kTile;   // first element of the tile in the run
+    if (tile >= numel) return;
+    const uint64_t t0 = a.offset0 + at + tile;
+    const uint64_t tb = a.msg0 + (uint64_t)wg * kTile;
+    const uint64_t s0 = !a.staged ? t0 : is_span_scaled(FMT) ? a.soff0 + soff + tile : a.soff0 + (uint64_t)wg * kTile;
+    const uint32_t left = numel - tile;
+    if (left < kTile && ((size & kVectorBit) || numel % kVec != 0u)) {
+        const TailIO io{a, t0, tb, s0, left, threadIdx.x, sidx};
         process<MODE, FMT, 0, ALIASED, EMIT, ROWS>(a, io);
-    } else if (path == kPathBuffer) {
-        const TileIOT<true, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0};
+    } else if (!(size & kVectorBit)) {
+        const TileIOT<true, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0, left < kTile ? left : kTile};
         process<MODE, FMT, MT, ALIASED, EMIT, ROWS>(a, io);
     } else {
-        const TileIOT<false, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0};
+        const TileIOT<false, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0, kTile};
         process<MODE, FMT, MT, ALIASED, EMIT, ROWS>(a, io);
     }
 }
@@ -1340,12 +1370,21 @@ hipError_t launch(const Args& a, sdl_format_t fmt, uint32_t n_wg, hipStream_t s)
 
 bool valid_format(sdl_format_t fmt) { return fmt >= SDL_FMT_FP32 && fmt <= SDL_FMT_E3M0_RN; }
 
-// 16-byte alignment of a call's pointers: model = g, mom and the replicas; msg = codes (scale
-// bytes need none).
-struct Align16 {
-    bool model = true, msg = true;
+// Alignment of a call's pointers (model: g, mom and the replicas; msg: the codes, scale bytes need none), and then of a run's
+// first element: model asks for what the four elements of a lane need, wide for 16 bytes in every array, line for a cache line.
+struct Align {
+    bool model = true, wide = true, line = true, msg = true;
+    void add_model(const void* p)
+    {
+        model = wide = model && aligned(p, 16);
+        line = line && aligned(p, 128);
+    }
+    Align at(uint64_t offset, uint64_t soff) const
+    {
+        const uint64_t low = offset | soff;
+        return Align{model && low % kVec == 0, wide && low % 8 == 0, line && low % 64 == 0, msg};
+    }
     TilePath path() const { return model && msg ? kPathBuffer : kPathVector; }
-    Align16 at(bool run_start_aligned) const { return Align16{model && run_start_aligned, msg}; }
 };
 
 // Parameters per workgroup of the kernel variant that a call in this mode will run.
@@ -1354,39 +1393,45 @@ uint32_t tile_elems(int mode, const Args& a, sdl_format_t fmt)
     return (uint32_t)(tile_rows(mode, (int)variant_mt(mode, a.M, a.emit != 0u), (int)fmt) * kRow);
 }
 
-// Fills a.runs from a list of pieces, launch by launch.  A piece longer than kMaxRunElems takes several runs (they start at
+// Fills a launch's run table from a list of pieces.  A piece longer than kMaxRunElems takes several runs (they start at
 // multiples of 512 elements, so scale blocks and tiles stay where they were).
 struct RunBuilder {
     Args* a;
     uint64_t tile;       // parameters per workgroup
+    uint32_t words, most;      // of a run; runs that the table has room for
     uint64_t n_wg = 0, n_unaligned = 0;
-    RunBuilder(Args* args, uint32_t tile_elems) : a(args), tile(tile_elems) { reset(); }
+    RunBuilder(Args* args, uint32_t tile_elems, sdl_format_t fmt)
+        : a(args), tile(tile_elems), words((uint32_t)run_words(fmt)), most((uint32_t)max_runs(fmt)) { reset(); }
     void reset()
     {
         a->n_runs = 0;
         n_wg = n_unaligned = 0;
-        std::memset(a->first_wg, 0xff, sizeof(a->first_wg));
+        std::memset(a->table, 0xff, sizeof(uint32_t) * most);
         std::memset(a->group_wg, 0xff, sizeof(a->group_wg));
     }
+    // Workgroups of a run: those of whole 512-element pieces.
+    uint64_t wgs(uint64_t n) const { return (n + kPad - 1) / kPad * (kPad / tile); }
     // Whether a run of n elements still fits this launch: a free entry, numbers that fit 32 bits from the first run's,
     // and a grid that stays within the launch limit.
-    bool fits(uint64_t offset, uint64_t n, uint64_t msg, uint64_t soff) const
+    bool fits(uint64_t offset, uint64_t n, uint64_t soff) const
     {
         if (a->n_runs == 0) return true;
-        return a->n_runs < (uint32_t)kMaxRuns && offset >= a->offset0 && offset - a->offset0 <= 0xffffffffull
-               && (!a->staged || (soff >= a->soff0 && soff - a->soff0 <= 0xffffffffull)) && n_wg + (n + tile - 1) / tile <= 0x7fffffffull
-               && msg / kPad <= 0xffffffffull;
+        return a->n_runs < most && offset >= a->offset0 && offset - a->offset0 <= 0xffffffffull
+               && (!a->staged || (soff >= a->soff0 && soff - a->soff0 <= 0xffffffffull)) && n_wg + wgs(n) <= 0x7fffffffull;
     }
-    void add(uint64_t offset, uint64_t n, Align16 al, uint64_t msg, uint32_t sidx, uint64_t soff)
+    // msg and soff of a run are those of the run before it and its 512-element pieces (soff with a whole-span format is not).
+    void add(uint64_t offset, uint64_t n, Align al, uint64_t msg, uint32_t sidx, uint64_t soff)
     {
-        if (!a->staged) soff = offset;
-        if (a->n_runs == 0) { a->offset0 = offset; a->soff0 = soff; }
-        a->first_wg[a->n_runs] = (uint32_t)n_wg;
-        if (a->n_runs % kRunGroup == 0) a->group_wg[a->n_runs / kRunGroup] = (uint32_t)n_wg;
-        a->runs[a->n_runs++] = Run{(uint32_t)n_wg, (uint32_t)(offset - a->offset0), (uint32_t)n, (uint32_t)(msg / kPad),
-                                   (uint32_t)(soff - a->soff0), (sidx << 2) | (uint32_t)al.path()};
-        n_wg += (n + tile - 1) / tile;
-        if (!al.model) n_unaligned += (n + tile - 1) / tile;
+        if (a->n_runs == 0) { a->offset0 = offset; a->msg0 = msg; a->soff0 = soff; }
+        const uint32_t r = a->n_runs++;
+        a->table[r] = (uint32_t)n_wg;
+        if (r % kRunGroup == 0 && r) a->group_wg[r / kRunGroup - 1] = (uint32_t)n_wg;
+        uint32_t* const run = a->table + most + r * (words - 1);
+        run[0] = (uint32_t)(offset - a->offset0);
+        run[1] = (uint32_t)n | (al.path() == kPathVector ? kVectorBit : 0u);
+        if (words == (uint32_t)kSpanRunWords) { run[2] = sidx; run[3] = (uint32_t)(soff - a->soff0); }
+        n_wg += wgs(n);
+        if (!al.line) n_unaligned += wgs(n);
     }
 };
 
@@ -1426,7 +1471,9 @@ template <int MODE>
 bool flush(RunBuilder& rb, sdl_format_t fmt, void* stream)
 {
     if (rb.a->n_runs == 0) return true;
-    rb.a->chunked = 2 * rb.n_unaligned > rb.n_wg ? 1u : 0u;   // what most of the launch's tiles want (see chunked_tile)
+    // what most of the launch's tiles want (see chunked_tile)
+    const uint32_t whole = kXcds * kChunkRows / (uint32_t)(rb.tile / kRow);
+    rb.a->chunked = 2 * rb.n_unaligned > rb.n_wg ? (uint32_t)rb.n_wg / whole * whole : 0u;
     const hipError_t e = launch<MODE>(*rb.a, fmt, (uint32_t)rb.n_wg, (hipStream_t)stream);
     rb.reset();
     return e == hipSuccess;
@@ -1434,12 +1481,12 @@ bool flush(RunBuilder& rb, sdl_format_t fmt, void* stream)
 
 // Adds one piece, cut to kMaxRunElems, launching whenever the launch is full.
 template <int MODE>
-bool add_piece(RunBuilder& rb, sdl_format_t fmt, uint64_t offset, uint64_t numel, Align16 al, uint64_t msg, uint32_t sidx,
+bool add_piece(RunBuilder& rb, sdl_format_t fmt, uint64_t offset, uint64_t numel, Align al, uint64_t msg, uint32_t sidx,
                uint64_t soff, void* stream)
 {
     for (uint64_t at = 0; at < numel; at += kMaxRunElems) {
         const uint64_t n = numel - at < kMaxRunElems ? numel - at : kMaxRunElems;
-        if (!rb.fits(offset + at, n, msg + at, soff + at) && !flush<MODE>(rb, fmt, stream)) return false;
+        if (!rb.fits(offset + at, n, soff + at) && !flush<MODE>(rb, fmt, stream)) return false;
         rb.add(offset + at, n, al, msg + at, sidx, soff + at);
     }
     return true;
@@ -1447,7 +1494,7 @@ bool add_piece(RunBuilder& rb, sdl_format_t fmt, uint64_t offset, uint64_t numel
 
 // One span starting at the given pointers (offset 0).
 template <int MODE>
-int run_single_span(Args& a, uint64_t n, sdl_format_t fmt, Align16 al, void* stream)
+int run_single_span(Args& a, uint64_t n, sdl_format_t fmt, Align al, void* stream)
 {
     if (n == 0) return SDL_OK;
     const uint32_t tile = tile_elems(MODE, a, fmt);
@@ -1460,11 +1507,11 @@ int run_single_span(Args& a, uint64_t n, sdl_format_t fmt, Align16 al, void* str
     if constexpr (MODE == kQuantize || MODE == kFused) {
         if (is_span_scaled(fmt)) {
             // whole-span scale: clear the scale word, take the grid-wide maximum, then encode
-            const SpanRun one{0, n, 0, al.model, 0};
+            const SpanRun one{0, n, 0, al.wide, 0};
             if (launch_span_prepass(a, &one, 1, (hipStream_t)stream) != hipSuccess) return SDL_ERR_DEVICE;
         }
     }
-    RunBuilder rb(&a, tile);
+    RunBuilder rb(&a, tile, fmt);
     return add_piece<MODE>(rb, fmt, 0, n, al, 0, 0, 0, stream) && flush<MODE>(rb, fmt, stream) ? SDL_OK : SDL_ERR_DEVICE;
 }
 
@@ -1483,14 +1530,14 @@ int sdl_quantize_outer_grad(const float* g, const void* const* w_send, uint32_t 
     std::memset(&a, 0, sizeof(a));
     a.g = const_cast<float*>(g);
     a.M = M;
-    Align16 al;
-    al.model = aligned(g, 16);
+    Align al;
+    al.add_model(g);
     if (!aligned(g, 4)) return SDL_ERR_ALIGNMENT;
     for (uint32_t m = 0; m < M; ++m) {
         if (!w_send[m] || !codes[m] || (scaled && !scales[m])) return SDL_ERR_INVALID_ARG;
         if (!aligned(w_send[m], 2) || !aligned(codes[m], code_align(fmt))) return SDL_ERR_ALIGNMENT;
         if (scaled && !aligned(scales[m], scale_align(fmt))) return SDL_ERR_ALIGNMENT;
-        al.model = al.model && aligned(w_send[m], 16);
+        al.add_model(w_send[m]);
         al.msg = al.msg && aligned(codes[m], 16);
         a.w_send[m] = static_cast<const uint16_t*>(w_send[m]);
         a.codes[m] = static_cast<uint8_t*>(codes[m]);
@@ -1511,8 +1558,9 @@ int sdl_dequant_reduce_nesterov(float* g, float* mom, const void* const* codes,
     Args a;
     std::memset(&a, 0, sizeof(a));
     a.g = g; a.mom = mom; a.M = M; a.lr = lr; a.mu = mu;
-    Align16 al;
-    al.model = aligned(g, 16) && aligned(mom, 16);
+    Align al;
+    al.add_model(g);
+    al.add_model(mom);
     for (uint32_t m = 0; m < M; ++m) {
         if (!codes[m] || (scaled && !scales[m])) return SDL_ERR_INVALID_ARG;
         if (!aligned(codes[m], code_align(fmt))) return SDL_ERR_ALIGNMENT;
@@ -1527,7 +1575,7 @@ int sdl_dequant_reduce_nesterov(float* g, float* mom, const void* const* codes,
 // Argument marshalling shared by the receive-side calls that also merge.
 static int fill_receive_args(Args& a, float* g, float* mom, const void* const* codes, const void* const* scales,
                              void* const* w_now, uint32_t M, sdl_format_t fmt, float lr, float mu, float alpha,
-                             Align16* al)
+                             Align* al)
 {
     if (!valid_format(fmt) || M == 0 || M > SDL_MAX_WORKERS) return SDL_ERR_INVALID_ARG;
     const bool scaled = is_scaled(fmt);
@@ -1535,12 +1583,14 @@ static int fill_receive_args(Args& a, float* g, float* mom, const void* const* c
     if (!aligned(g, 4) || !aligned(mom, 4)) return SDL_ERR_ALIGNMENT;
     std::memset(&a, 0, sizeof(a));
     a.g = g; a.mom = mom; a.M = M; a.lr = lr; a.mu = mu; a.alpha = alpha; a.one_minus_alpha = 1.0f - alpha;
-    *al = Align16{aligned(g, 16) && aligned(mom, 16), true};
+    *al = Align{};
+    al->add_model(g);
+    al->add_model(mom);
     for (uint32_t m = 0; m < M; ++m) {
         if (!codes[m] || !w_now[m] || (scaled && !scales[m])) return SDL_ERR_INVALID_ARG;
         if (!aligned(codes[m], code_align(fmt)) || !aligned(w_now[m], 2)) return SDL_ERR_ALIGNMENT;
         if (scaled && !aligned(scales[m], scale_align(fmt))) return SDL_ERR_ALIGNMENT;
-        al->model = al->model && aligned(w_now[m], 16);
+        al->add_model(w_now[m]);
         al->msg = al->msg && aligned(codes[m], 16);
         a.codes[m] = static_cast<uint8_t*>(const_cast<void*>(codes[m]));
         a.scales[m] = scaled ? static_cast<uint8_t*>(const_cast<void*>(scales[m])) : nullptr;
@@ -1555,7 +1605,7 @@ int sdl_receive_outer_step(float* g, float* mom, const void* const* codes, const
 {
     if (n == 0) return (valid_format(fmt) && M >= 1 && M <= SDL_MAX_WORKERS) ? SDL_OK : SDL_ERR_INVALID_ARG;
     Args a;
-    Align16 al;
+    Align al;
     int rc = fill_receive_args(a, g, mom, codes, scales, w_now, M, fmt, lr, mu, alpha, &al);
     if (rc != SDL_OK) return rc;
     return run_single_span<kReceive>(a, n, fmt, al, stream);
@@ -1571,12 +1621,12 @@ int sdl_merge_overlap(const float* g_new, void* const* w_now, uint32_t M, uint64
     Args a;
     std::memset(&a, 0, sizeof(a));
     a.g = const_cast<float*>(g_new); a.M = M; a.alpha = alpha; a.one_minus_alpha = 1.0f - alpha;
-    Align16 al;
-    al.model = aligned(g_new, 16);
+    Align al;
+    al.add_model(g_new);
     for (uint32_t m = 0; m < M; ++m) {
         if (!w_now[m]) return SDL_ERR_INVALID_ARG;
         if (!aligned(w_now[m], 2)) return SDL_ERR_ALIGNMENT;
-        al.model = al.model && aligned(w_now[m], 16);
+        al.add_model(w_now[m]);
         a.w_now[m] = static_cast<uint16_t*>(w_now[m]);
     }
     return run_single_span<kMerge>(a, n, SDL_FMT_FP32, al, stream);
@@ -1584,7 +1634,7 @@ int sdl_merge_overlap(const float* g_new, void* const* w_now, uint32_t M, uint64
 
 // Shared argument marshalling of the two fused entry points.
 static int fill_fused_args(Args& a, float* g, float* mom, const void* const* w_send, void* const* w_now,
-                           uint32_t M, sdl_format_t fmt, float lr, float mu, float alpha, Align16* al)
+                           uint32_t M, sdl_format_t fmt, float lr, float mu, float alpha, Align* al)
 {
     if (!valid_format(fmt) || M == 0 || M > SDL_MAX_WORKERS) return SDL_ERR_INVALID_ARG;
     if (!g || !mom || !w_send || !w_now) return SDL_ERR_INVALID_ARG;
@@ -1592,12 +1642,15 @@ static int fill_fused_args(Args& a, float* g, float* mom, const void* const* w_s
     std::memset(&a, 0, sizeof(a));
     a.g = g; a.mom = mom; a.M = M; a.lr = lr; a.mu = mu; a.alpha = alpha;
     a.one_minus_alpha = 1.0f - alpha;
-    *al = Align16{aligned(g, 16) && aligned(mom, 16), true};
+    *al = Align{};
+    al->add_model(g);
+    al->add_model(mom);
     uint32_t same = 0;
     for (uint32_t m = 0; m < M; ++m) {
         if (!w_send[m] || !w_now[m]) return SDL_ERR_INVALID_ARG;
         if (!aligned(w_send[m], 2) || !aligned(w_now[m], 2)) return SDL_ERR_ALIGNMENT;
-        al->model = al->model && aligned(w_send[m], 16) && aligned(w_now[m], 16);
+        al->add_model(w_send[m]);
+        al->add_model(w_now[m]);
         same += (w_send[m] == w_now[m]);
         a.w_send[m] = static_cast<const uint16_t*>(w_send[m]);
         a.w_now[m] = static_cast<uint16_t*>(w_now[m]);
@@ -1610,7 +1663,7 @@ static int fill_fused_args(Args& a, float* g, float* mom, const void* const* w_s
 // Optional message outputs of a fused call; the whole-span scale needs its scale words as
 // workspace even when no message is written.
 static int attach_fused_messages(Args& a, uint32_t M, sdl_format_t fmt, void* const* codes_or_null,
-                                 void* const* scales_or_null, Align16* al)
+                                 void* const* scales_or_null, Align* al)
 {
     if (codes_or_null) {
         const bool scaled = is_scaled(fmt);
@@ -1641,7 +1694,7 @@ int sdl_fragment_outer_step(float* g, float* mom, const void* const* w_send, voi
 {
     if (n == 0) return (valid_format(fmt) && M >= 1 && M <= SDL_MAX_WORKERS) ? SDL_OK : SDL_ERR_INVALID_ARG;
     Args a;
-    Align16 al;
+    Align al;
     int rc = fill_fused_args(a, g, mom, w_send, w_now, M, fmt, lr, mu, alpha, &al);
     if (rc != SDL_OK) return rc;
     rc = attach_fused_messages(a, M, fmt, codes_or_null, scales_or_null, &al);
@@ -1657,11 +1710,11 @@ int sdl_fragment_outer_step(float* g, float* mom, const void* const* w_send, voi
 // each padded to whole tiles) and in staged g / mom (the fragment's runs back to back, each padded
 // to whole tiles).  Holds no storage of its own: the callers walk it once per pass.
 struct PieceWalk {
-    struct Piece { uint64_t offset, numel, msg, soff; Align16 al; uint32_t sidx; };
+    struct Piece { uint64_t offset, numel, msg, soff; Align al; uint32_t sidx; };
     const sdl_span_t* runs;
     const sdl_span_t* pieces;
     uint32_t n_runs, n_pieces;
-    Align16 al;
+    Align al;
     bool staged;
     uint32_t i = 0, run_i = 0;
     uint64_t msg = 0, run_start = 0;
@@ -1676,8 +1729,7 @@ struct PieceWalk {
                 ++run_i;
             }
             const uint64_t soff = run_i < n_runs ? run_start + (pieces[i].offset - runs[run_i].offset) : 0;
-            // a piece keeps the 16-byte alignment of the bases when it starts on a multiple of 8 elements
-            const Align16 piece_al = al.at((pieces[i].offset % 8 == 0) && (!staged || soff % 8 == 0));
+            const Align piece_al = al.at(pieces[i].offset, staged ? soff : pieces[i].offset);
             *out = Piece{pieces[i].offset, pieces[i].numel, msg, soff, piece_al, i};
             msg += (pieces[i].numel + kPad - 1) / kPad * kPad;
             ++i;
@@ -1691,7 +1743,7 @@ struct PieceWalk {
 // the concatenation of its runs, each padded to a multiple of 512 elements.  No host or device
 // memory is allocated on the way.
 template <int MODE>
-static int launch_fragment(Args& a, const sdl_plan_t* plan, uint32_t p, Align16 al, sdl_format_t fmt, void* stream)
+static int launch_fragment(Args& a, const sdl_plan_t* plan, uint32_t p, Align al, sdl_format_t fmt, void* stream)
 {
     const sdl_span_t* runs = nullptr;
     const sdl_span_t* pieces = nullptr;
@@ -1731,7 +1783,7 @@ static int launch_fragment(Args& a, const sdl_plan_t* plan, uint32_t p, Align16 
         uint32_t nb = 0;
         PieceWalk walk = start;
         for (bool more = walk.next(&pc); more || nb;) {
-            if (more) batch[nb++] = SpanRun{pc.offset, pc.numel, pc.soff, pc.al.model, pc.sidx};
+            if (more) batch[nb++] = SpanRun{pc.offset, pc.numel, pc.soff, pc.al.wide, pc.sidx};
             more = more && walk.next(&pc);
             if (nb == (uint32_t)kAbsmaxMaxRuns || !more) {
                 if (launch_span_prepass(a, batch, nb, (hipStream_t)stream) != hipSuccess) return SDL_ERR_DEVICE;
@@ -1739,7 +1791,7 @@ static int launch_fragment(Args& a, const sdl_plan_t* plan, uint32_t p, Align16 
             }
         }
     }
-    RunBuilder rb(&a, tile);
+    RunBuilder rb(&a, tile, fmt);
     PieceWalk walk = start;
     while (walk.next(&pc))
         if (!add_piece<MODE>(rb, fmt, pc.offset, pc.numel, pc.al, pc.msg, pc.sidx, pc.soff, stream)) return SDL_ERR_DEVICE;
@@ -1774,7 +1826,7 @@ static int fused_fragment(const sdl_plan_t* plan, uint32_t p, float* g_base, flo
     // the whole-span scale needs scale words as workspace: only the calls that take them support it
     if (valid_format(fmt) && is_span_scaled(fmt) && !scales_or_null) return SDL_ERR_UNSUPPORTED;
     Args a;
-    Align16 al;
+    Align al;
     int rc = fill_fused_args(a, g_base, mom_base, w_send_base, w_now_base, M, fmt, lr, mu, alpha, &al);
     if (rc != SDL_OK) return rc;
     rc = attach_fused_messages(a, M, fmt, codes_or_null, scales_or_null, &al);
@@ -1796,13 +1848,13 @@ static int quantize_fragment(const sdl_plan_t* plan, uint32_t p, const float* g_
     std::memset(&a, 0, sizeof(a));
     a.g = const_cast<float*>(g_base);
     a.M = M;
-    Align16 al;
-    al.model = aligned(g_base, 16);
+    Align al;
+    al.add_model(g_base);
     for (uint32_t m = 0; m < M; ++m) {
         if (!w_send_base[m] || !codes[m] || (scaled && !scales[m])) return SDL_ERR_INVALID_ARG;
         if (!aligned(w_send_base[m], 2) || !aligned(codes[m], code_align(fmt))) return SDL_ERR_ALIGNMENT;
         if (scaled && !aligned(scales[m], scale_align(fmt))) return SDL_ERR_ALIGNMENT;
-        al.model = al.model && aligned(w_send_base[m], 16);
+        al.add_model(w_send_base[m]);
         al.msg = al.msg && aligned(codes[m], 16);
         a.w_send[m] = static_cast<const uint16_t*>(w_send_base[m]);
         a.codes[m] = static_cast<uint8_t*>(codes[m]);
@@ -1824,8 +1876,9 @@ static int reduce_fragment(const sdl_plan_t* plan, uint32_t p, float* g_base, fl
     Args a;
     std::memset(&a, 0, sizeof(a));
     a.g = g_base; a.mom = mom_base; a.M = M; a.lr = lr; a.mu = mu;
-    Align16 al;
-    al.model = aligned(g_base, 16) && aligned(mom_base, 16);
+    Align al;
+    al.add_model(g_base);
+    al.add_model(mom_base);
     for (uint32_t m = 0; m < M; ++m) {
         if (!codes[m] || (scaled && !scales[m])) return SDL_ERR_INVALID_ARG;
         if (!aligned(codes[m], code_align(fmt))) return SDL_ERR_ALIGNMENT;
@@ -1844,7 +1897,7 @@ static int receive_fragment(const sdl_plan_t* plan, uint32_t p, float* g_base, f
 {
     if (!plan || p >= sdl_plan_num_fragments(plan)) return SDL_ERR_INVALID_ARG;
     Args a;
-    Align16 al;
+    Align al;
     int rc = fill_receive_args(a, g_base, mom_base, codes, scales, w_now_base, M, fmt, lr, mu, alpha, &al);
     if (rc != SDL_OK) return rc;
     a.staged = staged ? 1u : 0u;
@@ -1860,12 +1913,12 @@ static int merge_fragment(const sdl_plan_t* plan, uint32_t p, const float* g_new
     Args a;
     std::memset(&a, 0, sizeof(a));
     a.g = const_cast<float*>(g_new_base); a.M = M; a.alpha = alpha; a.one_minus_alpha = 1.0f - alpha;
-    Align16 al;
-    al.model = aligned(g_new_base, 16);
+    Align al;
+    al.add_model(g_new_base);
     for (uint32_t m = 0; m < M; ++m) {
         if (!w_now_base[m]) return SDL_ERR_INVALID_ARG;
         if (!aligned(w_now_base[m], 2)) return SDL_ERR_ALIGNMENT;
-        al.model = al.model && aligned(w_now_base[m], 16);
+        al.add_model(w_now_base[m]);
         a.w_now[m] = static_cast<uint16_t*>(w_now_base[m]);
     }
     a.staged = staged ? 1u : 0u;
