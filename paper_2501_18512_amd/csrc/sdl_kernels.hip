@@ -1243,6 +1243,21 @@ uint32_t waves_per_cu(int mode, uint32_t mt, uint32_t M, int fmt, bool aliased, 
     }
 }
 
+// Launches that end within a few rounds of workgroups have no page locality to lose and want at least 16: up to 112 MiB moved.
+// us on one card, states that rotate through more than the memory-side cache, as capped above and with 16 (fused, E3M0, but where named):
+// M = 2, 29 MB 7.2 7.0, 59 MB 12.1 11.8, 117 MB 21.8 21.3, 235 MB 39.5 39.7; M = 4, 42 MB 9.9 9.5, 84 MB 16.7 16.6, 126 MB 22.9 23.5,
+// 168 MB 29.6 30.4; w_send aliases w_now, M = 2, 25 MB 6.5 5.6; receive, M = 4, 64 MB 15.5 14.9; M = 5, 72 MB 18.2 17.2; M = 16, 160 MB
+// 40.3 37.3; messages, BF16, M = 4, 88 MB 19.4 19.0, 280 MB 47.1 49.3; 193 groups of 100 to 30000 parameters, M = 2, 70 MB 16.1 15.4.
+constexpr uint64_t kSmallLaunch = 112ull << 20;
+constexpr uint32_t kSmallWaves = 16;
+uint64_t bytes_per_param(int mode, uint32_t M, bool aliased, bool emit, int fmt)
+{
+    const uint64_t state = mode == kMerge ? 4 : mode == kQuantize ? 4 : 16;
+    const uint64_t send = (mode == kQuantize || (mode == kFused && !aliased)) ? 2 : 0, merge = (mode == kReduce || mode == kQuantize) ? 0 : 4;
+    const uint64_t code = fmt == SDL_FMT_FP32 ? 4 : fmt == SDL_FMT_BF16 ? 2 : 1;
+    return state + M * (send + merge + (mode == kFused && !emit ? 0 : mode == kMerge ? 0 : code));
+}
+
 // The cap takes the form of dynamic LDS that nothing uses: 160 KiB per CU, given out in units of 1280 bytes (measured: 6826
 // and 7680 bytes leave 21 wavefronts on a CU, 7681 leave 18, 12800 12, 13653 and 14080 11, 14081 10).
 constexpr uint32_t kLdsPerCu = 163840, kLdsUnit = 1280;
@@ -1255,7 +1270,10 @@ hipError_t launch_m(const Args& a, uint32_t n_wg, hipStream_t s)
 {
     const dim3 grid(n_wg), block(kWave);
     const uint32_t mt = variant_mt(MODE, a.M, EMIT);   // the grid was sized for this variant's tile
-    const uint32_t lds = lds_cap_bytes(waves_per_cu(MODE, mt, a.M, FMT, ALIASED, EMIT));
+    uint32_t waves = waves_per_cu(MODE, mt, a.M, FMT, ALIASED, EMIT);
+    const uint64_t params = (uint64_t)n_wg * (uint64_t)(tile_rows(MODE, (int)mt, FMT) * kRow);
+    if (waves && waves < kSmallWaves && params * bytes_per_param(MODE, a.M, ALIASED, EMIT, FMT) <= kSmallLaunch) waves = kSmallWaves;
+    const uint32_t lds = lds_cap_bytes(waves);
     switch (mt) {
     case 1: if constexpr (!EMIT) hipLaunchKernelGGL((sdl_kernel<MODE, FMT, 1, ALIASED, EMIT>), grid, block, lds, s, a); break;
     case 2: if constexpr (!EMIT) hipLaunchKernelGGL((sdl_kernel<MODE, FMT, 2, ALIASED, EMIT>), grid, block, lds, s, a); break;
