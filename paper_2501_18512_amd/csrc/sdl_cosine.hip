@@ -12,8 +12,8 @@
 //                     wavefront covers one contiguous piece of an array (2 x 1 KiB of fp32,
 //                     1 KiB of bf16 through 128-bit accesses).  Each lane keeps its M(M+1)/2
 //                     sums in fp64 registers (products of fp32 values are exact in fp64); at
-//                     the end the wavefront folds them with a butterfly of lane exchanges and
-//                     lane 0 writes one partial Gram matrix.  The next tile's loads are issued
+//                     the end the wavefront folds them, half of the sums at each exchange, and
+//                     its lanes write one partial Gram matrix.  The next tile's loads are issued
 //                     before the current tile is consumed.
 //   sdl_gramfma_pair_kernel  the same for 9 to 16 replicas: two wavefronts with half of the matrix each, which
 //                     exchange the outer gradients through LDS.
@@ -67,6 +67,8 @@ struct GramArgs {
     double* partial;               // [workgroup of the launch][M*M]
     uint32_t M;                    // side of the matrix
     uint32_t n_pieces;
+    uint32_t group_wg[kMaxPieces / 16 - 1];   // first workgroup of the 16th, 32nd, ... piece
+    uint32_t first_wg[kMaxPieces];            // of each piece; 0xffffffff behind the last
     Piece pieces[kMaxPieces];
 };
 static_assert(sizeof(GramArgs) <= 4096, "kernel arguments");
@@ -133,21 +135,82 @@ __device__ __forceinline__ void deltas(const u32x4& g0, const u32x4& g1, const u
     }
 }
 
-__device__ __forceinline__ double wave_sum(double v)
+// The wavefront's totals of the N sums that each lane holds in v, lane by lane fewer of them: at each of the six levels two
+// lanes split the sums they both hold, so that N / 2, N / 4, ... exchanges take the place of N at every level.  Afterwards a lane
+// holds halved(N) totals.  (sdl_gram_kernel, every sum by a butterfly of six exchanges and the pieces looked at one by one, and
+// now, whole call: 8.1 M parameters in 96 sets M = 2 86 us and 51; 1.8 M M = 8 40 and 23, M = 4 18 and 14; 302 M in 48 sets M = 4 542 and 539.)
+constexpr int halved(int n) { for (int l = 0; l < 6; ++l) n = (n + 1) / 2; return n; }
+
+template <int LEVEL> __device__ __forceinline__ double from_partner(double x)
 {
+    constexpr int kCtrl = LEVEL == 2 ? 0x140 : LEVEL == 3 ? 0x141 : LEVEL == 4 ? 0x4E : 0xB1;   // mirrors of 16 and 8, quad_perm
+    const u32x2 u = __builtin_bit_cast(u32x2, x);
+    const u32x2 r = {(uint32_t)__builtin_amdgcn_mov_dpp((int)u.x, kCtrl, 0xF, 0xF, true),
+                     (uint32_t)__builtin_amdgcn_mov_dpp((int)u.y, kCtrl, 0xF, 0xF, true)};
+    return __builtin_bit_cast(double, r);
+}
+
+template <int N, int LEVEL, int MAX>
+__device__ __forceinline__ void halve(double (&v)[MAX], uint32_t lane)
+{
+    if constexpr (LEVEL < 6) {
+        constexpr int half = (N + 1) / 2;
+        const bool upper = (lane >> (5 - LEVEL)) & 1u;
 #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) v += __shfl_xor(v, off, kWave);
-    return v;
+        for (int i = 0; i < half; ++i) {
+            double lo = v[i], hi = half + i < N ? v[half + i] : 0.0;
+            if constexpr (LEVEL < 2) {
+                const u32x2 a = __builtin_bit_cast(u32x2, lo), b = __builtin_bit_cast(u32x2, hi);
+                u32x2 x, y;
+                if constexpr (LEVEL == 0) {
+                    x = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false);
+                    y = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
+                } else {
+                    x = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
+                    y = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
+                }
+                lo = __builtin_bit_cast(double, u32x2{x.x, y.x});
+                hi = __builtin_bit_cast(double, u32x2{x.y, y.y});
+                v[i] = lo + hi;
+            } else {
+                v[i] = (upper ? hi : lo) + from_partner<LEVEL>(upper ? lo : hi);
+            }
+        }
+        halve<half, LEVEL + 1>(v, lane);
+    }
+}
+
+// Which of the N sums a lane has after halve, and how many: at each level the lower lane kept the first half of them.
+template <int N> __device__ __forceinline__ void halves_of(uint32_t lane, uint32_t* first, uint32_t* count)
+{
+    *first = 0;
+    *count = N;
+    uint32_t n = N;
+    for (int level = 0; level < 6; ++level) {
+        const uint32_t half = (n + 1u) / 2u;
+        if ((lane >> (5 - level)) & 1u) { *first += half; *count = *count > half ? *count - half : 0u; }
+        else *count = *count < half ? *count : half;
+        n = half;
+    }
 }
 
 // Up to 8 replicas: every lane holds the whole upper triangle.
 template <int M>
 __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
 {
+    constexpr int kSums = M * (M + 1) / 2, kLeft = halved(kSums);
     const uint32_t lane = threadIdx.x;
-    uint32_t s = 0;
-    while (s + 1 < a.n_pieces && blockIdx.x >= a.pieces[s + 1].first_wg) ++s;
-    const Piece set = a.pieces[s];
+    // the first workgroups of 16 pieces are one scalar load, those of every 16th piece come first
+    uint32_t base = 0, s = 15;
+    if (a.n_pieces > 16u) {
+#pragma unroll
+        for (int i = 1; i < kMaxPieces / 16; ++i)
+            if (blockIdx.x >= a.group_wg[i - 1]) base = (uint32_t)(i * 16);
+    }
+#pragma unroll
+    for (int i = 15; i >= 1; --i)
+        if (blockIdx.x < a.first_wg[base + i]) s = (uint32_t)(i - 1);
+    const Piece set = a.pieces[base + s];
     const uint32_t k = blockIdx.x - set.first_wg;
     const bool fast = set.fast != 0u;
     const uint64_t n_tiles = (set.numel + kTile - 1) / kTile;
@@ -156,11 +219,9 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
 #pragma unroll
     for (int m = 0; m < M; ++m) w[m] = a.w[m];
 
-    double acc[M][M];
+    double sum[kSums];               // the triangle, row by row
 #pragma unroll
-    for (int r = 0; r < M; ++r)
-#pragma unroll
-        for (int c = 0; c < M; ++c) acc[r][c] = 0.0;
+    for (int i = 0; i < kSums; ++i) sum[i] = 0.0;
 
     auto valid_of = [&](uint64_t t) -> uint32_t {
         const uint64_t rem = set.numel - t * kTile;
@@ -176,10 +237,11 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
             double d[M];
 #pragma unroll
             for (int m = 0; m < M; ++m) d[m] = (double)f[m][j];
+            int i = 0;
 #pragma unroll
             for (int r = 0; r < M; ++r)
 #pragma unroll
-                for (int c = r; c < M; ++c) acc[r][c] = __builtin_fma(d[r], d[c], acc[r][c]);
+                for (int c = r; c < M; ++c, ++i) sum[i] = __builtin_fma(d[r], d[c], sum[i]);
         }
     };
 
@@ -196,14 +258,17 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
         cur = nxt;
     }
 
+    halve<kSums, 0>(sum, lane);
     double* out = a.partial + (uint64_t)blockIdx.x * M * M;
+    uint32_t held, count;
+    halves_of<kSums>(lane, &held, &count);
 #pragma unroll
-    for (int r = 0; r < M; ++r)
-#pragma unroll
-        for (int c = r; c < M; ++c) {
-            const double v = wave_sum(acc[r][c]);
-            if (lane == 0) out[r * M + c] = v;
-        }
+    for (uint32_t v = 0; v < (uint32_t)kLeft; ++v) {
+        if (v >= count) continue;
+        uint32_t r = 0, c = held + v;
+        while (c >= M - r) { c -= M - r; ++r; }
+        out[r * M + r + c] = sum[v];
+    }
 }
 
 // 9 to 16 replicas, H = ceil(M / 2) of them to each of the two wavefronts of a workgroup.  One lane cannot hold up to 136 sums.
@@ -265,49 +330,6 @@ __device__ __forceinline__ void load_pair_tail(PairRaw<H>& t, const float* g, co
         for (int j = 0; j < 4; ++j)
             h[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (int)((lane * 4 + j) * 2), 0, 0) & 0xffffu;
         t.w[m] = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
-    }
-}
-
-// The wavefront's totals of the N sums that each lane holds in v, lane by lane fewer of them: at each of the six levels two
-// lanes split the sums they both hold, so that N / 2 exchanges take the place of N.  Afterwards a lane holds halved(N) totals.
-constexpr int halved(int n) { for (int l = 0; l < 6; ++l) n = (n + 1) / 2; return n; }
-
-template <int LEVEL> __device__ __forceinline__ double from_partner(double x)
-{
-    constexpr int kCtrl = LEVEL == 2 ? 0x140 : LEVEL == 3 ? 0x141 : LEVEL == 4 ? 0x4E : 0xB1;   // mirrors of 16 and 8, quad_perm
-    const u32x2 u = __builtin_bit_cast(u32x2, x);
-    const u32x2 r = {(uint32_t)__builtin_amdgcn_mov_dpp((int)u.x, kCtrl, 0xF, 0xF, true),
-                     (uint32_t)__builtin_amdgcn_mov_dpp((int)u.y, kCtrl, 0xF, 0xF, true)};
-    return __builtin_bit_cast(double, r);
-}
-
-template <int N, int LEVEL, int MAX>
-__device__ __forceinline__ void halve(double (&v)[MAX], uint32_t lane)
-{
-    if constexpr (LEVEL < 6) {
-        constexpr int half = (N + 1) / 2;
-        const bool upper = (lane >> (5 - LEVEL)) & 1u;
-#pragma unroll
-        for (int i = 0; i < half; ++i) {
-            double lo = v[i], hi = half + i < N ? v[half + i] : 0.0;
-            if constexpr (LEVEL < 2) {
-                const u32x2 a = __builtin_bit_cast(u32x2, lo), b = __builtin_bit_cast(u32x2, hi);
-                u32x2 x, y;
-                if constexpr (LEVEL == 0) {
-                    x = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false);
-                    y = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
-                } else {
-                    x = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
-                    y = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
-                }
-                lo = __builtin_bit_cast(double, u32x2{x.x, y.x});
-                hi = __builtin_bit_cast(double, u32x2{x.y, y.y});
-                v[i] = lo + hi;
-            } else {
-                v[i] = (upper ? hi : lo) + from_partner<LEVEL>(upper ? lo : hi);
-            }
-        }
-        halve<half, LEVEL + 1>(v, lane);
     }
 }
 
@@ -489,15 +511,9 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
         }
         halve<kSums, 0>(sum, lane);
 
-        // which sums the lane ended up with: at each level the lower lane kept the first half of them
-        uint32_t first = 0, count = kSums, n = kSums, lane_here = lane;
+        uint32_t first, count, lane_here = lane;
         asm volatile("" : "+v"(lane_here));      // (computed ahead of the loop, this would hold registers that it needs)
-        for (int level = 0; level < 6; ++level) {
-            const uint32_t half = (n + 1u) / 2u;
-            if ((lane_here >> (5 - level)) & 1u) { first += half; count = count > half ? count - half : 0u; }
-            else count = count < half ? count : half;
-            n = half;
-        }
+        halves_of<kSums>(lane_here, &first, &count);
         double* out = a.partial + (uint64_t)(uint32_t)((int32_t)b + a.slot[s]) * M * M;
 #pragma unroll
         for (uint32_t v = 0; v < (uint32_t)kLeft; ++v) {
@@ -606,13 +622,16 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
         o[M * M + i] = c;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        uint32_t n = 0;
-        for (uint32_t a = 0; a < M; ++a)
-            for (uint32_t b = a + 1; b < M; ++b, ++n) s += C[a * M + b];
-        o[2 * M * M] = n ? s / (double)n : 0.0;
+    // the mean over the pairs a < b, by the threads of the first slice, as a tree (pair after pair in one thread: 2 us at 16 replicas)
+    if (threadIdx.x < entries) part[threadIdx.x] = a < b ? C[a * M + b] : 0.0;
+    __syncthreads();
+    for (uint32_t n = entries; n > 1u;) {
+        const uint32_t half = (n + 1u) / 2u;
+        if (threadIdx.x + half < n) part[threadIdx.x] += part[threadIdx.x + half];
+        n = half;
+        __syncthreads();
     }
+    if (threadIdx.x == 0) o[2 * M * M] = M > 1u ? part[0] / (double)(entries - M) : 0.0;
 }
 
 // ------------------------------------------------------------------ host side
@@ -664,6 +683,8 @@ int launch_gram(const float* g, const void* const* w, uint32_t M, const Set* set
     a.g = g;
     a.partial = partial;
     a.M = M;
+    for (uint32_t& x : a.group_wg) x = 0xffffffffu;
+    for (uint32_t& x : a.first_wg) x = 0xffffffffu;
     // cut the sets into windows: about `windows` pieces per launch, shared out like the workgroups
     const uint32_t windows = kWindows;
     uint64_t total_G = 0;
@@ -691,6 +712,9 @@ int launch_gram(const float* g, const void* const* w, uint32_t M, const Set* set
             for (uint32_t m = 0; m < M; ++m)
                 fast = fast && aligned16(static_cast<const uint16_t*>(w[m]) + pc.offset);
             pc.fast = fast ? 1u : 0u;
+            const uint32_t number = a.n_pieces - 1u;
+            a.first_wg[number] = pc.first_wg;
+            if (number % 16u == 0u && number) a.group_wg[number / 16u - 1u] = pc.first_wg;
         }
     }
     for (uint32_t m = 0; m < M; ++m) a.w[m] = static_cast<const uint16_t*>(w[m]);
