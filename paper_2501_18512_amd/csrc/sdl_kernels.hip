@@ -328,6 +328,14 @@ __device__ __forceinline__ void decode_e4m3(uint32_t c0, float scale, float (&dq
     }
 }
 
+// A span's scale word, by a vector load that is under way with the tile's (a scalar one is waited for before the next instruction
+// that needs any).
+__device__ __forceinline__ uint32_t load_word(const uint8_t* words, uint32_t index)
+{
+    asm("" : "+v"(index));
+    return reinterpret_cast<const uint32_t*>(words)[index];
+}
+
 // ------------------------------------------------------------------ tile I/O policies
 // The arithmetic is written once against an I/O policy that moves a lane's 4 elements
 // of row `row` of each array.
@@ -342,7 +350,7 @@ __device__ __forceinline__ void decode_e4m3(uint32_t c0, float scale, float (&dq
 //              which returns 0 past the end and drops stores there -- no branches, so that all
 //              of a tile's loads are in flight at once
 
-template <bool ALIGNED, int ROWS>
+template <bool ALIGNED, int ROWS, bool PART = false>
 struct TileIOT {
     static constexpr int kTile = ROWS * kRow;   // parameters of the tile
     const Args& a;
@@ -351,13 +359,17 @@ struct TileIOT {
     uint32_t lane;
     uint32_t sidx;    // whole-span scale: index of the run's scale word
     uint64_t s0;      // tile's first element in g / mom (= t0 unless the state is staged)
-    uint32_t limit;   // ALIGNED: elements of the tile that exist (a multiple of 4, so that a lane has all four or none)
+    uint32_t left;    // PART: elements of the tile that exist (a multiple of 4, so that a lane has all four or none)
 
-    template <int B> __device__ __forceinline__ uint32_t scale_bytes() const { return ALIGNED ? (limit + B - 1) / B : kTile / B; }
+    // (a number in a whole tile: as a variable it moved the message loads of the one-pass receive at M = 8 behind each other, 2521 us
+    // against 2772 for 302 M parameters)
+    __device__ __forceinline__ uint32_t limit() const { return PART ? left : (uint32_t)kTile; }
+
+    template <int B> __device__ __forceinline__ uint32_t scale_bytes() const { return (limit() + B - 1) / B; }
     // bit pattern of the span's absolute maximum (whole-span scale)
     __device__ __forceinline__ uint32_t span_amax(uint32_t m) const
     {
-        return reinterpret_cast<const uint32_t*>(a.scales[m])[sidx];
+        return load_word(a.scales[m], sidx);
     }
     template <int FMT> __device__ __forceinline__ float load_scale(uint32_t m, int row) const
     {
@@ -382,26 +394,26 @@ struct TileIOT {
     // p = address of the tile's first element in the array
     __device__ __forceinline__ void ld_f32(const float* p, int row, float (&v)[kVec]) const
     {
-        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rsrc(p, limit * 4),
+        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rsrc(p, limit() * 4),
                                                               (int)(row * kRow * 4 + lane * 16), 0, kAuxLoad);
         v[0] = u2f(x.x); v[1] = u2f(x.y); v[2] = u2f(x.z); v[3] = u2f(x.w);
     }
     __device__ __forceinline__ void st_f32(float* p, int row, const float (&v)[kVec]) const
     {
         const u32x4 x = {f2u(v[0]), f2u(v[1]), f2u(v[2]), f2u(v[3])};
-        __builtin_amdgcn_raw_buffer_store_b128(x, rsrc(p, limit * 4), (int)(row * kRow * 4 + lane * 16), 0,
+        __builtin_amdgcn_raw_buffer_store_b128(x, rsrc(p, limit() * 4), (int)(row * kRow * 4 + lane * 16), 0,
                                                kAuxStore);
     }
     __device__ __forceinline__ void ld_bf16(const uint16_t* p, int row, uint32_t (&u)[2]) const
     {
-        const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(rsrc(p, limit * 2),
+        const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(rsrc(p, limit() * 2),
                                                              (int)(row * kRow * 2 + lane * 8), 0, kAuxLoad);
         u[0] = x.x; u[1] = x.y;
     }
     __device__ __forceinline__ void st_bf16(uint16_t* p, int row, const uint32_t (&u)[2]) const
     {
         const u32x2 x = {u[0], u[1]};
-        __builtin_amdgcn_raw_buffer_store_b64(x, rsrc(p, limit * 2), (int)(row * kRow * 2 + lane * 8), 0,
+        __builtin_amdgcn_raw_buffer_store_b64(x, rsrc(p, limit() * 2), (int)(row * kRow * 2 + lane * 8), 0,
                                               kAuxStore);
     }
 
@@ -489,12 +501,12 @@ struct TileIOT {
         } else {
             const float scale = load_scale<FMT>(m, row);
             if constexpr (is_e3m0(FMT)) {
-                const uint32_t c0 = __builtin_amdgcn_raw_buffer_load_b16(rsrc(codes + tb / 2, limit / 2),
+                const uint32_t c0 = __builtin_amdgcn_raw_buffer_load_b16(rsrc(codes + tb / 2, limit() / 2),
                                                                          (int)(row * (kRow / 2) + lane * 2), 0,
                                                                          kAuxLoad);
                 decode_e3m0(c0, scale, dq);
             } else {
-                const uint32_t c0 = __builtin_amdgcn_raw_buffer_load_b32(rsrc(codes + tb, limit),
+                const uint32_t c0 = __builtin_amdgcn_raw_buffer_load_b32(rsrc(codes + tb, limit()),
                                                                          (int)(row * kRow + lane * 4), 0, kAuxLoad);
                 decode_e4m3<EXACT>(c0, scale, dq);
             }
@@ -516,19 +528,19 @@ struct TileIOT {
             }
         } else if constexpr (FMT == SDL_FMT_FP32) {
             const u32x4 x = {c[0], c[1], c[2], c[3]};
-            __builtin_amdgcn_raw_buffer_store_b128(x, rsrc(codes + tb * 4, limit * 4),
+            __builtin_amdgcn_raw_buffer_store_b128(x, rsrc(codes + tb * 4, limit() * 4),
                                                    (int)(row * kRow * 4 + lane * 16), 0, kAuxStore);
         } else if constexpr (FMT == SDL_FMT_BF16) {
             const u32x2 x = {c[0], c[1]};
-            __builtin_amdgcn_raw_buffer_store_b64(x, rsrc(codes + tb * 2, limit * 2),
+            __builtin_amdgcn_raw_buffer_store_b64(x, rsrc(codes + tb * 2, limit() * 2),
                                                   (int)(row * kRow * 2 + lane * 8), 0, kAuxStore);
         } else {
             store_scale<FMT>(m, row, sb);
             if constexpr (is_e3m0(FMT)) {
-                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)c[0], rsrc(codes + tb / 2, limit / 2),
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)c[0], rsrc(codes + tb / 2, limit() / 2),
                                                       (int)(row * (kRow / 2) + lane * 2), 0, kAuxStore);
             } else {
-                __builtin_amdgcn_raw_buffer_store_b32(c[0], rsrc(codes + tb, limit), (int)(row * kRow + lane * 4), 0,
+                __builtin_amdgcn_raw_buffer_store_b32(c[0], rsrc(codes + tb, limit()), (int)(row * kRow + lane * 4), 0,
                                                       kAuxStore);
             }
         }
@@ -546,7 +558,7 @@ struct TailIO {
 
     __device__ __forceinline__ uint32_t span_amax(uint32_t m) const
     {
-        return reinterpret_cast<const uint32_t*>(a.scales[m])[sidx];
+        return load_word(a.scales[m], sidx);
     }
     // elements of a row that exist
     __device__ __forceinline__ uint32_t valid(int row) const
@@ -665,10 +677,10 @@ struct TailIO {
 // two and one replicas whose loads are issued together (one replica at a time costs 6-8 %).
 
 // One replica's contribution to the sum of one row: its message decoded (receive side), or its
-// outer gradient encoded (send side and fused; ws = the replica's words at the send step).
+// outer gradient encoded (send side and fused; ws = the replica's words at the send step, samax = its scale word).
 template <int MODE, int FMT, bool EMIT, class IO>
 __device__ __forceinline__ void add_replica(const IO& io, uint32_t m, int r, const uint32_t (&ws)[2],
-                                            const float (&g)[kVec], float (&acc)[kVec])
+                                            const float (&g)[kVec], float (&acc)[kVec], uint32_t samax)
 {
     float dq[kVec];
     if constexpr (MODE == kReduce || MODE == kReceive) {
@@ -680,8 +692,6 @@ __device__ __forceinline__ void add_replica(const IO& io, uint32_t m, int r, con
 #pragma unroll
         for (int j = 0; j < kVec; ++j) d[j] = g[j] - w[j];
         constexpr bool want = MODE == kQuantize || EMIT;
-        uint32_t samax = 0;
-        if constexpr (is_span_scaled(FMT)) samax = io.span_amax(m);
         encode<FMT>(d, dq, c, sb, want, samax);
         if constexpr (want) io.template store_message<FMT>(m, r, c, sb);
     }
@@ -694,8 +704,12 @@ template <int MODE, int FMT, bool EMIT, int kRows, int G, class IO>
 __device__ __forceinline__ void add_replica_group(const IO& io, uint32_t m0, const float (&g)[kRows][kVec],
                                                   float (&acc)[kRows][kVec])
 {
-    uint32_t ws[G][kRows][2] = {};
+    uint32_t ws[G][kRows][2] = {}, samax[G] = {};
     if constexpr (MODE == kQuantize || MODE == kFused) {
+        if constexpr (is_span_scaled(FMT)) {
+#pragma unroll
+            for (int k = 0; k < G; ++k) samax[k] = io.span_amax(m0 + k);
+        }
 #pragma unroll
         for (int k = 0; k < G; ++k)
 #pragma unroll
@@ -704,7 +718,7 @@ __device__ __forceinline__ void add_replica_group(const IO& io, uint32_t m0, con
 #pragma unroll
     for (int k = 0; k < G; ++k)
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) add_replica<MODE, FMT, EMIT>(io, m0 + k, r, ws[k][r], g[r], acc[r]);
+        for (int r = 0; r < kRows; ++r) add_replica<MODE, FMT, EMIT>(io, m0 + k, r, ws[k][r], g[r], acc[r], samax[k]);
 }
 
 // alpha-merge of the new global parameters into one row of one replica (wn = its words now).
@@ -745,9 +759,16 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
     constexpr int MU = MT > 0 ? MT : 1;
 
     float g[kRows][kVec], mom[kRows][kVec], acc[kRows][kVec];
-    uint32_t ws[MU][kRows][2] = {}, wn[MU][kRows][2];
+    uint32_t ws[MU][kRows][2] = {}, wn[MU][kRows][2], samax[MU] = {};
 
-    // ---- loads that do not depend on anything
+    // ---- loads that do not depend on anything; the scale words first: loads return in order, and the first replica cannot be encoded
+    // without its own (28 M parameters, us, behind the tile's loads and ahead of them: fused, the whole call, M = 2 160.9 and 158.3,
+    // M = 4 251 and 249; send M = 4 134 and 128)
+    if constexpr (MT > 0 && is_span_scaled(FMT) && (MODE == kQuantize || MODE == kFused)) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) samax[m] = io.span_amax(m);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
         io.load_g(r, g[r]);
@@ -784,7 +805,7 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
 #pragma unroll
             for (int m = 0; m < MT; ++m)
 #pragma unroll
-                for (int r = 0; r < kRows; ++r) add_replica<MODE, FMT, EMIT>(io, (uint32_t)m, r, ws[m][r], g[r], acc[r]);
+                for (int r = 0; r < kRows; ++r) add_replica<MODE, FMT, EMIT>(io, (uint32_t)m, r, ws[m][r], g[r], acc[r], samax[m]);
         } else {
             uint32_t m = 0;
             for (; m + 4u <= M; m += 4u) add_replica_group<MODE, FMT, EMIT, kRows, 4>(io, m, g, acc);
@@ -956,8 +977,11 @@ void sdl_kernel(const Args a)
     if (left < kTile && ((size & kVectorBit) || numel % kVec != 0u)) {
         const TailIO io{a, t0, tb, s0, left, threadIdx.x, sidx};
         process<MODE, FMT, 0, ALIASED, EMIT, ROWS>(a, io);
+    } else if (left < kTile) {
+        const TileIOT<true, ROWS, true> io{a, t0, tb, threadIdx.x, sidx, s0, left};
+        process<MODE, FMT, MT, ALIASED, EMIT, ROWS>(a, io);
     } else if (!(size & kVectorBit)) {
-        const TileIOT<true, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0, left < kTile ? left : kTile};
+        const TileIOT<true, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0, kTile};
         process<MODE, FMT, MT, ALIASED, EMIT, ROWS>(a, io);
     } else {
         const TileIOT<false, ROWS> io{a, t0, tb, threadIdx.x, sidx, s0, kTile};
