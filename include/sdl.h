@@ -239,7 +239,7 @@ int sdl_fragment_outer_step(float* g, float* mom, const void* const* w_send, voi
                             void* const* codes_or_null, void* const* scales_or_null, void* stream);
 
 /* Fused outer step of a whole fragment of a plan: every run of fragment p, in one
- * kernel launch per group of up to 112 runs.  The pointers are the bases of the flat model arrays
+ * kernel launch per group of up to 272 runs.  The pointers are the bases of the flat model arrays
  * (element 0 of the model); run r is processed at element offset runs[r].offset.
  * Messages are not written.  SDL_FMT_E3M0_SPAN is not supported here (SDL_ERR_UNSUPPORTED): it needs the
  * scale words that the _ex form below takes. */

@@ -281,11 +281,11 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
 // A wavefront loads its own replicas, forms their outer gradients and puts them into LDS, where both find what they need as
 // fp32: each difference is formed once, and the tile on its way takes 2H + 4 registers.  Bound: fp64 FMAs, 136 for a parameter at
 // 16 replicas where a matrix instruction forms all 256 entries (both run at 16 a cycle and SIMD, and neither overlaps with the
-// other).  On real differences an FMA takes 2.4 ns, not the 1.7 of 2.4 GHz: 52.9 M parameters at 16 replicas are 263 us of FMAs and
-// 110 of conversions and subtractions; 300 us measured with the loads and the staging left out.  Whole call at 52.9 M parameters, M = 9 / 12 /
-// 13 / 16: 299 / 402 / 503 / 508 us as two wavefronts that each load everything (M <= 12) or on the matrix
-// cores, 246 / 324 / 400 /
-// 466 now (HBM 164 / 209 / 223 / 268); arrays at odd elements, M = 13 / 16: 541 / 584 and 416 / 490; 2.1 M parameters at 13 / 16: 54 / 57 and 37 / 43.
+// other).  On random data an FMA takes 2.4 ns, not the 1.7 of 2.4 GHz: 52.9 M parameters at 16 replicas are 263 us of FMAs, the
+// rest conversions and subtractions; 310 us measured with the loads and the staging left out, 350 with the staging, 385 with
+// loads from the caches.  Whole call at 52.9 M parameters, M = 9 / 12 / 13 / 16: 299 / 402 / 503 / 508 us as two wavefronts that
+// each load everything (M <= 12) or on the matrix cores, 246 / 322 / 400 / 458 to 466 now (HBM 164 / 209 / 223 / 268); arrays at
+// odd elements, M = 13 / 16: 541 / 584 and 416 / 490; 2.1 M parameters at 13 / 16: 54 / 57 and 37 / 43.
 // Four wavefronts with a quarter of the matrix each (more of them in flight, 48 conversions instead of 32): 503.  The tile copied
 // to LDS past the registers, up to three tiles ahead: 478.
 template <int H>
