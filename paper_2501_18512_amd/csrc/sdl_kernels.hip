@@ -14,11 +14,12 @@
 //   - eight neighbouring lanes own one 32-element scale block, and the block maximum
 //     is three DPP exchanges (two inside the quad, one across the half row); wider
 //     blocks add a row mirror and ds_bpermute exchanges.  No LDS storage is used.
-// Full, 16-byte aligned tiles use buffer instructions with non-temporal cache policy
-// (every byte is touched once); full tiles of runs in which some array starts at some other
-// element use vector accesses of element alignment in the same lane layout; ragged tails use
+// Tiles of runs that start on a multiple of four elements in 16-byte aligned arrays use buffer
+// instructions with non-temporal cache policy (every byte is touched once), ragged tails of a multiple
+// of four elements among them; full tiles of runs in which some array starts at some other
+// element use vector accesses of element alignment in the same lane layout; other ragged tails use
 // range-checked accesses of one element each.  A launch covers up to 272 contiguous runs of the flat
-// model; every workgroup belongs to exactly one run, so scale blocks never straddle
+// model (160 of a whole-span format); every workgroup belongs to exactly one run, so scale blocks never straddle
 // runs.
 //
 // Arithmetic contract (Algorithm 2 and Sections 2.1, 2.3, 2.4 of the paper, with the
@@ -90,9 +91,10 @@ constexpr int block_elems(int f)
     return f == SDL_FMT_E3M0_B64 ? 64 : f == SDL_FMT_E3M0_B128 ? 128 : f == SDL_FMT_E3M0_SPAN ? 0 : SDL_BLOCK;
 }
 
-// How the whole tiles of a run reach memory (a ragged last tile always takes the range-checked path).
+// How the whole tiles of a run reach memory (a ragged last tile: the buffer path too if the run takes it and
+// its length is a multiple of 4, else one access per element).
 enum TilePath : uint32_t {
-    kPathBuffer = 1,    // every array of the call is 16-byte aligned at the run's first element
+    kPathBuffer = 1,    // the call's arrays are 16-byte aligned and the run starts on a multiple of 4 elements
     kPathVector = 2,    // some array starts at some other element (or, messages of 4 and 8 bits, byte)
 };
 
@@ -339,13 +341,14 @@ __device__ __forceinline__ uint32_t load_word(const uint8_t* words, uint32_t ind
 // ------------------------------------------------------------------ tile I/O policies
 // The arithmetic is written once against an I/O policy that moves a lane's 4 elements
 // of row `row` of each array.
-//   TileIO     a whole, 16-byte aligned tile: buffer loads / stores through one resource
-//              per array (scalar base, 32-bit lane offset) with explicit cache policy
+//   TileIOT<true>   a tile whose lanes start on the alignment of their accesses: buffer loads / stores through one
+//              resource per array (scalar base, 32-bit lane offset) with explicit cache policy; PART: the ragged
+//              last tile of a run whose length is a multiple of 4
 //   TileIOT<false>  a whole tile of arrays that start at any element (a run behind a parameter
 //              group of odd length, messages packed back to back): the same lane layout through
 //              plain vector loads / stores of element alignment (byte alignment for the 4- and
 //              8-bit codes)
-//   TailIO     the ragged last tile of a run, any alignment: one buffer access per element (per
+//   TailIO     the other ragged last tiles, any alignment: one buffer access per element (per
 //              byte of 4- and 8-bit codes) under the range check of the buffer instructions,
 //              which returns 0 past the end and drops stores there -- no branches, so that all
 //              of a tile's loads are in flight at once
