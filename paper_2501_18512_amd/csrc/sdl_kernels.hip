@@ -374,6 +374,11 @@ struct TileIOT {
     {
         return load_word(a.scales[m], sidx);
     }
+    // the same by a scalar load
+    __device__ __forceinline__ uint32_t span_amax_scalar(uint32_t m) const
+    {
+        return reinterpret_cast<const uint32_t*>(a.scales[m])[sidx];
+    }
     template <int FMT> __device__ __forceinline__ float load_scale(uint32_t m, int row) const
     {
         if constexpr (is_span_scaled(FMT)) {
@@ -680,8 +685,9 @@ struct TailIO {
 // two and one replicas whose loads are issued together (one replica at a time costs 6-8 %).
 
 // One replica's contribution to the sum of one row: its message decoded (receive side), or its
-// outer gradient encoded (send side and fused; ws = the replica's words at the send step, samax = its scale word).
-template <int MODE, int FMT, bool EMIT, class IO>
+// outer gradient encoded (send side and fused; ws = the replica's words at the send step, samax = its scale word unless
+// it is asked for here).
+template <int MODE, int FMT, bool EMIT, bool WORD_HERE = false, class IO>
 __device__ __forceinline__ void add_replica(const IO& io, uint32_t m, int r, const uint32_t (&ws)[2],
                                             const float (&g)[kVec], float (&acc)[kVec], uint32_t samax)
 {
@@ -695,6 +701,7 @@ __device__ __forceinline__ void add_replica(const IO& io, uint32_t m, int r, con
 #pragma unroll
         for (int j = 0; j < kVec; ++j) d[j] = g[j] - w[j];
         constexpr bool want = MODE == kQuantize || EMIT;
+        if constexpr (WORD_HERE) samax = io.span_amax_scalar(m);
         encode<FMT>(d, dq, c, sb, want, samax);
         if constexpr (want) io.template store_message<FMT>(m, r, c, sb);
     }
@@ -765,9 +772,11 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
     uint32_t ws[MU][kRows][2] = {}, wn[MU][kRows][2], samax[MU] = {};
 
     // ---- loads that do not depend on anything; the scale words first: loads return in order, and the first replica cannot be encoded
-    // without its own (28 M parameters, us, behind the tile's loads and ahead of them: fused, the whole call, M = 2 160.9 and 158.3,
-    // M = 4 251 and 249; send M = 4 134 and 128)
-    if constexpr (MT > 0 && is_span_scaled(FMT) && (MODE == kQuantize || MODE == kFused)) {
+    // without its own (28 M parameters, us, behind the tile's loads and ahead of them: fused, the whole call, M = 2 160.9 and 158.3;
+    // send M = 4 134 and 128).  From 4 replicas the fused step has enough on the way and takes scalar loads where it needs the
+    // words (50 M parameters, whole call, M = 4: 418 so, 423 ahead of the tile, 425 by scalar loads ahead of it).
+    constexpr bool kWordHere = MODE == kFused && MT >= 4 && is_span_scaled(FMT);
+    if constexpr (MT > 0 && is_span_scaled(FMT) && (MODE == kQuantize || MODE == kFused) && !kWordHere) {
 #pragma unroll
         for (int m = 0; m < MT; ++m) samax[m] = io.span_amax(m);
         __builtin_amdgcn_sched_barrier(0);
@@ -808,7 +817,7 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
 #pragma unroll
             for (int m = 0; m < MT; ++m)
 #pragma unroll
-                for (int r = 0; r < kRows; ++r) add_replica<MODE, FMT, EMIT>(io, (uint32_t)m, r, ws[m][r], g[r], acc[r], samax[m]);
+                for (int r = 0; r < kRows; ++r) add_replica<MODE, FMT, EMIT, kWordHere>(io, (uint32_t)m, r, ws[m][r], g[r], acc[r], samax[m]);
         } else {
             uint32_t m = 0;
             for (; m + 4u <= M; m += 4u) add_replica_group<MODE, FMT, EMIT, kRows, 4>(io, m, g, acc);
