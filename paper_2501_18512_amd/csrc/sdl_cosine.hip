@@ -139,7 +139,7 @@ __device__ __forceinline__ void deltas(const u32x4& g0, const u32x4& g1, const u
 // lanes split the sums they both hold, so that N / 2, N / 4, ... exchanges take the place of N at every level.  Afterwards a lane
 // holds halved(N) totals.  (sdl_gram_kernel, every sum by a butterfly of six exchanges and the pieces looked at one by one, and
 // now, whole call: 8.1 M parameters in 96 sets M = 2 86 us and 51; 1.8 M M = 8 40 and 23, M = 4 18 and 14; 302 M in 48 sets M = 4 542 and 539.)
-constexpr int halved(int n) { for (int l = 0; l < 6; ++l) n = (n + 1) / 2; return n; }
+constexpr int halved(int n, int levels = 6) { for (int l = 0; l < levels; ++l) n = (n + 1) / 2; return n; }
 
 template <int LEVEL> __device__ __forceinline__ double from_partner(double x)
 {
@@ -150,10 +150,11 @@ template <int LEVEL> __device__ __forceinline__ double from_partner(double x)
     return __builtin_bit_cast(double, r);
 }
 
-template <int N, int LEVEL, int MAX>
+// (levels LEVEL to END - 1 alone)
+template <int N, int LEVEL, int END = 6, int MAX>
 __device__ __forceinline__ void halve(double (&v)[MAX], uint32_t lane)
 {
-    if constexpr (LEVEL < 6) {
+    if constexpr (LEVEL < END) {
         constexpr int half = (N + 1) / 2;
         const bool upper = (lane >> (5 - LEVEL)) & 1u;
 #pragma unroll
@@ -176,7 +177,7 @@ __device__ __forceinline__ void halve(double (&v)[MAX], uint32_t lane)
                 v[i] = (upper ? hi : lo) + from_partner<LEVEL>(upper ? lo : hi);
             }
         }
-        halve<half, LEVEL + 1>(v, lane);
+        halve<half, LEVEL + 1, END>(v, lane);
     }
 }
 
@@ -282,19 +283,20 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
 // fp32: each difference is formed once, and the tile on its way takes 2H + 4 registers.  Bound: fp64 FMAs, 136 for a parameter at
 // 16 replicas where a matrix instruction forms all 256 entries (both run at 16 a cycle and SIMD, and neither overlaps with the
 // other).  On random data an FMA takes 2.4 ns, not the 1.7 of 2.4 GHz: 52.9 M parameters at 16 replicas are 263 us of FMAs, the
-// rest conversions and subtractions; 310 us measured with the loads and the staging left out, 350 with the staging, 385 with
-// loads from the caches.  Whole call at 52.9 M parameters, M = 9 / 12 / 13 / 16: 299 / 402 / 503 / 508 us as two wavefronts that
-// each load everything (M <= 12) or on the matrix cores, 246 / 322 / 400 / 458 to 466 now (HBM 164 / 209 / 223 / 268); arrays at
-// odd elements, M = 13 / 16: 541 / 584 and 416 / 490; 2.1 M parameters at 13 / 16: 54 / 57 and 37 / 43.
-// Four wavefronts with a quarter of the matrix each (more of them in flight, 48 conversions instead of 32): 503.  The tile copied
-// to LDS past the registers, up to three tiles ahead: 478.
+// rest conversions and subtractions; with one chain of additions for all of a lane's parameters 310 us measured with the loads
+// and the staging left out, 350 with the staging, 385 with loads from the caches, 456 to 462 in all, and 30 to 35 more with chains
+// of 16 (see total below).  Whole call at 52.9 M parameters, M = 9 / 12 / 13 / 16: 295 / 401 / 500 / 509 us as two wavefronts that
+// each load everything (M <= 12) or on the matrix cores, 253 / 334 / 416 / 495 now (HBM 164 / 209 / 223 / 268); arrays at
+// odd elements 393 / 486 / 764 / 860 and 276 / 357 / 442 / 525; 2.1 M parameters 51 / 80 / 59 / 63 and 28 / 32 / 37 / 42.
+// Four wavefronts with a quarter of the matrix each (more of them in flight, 48 conversions instead of 32) 503 at 16 replicas,
+// the tile copied to LDS past the registers, up to three tiles ahead, 478, each beside 463 and with one chain.
 template <int H>
 struct PairRaw {
     f32x4_elem g;
     u32x2 w[H];
 };
 constexpr int kPairTile = 4 * kWave;      // parameters a workgroup takes at a time
-constexpr int kPairChain = 4;             // tiles after which the diagonal entries start a new chain (16 parameters of a lane)
+constexpr int kPairChain = 4;             // tiles after which the sums start a new chain (16 parameters of a lane)
 
 // A whole tile of sets whose arrays are all 16-byte aligned (FAST) or start at any element.
 template <int H, bool FAST>
@@ -402,13 +404,21 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
         __builtin_amdgcn_sched_barrier(0);
     };
     double sum[kSums];                               // the rows' triangle, then the block's entries
-    // Whole chains of the diagonal entries.  Squares of short mantissas end alike, so where a sum has outgrown them the ties of its
-    // roundings all go one way, and the error grows with the chain: with chains of a lane's 800 parameters the entries G[m][m]
-    // err by 7.5e-16 for replicas with outliers (52.9 M parameters), with chains of 16 by 0.9e-16.  Products of different
-    // replicas do not.
-    double squares[H];
-    // the sums of one parameter; once it is converted, the next one is read into the same registers
-    auto consume = [&](auto read_next) {
+    // Whole chains, added over 4 lanes (8 at H = 8).  Products of short mantissas end alike, so where a sum has outgrown them its
+    // roundings all go one way, and the error grows with the chain: for squares, and for two replicas that point the same way as well.
+    // 52.9 M parameters with outliers, rms error in units of 1e-16 of sqrt(G[a][a] G[b][b]), a = b / a != b, replicas correlated by
+    // 0.9, at 9 / 12 / 13 / 16 replicas: one chain for a lane's 690 parameters (the diagonal alone in chains of 16) 0.5/13 0.9/18
+    // 1.1/19 0.9/19; chains of 64 1.8/2.3 1.9/2.2 2.1/2.1 2.4/2.2; of 32 1.0/1.5 1.3/1.5 1.1/1.3 1.3/1.4; of 16 0.9/1.1 1.1/1.0
+    // 0.9/1.0 1.1/1.1.  Whole call: 240 / 320 / 392 / 461 us with one chain, 253 / 334 / 416 / 495 with chains of 16.  A third
+    // exchange costs 1 % (three levels, which 16 replicas need, as two spill there), all six 5 %; added up through LDS, eight
+    // values to a lane, 538 at 16 replicas; with sums that are set to 0 instead of begun by their first product 506.  One chain of products that
+    // a factor of 28 bits fills up at the bottom: as exact, 262 / 346 / 424 / 498.
+    constexpr int kFolds = H == 8 ? 3 : 2, kHeld = halved(kSums, kFolds);
+    double total[kHeld];
+    // the sums of one parameter, the first of its chain or a later one; once it is converted, the next one is read into the same
+    // registers
+    auto consume = [&](auto is_first, auto read_next) {
+        constexpr bool FIRST = decltype(is_first)::value;
         double d[2 * H];
 #pragma unroll
         for (int m = 0; m < 2 * H; ++m) d[m] = (double)f[m];
@@ -419,17 +429,17 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (int i = 0; i < H; ++i)
 #pragma unroll
-            for (int j = i; j < H; ++j, ++k) sum[k] = __builtin_fma(d[i], d[j], sum[k]);
+            for (int j = i; j < H; ++j, ++k) sum[k] = __builtin_fma(d[i], d[j], FIRST ? 0.0 : sum[k]);
 #pragma unroll
         for (int i = 0; i < H; ++i)
 #pragma unroll
-            for (int j = 0; j < kOff; ++j, ++k) sum[k] = __builtin_fma(d[i], d[H + (i + j) % H], sum[k]);
+            for (int j = 0; j < kOff; ++j, ++k) sum[k] = __builtin_fma(d[i], d[H + (i + j) % H], FIRST ? 0.0 : sum[k]);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto end_chain = [&]() {
-        int k = 0;
+        halve<kSums, 0, kFolds>(sum, lane);
 #pragma unroll
-        for (int i = 0; i < H; k += H - i, ++i) { squares[i] += sum[k]; sum[k] = 0.0; }
+        for (int i = 0; i < kHeld; ++i) total[i] += sum[i];
     };
 
     const uint32_t b = blockIdx.x;
@@ -454,9 +464,7 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
         const uint32_t whole = (uint32_t)(numel / kPairTile), last = stop - set_first < whole ? stop - set_first : whole;
         uint32_t k = t - set_first;
 #pragma unroll
-        for (int i = 0; i < kSums; ++i) sum[i] = 0.0;
-#pragma unroll
-        for (int i = 0; i < H; ++i) squares[i] = 0.0;
+        for (int i = 0; i < kHeld; ++i) total[i] = 0.0;
 
         // whole tiles k, k + 1, ...: while one is consumed the next one lies in the other half of diff, or will by the time of
         // the barrier, and the one after it is on its way into registers (behind the last tile: that tile again)
@@ -475,15 +483,19 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
             read(0, 0);
             while (k < last) {
                 const uint32_t chain = last - k < (uint32_t)kPairChain ? last : k + kPairChain;
-                for (; k < chain; ++k, buf ^= 1u) {
-                    consume([&]() { read(buf, 1); });
-                    consume([&]() { read(buf, 2); });
+                auto tile = [&](auto is_first) {
+                    consume(is_first, [&]() { read(buf, 1); });
+                    consume(std::false_type{}, [&]() { read(buf, 2); });
                     stage(buf ^ 1u, raw);
                     load(k + 2u);
-                    consume([&]() { read(buf, 3); });
+                    consume(std::false_type{}, [&]() { read(buf, 3); });
                     lds_barrier();
-                    consume([&]() { read(buf ^ 1u, 0); });
-                }
+                    consume(std::false_type{}, [&]() { read(buf ^ 1u, 0); });
+                    buf ^= 1u;
+                    ++k;
+                };
+                tile(std::true_type{});
+                while (k < chain) tile(std::false_type{});
                 end_chain();
             }
         };
@@ -497,19 +509,16 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
             lds_barrier();
             stage(0, raw);
             lds_barrier();
+#pragma unroll
+            for (int i = 0; i < kSums; ++i) sum[i] = 0.0;
 #pragma unroll 1
             for (int part = 0; part < kPairTile / kWave; ++part) {
                 read(0, part);
-                consume([]() {});
+                consume(std::false_type{}, []() {});
             }
+            end_chain();
         }
-        end_chain();
-        {
-            int d = 0;
-#pragma unroll
-            for (int i = 0; i < H; d += H - i, ++i) sum[d] = squares[i];
-        }
-        halve<kSums, 0>(sum, lane);
+        halve<kHeld, kFolds>(total, lane);
 
         uint32_t first, count, lane_here = lane;
         asm volatile("" : "+v"(lane_here));      // (computed ahead of the loop, this would hold registers that it needs)
@@ -529,7 +538,7 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
                 j = col((i + o) % H);
             }
             i = row(i);
-            if (i < M && j < M) out[i < j ? i * M + j : j * M + i] = sum[v];
+            if (i < M && j < M) out[i < j ? i * M + j : j * M + i] = total[v];
         }
         t = stop;
     }

@@ -63,3 +63,55 @@ def test_wide_sums_are_as_exact_as_those_of_8_replicas(recipe, n, seeds):
     print(f"{recipe} n={n}: " + ", ".join(f"M={M} {x:.2e}" for M, x in rms.items()), flush=True)
     for M in errors:
         assert rms[M] <= 1.6 * max(rms[8], 0.6 * 2.0 ** -53), f"M={M}: {rms}"
+
+
+def _agreeing(recipe, rho, n, M, seed):
+    """Replicas whose outer gradients share a part: correlated by rho, outliers in the same places."""
+    gen = torch.Generator("cuda").manual_seed(seed)
+    draw = lambda: torch.randn(n, device="cuda", generator=gen) * 1e-3
+    g, common, u = draw() * 20, draw(), torch.rand(n, device="cuda", generator=gen)
+    w = []
+    for _ in range(M):
+        z = common * rho ** 0.5 + draw() * (1 - rho) ** 0.5
+        if recipe == "outliers":
+            z = torch.where(u < 1e-3, torch.where(u < 5e-4, 0.1, -0.1), z)
+        w.append((g - z).to(torch.bfloat16))
+    return g, w
+
+
+@pytest.mark.parametrize("rho", [0.5, 0.9])
+@pytest.mark.parametrize("recipe", ["normal", "outliers"])
+def test_products_of_replicas_that_agree_are_as_exact_as_those_of_8(recipe, rho):
+    """The entries a != b, their error in units of sqrt(G[a][a] G[b][b]): products of replicas that point the same way are biased like
+    squares, and what holds for the diagonal has to hold for them.  Same yardstick and bound.  (One chain of additions for all of
+    a lane's parameters: 2 to 8 times the yardstick.)"""
+    n, seeds, pick = 52_900_001, 2, [0, 1, 3, 6, 8, 11, 12, 15]
+    errors = {M: [] for M in (8, 9, 12, 13, 16)}
+    for seed in range(seeds):
+        g, w = _agreeing(recipe, rho, n, 16, seed)
+        d = {a: (g - w[a].float()).double() for a in pick}
+        norm = {a: _exact(d[a].square())[0] ** 0.5 for a in pick}
+        exact = {(a, b): _exact(d[a] * d[b]) for a in pick for b in pick if a < b}
+        del d
+        for M in errors:
+            result, workspace = sdl.alloc_cosine(M)
+            sdl.sdl_outer_grad_cosine(g, w[:M], n, result[0], workspace)
+            G = sdl.split_cosine_result(result[0], M)[0].cpu()
+            errors[M] += [((float(G[a, b]) - hi) - lo) / (norm[a] * norm[b]) for (a, b), (hi, lo) in exact.items() if b < M]
+    rms = {M: (sum(e * e for e in x) / len(x)) ** 0.5 for M, x in errors.items()}
+    print(f"{recipe} rho={rho}: " + ", ".join(f"M={M} {x:.2e}" for M, x in rms.items()), flush=True)
+    for M in errors:
+        assert rms[M] <= 1.6 * max(rms[8], 0.6 * 2.0 ** -53), f"M={M}: {rms}"
+
+
+@pytest.mark.parametrize("n", [700, (1 << 18), (1 << 23) + 333, 52_900_001])
+@pytest.mark.parametrize("M", range(8, 17))
+def test_equal_replicas_have_equal_entries(M, n):
+    """Every entry is the same sum in the same order, so that norms and products are the same number and cos is 1 (one rounding for
+    each of two square roots, their product and the quotient: 4 units in the last place)."""
+    g, w = _agreeing("outliers", 1.0, n, 1, M)
+    result, workspace = sdl.alloc_cosine(M)
+    sdl.sdl_outer_grad_cosine(g, w * M, n, result[0], workspace)
+    G, cos, _ = sdl.split_cosine_result(result[0], M)
+    assert (G == G[0, 0]).all(), (G / G[0, 0] - 1).abs().max().item()
+    assert (cos - 1).abs().max().item() <= 4 * 2.0 ** -52
