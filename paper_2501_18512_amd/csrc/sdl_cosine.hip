@@ -298,7 +298,7 @@ struct PairRaw {
 constexpr int kPairTile = 4 * kWave;      // parameters a workgroup takes at a time
 constexpr int kPairChain = 4;             // tiles after which the sums start a new chain (16 parameters of a lane)
 
-// A whole tile of sets whose arrays are all 16-byte aligned (FAST) or start at any element.
+// A whole tile of a set whose arrays are all 16-byte aligned (FAST) or start at any element.
 template <int H, bool FAST>
 __device__ __forceinline__ void load_pair_raw(PairRaw<H>& t, const float* g, const uint16_t* const (&w)[H], uint64_t e0, uint32_t lane)
 {
@@ -357,15 +357,16 @@ struct PairArgs {
     const float* g;
     const uint16_t* w[SDL_MAX_WORKERS];
     double* partial;
+    uint64_t fast;                    // bit s: every array is 16-byte aligned at set s's start (24 sets of 48 off it, 52.9 M parameters, M = 9 / 16:
+                                      // 268.6 / 517 us with all sets on the path for any alignment, 266.3 / 514 so)
     uint32_t M;
-    uint32_t fast;                    // every array is 16-byte aligned at every set's start
     uint32_t first_tile[kMaxSets + 1];   // of each set, then the number of tiles; 0xffffffff behind it
     Share shares[kShares];
     int32_t slot[kMaxSets];           // workgroup b's matrix of set s is partial[b + slot[s]]
     uint64_t offset[kMaxSets];
     uint64_t numel[kMaxSets];
 };
-static_assert(sizeof(PairArgs) <= 4096, "kernel arguments");
+static_assert(sizeof(PairArgs) <= 4096 && kMaxSets <= 64, "kernel arguments");
 
 template <int H>
 __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(H <= 5 ? 3 : 2))) sdl_gramfma_pair_kernel(const PairArgs a)
@@ -500,7 +501,7 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
             }
         };
         if (k < last) {
-            if (a.fast) walk(std::true_type{});
+            if ((a.fast >> s) & 1u) walk(std::true_type{});
             else walk(std::false_type{});
         }
         if (stop - set_first > whole) {
@@ -742,17 +743,16 @@ int launch_pair(const float* g, const void* const* w, uint32_t M, Set* sets, uin
     a.M = M;
     for (uint32_t m = 0; m < M; ++m) a.w[m] = static_cast<const uint16_t*>(w[m]);
     uint64_t tiles = 0;
-    bool fast = true;
     for (uint32_t s = 0; s < n_sets; ++s) {
         a.first_tile[s] = (uint32_t)tiles;
         a.offset[s] = sets[s].offset;
         a.numel[s] = sets[s].numel;
         tiles += (sets[s].numel + kPairTile - 1) / kPairTile;
         if (tiles >= 0xffffffffull) return SDL_ERR_UNSUPPORTED;
-        fast = fast && aligned16(g + sets[s].offset);
+        bool fast = aligned16(g + sets[s].offset);
         for (uint32_t m = 0; m < M; ++m) fast = fast && aligned16(static_cast<const uint16_t*>(w[m]) + sets[s].offset);
+        a.fast |= (uint64_t)fast << s;
     }
-    a.fast = fast ? 1u : 0u;
     a.first_tile[n_sets] = (uint32_t)tiles;
     for (uint32_t s = n_sets + 1u; s <= (uint32_t)kMaxSets; ++s) a.first_tile[s] = 0xffffffffu;
     const uint32_t resident = pair_resident(M);

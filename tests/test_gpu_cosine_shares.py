@@ -45,3 +45,26 @@ def test_sets_and_their_fragment(M, name):
         c = np.divide(ref, np.outer(norm, norm), out=np.zeros_like(ref), where=np.outer(norm, norm) > 0)
         np.testing.assert_allclose(cos, c, atol=1e-11, rtol=0)
         np.testing.assert_allclose(mean, c[np.triu_indices(M, 1)].mean(), atol=1e-11, rtol=0)
+
+
+@pytest.mark.parametrize("M", [9, 12, 13, 16])
+def test_each_set_by_its_own_alignment(M):
+    """Sets on 16 bytes in every array, on 16 bytes of fp32 and 8 of bf16, and at odd elements, one behind the other in one launch:
+    the first and the last of 48 sets aligned, and neither."""
+    for shift in (0, 4):
+        numel = [8 * T] + [[3 * T + 1, 2 * T + 7, T + 4, 5 * T + 4][k % 4] for k in range(46)] + [4 * T + 3]
+        plan = sdl.sdl_fragment_plan(numel, [0] * 48, 1, 1, sdl.PATTERN_STRIDED, 10, 0)
+        g0, _, w0, _ = workloads.make_span(plan.total_numel + shift, M, tau=0, delta="shared10", base_seed=M, device="cuda")
+        g, w = g0[shift:], [x[shift:] for x in w0]
+        spans = sdl.sdl_plan_fragment_spans(plan, 0)
+        assert {(o + shift) % 8 for o, _, _ in spans} == {0, 4, 1 + shift}
+        results, workspace = sdl.alloc_cosine(M, 48)
+        fragment = torch.empty(sdl.cosine_result_doubles(M), dtype=torch.float64, device="cuda")
+        sdl.sdl_outer_grad_cosine_plan(plan, 0, g, w, results, fragment, workspace)
+        d = torch.stack([(g - x.float()).double() for x in w])
+        want = [(d[:, o:o + n] @ d[:, o:o + n].T).cpu().numpy() for o, n, _ in spans]
+        for got, ref in [(results[k], x) for k, x in enumerate(want)] + [(fragment, sum(want))]:
+            G = sdl.split_cosine_result(got, M)[0].cpu().numpy()
+            norm = np.sqrt(np.diag(ref))
+            # the same exact products in another order: rounding of fp64 sums only
+            assert np.abs(G - ref).max() <= 1e-11 * np.outer(norm, norm).max()
