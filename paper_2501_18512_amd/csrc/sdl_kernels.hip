@@ -382,7 +382,11 @@ struct TileIOT {
     template <int FMT> __device__ __forceinline__ float load_scale(uint32_t m, int row) const
     {
         if constexpr (is_span_scaled(FMT)) {
-            return block_scale_from_exponent<FMT>(span_amax(m) >> 23).scale;
+            // us, vector and scalar loads, 28 M parameters: one-pass receive M = 4 168 and 162, M = 8 256 and 244; without the merge M = 8
+            // 94.8 and 93.4, M = 16 116.8 and 115.3, other counts the same; groups at odd elements, receive M = 8 380 and 385, without
+            // the merge 125 and 127
+            constexpr bool kScalar = ALIGNED && !PART;
+            return block_scale_from_exponent<FMT>((kScalar ? span_amax_scalar(m) : span_amax(m)) >> 23).scale;
         } else {
             constexpr int B = block_elems(FMT);
             const uint32_t sb = __builtin_amdgcn_raw_buffer_load_b8(
@@ -773,8 +777,11 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
 
     // ---- loads that do not depend on anything; the scale words first: loads return in order, and the first replica cannot be encoded
     // without its own (28 M parameters, us, behind the tile's loads and ahead of them: fused, the whole call, M = 2 160.9 and 158.3;
-    // send M = 4 134 and 128).  From 4 replicas the fused step has enough on the way and takes scalar loads where it needs the
-    // words (50 M parameters, whole call, M = 4: 418 so, 423 ahead of the tile, 425 by scalar loads ahead of it).
+    // send M = 4 134 and 128).  With 4 and 8 replicas compiled in, the fused step has enough on the way and takes scalar loads where it needs
+    // the words (50 M parameters, whole call, M = 4: 418 so, 423 ahead of the tile, 425 by scalar loads ahead of it).  Of any M, the words
+    // of a group of replicas go ahead of the group's loads as well: 28 M parameters, ahead and by scalar loads where needed, fused M = 3 / 6 / 12 /
+    // 16 211 / 320 / 582 / 764 and 212 / 321 / 583 / 764; with messages M = 2 / 4 / 8 / 16 166 / 265.5 / 440 / 844 and 169 / 264 / 482 / 913;
+    // send M = 3 / 12 107 / 330 and 110 / 342.  (Behind the group's loads: fused M = 3 222, M = 6 335.)
     constexpr bool kWordHere = MODE == kFused && MT >= 4 && is_span_scaled(FMT);
     if constexpr (MT > 0 && is_span_scaled(FMT) && (MODE == kQuantize || MODE == kFused) && !kWordHere) {
 #pragma unroll
