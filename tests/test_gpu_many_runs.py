@@ -1,6 +1,8 @@
-"""Fragments of many runs: a launch takes up to 112 of them, found in groups of 16 by their first workgroups, and the next
-launch starts where it ends.  Run counts at the edges of a group and of a launch, against the oracle run by run: the fused
-step without messages at all of them, the calls that read or write messages behind the end of a launch."""
+"""Fragments of many runs: a launch takes up to 272 of them (160 with a whole-span scale), found in groups of 16 by their first
+workgroups, and the next launch starts where it ends, in the messages and in staged state too.  Run counts at the edges of a
+group and of a launch, against the oracle run by run: the fused step without messages at all of them, the calls that read or write
+messages behind the end of a launch.  Runs of odd lengths, whose last tiles take range-checked accesses of single elements, and of
+multiples of four, whose last tiles take the wide ones."""
 import numpy as np
 import pytest
 import torch
@@ -13,12 +15,18 @@ from gpu_util import HostCopy, assert_bf16_within_ulp, assert_bytes_equal, asser
 pytestmark = pytest.mark.gpu
 
 
+def _lengths(rng, n, odd):
+    """Lengths that never join (odd ones, or multiples of 4 and not of 128); some runs take several tiles, so that first workgroups
+    are not run numbers."""
+    return [int(x) * 2 + 1 if odd else int(x) // 31 * 128 + int(x) % 31 * 4 + 4 for x in rng.integers(0, 700 if odd else 340, n)]
+
+
+@pytest.mark.parametrize("odd", [True, False])
 @pytest.mark.parametrize("staged", [False, True])
-@pytest.mark.parametrize("n_runs", [1, 15, 16, 17, 33, 111, 112, 113, 128, 225])
-def test_fused_step_over_many_runs(n_runs, staged):
+@pytest.mark.parametrize("n_runs", [1, 15, 16, 17, 33, 111, 112, 113, 128, 225, 271, 272, 273, 545])
+def test_fused_step_over_many_runs(n_runs, staged, odd):
     rng = np.random.default_rng(n_runs)
-    # odd sizes never join, and some runs take several tiles, so that first workgroups are not run numbers
-    numel = [int(n) * 2 + 1 for n in rng.integers(0, 700, n_runs)]
+    numel = _lengths(rng, n_runs, odd)
     plan = sdl.sdl_fragment_plan(numel, [0] * n_runs, 1, 1, sdl.PATTERN_STRIDED, 10, 1)
     runs = sdl.sdl_plan_fragment_runs(plan, 0)
     assert len(runs) == n_runs
@@ -80,14 +88,15 @@ def _receive(staged, plan, g, mom, codes, scales, w_now, fmt):
                                                sdl._stream(None)))
 
 
+@pytest.mark.parametrize("odd", [True, False])
 @pytest.mark.parametrize("staged", [False, True])
 @pytest.mark.parametrize("M", [2, 3])                      # tiles of one row and of two
-@pytest.mark.parametrize("fmt", [sdl.FMT_E3M0_B128, sdl.FMT_E3M0_SPAN, sdl.FMT_BF16])
-@pytest.mark.parametrize("n_runs", [113, 225])
-def test_messages_over_several_launches(n_runs, fmt, M, staged):
+@pytest.mark.parametrize("fmt,n_runs", [(sdl.FMT_E3M0_B128, 273), (sdl.FMT_E3M0_B128, 545), (sdl.FMT_E3M0_SPAN, 161),
+                                        (sdl.FMT_E3M0_SPAN, 321), (sdl.FMT_BF16, 272), (sdl.FMT_BF16, 273)])
+def test_messages_over_several_launches(n_runs, fmt, M, staged, odd):
     rng = np.random.default_rng(n_runs + M)
-    # odd sizes never join, and every second group is the other fragment's: the runs lie apart, the first not at the start
-    numel = [int(n) * 2 + 1 for n in rng.integers(0, 700, 2 * n_runs)]
+    # every second group is the other fragment's: the runs lie apart, the first not at the start
+    numel = _lengths(rng, 2 * n_runs, odd)
     plan = sdl.sdl_fragment_plan(numel, [k % 2 for k in range(2 * n_runs)], 2, 2, sdl.PATTERN_STRIDED, 10, 1)
     runs = sdl.sdl_plan_fragment_runs(plan, 1)
     assert len(runs) == n_runs
