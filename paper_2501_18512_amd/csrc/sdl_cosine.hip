@@ -15,7 +15,7 @@
 //                     the end the wavefront folds them, half of the sums at each exchange, and
 //                     its lanes write one partial Gram matrix.  The next tile's loads are issued
 //                     before the current tile is consumed.
-//   sdl_gramfma_pair_kernel  the same for 9 to 16 replicas: two wavefronts with half of the matrix each, which
+//   sdl_gram_pair_kernel  the same for 9 to 16 replicas: two wavefronts with half of the matrix each, which
 //                     exchange the outer gradients through LDS.
 //   sdl_gram_finalize adds the partial matrices of a set in a fixed order (one thread per entry and
 //                     slice of the matrices, then the slices as a tree; a set with many partial matrices in
@@ -369,7 +369,7 @@ struct PairArgs {
 static_assert(sizeof(PairArgs) <= 4096 && kMaxSets <= 64, "kernel arguments");
 
 template <int H>
-__global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(H <= 5 ? 3 : 2))) sdl_gramfma_pair_kernel(const PairArgs a)
+__global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(H <= 5 ? 3 : 2))) sdl_gram_pair_kernel(const PairArgs a)
 {
     constexpr int kOff = (H + 1) / 2;                // entries of the block rows x columns per row
     constexpr int kTri = H * (H + 1) / 2, kSums = kTri + H * kOff, kLeft = halved(kSums);
@@ -785,10 +785,10 @@ int launch_pair(const float* g, const void* const* w, uint32_t M, Set* sets, uin
     if (!n_wg) return SDL_OK;
     const dim3 grid(n_wg), block(2 * kWave);
     switch (H) {
-    case 5: hipLaunchKernelGGL((sdl_gramfma_pair_kernel<5>), grid, block, 0, st, a); break;
-    case 6: hipLaunchKernelGGL((sdl_gramfma_pair_kernel<6>), grid, block, 0, st, a); break;
-    case 7: hipLaunchKernelGGL((sdl_gramfma_pair_kernel<7>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((sdl_gramfma_pair_kernel<8>), grid, block, 0, st, a); break;
+    case 5: hipLaunchKernelGGL((sdl_gram_pair_kernel<5>), grid, block, 0, st, a); break;
+    case 6: hipLaunchKernelGGL((sdl_gram_pair_kernel<6>), grid, block, 0, st, a); break;
+    case 7: hipLaunchKernelGGL((sdl_gram_pair_kernel<7>), grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL((sdl_gram_pair_kernel<8>), grid, block, 0, st, a); break;
     }
     return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
 }

@@ -1,14 +1,13 @@
-"""The sums of 9 to 16 replicas come from other kernels than those of up to 8 (two wavefronts; matrix cores, which round towards
-zero) and must be no further from the exact ones.
+"""The sums of 9 to 16 replicas come from other kernels than those of up to 8 (two wavefronts, which begin a new chain of additions
+every 16 parameters of a lane) and must be no further from the exact ones.
 
 Exact: the fp64 products of fp32 differences are exact; they are folded in halves with the error of every addition kept
 (two-sum), which leaves about 1e-30.  Measure: root mean square of the relative error of the diagonal entries, over seeds.  The
 same entries from a call with the first 8 replicas alone are the yardstick, but no less than what any tree of additions leaves:
 a rounding to nearest errs by u / sqrt(3) of the binade, u = 2^-53, 0.43 u of the value on average over mantissas, and the
 levels of a tree, 2^k operands of 2^-k of the size, add up to 0.43 u * sqrt(1 + 1/2 + 1/4 + ...) = 0.6 u.  The entries of a seed
-share g, so a ratio of two measures scatters by a fifth: the bound is 1.6.  Sums of the matrix cores in chains of 64
-parameters are at 1.5 to 3 times the yardstick, those of two wavefronts with half as many workgroups at twice of it for
-52.9 M parameters."""
+share g, so a ratio of two measures scatters by a fifth: the bound is 1.6.  Diagonal entries in one chain of a lane's 800 parameters
+are at twice the yardstick for 52.9 M parameters with outliers."""
 import pytest
 import torch
 

@@ -1,7 +1,7 @@
-"""More than 8 replicas: 9 to 12 by two wavefronts with half of the matrix each, 13 to 16 on the matrix cores.  Sizes at the
-edges of their tiles (256 and 64 / 512 parameters), arrays at any element, a set that several workgroups share, sets and
-their fragment out of one launch and of two, and a NaN and an infinity in one replica, which must stay in that replica's row
-and column."""
+"""More than 8 replicas: two wavefronts with half of the matrix each, by kernels for 9 and 10, 11 and 12, 13 and 14, 15 and 16 (8
+replicas, whose tiles have 512 parameters, beside them).  Sizes at the edges of the tiles (256 parameters, 64 of them at a
+time), arrays at any element, a set that several workgroups share, sets and their fragment out of one launch and of two, and a
+NaN and an infinity in one replica, which must stay in that replica's row and column."""
 import numpy as np
 import pytest
 import torch

@@ -20,6 +20,7 @@ def test_cosine_kernels_use_no_scratch(tmp_path):
     out = subprocess.run([HIPCC, *flags, "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o",
                           str(tmp_path / "cosine.o")], check=True, capture_output=True, text=True).stderr
     scratch = dict(re.findall(r"Function Name: (\S+).*?ScratchSize \[bytes/lane\]: (\d+)", out, re.S))
-    kernels = [k for k in scratch if "sdl_gram" in k]
-    assert len(kernels) >= 12 and any("mfma" in k for k in kernels)
-    assert {k: int(scratch[k]) for k in kernels if int(scratch[k])} == {}
+    kernels = {re.sub(r"^_Z\D*\d+\w+?_N_1\d+", "", k): int(x) for k, x in scratch.items() if "sdl_gram" in k}
+    names = [f"sdl_gram_kernelILi{M}E" for M in range(1, 9)] + [f"sdl_gram_pair_kernelILi{H}E" for H in range(5, 9)] + ["sdl_gram_finalizeE"]
+    assert sorted(n for n in names for k in kernels if k.startswith(n)) == sorted(names) and len(kernels) == len(names)
+    assert {k: x for k, x in kernels.items() if x} == {}
