@@ -65,7 +65,6 @@ struct GramArgs {
     const float* g;
     const uint16_t* w[SDL_MAX_WORKERS];
     double* partial;               // [workgroup of the launch][M*M]
-    uint32_t M;                    // side of the matrix
     uint32_t n_pieces;
     uint32_t group_wg[kMaxPieces / 16 - 1];   // first workgroup of the 16th, 32nd, ... piece
     uint32_t first_wg[kMaxPieces];            // of each piece; 0xffffffff behind the last
@@ -692,7 +691,6 @@ int launch_gram(const float* g, const void* const* w, uint32_t M, const Set* set
     GramArgs a{};
     a.g = g;
     a.partial = partial;
-    a.M = M;
     for (uint32_t& x : a.group_wg) x = 0xffffffffu;
     for (uint32_t& x : a.first_wg) x = 0xffffffffu;
     // cut the sets into windows: about `windows` pieces per launch, shared out like the workgroups

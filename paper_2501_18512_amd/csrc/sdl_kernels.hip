@@ -53,7 +53,7 @@ constexpr int kPad = kRow * kMaxRows;          // message and staging layouts pa
                                               // parameters (512): a whole number of tiles of either height
 constexpr int kRunGroup = 16;                 // runs whose first workgroups a workgroup compares at once
 constexpr int kTableWords = 3 * 17 * kRunGroup;   // what a launch says about its runs (3.9 KB of kernel arguments in all)
-constexpr int kCheckedRuns = 16;              // pieces over which a fragment's workgroups are added up for the size check
+constexpr int kCheckedRuns = 16;              // pieces over which a fragment's workgroups are added up for the check of its size
 constexpr uint64_t kMaxRunElems = 1ull << 30;  // longest run of a launch (its numbers are 32-bit); longer ones are cut here
 
 enum Mode { kQuantize = 0, kReduce = 1, kMerge = 2, kFused = 3, kReceive = 5 };   // kReceive = kReduce + kMerge
@@ -1818,7 +1818,8 @@ static int launch_fragment(Args& a, const sdl_plan_t* plan, uint32_t p, Align al
     PieceWalk::Piece pc;
     const uint32_t tile = tile_elems(MODE, a, fmt);
     {
-        // sizes are checked for every launch of the call before the first one is made
+        // refused before anything is launched: a fragment of which 16 consecutive pieces need more than 2^31 - 1 workgroups.  (Launches
+        // are cut to the grid's limit by themselves, see RunBuilder::fits.)
         PieceWalk walk = start;
         uint64_t n_wg = 0;
         for (uint32_t in_group = 0; walk.next(&pc);) {
