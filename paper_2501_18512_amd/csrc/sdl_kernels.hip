@@ -94,8 +94,9 @@ constexpr int block_elems(int f)
 // How the whole tiles of a run reach memory (a ragged last tile: the buffer path too if the run takes it and
 // its length is a multiple of 4, else one access per element).
 enum TilePath : uint32_t {
-    kPathBuffer = 1,    // the call's arrays are 16-byte aligned and the run starts on a multiple of 4 elements
-    kPathVector = 2,    // some array starts at some other element (or, messages of 4 and 8 bits, byte)
+    kPathBuffer = 1,    // the call's arrays are 16-byte aligned and the run starts on a multiple of 4 elements, and if it is long
+                        // on one of 8 (see Align)
+    kPathVector = 2,    // any other run (messages of 4 and 8 bits may start at any byte)
 };
 
 // What a launch says about its runs, in 32-bit numbers relative to the launch's bases, three words a run so that as many as
@@ -1433,6 +1434,17 @@ bool valid_format(sdl_format_t fmt) { return fmt >= SDL_FMT_FP32 && fmt <= SDL_F
 
 // Alignment of a call's pointers (model: g, mom and the replicas; msg: the codes, scale bytes need none), and then of a run's
 // first element: model asks for what the four elements of a lane need, wide for 16 bytes in every array, line for a cache line.
+//
+// The buffer path needs no more than model, but the whole tiles of a long run that is off 16 bytes are faster on the vector path (but for
+// the send side).  us, on the buffer path and on the vector path:
+//   runs of 3 and 4 M parameters, 42 M, half of them 4 elements off: reduce M = 2 bf16 143 and 130, receive M = 5 E4M3 312 and 295,
+//   merge M = 8 296 and 289, with messages M = 2 bf16 247 and 225, fused M = 8 539 and 528, M = 2 201 and 200; send M = 1 47 and 49, M = 4 108 and
+//   110, M = 8 196 and 202;
+//   160004 each: reduce M = 2 112 and 106, with messages 186 and 178, receive M = 4 and fused M = 2 the same;
+//   40004 each: reduce 87 and 83, with messages 145 and 143, the others the same;
+//   10004 each: receive M = 8 E4M3 125 and 144, with messages M = 8 156 and 169, merge M = 4 46 and 49, reduce M = 2 44 and 42.
+// So the line is kLongRun.
+constexpr uint64_t kLongRun = 1u << 16;
 struct Align {
     bool model = true, wide = true, line = true, msg = true;
     void add_model(const void* p)
@@ -1445,7 +1457,10 @@ struct Align {
         const uint64_t low = offset | soff;
         return Align{model && low % kVec == 0, wide && low % 8 == 0, line && low % 64 == 0, msg};
     }
-    TilePath path() const { return model && msg ? kPathBuffer : kPathVector; }
+    TilePath path(int mode, uint64_t n) const
+    {
+        return (wide || (model && (mode == kQuantize || n < kLongRun))) && msg ? kPathBuffer : kPathVector;
+    }
 };
 
 // Parameters per workgroup of the kernel variant that a call in this mode will run.
@@ -1459,10 +1474,11 @@ uint32_t tile_elems(int mode, const Args& a, sdl_format_t fmt)
 struct RunBuilder {
     Args* a;
     uint64_t tile;       // parameters per workgroup
+    int mode;
     uint32_t words, most;      // of a run; runs that the table has room for
     uint64_t n_wg = 0, n_unaligned = 0;
-    RunBuilder(Args* args, uint32_t tile_elems, sdl_format_t fmt)
-        : a(args), tile(tile_elems), words((uint32_t)run_words(fmt)), most((uint32_t)max_runs(fmt)) { reset(); }
+    RunBuilder(Args* args, int mode, uint32_t tile_elems, sdl_format_t fmt)
+        : a(args), tile(tile_elems), mode(mode), words((uint32_t)run_words(fmt)), most((uint32_t)max_runs(fmt)) { reset(); }
     void reset()
     {
         a->n_runs = 0;
@@ -1489,7 +1505,7 @@ struct RunBuilder {
         if (r % kRunGroup == 0 && r) a->group_wg[r / kRunGroup - 1] = (uint32_t)n_wg;
         uint32_t* const run = a->table + most + r * (words - 1);
         run[0] = (uint32_t)(offset - a->offset0);
-        run[1] = (uint32_t)n | (al.path() == kPathVector ? kVectorBit : 0u);
+        run[1] = (uint32_t)n | (al.path(mode, n) == kPathVector ? kVectorBit : 0u);
         if (words == (uint32_t)kSpanRunWords) { run[2] = sidx; run[3] = (uint32_t)(soff - a->soff0); }
         n_wg += wgs(n);
         if (!al.line) n_unaligned += wgs(n);
@@ -1572,7 +1588,7 @@ int run_single_span(Args& a, uint64_t n, sdl_format_t fmt, Align al, void* strea
             if (launch_span_prepass(a, &one, 1, (hipStream_t)stream) != hipSuccess) return SDL_ERR_DEVICE;
         }
     }
-    RunBuilder rb(&a, tile, fmt);
+    RunBuilder rb(&a, MODE, tile, fmt);
     return add_piece<MODE>(rb, fmt, 0, n, al, 0, 0, 0, stream) && flush<MODE>(rb, fmt, stream) ? SDL_OK : SDL_ERR_DEVICE;
 }
 
@@ -1853,7 +1869,7 @@ static int launch_fragment(Args& a, const sdl_plan_t* plan, uint32_t p, Align al
             }
         }
     }
-    RunBuilder rb(&a, tile, fmt);
+    RunBuilder rb(&a, MODE, tile, fmt);
     PieceWalk walk = start;
     while (walk.next(&pc))
         if (!add_piece<MODE>(rb, fmt, pc.offset, pc.numel, pc.al, pc.msg, pc.sidx, pc.soff, stream)) return SDL_ERR_DEVICE;

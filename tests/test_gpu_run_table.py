@@ -95,3 +95,13 @@ def test_more_runs_than_a_launch_takes(fmt, n_runs):
                                     codes, scales)
     fused = whole[-2 * (2 + M):-(2 + M)]
     _same(fused, [g, mom] + wn)
+
+
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 8])
+@pytest.mark.parametrize("fmt", ["e3m0", "e3m0_span", "e4m3", "bf16"])
+def test_long_runs_off_16_bytes_give_what_any_alignment_gives(fmt, M):
+    """From 65536 parameters a run that starts on a multiple of four elements and not of eight takes the path for any alignment in
+    every call but the send: lengths around that, each off 16 bytes and on them, against the same model one element further."""
+    numel = [4, 65532, 65532, 65540, 65548, 131076, 4, 65536]
+    assert {sum(numel[:k]) % 8 for k in (1, 3, 5, 7)} == {4} and {sum(numel[:k]) % 8 for k in (2, 4)} == {0}
+    _same(_all_calls(numel, sdl.FORMATS[fmt], M, 0), _all_calls(numel, sdl.FORMATS[fmt], M, 1))
