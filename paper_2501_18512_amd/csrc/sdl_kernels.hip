@@ -1228,8 +1228,8 @@ size_t code_bytes_at(sdl_format_t fmt, uint64_t elem)
 // grows and DRAM page locality is lost: the knob that matters for a streaming kernel.  The kernels that write the replicas
 // back want few, and fewer the more arrays they walk, but never less than 8 (6 cost 15-20 %); the receive side without the
 // merge reads many small messages and writes two arrays, and wants more as decoding grows with the replicas; the send side
-// wants all it can get.  Formats that run the codec want more than those that only round.  us in one process, the caps in turn
-// on the same arrays, E3M0 unless named (between processes all of a row move by up to 4 %, with where the arrays lie; within one
+// wants all it can get, except where it writes whole words for many replicas.  Formats that run the codec want more than
+// those that only round.  us in one process, the caps in turn on the same arrays, E3M0 unless named (between processes all of a row move by up to 4 %, with where the arrays lie; within one
 // a figure repeats to 1 %):
 //                                         M    none   21   16   11    8
 //   fused, 105 M parameters               2     489  485  476  469  495
@@ -1258,6 +1258,10 @@ size_t code_bytes_at(sdl_format_t fmt, uint64_t elem)
 //                                        10     236  232  228  258  316
 //                                        12     253  247  254  297  366
 //                                        16     280  277  302  362  444
+//   send, FP32, 50 M                      5     296  306  298  285  281
+//                                         6     355  367  358  345  336
+//                                        12     706  728  719  699  679
+//                                        16     940  969  961  938  922
 //   messages written, BF16, 53 M          2     295  289  278  273  279
 //                                         4     454  456  448  430  415
 //                                         8     785  793  785  753  731
@@ -1279,6 +1283,8 @@ uint32_t waves_per_cu(int mode, uint32_t mt, uint32_t M, int fmt, bool aliased, 
     case kMerge:
         if (mt == 0) return M == 3 ? 21 : (M == 5 ? 16 : (M <= 7 ? 11 : 8));
         return mt == 1 ? 0 : (mt == 2 ? 16 : (mt == 4 ? 11 : 8));
+    case kQuantize:
+        return mt == 0 && M >= 5 && fmt == SDL_FMT_FP32 ? 8 : 0;
     case kReduce:
         if (mt == 0) return M <= 10 ? 16 : 21;
         return mt == 4 ? 16 : 0;
