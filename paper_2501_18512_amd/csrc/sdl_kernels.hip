@@ -1549,6 +1549,18 @@ bool arrays_clash(const Args& a, sdl_format_t fmt, uint64_t model_elems, uint64_
     return false;
 }
 
+// The pass behind the pre-pass of a whole-span scale finds g and w_send in the memory-side cache, if they are small.  A line that two
+// XCDs fetch is cheap there, and chunks cost more than they save.  us, chunks and the order of the grid, one run 8 elements
+// off a line, by what the pre-pass read: send M = 1 25 MB 19.0 17.2, 50 MB 26.9 24.6, 200 MB 75.0 73.7, M = 4 25 MB 18.1 17.4, 100 MB
+// 42.7 42.0, 400 MB 158 160; fused M = 1 25 MB 31.1 29.5, 50 MB 50.0 48.7, M = 2 34 MB 35.1 33.2, 67 MB 59.5 59.2, 134 MB 104.6 105.3, M = 4
+// 25 MB 29.7 27.9, 100 MB 80.1 81.2, M = 8 42 MB 41.1 39.9, 84 MB 71.4 72.4.  With many runs the pre-pass leaves them in another order:
+// 193 runs of 100 to 30000 parameters, 30 MB, fused M = 4 50.1 51.2.
+constexpr uint64_t kFoundBytes = 64ull << 20;
+template <int MODE> constexpr bool after_prepass(sdl_format_t fmt)
+{
+    return (MODE == kQuantize || MODE == kFused) && is_span_scaled(fmt);
+}
+
 // Launches what the builder holds; false if the launch failed.
 template <int MODE>
 bool flush(RunBuilder& rb, sdl_format_t fmt, void* stream)
@@ -1556,7 +1568,8 @@ bool flush(RunBuilder& rb, sdl_format_t fmt, void* stream)
     if (rb.a->n_runs == 0) return true;
     // what most of the launch's tiles want (see chunked_tile)
     const uint32_t whole = kXcds * kChunkRows / (uint32_t)(rb.tile / kRow);
-    rb.a->chunked = 2 * rb.n_unaligned > rb.n_wg ? (uint32_t)rb.n_wg / whole * whole : 0u;
+    const bool chunks = 2 * rb.n_unaligned > rb.n_wg && !(after_prepass<MODE>(fmt) && rb.a->n_runs == 1 && rb.n_wg * rb.tile * (4 + 2 * rb.a->M) <= kFoundBytes);
+    rb.a->chunked = chunks ? (uint32_t)rb.n_wg / whole * whole : 0u;
     const hipError_t e = launch<MODE>(*rb.a, fmt, (uint32_t)rb.n_wg, (hipStream_t)stream);
     rb.reset();
     return e == hipSuccess;
