@@ -14,10 +14,9 @@
 //   - eight neighbouring lanes own one 32-element scale block, and the block maximum
 //     is three DPP exchanges (two inside the quad, one across the half row); wider
 //     blocks add a row mirror and ds_bpermute exchanges.  No LDS storage is used.
-// Tiles of runs that start on a multiple of four elements in 16-byte aligned arrays use buffer
+// Tiles of runs that start on a multiple of four elements in 16-byte aligned arrays (long runs: of eight) use buffer
 // instructions with non-temporal cache policy (every byte is touched once), ragged tails of a multiple
-// of four elements among them; full tiles of runs in which some array starts at some other
-// element use vector accesses of element alignment in the same lane layout; other ragged tails use
+// of four elements among them; full tiles of other runs use vector accesses of element alignment in the same lane layout; other ragged tails use
 // range-checked accesses of one element each.  A launch covers up to 272 contiguous runs of the flat
 // model (160 of a whole-span format); every workgroup belongs to exactly one run, so scale blocks never straddle
 // runs.
@@ -910,7 +909,7 @@ __device__ __forceinline__ void process(const Args& a, const IO& io)
 // 388 -> 329 us, M = 4 572 -> 483, M = 8 892 -> 869; half or twice the chunk is up to 2 % slower, and arrays that start on a
 // line lose 3-8 % with it).  The rule (RunBuilder, flush) asks whether a run starts on a line in every array: groups of 1000 and
 // 3 M parameters, which start on 16 bytes, without chunks and with: fused M = 2 374 and 342 us, M = 4 545 and 475, M = 8 856 and
-// 826, send M = 4 179 and 174, receive M = 4 475 and 420, M = 2 332 and 294.
+// 826, send M = 4 179 and 174, receive M = 4 475 and 420, M = 2 332 and 294.  (One exception: kFoundBytes.)
 constexpr int kXcds = 8;
 constexpr int kChunkRows = 8;
 template <int ROWS>
