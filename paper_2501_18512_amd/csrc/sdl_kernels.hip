@@ -1228,8 +1228,8 @@ size_t code_bytes_at(sdl_format_t fmt, uint64_t elem)
 // back want few, and fewer the more arrays they walk, but never less than 8 (6 cost 15-20 %); the receive side without the
 // merge reads many small messages and writes two arrays, and wants more as decoding grows with the replicas; the send side
 // wants all it can get, except where it writes whole words for many replicas.  Formats that run the codec want more than
-// those that only round.  us in one process, the caps in turn on the same arrays, E3M0 unless named (between processes all of a row move by up to 4 %, with where the arrays lie; within one
-// a figure repeats to 1 %):
+// those that only round.  us in one process, the caps in turn on the same arrays, E3M0 unless named (between processes all
+// of a row move by up to 4 %, with where the arrays lie; within one a figure repeats to 1 %):
 //                                         M    none   21   16   11    8
 //   fused, 105 M parameters               2     489  485  476  469  495
 //                                         3     609  609  600  589  629
