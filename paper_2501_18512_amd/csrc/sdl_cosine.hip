@@ -1,7 +1,7 @@
 // Cosine similarity between the replicas' outer gradients (Appendix of the paper, paragraph on
 // the outer gradients' cosine similarity) for gfx950 (MI355X).
 //
-// Three kernels.
+// Four kernels.
 //   sdl_gram_kernel   up to 8 replicas: streams g and the M replicas once and accumulates the Gram matrix of
 //                     the outer gradients Delta_m = g - float(w_m).  A workgroup is one
 //                     64-lane wavefront; a set of parameters gets a share G of the launch's
@@ -17,6 +17,8 @@
 //                     before the current tile is consumed.
 //   sdl_gram_pair_kernel  the same for 9 to 16 replicas: two wavefronts with half of the matrix each, which
 //                     exchange the outer gradients through LDS.
+//   sdl_digit_sums_kernel  the same for 13 to 16 replicas and many parameters: the outer gradients as 8-bit digits, whose products
+//                     the matrix cores add up exactly.
 //   sdl_gram_finalize adds the partial matrices of a set in a fixed order (one thread per entry and
 //                     slice of the matrices, then the slices as a tree; a set with many partial matrices in
 //                     two launches) and derives cos and the mean over pairs.  The same kernel adds
@@ -351,7 +353,7 @@ struct Share {
     uint32_t first_wg, first_tile, per_wg, extra;     // workgroup first_wg + i takes per_wg tiles, one more if i < extra
 };
 // Workgroups of a launch that are on the chip at once: 12 wavefronts on a compute unit with up to 168 registers, else 8.
-constexpr uint32_t pair_resident(uint32_t M) { return 256u * (M <= 10u ? 6u : 4u); }
+constexpr uint32_t pair_resident(uint32_t M, bool digits) { return 256u * (M <= 10u || digits ? 6u : 4u); }
 struct PairArgs {
     const float* g;
     const uint16_t* w[SDL_MAX_WORKERS];
@@ -366,6 +368,20 @@ struct PairArgs {
     uint64_t numel[kMaxSets];
 };
 static_assert(sizeof(PairArgs) <= 4096 && kMaxSets <= 64, "kernel arguments");
+
+// The set that tile t belongs to.
+__device__ __forceinline__ uint32_t set_of(const PairArgs& a, uint32_t t)
+{
+    uint32_t group = 0;
+#pragma unroll
+    for (int i = 16; i < kMaxSets; i += 16)
+        if (t >= a.first_tile[i]) group = (uint32_t)i;
+    uint32_t s = group;
+#pragma unroll
+    for (int i = 1; i < 16; ++i)
+        if (t >= a.first_tile[group + i]) s = group + (uint32_t)i;
+    return s;
+}
 
 template <int H>
 __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(H <= 5 ? 3 : 2))) sdl_gram_pair_kernel(const PairArgs a)
@@ -451,14 +467,7 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
     uint32_t t = share.first_tile + nth * share.per_wg + (nth < share.extra ? nth : share.extra);
     const uint32_t end = t + share.per_wg + (nth < share.extra ? 1u : 0u);
     while (t < end) {
-        uint32_t group = 0;
-#pragma unroll
-        for (int i = 16; i < kMaxSets; i += 16)
-            if (t >= a.first_tile[i]) group = (uint32_t)i;
-        uint32_t s = group;
-#pragma unroll
-        for (int i = 1; i < 16; ++i)
-            if (t >= a.first_tile[group + i]) s = group + (uint32_t)i;
+        const uint32_t s = set_of(a, t);
         const uint32_t set_first = a.first_tile[s], set_end = a.first_tile[s + 1], stop = end < set_end ? end : set_end;
         const uint64_t offset = a.offset[s], numel = a.numel[s];
         const uint32_t whole = (uint32_t)(numel / kPairTile), last = stop - set_first < whole ? stop - set_first : whole;
@@ -544,6 +553,289 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
+// 13 to 16 replicas and many parameters: the sums in whole numbers on the matrix cores.  A replica's outer gradients, times a power
+// of two that brings the largest of them near 2^21, are rounded to multiples of 2^-22 and written as six signed digits of 8 bits; the
+// products of two replicas' digits are whole numbers that v_mfma_i32_16x16x64_i8 adds up without rounding, 64 parameters of all 256
+// entries at a time, and what 16384 parameters gave is converted and added up in fp64.
+//
+// The digits.  x is a difference, t = x * scale, |t| <= kRoom.  As the sum with kBias is in [2^23, 2^24), fma(x, scale, kBias)
+// is the bit pattern of t rounded to a whole number, plus 0x408080: in each of the two low bytes, and in the seven bits above, a digit
+// with 128 (64) added, which the exclusive or (and an addition of 64 ahead of it) takes off all four bytes of a register at
+// once.  What the rounding left, at most 1/2, is exact as an fma; times 2^22 it gives three more digits in the same way.  A difference
+// has 24 bits, so whatever is larger than 2^-18 of the largest is exact, and smaller ones are off by 2^-44 of the largest at most.
+// Weights of the digits: 2^16, 2^8, 1 and 2^-6, 2^-14, 2^-22.  Three of the 21 products are left out: their weights are 2^-28,
+// 2^-36 and 2^-44, and the signs of their factors have nothing to do with each other.  (Without the square of weight 2^-28 the
+// diagonal would err by 2^-52 to one side where differences have 24 bits.)
+// The products of the digits a < b are formed once and their transpose is added at the end: T + T^T is the matrix of sums if T has
+// half of the squares.
+//
+// The scale of a replica is that of the wavefront's parameters so far: where a difference exceeds what it has room for, the
+// sums so far are put into fp64 and a new one is taken, with room for twice as much and more.  Infinities, NaN and differences below
+// 2^-98 (whose scale would not be a normal number) are added up 64 parameters at a time in fp64.
+//
+// Error against exact sums, 1e-16 of sqrt(G[a][a] G[b][b]), a = b / a != b, rms, by FMAs and here, at 13 and at 16 replicas, 20 M
+// parameters: normal 0.6/0.01 0.7/0.01 and 0.7/0.00 0.7/0.00; Student t3 0.9/0.02 0.8/0.01 and 0.5/0.00 1.2/0.00; with outliers 0.8/0.01
+// 0.8/0.00 and 0.7/0.00 0.9/0.00; replicas that agree, outliers in the same places, 1.4/0.9 0.9/1.0 and 0.9/0.5 0.8/0.9; differences
+// with all 24 bits 0.8/0.7 0.9/1.1 and 0.7/0.6 1.4/0.9; 2.1 M alike.  Sizes that vary by 2^40 from one parameter to the next: 1.0/0.00
+// 0.9/0.00 and 0.5/0.3 1.0/0.3, at 2.1 M 0.8/0.00 1.1/0.00 and 0.9/0.8 0.7/0.8.
+//
+// Bound: vector instructions, 12.5 for a difference (two to form it, a half to look at its size, four for the digits, 3.5 that
+// bring each digit's bytes together and 2 for the signs), and the matrix instructions, 18 for 64 parameters of 16 cycles each, beside which
+// a SIMD issues little else: 346 us at 52.9 M parameters and 16 replicas without the loads, 250 without the matrix instructions either, 312
+// the loads alone, 397 in all (HBM 268).  Whole call, FMAs and here, M = 13 / 14 / 15 / 16: 52.9 M parameters 422 / 424 / 492 / 494
+// and 364 / 370 / 380 / 385; at odd elements 439 / 444 / 515 / 522 and 396 / 402 / 429 / 433.  (The time hardly depends
+// on the replicas, as a matrix instruction has 16 rows whatever they are: at 12 replicas 336 and 354.)  Tried, each beside 390 to 409: a tile of 512
+// for each wavefront, 252 registers, 409; 256 parameters, two tiles in LDS 401; the digits' products one step behind, between the
+// vector instructions of the next, which takes 220 registers 427; workgroups that take turns at the tiles 397; subtraction by
+// v_dot2_f32_bf16, which does not round to nearest.
+constexpr int kDigitTile = kTile;                 // parameters a workgroup takes at a time, 64 of them a step, the wavefronts in turn
+constexpr int kDigitSteps = kDigitTile / kWave;
+constexpr uint32_t kFlushTiles = 64;              // after so many a sum has three products of 2^14 for each of 16384 parameters: 2^30
+// (A launch of fewer parameters has too few of these tiles to fill the chip evenly: 1 M parameters, M = 13 27.4 us by FMAs and 28.9, M = 16 30.8
+// and 30.0; 1.5 M 31.6 and 32.5, 35.8 and 33.9; 2.1 M 38.0 and 36.4, 41.1 and 36.5; 8 M 76 and 71, 89 and 75.)
+constexpr uint64_t kDigitParams = 1ull << 21;
+constexpr bool takes_digits(uint32_t M, uint64_t params) { return M > 12u && params >= kDigitParams; }
+
+constexpr float kBias = 12615808.0f;              // 2^23 + 0x408080
+constexpr float kRoom = 4161407.0f;               // 2^23 - 1 - 0x408080
+constexpr float kLoScale = 4194304.0f;            // 2^22
+constexpr float kFltMax = 3.402823466e+38f;
+
+enum Digit { kHi2, kHi1, kHi0, kLo2, kLo1, kLo0, kDigits };
+struct Product { int a, b, acc; };
+struct DigitSum { int weight; bool square; };     // 2^weight
+constexpr int kDigitSums = 14;
+constexpr DigitSum kSumOf[kDigitSums] = {{32, true}, {24, false}, {16, false}, {16, true}, {8, false}, {0, true}, {10, false},
+                                         {2, false}, {-6, false}, {-14, false}, {-22, false}, {-12, true}, {-20, false}, {-28, true}};
+constexpr Product kProducts[] = {
+    {kHi2, kHi2, 0}, {kHi2, kHi1, 1}, {kHi2, kHi0, 2}, {kHi1, kHi1, 3}, {kHi1, kHi0, 4}, {kHi0, kHi0, 5},
+    {kHi2, kLo2, 6}, {kHi2, kLo1, 7}, {kHi1, kLo2, 7}, {kHi2, kLo0, 8}, {kHi1, kLo1, 8}, {kHi0, kLo2, 8},
+    {kHi1, kLo0, 9}, {kHi0, kLo1, 9}, {kHi0, kLo0, 10}, {kLo2, kLo2, 11}, {kLo2, kLo1, 12}, {kLo1, kLo1, 13}};
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// The lane's number, counted anew: what is computed from it is computed here, not ahead of a loop that needs the registers.
+__device__ __forceinline__ uint32_t lane_here()
+{
+    uint32_t all = ~0u;
+    asm volatile("" : "+s"(all));
+    return __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+}
+__device__ __forceinline__ float from_lane(float x, uint32_t lane)
+{
+    return u2f((uint32_t)__builtin_amdgcn_ds_bpermute((int)(lane << 2), (int)f2u(x)));
+}
+
+// What a wavefront loads of a tile: half of the replicas, and of every lane's 8 parameters of g the first or the last four.
+template <int H>
+struct HalfTile {
+    u32x4 g;
+    u32x4 w[H];
+};
+template <int H>
+__device__ __forceinline__ void load_half(HalfTile<H>& t, const float* g, uint32_t half, const uint16_t* (&w)[H], uint64_t e0,
+                                          uint32_t valid, bool fast, uint32_t lane)
+{
+    if (fast && valid == (uint32_t)kDigitTile) {
+        t.g = __builtin_amdgcn_raw_buffer_load_b128(rsrc(g + e0, kDigitTile * 4), (int)(lane * 32 + half * 16), 0, 2);
+#pragma unroll
+        for (int m = 0; m < H; ++m)
+            t.w[m] = __builtin_amdgcn_raw_buffer_load_b128(rsrc(w[m] + e0, kDigitTile * 2), (int)(lane * 16), 0, 2);
+    } else if (valid == (uint32_t)kDigitTile) {
+        lane = lane_here();
+        t.g = __builtin_nontemporal_load(reinterpret_cast<const u32x4_f32elem*>(g + e0 + lane * kLaneElems + half * 4));
+#pragma unroll
+        for (int m = 0; m < H; ++m)
+            t.w[m] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_bf16elem*>(w[m] + e0 + lane * kLaneElems));
+    } else {                                       // a set's ragged last tile: 0 past the end of g and of every replica
+        lane = lane_here();
+        const __amdgpu_buffer_rsrc_t rg = rsrc(g + e0, valid * 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            t.g[j] = __builtin_amdgcn_raw_buffer_load_b32(rg, (int)((lane * kLaneElems + half * 4 + j) * 4), 0, 0);
+#pragma unroll
+        for (int m = 0; m < H; ++m) {
+            const __amdgpu_buffer_rsrc_t rw = rsrc(w[m] + e0, valid * 2);
+            uint32_t h[kLaneElems];
+#pragma unroll
+            for (int j = 0; j < kLaneElems; ++j)
+                h[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rw, (int)((lane * kLaneElems + j) * 2), 0, 0) & 0xffffu;
+            t.w[m] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+        }
+    }
+}
+
+template <int H>
+__global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(3))) sdl_digit_sums_kernel(const PairArgs a)
+{
+    // A tile in LDS: the replicas, then g, both as they are in memory.  In a step lane l = 16 q + r has 16 parameters of replica r (0 where
+    // there is none), of the q-th quarter of the tile.  The distances make the 16 replicas' pieces, and the four quarters of g, lie in
+    // different banks.
+    constexpr int R = 2 * H, kRowWords = kDigitTile / 2 + 4, kQuarterWords = kDigitTile / 4 + 4;
+    __shared__ __attribute__((aligned(16))) uint32_t stage[R * kRowWords + 4 * kQuarterWords];
+    __shared__ double totals[2][256];                // T of each wavefront: [16 q + r][v] is its row 4 q + v, column r
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const uint32_t M = a.M, r = lane % 16u, q = lane / 16u;
+    const u32x4* const my_w = reinterpret_cast<const u32x4*>(stage + (r < (uint32_t)R ? r : 0u) * kRowWords + q * (kDigitTile / 8));
+    const u32x4* const my_g = reinterpret_cast<const u32x4*>(stage + R * kRowWords + q * kQuarterWords);
+    const uint16_t* w[H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) w[i] = a.w[wave * H + i < M ? wave * H + i : 0u];
+
+    i32x4 sum[kDigitSums];                           // [v] is row 4 q + v, column r
+    float scale = 0.0f, limit = -1.0f;               // of the lane's replica
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < kDigitSums; ++i) sum[i] = i32x4{0, 0, 0, 0};
+    };
+    auto flush = [&]() {
+        const uint32_t l = lane_here(), q = l / 16u;
+        double* const total = &totals[wave][4u * l];
+        const float inv = scale > 0.0f ? 1.0f / scale : 0.0f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            double t = 0.0;
+#pragma unroll
+            for (int i = kDigitSums - 1; i >= 0; --i)
+                t += __builtin_ldexp((double)sum[i][v], kSumOf[i].weight - (kSumOf[i].square ? 1 : 0));
+            total[v] += t * ((double)inv * (double)from_lane(inv, 4u * q + (uint32_t)v));
+        }
+        clear();
+    };
+    // A step that the limits do not cover: true if its products have been added up here.
+    auto adjust = [&](const float (&d)[16], float largest) -> bool {
+        const uint32_t l = lane_here(), q = l / 16u, r = l % 16u;
+        double* const total = &totals[wave][4u * l];
+        float m = __builtin_elementwise_maximum(largest, from_lane(largest, l ^ 16u));
+        m = __builtin_elementwise_maximum(m, from_lane(m, l ^ 32u));
+        const bool fits = m <= limit;
+        if (__builtin_amdgcn_ballot_w64(!fits && (!(m <= kFltMax) || (m > 0.0f && m < 0x1p-98f)))) {
+#pragma unroll 1
+            for (uint32_t from = 0; from < (uint32_t)kWave; from += 16u) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const double half = 0.5 * (double)from_lane(d[e], from + r);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        total[v] = __builtin_fma(half, (double)from_lane(d[e], from + 4u * q + (uint32_t)v), total[v]);
+                }
+            }
+            return true;
+        }
+        flush();
+        if (!fits) {                                 // 2^20 <= m * scale < 2^21
+            const uint32_t e = f2u(m) >> 23;
+            scale = m > 0.0f ? u2f((127u + 127u + 20u - e) << 23) : 0.0f;
+            limit = m > 0.0f ? kRoom * u2f((e - 20u) << 23) : 0.0f;
+            limit = limit <= kFltMax ? limit : kFltMax;
+        }
+        return false;
+    };
+    // 64 parameters of every replica; read_next reads what the next step needs into the registers that wv and gv are in.
+    auto step = [&](const u32x4 (&wv)[2], const u32x4 (&gv)[4], auto read_next) {
+        float d[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const uint32_t x = wv[j / 8][(j % 8) / 2];
+            d[j] = u2f(gv[j / 4][j % 4]) - u2f(j & 1 ? x & 0xffff0000u : x << 16);
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(d[j]));     // formed here, not where it is first used
+        float largest = __builtin_fabsf(d[0]);                         // NaN if any is
+#pragma unroll
+        for (int j = 1; j < 15; j += 2)
+            largest = __builtin_elementwise_maximum(__builtin_elementwise_maximum(largest, __builtin_fabsf(d[j])), __builtin_fabsf(d[j + 1]));
+        largest = __builtin_elementwise_maximum(largest, __builtin_fabsf(d[15]));
+        read_next();
+        if (__builtin_amdgcn_ballot_w64(!(largest <= limit)))
+            if (adjust(d, largest)) return;
+        i32x4 digit[kDigits];
+        auto planes = [&](int k, const uint32_t (&h)[4], int top, int middle, int low) {
+            const uint32_t x = __builtin_amdgcn_perm(h[1], h[0], 0x05010400u), y = __builtin_amdgcn_perm(h[3], h[2], 0x05010400u);
+            const uint32_t u = __builtin_amdgcn_perm(h[1], h[0], 0x0c0c0602u), v = __builtin_amdgcn_perm(h[3], h[2], 0x0c0c0602u);
+            digit[low][k] = (int)(__builtin_amdgcn_perm(y, x, 0x05040100u) ^ 0x80808080u);
+            digit[middle][k] = (int)(__builtin_amdgcn_perm(y, x, 0x07060302u) ^ 0x80808080u);
+            digit[top][k] = (int)((__builtin_amdgcn_perm(v, u, 0x05040100u) + 0x40404040u) ^ 0x80808080u);
+        };
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float x = d[4 * k + j], h = __builtin_fmaf(x, scale, kBias), rest = __builtin_fmaf(x, scale, kBias - h);
+                hi[j] = f2u(h);
+                lo[j] = f2u(__builtin_fmaf(rest, kLoScale, kBias));
+            }
+            planes(k, hi, kHi2, kHi1, kHi0);
+            planes(k, lo, kLo2, kLo1, kLo0);
+        }
+#pragma unroll
+        for (const Product& x : kProducts)
+            sum[x.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(digit[x.a], digit[x.b], sum[x.acc], 0, 0, 0);
+    };
+
+    const uint32_t b = blockIdx.x;
+    Share share = a.shares[0];
+#pragma unroll
+    for (int i = 1; i < kShares; ++i)
+        if (b >= a.shares[i].first_wg) share = a.shares[i];
+    const uint32_t nth = b - share.first_wg;
+    uint32_t t = share.first_tile + nth * share.per_wg + (nth < share.extra ? nth : share.extra);
+    const uint32_t end = t + share.per_wg + (nth < share.extra ? 1u : 0u);
+    while (t < end) {
+        const uint32_t s = set_of(a, t);
+        const uint32_t set_first = a.first_tile[s], set_end = a.first_tile[s + 1], stop = end < set_end ? end : set_end;
+        const uint64_t offset = a.offset[s], numel = a.numel[s];
+        const bool fast = (a.fast >> s) & 1u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) totals[wave][4u * lane_here() + i] = 0.0;
+        clear();
+        scale = 0.0f;
+        limit = -1.0f;
+
+        HalfTile<H> raw;
+        auto load = [&](uint32_t k) {
+            const uint64_t at = (uint64_t)k * kDigitTile, rem = numel - at;
+            load_half<H>(raw, a.g, wave, w, offset + at, rem < (uint64_t)kDigitTile ? (uint32_t)rem : (uint32_t)kDigitTile, fast, lane);
+        };
+        u32x4 wv[2], gv[4];
+        auto read = [&](uint32_t j) {
+#pragma unroll
+            for (uint32_t i = 0; i < 2u; ++i) wv[i] = my_w[2u * j + i];
+#pragma unroll
+            for (uint32_t i = 0; i < 4u; ++i) gv[i] = my_g[4u * j + i];
+        };
+        const uint32_t last = stop - set_first;
+        uint32_t k = t - set_first, tiles = 0;
+        load(k);
+#pragma unroll 1
+        for (; k < last; ++k) {
+            lds_barrier();       // the tile before has been read
+            u32x4* const to = reinterpret_cast<u32x4*>(stage + wave * H * kRowWords) + lane;
+#pragma unroll
+            for (int i = 0; i < H; ++i) to[i * (kRowWords / 4)] = raw.w[i];
+            *reinterpret_cast<u32x4*>(stage + R * kRowWords + lane * 8u + q * 4u + wave * 4u) = raw.g;
+            if (k + 1u < last) load(k + 1u);
+            lds_barrier();
+            if (tiles == kFlushTiles) { flush(); tiles = 0; }
+            ++tiles;
+            read(wave);
+#pragma unroll 1
+            for (uint32_t j = wave; j < (uint32_t)kDigitSteps; j += 2u)
+                step(wv, gv, [&]() { read((j + 2u) % kDigitSteps); });     // (behind the last: read and not used)
+        }
+        flush();
+        __syncthreads();
+        double* out = a.partial + (uint64_t)(uint32_t)((int32_t)b + a.slot[s]) * M * M;
+        for (uint32_t i = wave * kWave + lane_here(); i < 256u; i += 2 * kWave) {
+            const uint32_t x = i / 16u, y = i % 16u, at = (x / 4u * 16u + y) * 4u + x % 4u, turned = (y / 4u * 16u + x) * 4u + y % 4u;
+            if (x <= y && y < M) out[x * M + y] = (totals[0][at] + totals[1][at]) + (totals[0][turned] + totals[1][turned]);
+        }
+        __syncthreads();
+        t = stop;
+    }
+}
+
 // What each output of the finalize kernel adds up.
 constexpr uint32_t kFinThreads = 1024;                                     // most threads of a workgroup
 
@@ -557,7 +849,7 @@ __host__ __device__ constexpr uint32_t fin_slices(uint32_t M)
 constexpr uint32_t fin_chunk(uint32_t M) { return 8u * fin_slices(M); }
 
 // matrices of a launch, without one for each set
-constexpr uint32_t mats_per_launch(uint32_t M) { return M > 8u ? kShares * pair_resident(M) : kGroups; }
+constexpr uint32_t mats_per_launch(uint32_t M) { return M > 8u ? kShares * pair_resident(M, M > 12u) : kGroups; }
 
 // A launch over n sets leaves at most mats_per_launch + n matrices, so at most (mats_per_launch + n) / fin_chunk + n
 // first-level outputs: kFirstLevel and one for each set, of which the workspace and the arguments have room.
@@ -740,12 +1032,15 @@ int launch_pair(const float* g, const void* const* w, uint32_t M, Set* sets, uin
     a.partial = partial;
     a.M = M;
     for (uint32_t m = 0; m < M; ++m) a.w[m] = static_cast<const uint16_t*>(w[m]);
-    uint64_t tiles = 0;
+    uint64_t tiles = 0, params = 0;
+    for (uint32_t s = 0; s < n_sets; ++s) params += sets[s].numel;
+    const bool digits = takes_digits(M, params);
+    const uint64_t tile = digits ? kDigitTile : kPairTile;
     for (uint32_t s = 0; s < n_sets; ++s) {
         a.first_tile[s] = (uint32_t)tiles;
         a.offset[s] = sets[s].offset;
         a.numel[s] = sets[s].numel;
-        tiles += (sets[s].numel + kPairTile - 1) / kPairTile;
+        tiles += (sets[s].numel + tile - 1) / tile;
         if (tiles >= 0xffffffffull) return SDL_ERR_UNSUPPORTED;
         bool fast = aligned16(g + sets[s].offset);
         for (uint32_t m = 0; m < M; ++m) fast = fast && aligned16(static_cast<const uint16_t*>(w[m]) + sets[s].offset);
@@ -753,7 +1048,7 @@ int launch_pair(const float* g, const void* const* w, uint32_t M, Set* sets, uin
     }
     a.first_tile[n_sets] = (uint32_t)tiles;
     for (uint32_t s = n_sets + 1u; s <= (uint32_t)kMaxSets; ++s) a.first_tile[s] = 0xffffffffu;
-    const uint32_t resident = pair_resident(M);
+    const uint32_t resident = pair_resident(M, digits);
     uint32_t mats = 0, n_wg = 0, at = 0;
     constexpr uint32_t kPercent[kShares] = {85, 70, 100};      // of what is left
     for (int i = 0; i < kShares; ++i) {
@@ -782,6 +1077,11 @@ int launch_pair(const float* g, const void* const* w, uint32_t M, Set* sets, uin
     *n_mats = mats;
     if (!n_wg) return SDL_OK;
     const dim3 grid(n_wg), block(2 * kWave);
+    if (digits) {
+        if (H == 7u) hipLaunchKernelGGL((sdl_digit_sums_kernel<7>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((sdl_digit_sums_kernel<8>), grid, block, 0, st, a);
+        return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
+    }
     switch (H) {
     case 5: hipLaunchKernelGGL((sdl_gram_pair_kernel<5>), grid, block, 0, st, a); break;
     case 6: hipLaunchKernelGGL((sdl_gram_pair_kernel<6>), grid, block, 0, st, a); break;

@@ -1,0 +1,124 @@
+"""13 to 16 replicas and 2^21 parameters in a launch or more: the differences as digits of a multiple of 2^-22 of a scale of their
+replica's, with products that the matrix cores add up in whole numbers.  Sizes at the edges of the tiles (512 parameters, the
+wavefronts 64 at a time) and of the range, arrays at any element, and differences that the scale does not suit: growing by 2^60 along
+the array, none at all, below 2^-98, near the largest fp32 number, not finite.
+
+Reference: fp64 products of the same fp32 differences.  A difference is off by at most 2^-44 of the largest of its replica's and
+the entry of a and b by 2^-44 of the sum of |a| times the largest of b, at most 2^-44 sqrt(n) of the product of the norms: 9e-11 at 2^21, if
+every error went the same way; rounded to nearest they add up like sqrt(n) of them, which leaves 2^-44.  The reference adds up
+2048 products at a time and then those sums: at most (2048 + 1100) 2^-53 = 3.5e-13."""
+import os
+import re
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_18512_amd as sdl
+from paper_2501_18512_amd import build
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+LINE = 1 << 21
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="needs hipcc")
+def test_the_digit_kernel_uses_no_scratch(tmp_path):
+    src = next(s for s in build.SOURCES if s.endswith("sdl_cosine.hip"))
+    flags = [f for f in build.FLAGS if f != "-shared"]
+    out = subprocess.run([HIPCC, *flags, "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o",
+                          str(tmp_path / "cosine.o")], check=True, capture_output=True, text=True).stderr
+    scratch = dict(re.findall(r"Function Name: (\S+).*?ScratchSize \[bytes/lane\]: (\d+)", out, re.S))
+    assert sorted(int(x) for k, x in scratch.items() if "sdl_digit_sums" in k) == [0, 0]
+
+
+def _inputs(kind, n, M, shift):
+    gen = torch.Generator("cuda").manual_seed(n + M)
+    draw = lambda: torch.randn(n + shift, device="cuda", generator=gen)
+    scale = 1.0
+    if kind == "growing":
+        scale = torch.exp2(torch.arange(n + shift, device="cuda") * (60.0 / n) - 40.0)
+    g = draw() * 0.02 * scale
+    w = [(g - draw() * 1e-3 * scale).to(torch.bfloat16) for _ in range(M)]
+    if kind == "outliers":
+        for x in w:
+            x[torch.randint(n, (n // 1000,), device="cuda", generator=gen)] += 0.1
+    if kind in ("tiny", "huge"):
+        power = 2.0 ** (-110 if kind == "tiny" else 120)
+        g, w = g * power, [x * power for x in w]
+    if kind == "uneven":                 # no difference, differences below 2^-98, a scale of their own
+        g = g.to(torch.bfloat16).float()
+        w[1] = g.to(torch.bfloat16)
+        w[4] = w[1].clone()
+        w[4][::3] = 0
+        g[::3] *= 2.0 ** -100
+        w[7] = w[7] * 2.0 ** 60
+    return g[shift:], [x[shift:] for x in w]
+
+
+def _check(got, want, M):
+    G, cos, mean = (x.cpu().numpy() for x in sdl.split_cosine_result(got, M))
+    norm = np.sqrt(np.diag(want))
+    outer = np.outer(norm, norm)
+    assert (np.abs(G - want) <= 1e-12 * outer).all(), np.abs(G - want).max() / outer.max()
+    want_cos = np.divide(want, outer, out=np.zeros_like(want), where=outer > 0)
+    np.testing.assert_allclose(cos, want_cos, atol=1e-12, rtol=0)
+    np.testing.assert_allclose(mean, want_cos[np.triu_indices(M, 1)].mean(), atol=1e-12, rtol=0)
+
+
+def _reference(g, w):
+    d = torch.stack([torch.nn.functional.pad((g - x.float()).double(), (0, -len(g) % 2048)) for x in w])
+    return sum(c @ c.T for c in d.split(2048, dim=1)).cpu().numpy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,shift", [(13, 0), (14, 1), (15, 0), (16, 1), (16, 0)])
+@pytest.mark.parametrize("kind,extra", [("normal", -1), ("normal", 0), ("normal", 1), ("outliers", 511), ("growing", 513), ("tiny", 65),
+                                        ("huge", 700), ("uneven", 0)])
+def test_sums_of_digits(kind, extra, M, shift):
+    n = LINE + extra
+    g, w = _inputs(kind, n, M, shift)
+    result, workspace = sdl.alloc_cosine(M)
+    sdl.sdl_outer_grad_cosine(g, w, n, result[0], workspace)
+    _check(result[0], _reference(g, w), M)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", [13, 16])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+def test_non_finite_replica_stays_in_its_row(M, bad):
+    n = LINE + 17
+    g, w = _inputs("normal", n, M, 0)
+    clean = _reference(g, w)
+    for m, at in ((0, 0), (M // 2, 70_003), (M - 1, n - 1)):
+        v = list(w)
+        v[m] = w[m].clone()
+        v[m][at] = bad
+        result, workspace = sdl.alloc_cosine(M)
+        sdl.sdl_outer_grad_cosine(g, v, n, result[0], workspace)
+        G = sdl.split_cosine_result(result[0], M)[0].cpu().numpy()
+        keep = np.arange(M) != m
+        np.testing.assert_allclose(G[np.ix_(keep, keep)], clean[np.ix_(keep, keep)], rtol=0, atol=1e-12 * clean.max())
+        want = (g - v[m].float()).double() @ torch.stack([(g - x.float()).double() for x in v]).T
+        np.testing.assert_array_equal(np.sign(G[m]), np.sign(want.cpu().numpy()))     # inf, -inf or NaN alike
+        assert not np.isfinite(G[m]).any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", [13, 16])
+@pytest.mark.parametrize("n_spans", [3, 48, 49])
+def test_spans_that_share_workgroups(M, n_spans):
+    rng = np.random.default_rng(n_spans)
+    numel = [int(x) for x in rng.integers(1, 3000, n_spans)]
+    numel[1] = LINE
+    plan = sdl.sdl_fragment_plan(numel, [0] * n_spans, 1, 1, sdl.PATTERN_STRIDED, 10, 0)
+    g, w = _inputs("normal", plan.total_numel, M, 0)
+    spans = sdl.sdl_plan_fragment_spans(plan, 0)
+    results, workspace = sdl.alloc_cosine(M, len(spans))
+    fragment = torch.empty(sdl.cosine_result_doubles(M), dtype=torch.float64, device="cuda")
+    sdl.sdl_outer_grad_cosine_plan(plan, 0, g, w, results, fragment, workspace)
+    parts = [_reference(g[o:o + n], [x[o:o + n] for x in w]) for o, n, _ in spans]
+    for k, want in enumerate(parts):
+        _check(results[k], want, M)
+    _check(fragment, sum(parts), M)
