@@ -74,6 +74,16 @@ struct GramArgs {
 };
 static_assert(sizeof(GramArgs) <= 4096, "kernel arguments");
 
+// The lane's number, counted anew: what is computed from it is computed here, not ahead of a loop that needs the registers.  (The offsets
+// of a ragged tile's accesses, computed ahead, took 20 to 30 of them: sdl_gram_kernel at 4 / 7 / 8 replicas 117 / 193 / 228 registers, 96 / 168 /
+// 199 so; 302 M parameters, M = 7 875 us and 861, the others the same.)
+__device__ __forceinline__ uint32_t lane_here()
+{
+    uint32_t all = ~0u;
+    asm volatile("" : "+s"(all));
+    return __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+}
+
 // Raw bits of one tile as a lane holds them: 8 fp32 of g, 8 bf16 of each replica.
 template <int NW>
 struct TileRegs {
@@ -97,6 +107,7 @@ __device__ __forceinline__ void load_tile(TileRegs<NW>& t, const float* g, const
         for (int m = 0; m < NW; ++m)
             t.w[m] = __builtin_amdgcn_raw_buffer_load_b128(rsrc(w[m] + e0, kTile * 2), (int)(lane * 16), 0, 2);
     } else if (valid == (uint32_t)kTile) {
+        lane = lane_here();
         const u32x4_f32elem* pg = reinterpret_cast<const u32x4_f32elem*>(g + e0 + lane * kLaneElems);
         t.g0 = __builtin_nontemporal_load(pg);
         t.g1 = __builtin_nontemporal_load(pg + 1);
@@ -104,6 +115,7 @@ __device__ __forceinline__ void load_tile(TileRegs<NW>& t, const float* g, const
         for (int m = 0; m < NW; ++m)
             t.w[m] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_bf16elem*>(w[m] + e0 + lane * kLaneElems));
     } else {
+        lane = lane_here();
         const __amdgpu_buffer_rsrc_t rg = rsrc(g + e0, valid * 4);
         uint32_t x[kLaneElems];
 #pragma unroll
@@ -247,17 +259,33 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
         }
     };
 
-    // workgroup k's tiles: first, first + step, ... below end; the next tile's loads are issued before the
-    // current tile is consumed
+    // workgroup k's tiles: first, first + step, ... below end
     const uint64_t first = k, step = set.G, end = n_tiles;
-    TileRegs<M> cur;
-    if (first < end) load_tile<M>(cur, a.g, w, set.offset + first * kTile, valid_of(first), fast, lane);
-    for (uint64_t t = first; t < end; t += step) {
-        TileRegs<M> nxt = cur;
-        const uint64_t tn = t + step;
-        if (tn < end) load_tile<M>(nxt, a.g, w, set.offset + tn * kTile, valid_of(tn), fast, lane);
-        consume(cur);
-        cur = nxt;
+    auto load = [&](TileRegs<M>& r, uint64_t t) { load_tile<M>(r, a.g, w, set.offset + t * kTile, valid_of(t), fast, lane); };
+    if constexpr (M <= 3) {
+        // Two sets of registers in turn, so that two tiles are on the way.  (A copy of what was loaded ahead, as below, has to wait for it.
+        // 302 M parameters in 48 spans, M = 1 / 2 / 3: 296 / 404 / 475 us with the copy, 288 / 386 / 473 so; at 4 to 7 replicas there is no
+        // difference, at 8 the registers end it: 982 and 1000.)
+        TileRegs<M> even, odd;
+        if (first < end) load(even, first);
+        if (first + step < end) load(odd, first + step);
+        for (uint64_t t = first; t < end; t += 2 * step) {
+            consume(even);
+            if (t + 2 * step < end) load(even, t + 2 * step);
+            if (t + step >= end) break;
+            consume(odd);
+            if (t + 3 * step < end) load(odd, t + 3 * step);
+        }
+    } else {
+        TileRegs<M> cur;
+        if (first < end) load(cur, first);
+        for (uint64_t t = first; t < end; t += step) {
+            TileRegs<M> nxt = cur;
+            const uint64_t tn = t + step;
+            if (tn < end) load(nxt, tn);
+            consume(cur);
+            cur = nxt;
+        }
     }
 
     halve<kSums, 0>(sum, lane);
@@ -613,13 +641,6 @@ constexpr Product kProducts[] = {
     {kHi1, kLo0, 9}, {kHi0, kLo1, 9}, {kHi0, kLo0, 10}, {kLo2, kLo2, 11}, {kLo2, kLo1, 12}, {kLo1, kLo1, 13}};
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-// The lane's number, counted anew: what is computed from it is computed here, not ahead of a loop that needs the registers.
-__device__ __forceinline__ uint32_t lane_here()
-{
-    uint32_t all = ~0u;
-    asm volatile("" : "+s"(all));
-    return __builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
-}
 __device__ __forceinline__ float from_lane(float x, uint32_t lane)
 {
     return u2f((uint32_t)__builtin_amdgcn_ds_bpermute((int)(lane << 2), (int)f2u(x)));
