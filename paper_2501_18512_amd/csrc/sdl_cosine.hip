@@ -38,9 +38,16 @@ using namespace sdl_device;
 
 constexpr int kLaneElems = 8;                   // consecutive parameters a lane owns in a tile
 constexpr int kTile = kLaneElems * kWave;       // 512
-constexpr int kMaxSets = 48;                    // parameter sets per launch
+constexpr int kMaxSets = 224;                   // parameter sets per launch
 constexpr int kWindows = 48;                    // windows per launch: a set holding a share of 4/48 or more is cut
 constexpr int kMaxPieces = kMaxSets + kWindows;
+// A launch takes more sets than kFewSets only while they have no more than kManyParams parameters: fewer launches, but each set gets a smaller
+// share of the workgroups, and up to 8 replicas a lane's chains of additions are as long as its share (16 parameters at kManyParams, which
+// adds nothing to the error of 1e-16).  Whole call with 48 sets a launch and each launch's sums finished by themselves, and now, M = 2 / 4 / 8 / 16:
+// 194 sets of 100 to 30000 parameters, 2.5 M in all, 44 / 51 / 69 / 139 us and 20 / 21 / 29 / 52; 195 sets of 256 to 8 M, 35 M in all, 96 / 125 /
+// 209 / 371 and 66 / 90 / 153 / 319.
+constexpr uint32_t kFewSets = 48;
+constexpr uint64_t kManyParams = 1ull << 23;
 constexpr uint32_t kGroups = 8192;              // workgroups per launch up to 8 replicas, shared out among the sets (32 per compute unit)
 constexpr uint32_t kMaxGroups = 8192;           // what the workspace is sized for
 
@@ -52,27 +59,22 @@ struct Set {
     uint32_t G;          // workgroups of this set (>= 1)
 };
 
-// What the kernel walks: a set, or a window of a large set (tile aligned), with its own
-// share of the set's workgroups.
-struct Piece {
-    uint64_t offset;
-    uint64_t numel;
-    uint32_t first_wg;
-    uint32_t G;
-    uint32_t fast;       // every array is 16-byte aligned at the piece's start
-    uint32_t pad_;
-};
-
+// What the kernel walks are pieces: a set, or a window of a large set (tile aligned), with its own share of the set's workgroups.  13 bytes
+// each, so that as many as possible fit the kernel arguments.
 struct GramArgs {
     const float* g;
-    const uint16_t* w[SDL_MAX_WORKERS];
+    const uint16_t* w[8];
     double* partial;               // [workgroup of the launch][M*M]
     uint32_t n_pieces;
     uint32_t group_wg[kMaxPieces / 16 - 1];   // first workgroup of the 16th, 32nd, ... piece
-    uint32_t first_wg[kMaxPieces];            // of each piece; 0xffffffff behind the last
-    Piece pieces[kMaxPieces];
+    uint32_t first_wg[kMaxPieces + 1];        // of each piece, then the number of workgroups; 0xffffffff behind it
+    uint32_t offset[kMaxPieces];              // first element in the flat arrays, low 32 bits
+    uint32_t numel[kMaxPieces];
+    uint32_t high[kMaxPieces / 4];            // a byte each: bits 32 to 38 of the offset, and kFast
 };
-static_assert(sizeof(GramArgs) <= 4096, "kernel arguments");
+static_assert(sizeof(GramArgs) <= 4096 && kMaxPieces % 16 == 0, "kernel arguments");
+constexpr uint32_t kFast = 0x80;              // every array is 16-byte aligned at the piece's start
+constexpr uint64_t kMaxOffset = 1ull << 39;
 
 // The lane's number, counted anew: what is computed from it is computed here, not ahead of a loop that needs the registers.  (The offsets
 // of a ragged tile's accesses, computed ahead, took 20 to 30 of them: sdl_gram_kernel at 4 / 7 / 8 replicas 117 / 193 / 228 registers, 96 / 168 /
@@ -215,19 +217,26 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
     constexpr int kSums = M * (M + 1) / 2, kLeft = halved(kSums);
     const uint32_t lane = threadIdx.x;
     // the first workgroups of 16 pieces are one scalar load, those of every 16th piece come first
+    constexpr int kGroupsOf16 = kMaxPieces / 16, kFew = 6;
     uint32_t base = 0, s = 15;
     if (a.n_pieces > 16u) {
 #pragma unroll
-        for (int i = 1; i < kMaxPieces / 16; ++i)
+        for (int i = 1; i < kFew; ++i)
             if (blockIdx.x >= a.group_wg[i - 1]) base = (uint32_t)(i * 16);
+        if (a.n_pieces > (uint32_t)(kFew * 16)) {
+#pragma unroll
+            for (int i = kFew; i < kGroupsOf16; ++i)
+                if (blockIdx.x >= a.group_wg[i - 1]) base = (uint32_t)(i * 16);
+        }
     }
 #pragma unroll
     for (int i = 15; i >= 1; --i)
         if (blockIdx.x < a.first_wg[base + i]) s = (uint32_t)(i - 1);
-    const Piece set = a.pieces[base + s];
-    const uint32_t k = blockIdx.x - set.first_wg;
-    const bool fast = set.fast != 0u;
-    const uint64_t n_tiles = (set.numel + kTile - 1) / kTile;
+    s += base;
+    const uint32_t k = blockIdx.x - a.first_wg[s], high = a.high[s / 4u] >> (s % 4u * 8u);
+    const bool fast = high & kFast;
+    const uint64_t offset = (uint64_t)(high & (kFast - 1u)) << 32 | a.offset[s];
+    const uint32_t numel = a.numel[s], n_tiles = numel / kTile + (numel % kTile ? 1u : 0u);
 
     const uint16_t* w[M];
 #pragma unroll
@@ -237,9 +246,9 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
 #pragma unroll
     for (int i = 0; i < kSums; ++i) sum[i] = 0.0;
 
-    auto valid_of = [&](uint64_t t) -> uint32_t {
-        const uint64_t rem = set.numel - t * kTile;
-        return rem < (uint64_t)kTile ? (uint32_t)rem : (uint32_t)kTile;
+    auto valid_of = [&](uint32_t t) -> uint32_t {
+        const uint32_t rem = numel - t * kTile;
+        return rem < (uint32_t)kTile ? rem : (uint32_t)kTile;
     };
 
     auto consume = [&](const TileRegs<M>& t) {
@@ -260,8 +269,8 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
     };
 
     // workgroup k's tiles: first, first + step, ... below end
-    const uint64_t first = k, step = set.G, end = n_tiles;
-    auto load = [&](TileRegs<M>& r, uint64_t t) { load_tile<M>(r, a.g, w, set.offset + t * kTile, valid_of(t), fast, lane); };
+    const uint32_t first = k, step = a.first_wg[s + 1u] - a.first_wg[s], end = n_tiles;
+    auto load = [&](TileRegs<M>& r, uint32_t t) { load_tile<M>(r, a.g, w, offset + (uint64_t)t * kTile, valid_of(t), fast, lane); };
     if constexpr (M <= 3) {
         // Two sets of registers in turn, so that two tiles are on the way.  (A copy of what was loaded ahead, as below, has to wait for it.
         // 302 M parameters in 48 spans, M = 1 / 2 / 3: 296 / 404 / 475 us with the copy, 288 / 386 / 473 so; at 4 to 7 replicas there is no
@@ -269,7 +278,7 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
         TileRegs<M> even, odd;
         if (first < end) load(even, first);
         if (first + step < end) load(odd, first + step);
-        for (uint64_t t = first; t < end; t += 2 * step) {
+        for (uint32_t t = first; t < end; t += 2 * step) {
             consume(even);
             if (t + 2 * step < end) load(even, t + 2 * step);
             if (t + step >= end) break;
@@ -279,9 +288,9 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
     } else {
         TileRegs<M> cur;
         if (first < end) load(cur, first);
-        for (uint64_t t = first; t < end; t += step) {
+        for (uint32_t t = first; t < end; t += step) {
             TileRegs<M> nxt = cur;
-            const uint64_t tn = t + step;
+            const uint32_t tn = t + step;
             if (tn < end) load(nxt, tn);
             consume(cur);
             cur = nxt;
@@ -386,24 +395,25 @@ struct PairArgs {
     const float* g;
     const uint16_t* w[SDL_MAX_WORKERS];
     double* partial;
-    uint64_t fast;                    // bit s: every array is 16-byte aligned at set s's start (24 sets of 48 off it, 52.9 M parameters, M = 9 / 16:
-                                      // 268.6 / 517 us with all sets on the path for any alignment, 266.3 / 514 so)
     uint32_t M;
+    uint32_t group_tile[kMaxSets / 16 - 1];   // first tile of the 16th, 32nd, ... set
     uint32_t first_tile[kMaxSets + 1];   // of each set, then the number of tiles; 0xffffffff behind it
     Share shares[kShares];
     int32_t slot[kMaxSets];           // workgroup b's matrix of set s is partial[b + slot[s]]
-    uint64_t offset[kMaxSets];
-    uint64_t numel[kMaxSets];
+    uint32_t offset[kMaxSets];        // first element in the flat arrays, low 32 bits
+    uint32_t more[kMaxSets];          // bits 32 to 38 of the offset; kFast: every array is 16-byte aligned at the set's start (24 sets of 48 off
+                                      // it, 52.9 M parameters, M = 9 / 16: 268.6 / 517 us with all sets on the path for any alignment,
+                                      // 266.3 / 514 so); from bit 8 on the parameters of the last tile
 };
-static_assert(sizeof(PairArgs) <= 4096 && kMaxSets <= 64, "kernel arguments");
+static_assert(sizeof(PairArgs) <= 4096 && kMaxSets % 16 == 0, "kernel arguments");
 
 // The set that tile t belongs to.
 __device__ __forceinline__ uint32_t set_of(const PairArgs& a, uint32_t t)
 {
     uint32_t group = 0;
 #pragma unroll
-    for (int i = 16; i < kMaxSets; i += 16)
-        if (t >= a.first_tile[i]) group = (uint32_t)i;
+    for (int i = 1; i < kMaxSets / 16; ++i)
+        if (t >= a.group_tile[i - 1]) group = (uint32_t)(i * 16);
     uint32_t s = group;
 #pragma unroll
     for (int i = 1; i < 16; ++i)
@@ -497,8 +507,9 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
     while (t < end) {
         const uint32_t s = set_of(a, t);
         const uint32_t set_first = a.first_tile[s], set_end = a.first_tile[s + 1], stop = end < set_end ? end : set_end;
-        const uint64_t offset = a.offset[s], numel = a.numel[s];
-        const uint32_t whole = (uint32_t)(numel / kPairTile), last = stop - set_first < whole ? stop - set_first : whole;
+        const uint32_t more = a.more[s], in_last = more >> 8;
+        const uint64_t offset = (uint64_t)(more & (kFast - 1u)) << 32 | a.offset[s];
+        const uint32_t whole = set_end - set_first - (in_last == (uint32_t)kPairTile ? 0u : 1u), last = stop - set_first < whole ? stop - set_first : whole;
         uint32_t k = t - set_first;
 #pragma unroll
         for (int i = 0; i < kHeld; ++i) total[i] = 0.0;
@@ -537,12 +548,12 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
             }
         };
         if (k < last) {
-            if ((a.fast >> s) & 1u) walk(std::true_type{});
+            if (more & kFast) walk(std::true_type{});
             else walk(std::false_type{});
         }
         if (stop - set_first > whole) {
             PairRaw<H> raw;
-            load_pair_tail<H>(raw, a.g, w, offset + (uint64_t)whole * kPairTile, (uint32_t)(numel - (uint64_t)whole * kPairTile), lane);
+            load_pair_tail<H>(raw, a.g, w, offset + (uint64_t)whole * kPairTile, in_last, lane);
             lds_barrier();
             stage(0, raw);
             lds_barrier();
@@ -806,8 +817,9 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
     while (t < end) {
         const uint32_t s = set_of(a, t);
         const uint32_t set_first = a.first_tile[s], set_end = a.first_tile[s + 1], stop = end < set_end ? end : set_end;
-        const uint64_t offset = a.offset[s], numel = a.numel[s];
-        const bool fast = (a.fast >> s) & 1u;
+        const uint32_t more = a.more[s], in_last = more >> 8, final_tile = set_end - set_first - 1u;
+        const uint64_t offset = (uint64_t)(more & (kFast - 1u)) << 32 | a.offset[s];
+        const bool fast = more & kFast;
 #pragma unroll
         for (int i = 0; i < 4; ++i) totals[wave][4u * lane_here() + i] = 0.0;
         clear();
@@ -816,8 +828,7 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 
         HalfTile<H> raw;
         auto load = [&](uint32_t k) {
-            const uint64_t at = (uint64_t)k * kDigitTile, rem = numel - at;
-            load_half<H>(raw, a.g, wave, w, offset + at, rem < (uint64_t)kDigitTile ? (uint32_t)rem : (uint32_t)kDigitTile, fast, lane);
+            load_half<H>(raw, a.g, wave, w, offset + (uint64_t)k * kDigitTile, k == final_tile ? in_last : (uint32_t)kDigitTile, fast, lane);
         };
         u32x4 wv[2], gv[4];
         auto read = [&](uint32_t j) {
@@ -873,9 +884,11 @@ constexpr uint32_t fin_chunk(uint32_t M) { return 8u * fin_slices(M); }
 constexpr uint32_t mats_per_launch(uint32_t M) { return M > 8u ? kShares * pair_resident(M, M > 12u) : kGroups; }
 
 // A launch over n sets leaves at most mats_per_launch + n matrices, so at most (mats_per_launch + n) / fin_chunk + n
-// first-level outputs: kFirstLevel and one for each set, of which the workspace and the arguments have room.
+// first-level outputs: kFirstLevel and one for each set, of which the workspace has room.
 constexpr uint32_t kFirstLevel = kMaxGroups / 64 + 2;
-constexpr int kMaxFin = kFirstLevel + 2 * kMaxSets;                       // outputs per finalize launch
+constexpr uint32_t kMaxFin = 896;                                         // outputs per finalize launch
+constexpr uint32_t kBatch = 11 * kFewSets;                                // sets that are finished together
+static_assert(kBatch < kMaxFin, "the last level is one launch");
 constexpr bool sums_fit()
 {
     for (uint32_t M = 1; M <= SDL_MAX_WORKERS; ++M)
@@ -892,9 +905,9 @@ struct FinArgs {
     uint64_t out_stride;
     uint32_t M;
     uint32_t emit;                 // 1: G, cos, mean (2*M*M + 1 doubles); 0: G only (M*M doubles)
-    uint32_t first[kMaxFin];       // output o adds the matrices first[o] .. first[o] + count[o] - 1
-    uint32_t count[kMaxFin];
+    uint32_t first[kMaxFin + 1];   // output o adds the matrices first[o] .. first[o + 1] - 1; one that goes to last_out those of all before it
 };
+static_assert(sizeof(FinArgs) <= 4096, "kernel arguments");
 
 // One workgroup per output.  A thread adds every S-th matrix's value of one entry a <= b (neighbouring threads read
 // neighbouring entries), then the S sums of an entry are added as a tree.  Latency bound: a range should give a thread a
@@ -905,8 +918,10 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
     __shared__ double G[SDL_MAX_WORKERS * SDL_MAX_WORKERS];
     __shared__ double C[SDL_MAX_WORKERS * SDL_MAX_WORKERS];
     __shared__ double part[kFinThreads];
-    const uint32_t M = f.M, count = f.count[blockIdx.x], entries = M * (M + 1u) / 2u, S = fin_slices(M);
-    const double* base = f.in + (uint64_t)f.first[blockIdx.x] * f.stride_k;
+    const bool all = f.last_out && blockIdx.x + 1u == gridDim.x;
+    const uint32_t first = f.first[all ? 0u : blockIdx.x], count = f.first[blockIdx.x + (all ? 0u : 1u)] - first;
+    const uint32_t M = f.M, entries = M * (M + 1u) / 2u, S = fin_slices(M);
+    const double* base = f.in + (uint64_t)first * f.stride_k;
     const uint32_t entry = threadIdx.x % entries, slice = threadIdx.x / entries;
     uint32_t a = 0, b = entry;             // entry number -> (a, b), row by row of the upper triangle
     while (b >= M - a) { b -= M - a; ++a; }
@@ -930,7 +945,7 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
         G[b * M + a] = part[threadIdx.x];
     }
     __syncthreads();
-    double* o = f.last_out && blockIdx.x + 1u == gridDim.x ? f.last_out : f.out + (uint64_t)blockIdx.x * f.out_stride;
+    double* o = all ? f.last_out : f.out + (uint64_t)blockIdx.x * f.out_stride;
     if (!f.emit) {
         for (uint32_t i = threadIdx.x; i < M * M; i += blockDim.x) o[i] = G[i];
         return;
@@ -960,7 +975,7 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
 
 int launch_kernel(uint32_t M, const GramArgs& a, hipStream_t st)
 {
-    const dim3 grid(a.pieces[a.n_pieces - 1].first_wg + a.pieces[a.n_pieces - 1].G), one(kWave);
+    const dim3 grid(a.first_wg[a.n_pieces]), one(kWave);
     switch (M) {
     case 1: hipLaunchKernelGGL((sdl_gram_kernel<1>), grid, one, 0, st, a); break;
     case 2: hipLaunchKernelGGL((sdl_gram_kernel<2>), grid, one, 0, st, a); break;
@@ -976,6 +991,12 @@ int launch_kernel(uint32_t M, const GramArgs& a, hipStream_t st)
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+bool all_aligned16(const float* g, const void* const* w, uint32_t M, uint64_t offset)
+{
+    bool fast = aligned16(g + offset);
+    for (uint32_t m = 0; m < M; ++m) fast = fast && aligned16(static_cast<const uint16_t*>(w[m]) + offset);
+    return fast;
+}
 
 // Shares the launch's workgroups out among the sets in proportion to their tiles (at least
 // one each); returns the total, at most groups + n_sets.
@@ -1021,23 +1042,21 @@ int launch_gram(const float* g, const void* const* w, uint32_t M, const Set* set
         if (nsub < 1) nsub = 1;
         const uint64_t tiles_per = (tiles + nsub - 1) / nsub;
         for (uint64_t j = 0; j < nsub; ++j) {
-            Piece& pc = a.pieces[a.n_pieces++];
+            const uint32_t number = a.n_pieces++;
             const uint64_t e0 = j * tiles_per * kTile;
             const uint64_t e1 = (j + 1) * tiles_per * kTile < sets[s].numel ? (j + 1) * tiles_per * kTile : sets[s].numel;
-            pc.offset = sets[s].offset + (e0 < sets[s].numel ? e0 : sets[s].numel);
-            pc.numel = e1 > e0 ? e1 - e0 : 0;
-            const uint32_t w0 = (uint32_t)((uint64_t)sets[s].G * j / nsub), w1 = (uint32_t)((uint64_t)sets[s].G * (j + 1) / nsub);
-            pc.first_wg = sets[s].first_wg + w0;
-            pc.G = w1 - w0;
-            bool fast = aligned16(g + pc.offset);
-            for (uint32_t m = 0; m < M; ++m)
-                fast = fast && aligned16(static_cast<const uint16_t*>(w[m]) + pc.offset);
-            pc.fast = fast ? 1u : 0u;
-            const uint32_t number = a.n_pieces - 1u;
-            a.first_wg[number] = pc.first_wg;
-            if (number % 16u == 0u && number) a.group_wg[number / 16u - 1u] = pc.first_wg;
+            const uint64_t offset = sets[s].offset + (e0 < sets[s].numel ? e0 : sets[s].numel), numel = e1 > e0 ? e1 - e0 : 0;
+            if (offset >= kMaxOffset || numel > 0xffffffffull) return SDL_ERR_UNSUPPORTED;     // more than any memory holds
+            const uint32_t first = sets[s].first_wg + (uint32_t)((uint64_t)sets[s].G * j / nsub);
+            a.first_wg[number] = first;
+            if (number % 16u == 0u && number) a.group_wg[number / 16u - 1u] = first;
+            a.offset[number] = (uint32_t)offset;
+            a.numel[number] = (uint32_t)numel;
+            const uint32_t high = (uint32_t)(offset >> 32) | (all_aligned16(g, w, M, offset) ? kFast : 0u);
+            a.high[number / 4u] |= high << (number % 4u * 8u);
         }
     }
+    a.first_wg[a.n_pieces] = sets[n_sets - 1].first_wg + sets[n_sets - 1].G;
     for (uint32_t m = 0; m < M; ++m) a.w[m] = static_cast<const uint16_t*>(w[m]);
     return launch_kernel(M, a, st);
 }
@@ -1059,15 +1078,16 @@ int launch_pair(const float* g, const void* const* w, uint32_t M, Set* sets, uin
     const uint64_t tile = digits ? kDigitTile : kPairTile;
     for (uint32_t s = 0; s < n_sets; ++s) {
         a.first_tile[s] = (uint32_t)tiles;
-        a.offset[s] = sets[s].offset;
-        a.numel[s] = sets[s].numel;
+        if (s % 16u == 0u && s) a.group_tile[s / 16u - 1u] = (uint32_t)tiles;
+        a.offset[s] = (uint32_t)sets[s].offset;
+        const uint64_t rest = sets[s].numel % tile;
+        a.more[s] = (uint32_t)(sets[s].offset >> 32) | (all_aligned16(g, w, M, sets[s].offset) ? kFast : 0u) | (uint32_t)(rest ? rest : tile) << 8;
         tiles += (sets[s].numel + tile - 1) / tile;
-        if (tiles >= 0xffffffffull) return SDL_ERR_UNSUPPORTED;
-        bool fast = aligned16(g + sets[s].offset);
-        for (uint32_t m = 0; m < M; ++m) fast = fast && aligned16(static_cast<const uint16_t*>(w[m]) + sets[s].offset);
-        a.fast |= (uint64_t)fast << s;
+        if (tiles >= 0xffffffffull || sets[s].offset >= kMaxOffset) return SDL_ERR_UNSUPPORTED;     // more than any memory holds
     }
     a.first_tile[n_sets] = (uint32_t)tiles;
+    for (uint32_t i = (n_sets + 15u) / 16u; i < (uint32_t)kMaxSets / 16u; ++i)
+        if (i) a.group_tile[i - 1u] = 0xffffffffu;
     for (uint32_t s = n_sets + 1u; s <= (uint32_t)kMaxSets; ++s) a.first_tile[s] = 0xffffffffu;
     const uint32_t resident = pair_resident(M, digits);
     uint32_t mats = 0, n_wg = 0, at = 0;
@@ -1129,7 +1149,7 @@ int launch_sums(const float* g, const void* const* w, uint32_t M, Set* sets, uin
     return launch_gram(g, w, M, sets, n_sets, partial, st);
 }
 
-// One result per set from the partial matrices of its workgroups (the sets' workgroups lie one behind the other) and, if
+// One result per set from the partial matrices of its workgroups (at partial + first_wg; the sets' matrices lie one behind the other) and, if
 // union_out is not null, the result of all of them together.  Sets with many workgroups are first added up in chunks (into
 // tmp), so that no thread of the finalize kernel walks a long range.
 int finalize_sets(const double* partial, const Set* sets, uint32_t n_sets, uint32_t M, double* out, double* union_out,
@@ -1151,31 +1171,40 @@ int finalize_sets(const double* partial, const Set* sets, uint32_t n_sets, uint3
     last.out_stride = SDL_COSINE_RESULT_DOUBLES(M);
     last.M = M;
     last.emit = 1;
-    last.in = partial;
-    for (uint32_t s = 0; s < n_sets; ++s) { last.first[s] = sets[s].first_wg; last.count[s] = sets[s].G; }
+    last.in = two_level ? tmp : partial;
     if (two_level) {
         FinArgs lvl1{};
         lvl1.in = partial;
-        lvl1.out = tmp;
         lvl1.stride_k = mm;
         lvl1.out_stride = mm;
         lvl1.M = M;
-        uint32_t n = 0;
+        uint32_t n = 0, done = 0;         // first-level outputs, and those of them that have been launched
+        auto launch = [&](uint32_t end) {
+            lvl1.first[n - done] = end;
+            lvl1.out = tmp + (uint64_t)done * mm;
+            const uint32_t count = n - done;
+            done = n;
+            return launch_finalize(lvl1, count, st);
+        };
         for (uint32_t s = 0; s < n_sets; ++s) {
             last.first[s] = n;
             for (uint32_t c = 0; c < sets[s].G; c += chunk) {
-                lvl1.first[n] = sets[s].first_wg + c;
-                lvl1.count[n] = sets[s].G - c < chunk ? sets[s].G - c : chunk;
-                ++n;
+                if (n - done == kMaxFin) {
+                    const int rc = launch(sets[s].first_wg + c);
+                    if (rc != SDL_OK) return rc;
+                }
+                lvl1.first[n++ - done] = sets[s].first_wg + c;
             }
-            last.count[s] = n - last.first[s];
         }
-        const int rc = launch_finalize(lvl1, n, st);
-        if (rc != SDL_OK) return rc;
-        last.in = tmp;
-        total = n;
+        last.first[n_sets] = n;
+        if (n > done) {
+            const int rc = launch(sets[0].first_wg + total);
+            if (rc != SDL_OK) return rc;
+        }
+    } else {
+        for (uint32_t s = 0; s < n_sets; ++s) last.first[s] = sets[s].first_wg;
+        last.first[n_sets] = sets[0].first_wg + total;
     }
-    if (union_out) { last.first[n_sets] = last.first[0]; last.count[n_sets] = total; }
     return launch_finalize(last, n_sets + (union_out ? 1u : 0u), st);
 }
 
@@ -1190,7 +1219,7 @@ int finalize_union(const double* results, uint64_t stride, uint32_t count, uint3
     f.M = M;
     f.emit = 1;
     f.first[0] = 0;
-    f.count[0] = count;
+    f.first[1] = count;
     return launch_finalize(f, 1, st);
 }
 
@@ -1199,12 +1228,12 @@ int finalize_union(const double* results, uint64_t stride, uint32_t count, uint3
 // result per set.
 size_t partial_mats(size_t n_sets)
 {
-    const size_t launches = (n_sets + kMaxSets - 1) / kMaxSets;
+    const size_t launches = (n_sets + kFewSets - 1) / kFewSets;     // or fewer
     return launches * kMaxGroups + n_sets;
 }
 size_t tmp_mats(size_t n_sets)
 {
-    const size_t launches = (n_sets + kMaxSets - 1) / kMaxSets;
+    const size_t launches = (n_sets + kFewSets - 1) / kFewSets;
     return launches * kFirstLevel + 2 * n_sets;
 }
 
@@ -1265,23 +1294,29 @@ int sdl_outer_grad_cosine_plan(const sdl_plan_t* plan, uint32_t p, const float* 
     double* partial = static_cast<double*>(workspace);
     double* tmp = partial + partial_mats(n_spans) * mm;
     double* per_span = span_results ? span_results : tmp + tmp_mats(n_spans) * mm;
-    uint64_t used = 0, used_tmp = 0;   // matrices handed out so far
-    for (uint32_t s0 = 0; s0 < n_spans; s0 += kMaxSets) {
-        const uint32_t ns = n_spans - s0 < (uint32_t)kMaxSets ? n_spans - s0 : (uint32_t)kMaxSets;
-        Set sets[kMaxSets];
-        for (uint32_t s = 0; s < ns; ++s) sets[s] = Set{spans[s0 + s].offset, spans[s0 + s].numel, 0, 0};
-        uint32_t n_mats = 0;
-        double* part = partial + used * mm;
-        rc = launch_sums(g_base, w_base, M, sets, ns, part, &n_mats, st);
+    for (uint32_t b0 = 0; b0 < n_spans; b0 += kBatch) {
+        const uint32_t n = n_spans - b0 < kBatch ? n_spans - b0 : kBatch;
+        Set sets[kBatch];
+        uint32_t used = 0;             // matrices so far
+        for (uint32_t s0 = 0, s1 = 0; s0 < n; s0 = s1) {
+            uint64_t params = 0;
+            for (; s1 < n && s1 - s0 < (uint32_t)kMaxSets; ++s1) {
+                params += spans[b0 + s1].numel;
+                if (s1 - s0 >= kFewSets && params > kManyParams) break;
+                sets[s1] = Set{spans[b0 + s1].offset, spans[b0 + s1].numel, 0, 0};
+            }
+            uint32_t n_mats = 0;
+            rc = launch_sums(g_base, w_base, M, sets + s0, s1 - s0, partial + (uint64_t)used * mm, &n_mats, st);
+            if (rc != SDL_OK) return rc;
+            for (uint32_t s = s0; s < s1; ++s) sets[s].first_wg += used;
+            used += n_mats;
+        }
+        // the spans of one batch give the fragment's result as well
+        rc = finalize_sets(partial, sets, n, M, per_span + (uint64_t)b0 * R, n == n_spans ? fragment_result : nullptr, tmp, st);
         if (rc != SDL_OK) return rc;
-        // the spans of one launch give the fragment's result as well
-        rc = finalize_sets(part, sets, ns, M, per_span + (uint64_t)s0 * R, ns == n_spans ? fragment_result : nullptr,
-                           tmp + used_tmp * mm, st);
-        if (rc != SDL_OK) return rc;
-        used += n_mats;
-        used_tmp += n_mats / fin_chunk(M) + ns;
+        partial += (uint64_t)used * mm;
     }
-    if (n_spans && n_spans <= (uint32_t)kMaxSets) return SDL_OK;
+    if (n_spans && n_spans <= kBatch) return SDL_OK;
     // the fragment: Gram matrices of its spans added in span order
     return finalize_union(per_span, R, n_spans, M, fragment_result, st);
 }
