@@ -11,7 +11,6 @@ from __future__ import annotations
 
 import ctypes
 import os
-import struct
 from typing import List, Optional, Sequence, Tuple
 
 import torch
@@ -127,6 +126,12 @@ def _load() -> ctypes.CDLL:
 
 _lib = _load()
 
+try:
+    from . import _binding
+except ImportError as e:
+    raise ImportError("the binding's extension module is missing or does not load: build it with `python paper_2501_18512_amd/build.py` "
+                      "(there is no fallback path)") from e
+
 
 def _check(status: int, where: str):
     if status != 0:
@@ -148,32 +153,6 @@ def _ptr_array(ts: Optional[Sequence]):
     return (ctypes.c_void_p * len(ts))(*[_ptr(t) for t in ts])
 
 
-def _device_ptr(t) -> int:
-    """_ptr of a tensor that has to be on a device and contiguous."""
-    try:
-        on_device, contiguous = t.is_cuda, t.is_contiguous()
-    except AttributeError:
-        return _ptr(t)
-    if not on_device:
-        raise ValueError("sdl calls take device tensors; there is no CPU path")
-    if not contiguous:
-        raise ValueError("sdl calls take contiguous tensors")
-    return t.data_ptr()
-
-
-_pack_addresses = [struct.Struct(f"{n}P").pack for n in range(MAX_WORKERS + 1)]
-
-
-def _device_ptrs(ts: Optional[Sequence]):
-    """_device_ptr of every tensor, as the array of addresses that the calls take.  Checked and read in one walk and packed
-    without a ctypes array, a call on 2^20 parameters and 2 replicas, whose kernel runs 4.9 us, takes 6.8 us instead
-    of 7.6, and one on 8 replicas 9.0 instead of 10.2."""
-    if ts is None:
-        return None
-    ptrs = [_device_ptr(t) for t in ts]
-    return _pack_addresses[len(ptrs)](*ptrs) if len(ptrs) <= MAX_WORKERS else struct.pack(f"{len(ptrs)}P", *ptrs)
-
-
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _get_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
@@ -188,6 +167,11 @@ def _stream(stream) -> int:
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
+
+
+# the device calls of every step convert their arguments in the extension module
+_binding.setup({name: ctypes.cast(getattr(_lib, name), ctypes.c_void_p).value for name in dir(_binding) if name.startswith("sdl_")},
+               _stream, torch.cuda.is_initialized, _get_device, _raw_stream)
 
 
 def _require_device(*tensors):
@@ -305,87 +289,41 @@ def sdl_exchange_bytes(fmt: int, numel: int) -> Tuple[int, int]:
 # ------------------------------------------------------------------------ device calls
 
 def sdl_quantize_outer_grad(g, w_send, n: int, fmt: int, codes, scales=None, stream=None):
-    g_p = _device_ptr(g)
-    w_send_p = _device_ptrs(w_send)
-    codes_p = _device_ptrs(codes)
-    scales_p = _device_ptrs(scales)
-    _check(_lib.sdl_quantize_outer_grad(g_p, w_send_p, len(w_send), n, fmt,
-                                        codes_p, scales_p, _stream(stream)),
-           "sdl_quantize_outer_grad")
+    _check(_binding.sdl_quantize_outer_grad(g, w_send, n, fmt, codes, scales, stream), "sdl_quantize_outer_grad")
 
 
 def sdl_dequant_reduce_nesterov(g, mom, codes, scales, n: int, fmt: int, lr: float, mu: float,
                                 stream=None):
-    g_p = _device_ptr(g)
-    mom_p = _device_ptr(mom)
-    codes_p = _device_ptrs(codes)
-    scales_p = _device_ptrs(scales)
-    _check(_lib.sdl_dequant_reduce_nesterov(g_p, mom_p, codes_p, scales_p,
-                                            len(codes), n, fmt, lr, mu, _stream(stream)),
-           "sdl_dequant_reduce_nesterov")
+    _check(_binding.sdl_dequant_reduce_nesterov(g, mom, codes, scales, n, fmt, lr, mu,
+                                                stream), "sdl_dequant_reduce_nesterov")
 
 
 def sdl_merge_overlap(g_new, w_now, n: int, alpha: float, stream=None):
-    g_new_p = _device_ptr(g_new)
-    w_now_p = _device_ptrs(w_now)
-    _check(_lib.sdl_merge_overlap(g_new_p, w_now_p, len(w_now), n, alpha,
-                                  _stream(stream)), "sdl_merge_overlap")
+    _check(_binding.sdl_merge_overlap(g_new, w_now, n, alpha, stream), "sdl_merge_overlap")
 
 
 def sdl_receive_outer_step(g, mom, codes, scales, w_now, n: int, fmt: int, lr: float, mu: float, alpha: float,
                            stream=None):
-    g_p = _device_ptr(g)
-    mom_p = _device_ptr(mom)
-    codes_p = _device_ptrs(codes)
-    scales_p = _device_ptrs(scales)
-    w_now_p = _device_ptrs(w_now)
-    if len(codes) != len(w_now):
-        raise SdlError(-1, "sdl_receive_outer_step")
-    _check(_lib.sdl_receive_outer_step(g_p, mom_p, codes_p, scales_p,
-                                       w_now_p, len(w_now), n, fmt, lr, mu, alpha, _stream(stream)),
-           "sdl_receive_outer_step")
+    _check(_binding.sdl_receive_outer_step(g, mom, codes, scales, w_now, n, fmt, lr, mu, alpha,
+                                           stream), "sdl_receive_outer_step")
 
 
 def sdl_receive_outer_step_plan(plan: "Plan", p: int, g_base, mom_base, codes, scales, w_now_base, fmt: int,
                                 lr: float, mu: float, alpha: float, stream=None):
-    g_p = _device_ptr(g_base)
-    mom_p = _device_ptr(mom_base)
-    codes_p = _device_ptrs(codes)
-    scales_p = _device_ptrs(scales)
-    w_now_p = _device_ptrs(w_now_base)
-    _check(_lib.sdl_receive_outer_step_plan(plan._h, p, g_p, mom_p, codes_p,
-                                            scales_p, w_now_p, len(w_now_base), fmt, lr,
-                                            mu, alpha, _stream(stream)), "sdl_receive_outer_step_plan")
+    _check(_binding.sdl_receive_outer_step_plan(plan, p, g_base, mom_base, codes, scales, w_now_base, fmt, lr, mu,
+                                                alpha, stream), "sdl_receive_outer_step_plan")
 
 
 def sdl_fragment_outer_step(g, mom, w_send, w_now, n: int, fmt: int, lr: float, mu: float,
                             alpha: float, codes=None, scales=None, stream=None):
-    g_p = _device_ptr(g)
-    mom_p = _device_ptr(mom)
-    w_send_p = _device_ptrs(w_send)
-    w_now_p = _device_ptrs(w_now)
-    codes_p = _device_ptrs(codes)
-    scales_p = _device_ptrs(scales)
-    if len(w_send) != len(w_now):
-        raise SdlError(-1, "sdl_fragment_outer_step")
-    _check(_lib.sdl_fragment_outer_step(g_p, mom_p, w_send_p, w_now_p,
-                                        len(w_send), n, fmt, lr, mu, alpha, codes_p,
-                                        scales_p, _stream(stream)),
-           "sdl_fragment_outer_step")
+    _check(_binding.sdl_fragment_outer_step(g, mom, w_send, w_now, n, fmt, lr, mu, alpha, codes, scales,
+                                            stream), "sdl_fragment_outer_step")
 
 
 def sdl_fragment_outer_step_plan(plan: Plan, p: int, g_base, mom_base, w_send_base, w_now_base,
                                  fmt: int, lr: float, mu: float, alpha: float, stream=None):
-    g_p = _device_ptr(g_base)
-    mom_p = _device_ptr(mom_base)
-    w_send_p = _device_ptrs(w_send_base)
-    w_now_p = _device_ptrs(w_now_base)
-    if len(w_send_base) != len(w_now_base):
-        raise SdlError(-1, "sdl_fragment_outer_step_plan")
-    _check(_lib.sdl_fragment_outer_step_plan(plan._h, p, g_p, mom_p,
-                                             w_send_p, w_now_p,
-                                             len(w_send_base), fmt, lr, mu, alpha, _stream(stream)),
-           "sdl_fragment_outer_step_plan")
+    _check(_binding.sdl_fragment_outer_step_plan(plan, p, g_base, mom_base, w_send_base, w_now_base, fmt, lr, mu, alpha,
+                                                 stream), "sdl_fragment_outer_step_plan")
 
 
 STATIC_MAX_SPANS = 1024
@@ -393,50 +331,23 @@ STATIC_MAX_SPANS = 1024
 
 def sdl_fragment_outer_step_plan_static(plan: Plan, p: int, g_base, mom_base, w_send_base, w_now_base,
                                         fmt: int, lr: float, mu: float, alpha: float, stream=None):
-    g_p = _device_ptr(g_base)
-    mom_p = _device_ptr(mom_base)
-    w_send_p = _device_ptrs(w_send_base)
-    w_now_p = _device_ptrs(w_now_base)
-    if len(w_send_base) != len(w_now_base):
-        raise SdlError(-1, "sdl_fragment_outer_step_plan_static")
-    _check(_lib.sdl_fragment_outer_step_plan_static(plan._h, p, g_p, mom_p,
-                                                    w_send_p, w_now_p,
-                                                    len(w_send_base), fmt, lr, mu, alpha, _stream(stream)),
-           "sdl_fragment_outer_step_plan_static")
+    _check(_binding.sdl_fragment_outer_step_plan_static(plan, p, g_base, mom_base, w_send_base, w_now_base, fmt, lr, mu,
+                                                        alpha, stream), "sdl_fragment_outer_step_plan_static")
 
 
 def sdl_fragment_outer_step_plan_ex(plan: Plan, p: int, g_base, mom_base, w_send_base, w_now_base,
                                     fmt: int, lr: float, mu: float, alpha: float, codes=None, scales=None,
                                     stream=None):
-    g_p = _device_ptr(g_base)
-    mom_p = _device_ptr(mom_base)
-    w_send_p = _device_ptrs(w_send_base)
-    w_now_p = _device_ptrs(w_now_base)
-    codes_p = _device_ptrs(codes)
-    scales_p = _device_ptrs(scales)
-    if len(w_send_base) != len(w_now_base):
-        raise SdlError(-1, "sdl_fragment_outer_step_plan_ex")
-    _check(_lib.sdl_fragment_outer_step_plan_ex(plan._h, p, g_p, mom_p,
-                                                w_send_p, w_now_p,
-                                                len(w_send_base), fmt, lr, mu, alpha, codes_p,
-                                                scales_p, _stream(stream)),
-           "sdl_fragment_outer_step_plan_ex")
+    _check(_binding.sdl_fragment_outer_step_plan_ex(plan, p, g_base, mom_base, w_send_base, w_now_base, fmt, lr, mu,
+                                                    alpha, codes, scales, stream), "sdl_fragment_outer_step_plan_ex")
 
 
 def sdl_fragment_outer_step_staged_ex(plan: Plan, p: int, g_frag, mom_frag, w_send_base, w_now_base,
                                       fmt: int, lr: float, mu: float, alpha: float, codes=None, scales=None,
                                       stream=None):
-    g_p = _device_ptr(g_frag)
-    mom_p = _device_ptr(mom_frag)
-    w_send_p = _device_ptrs(w_send_base)
-    w_now_p = _device_ptrs(w_now_base)
-    codes_p = _device_ptrs(codes)
-    scales_p = _device_ptrs(scales)
-    _check(_lib.sdl_fragment_outer_step_staged_ex(plan._h, p, g_p, mom_p,
-                                                  w_send_p, w_now_p,
-                                                  len(w_send_base), fmt, lr, mu, alpha, codes_p,
-                                                  scales_p, _stream(stream)),
-           "sdl_fragment_outer_step_staged_ex")
+    _check(_binding.sdl_fragment_outer_step_staged_ex(plan, p, g_frag, mom_frag, w_send_base, w_now_base, fmt, lr, mu,
+                                                      alpha, codes, scales,
+                                                      stream), "sdl_fragment_outer_step_staged_ex")
 
 
 def sdl_plan_message_bytes(plan: Plan, p: int, fmt: int) -> Tuple[int, int]:
@@ -448,31 +359,18 @@ def sdl_plan_message_bytes(plan: Plan, p: int, fmt: int) -> Tuple[int, int]:
 
 def sdl_quantize_outer_grad_plan(plan: Plan, p: int, g_base, w_send_base, fmt: int, codes, scales=None,
                                  stream=None):
-    g_p = _device_ptr(g_base)
-    w_send_p = _device_ptrs(w_send_base)
-    codes_p = _device_ptrs(codes)
-    scales_p = _device_ptrs(scales)
-    _check(_lib.sdl_quantize_outer_grad_plan(plan._h, p, g_p, w_send_p,
-                                             len(w_send_base), fmt, codes_p, scales_p,
-                                             _stream(stream)), "sdl_quantize_outer_grad_plan")
+    _check(_binding.sdl_quantize_outer_grad_plan(plan, p, g_base, w_send_base, fmt, codes, scales,
+                                                 stream), "sdl_quantize_outer_grad_plan")
 
 
 def sdl_dequant_reduce_nesterov_plan(plan: Plan, p: int, g_base, mom_base, codes, scales, fmt: int, lr: float,
                                      mu: float, stream=None):
-    g_p = _device_ptr(g_base)
-    mom_p = _device_ptr(mom_base)
-    codes_p = _device_ptrs(codes)
-    scales_p = _device_ptrs(scales)
-    _check(_lib.sdl_dequant_reduce_nesterov_plan(plan._h, p, g_p, mom_p, codes_p,
-                                                 scales_p, len(codes), fmt, lr, mu, _stream(stream)),
-           "sdl_dequant_reduce_nesterov_plan")
+    _check(_binding.sdl_dequant_reduce_nesterov_plan(plan, p, g_base, mom_base, codes, scales, fmt, lr, mu,
+                                                     stream), "sdl_dequant_reduce_nesterov_plan")
 
 
 def sdl_merge_overlap_plan(plan: Plan, p: int, g_new_base, w_now_base, alpha: float, stream=None):
-    g_new_p = _device_ptr(g_new_base)
-    w_now_p = _device_ptrs(w_now_base)
-    _check(_lib.sdl_merge_overlap_plan(plan._h, p, g_new_p, w_now_p, len(w_now_base),
-                                       alpha, _stream(stream)), "sdl_merge_overlap_plan")
+    _check(_binding.sdl_merge_overlap_plan(plan, p, g_new_base, w_now_base, alpha, stream), "sdl_merge_overlap_plan")
 
 
 class Engine:

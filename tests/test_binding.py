@@ -1,0 +1,179 @@
+"""The extension module that converts the arguments of the device calls (CPU only): with functions in the library's place that note what
+they are called with, every argument arrives where the C interface has it, as ctypes would convert it; and what the
+binding refuses is refused before the library is called."""
+import ctypes
+import inspect
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_18512_amd as sdl
+
+NAMES = sorted(n for n in dir(sdl._binding) if n.startswith("sdl_"))
+LISTS = {"w_send", "w_now", "w_send_base", "w_now_base", "codes", "scales"}
+SCALARS = {"n": 123_456_789_012, "fmt": 3, "p": 7, "lr": 0.7, "mu": 0.9, "alpha": 0.25, "stream": 0x5700}
+
+
+class Tensor:
+    def __init__(self, at, on_device=True, contiguous=True):
+        self.at, self.is_cuda, self.contiguous = at, on_device, contiguous
+
+    def is_contiguous(self):
+        return self.contiguous
+
+    def data_ptr(self):
+        return self.at
+
+
+class Owner:
+    _h = ctypes.c_void_p(0x7777000011)
+
+
+def _real():
+    return {n: ctypes.cast(getattr(sdl._lib, n), ctypes.c_void_p).value for n in NAMES}
+
+
+@pytest.fixture
+def calls():
+    """What the library's functions are called with: name -> argument tuples, arrays of addresses as lists of 16."""
+    seen, kept, table = {}, [], {}
+    for name in NAMES:
+        types = getattr(sdl._lib, name).argtypes
+
+        def note(*args, name=name):
+            seen.setdefault(name, []).append(args)
+            return 0
+        f = ctypes.CFUNCTYPE(ctypes.c_int, *types)(note)
+        kept.append(f)
+        table[name] = ctypes.cast(f, ctypes.c_void_p).value
+    hooks = (sdl._stream, torch.cuda.is_initialized, sdl._get_device, sdl._raw_stream)
+    sdl._binding.setup(table, *hooks)
+    yield seen
+    sdl._binding.setup(_real(), *hooks)
+
+
+def _arguments(name, M):
+    """Arguments of the binding's function, and what the C function of that name is to get (lists: M addresses)."""
+    given, at = {}, 0x100000000
+    for k in inspect.signature(getattr(sdl, name)).parameters:
+        if k == "plan":
+            given[k] = Owner()
+        elif k in LISTS:
+            given[k] = [Tensor(at + 64 * i) for i in range(M)]
+        elif k in SCALARS:
+            given[k] = SCALARS[k]
+        else:
+            given[k] = Tensor(at)
+        at += 0x10000
+    return given
+
+
+def _as_c(given):
+    """The arguments in the order of the C interface: the plan first, M behind the last list of replicas (or the codes), the lists of
+    messages where that interface has them."""
+    out = []
+    for k, v in given.items():
+        if k == "plan":
+            out.append(("plan", Owner._h.value))
+        elif k in LISTS:
+            out.append((k, [t.at for t in v]))
+        elif k in SCALARS:
+            out.append((k, v))
+        else:
+            out.append((k, v.at))
+    return dict(out)
+
+
+C_ORDER = {
+    "sdl_quantize_outer_grad": "g w_send M n fmt codes scales stream",
+    "sdl_dequant_reduce_nesterov": "g mom codes scales M n fmt lr mu stream",
+    "sdl_merge_overlap": "g_new w_now M n alpha stream",
+    "sdl_receive_outer_step": "g mom codes scales w_now M n fmt lr mu alpha stream",
+    "sdl_fragment_outer_step": "g mom w_send w_now M n fmt lr mu alpha codes scales stream",
+    "sdl_quantize_outer_grad_plan": "plan p g_base w_send_base M fmt codes scales stream",
+    "sdl_dequant_reduce_nesterov_plan": "plan p g_base mom_base codes scales M fmt lr mu stream",
+    "sdl_merge_overlap_plan": "plan p g_new_base w_now_base M alpha stream",
+    "sdl_receive_outer_step_plan": "plan p g_base mom_base codes scales w_now_base M fmt lr mu alpha stream",
+    "sdl_fragment_outer_step_plan": "plan p g_base mom_base w_send_base w_now_base M fmt lr mu alpha stream",
+    "sdl_fragment_outer_step_plan_static": "plan p g_base mom_base w_send_base w_now_base M fmt lr mu alpha stream",
+    "sdl_fragment_outer_step_plan_ex": "plan p g_base mom_base w_send_base w_now_base M fmt lr mu alpha codes scales stream",
+    "sdl_fragment_outer_step_staged_ex": "plan p g_frag mom_frag w_send_base w_now_base M fmt lr mu alpha codes scales stream",
+}
+
+
+def test_every_function_is_checked():
+    assert sorted(C_ORDER) == NAMES
+
+
+@pytest.mark.parametrize("name", NAMES)
+@pytest.mark.parametrize("M", [1, 3, 16])
+def test_arguments_arrive(calls, name, M):
+    given = _arguments(name, M)
+    want = dict(_as_c(given), M=M)
+    arrays = {}
+
+    def look(*args):
+        for k, v in zip(C_ORDER[name].split(), args):
+            if k in LISTS:
+                arrays[k] = list((ctypes.c_uint64 * M).from_address(v))
+        return 0
+    f = ctypes.CFUNCTYPE(ctypes.c_int, *getattr(sdl._lib, name).argtypes)(look)
+    getattr(sdl, name)(*given.values())
+    (got,) = calls[name]
+    assert len(got) == len(C_ORDER[name].split())
+    for k, v in zip(C_ORDER[name].split(), got):
+        if k in ("lr", "mu", "alpha"):
+            assert v == float(np.float32(want[k])), k
+        elif k not in LISTS:
+            assert v == want[k], k
+    table = dict(_real(), **{name: ctypes.cast(f, ctypes.c_void_p).value})
+    sdl._binding.setup(table, sdl._stream, torch.cuda.is_initialized, sdl._get_device, sdl._raw_stream)
+    getattr(sdl, name)(*given.values())           # arrays are looked at while the call lasts
+    assert arrays == {k: want[k] for k in C_ORDER[name].split() if k in LISTS}
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_what_is_refused(calls, name):
+    given = _arguments(name, 2)
+    call = getattr(sdl, name)
+    tensors = [k for k in given if k not in SCALARS and k != "plan"]
+    for k in tensors:
+        for bad in (Tensor(64, on_device=False), Tensor(64, contiguous=False), torch.zeros(4)):
+            with pytest.raises(ValueError):
+                call(*dict(given, **{k: [given[k][0], bad] if k in LISTS else bad}).values())
+        with pytest.raises(AttributeError):
+            call(*dict(given, **{k: ["x", "y"] if k in LISTS else object()}).values())
+    counted = [k for k in tensors if k in ("w_send", "w_now", "w_send_base", "w_now_base")] or ["codes"]
+    with pytest.raises(TypeError):
+        call(*dict(given, **{counted[-1]: None}).values())
+    with pytest.raises(TypeError):
+        call(*dict(given, **{counted[-1]: (t for t in given[counted[-1]])}).values())
+    if len(counted) == 2:
+        with pytest.raises(sdl.SdlError):
+            call(*dict(given, **{counted[0]: given[counted[0]][:1]}).values())
+    for k in ("n", "fmt", "p"):
+        if k in given:
+            with pytest.raises(TypeError):
+                call(*dict(given, **{k: 1.0}).values())
+    assert not calls
+    # accepted as ever: addresses, missing messages, integers and numbers of other kinds, more replicas than the library takes (for it to refuse)
+    plain = {k: [x.at for x in v] if k in LISTS else v.at if isinstance(v, Tensor) else v for k, v in given.items()}
+    plain.update({k: None for k in ("scales",) if k in given}, **{k: np.int64(v) for k, v in given.items() if k in ("n", "fmt", "p")},
+                 **{k: np.float32(v) for k, v in given.items() if k in ("lr", "mu", "alpha")})
+    call(*plain.values())
+    call(*{k: v * 20 if k in LISTS else v for k, v in given.items()}.values())
+    assert calls[name][0][C_ORDER[name].split().index("M")] == 2 and calls[name][1][C_ORDER[name].split().index("M")] == 40
+
+
+def test_too_many_replicas_are_refused_by_the_library():
+    given = _arguments("sdl_quantize_outer_grad", 17)
+    with pytest.raises(sdl.SdlError):
+        sdl.sdl_quantize_outer_grad(*given.values())
+
+
+def test_a_plan_that_has_been_given_back():
+    given = _arguments("sdl_merge_overlap_plan", 2)
+    given["plan"]._h = None
+    with pytest.raises(sdl.SdlError):
+        sdl.sdl_merge_overlap_plan(*given.values())
