@@ -324,8 +324,8 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
 // rest conversions and subtractions; with one chain of additions for all of a lane's parameters 310 us measured with the loads
 // and the staging left out, 350 with the staging, 385 with loads from the caches, 456 to 462 in all, and 30 to 35 more with chains
 // of 16 (see total below).  Whole call at 52.9 M parameters, M = 9 / 12 / 13 / 16: 295 / 401 / 500 / 509 us as two wavefronts that
-// each load everything (M <= 12) or on the matrix cores, 253 / 334 / 416 / 495 now (HBM 164 / 209 / 223 / 268); arrays at
-// odd elements 393 / 486 / 764 / 860 and 276 / 357 / 442 / 525; 2.1 M parameters 51 / 80 / 59 / 63 and 28 / 32 / 37 / 42.
+// each load everything (M <= 12) or on the matrix cores, 253 / 312 / 416 / 495 now (HBM 164 / 209 / 223 / 268); arrays at
+// odd elements 393 / 486 / 764 / 860 and 276 / 345 / 442 / 525; 2.1 M parameters 51 / 80 / 59 / 63 and 28 / 32 / 37 / 42.
 // Four wavefronts with a quarter of the matrix each (more of them in flight, 48 conversions instead of 32) 503 at 16 replicas,
 // the tile copied to LDS past the registers, up to three tiles ahead, 478, each beside 463 and with one chain.
 template <int H>
@@ -346,6 +346,7 @@ __device__ __forceinline__ void load_pair_raw(PairRaw<H>& t, const float* g, con
         for (int m = 0; m < H; ++m)
             t.w[m] = __builtin_amdgcn_raw_buffer_load_b64(rsrc(w[m] + e0, kPairTile * 2), (int)(lane * 8), 0, 2);
     } else {
+        lane = lane_here();
         t.g = *reinterpret_cast<const f32x4_elem*>(g + e0 + lane * 4);
 #pragma unroll
         for (int m = 0; m < H; ++m) {
@@ -359,6 +360,7 @@ template <int H>
 __device__ __forceinline__ void load_pair_tail(PairRaw<H>& t, const float* g, const uint16_t* const (&w)[H], uint64_t e0, uint32_t valid,
                                                uint32_t lane)
 {
+    lane = lane_here();
     const __amdgpu_buffer_rsrc_t rg = rsrc(g + e0, valid * 4);
 #pragma unroll
     for (int j = 0; j < 4; ++j) t.g[j] = u2f(__builtin_amdgcn_raw_buffer_load_b32(rg, (int)((lane * 4 + j) * 4), 0, 0));
@@ -389,8 +391,10 @@ constexpr int kShares = 3;
 struct Share {
     uint32_t first_wg, first_tile, per_wg, extra;     // workgroup first_wg + i takes per_wg tiles, one more if i < extra
 };
-// Workgroups of a launch that are on the chip at once: 12 wavefronts on a compute unit with up to 168 registers, else 8.
-constexpr uint32_t pair_resident(uint32_t M, bool digits) { return 256u * (M <= 10u || digits ? 6u : 4u); }
+// Workgroups of a launch that are on the chip at once: 12 wavefronts on a compute unit with up to 168 registers, else 8.  (With 198 at 11 and
+// 12 replicas, the offsets of a ragged tile among them: 52.9 M parameters 334 and 342 us, 306 and 312 with 12 wavefronts; 302 M 1867 and 1887,
+// 1719 and 1754.)
+constexpr uint32_t pair_resident(uint32_t M, bool digits) { return 256u * (M <= 12u || digits ? 6u : 4u); }
 struct PairArgs {
     const float* g;
     const uint16_t* w[SDL_MAX_WORKERS];
@@ -422,7 +426,7 @@ __device__ __forceinline__ uint32_t set_of(const PairArgs& a, uint32_t t)
 }
 
 template <int H>
-__global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(H <= 5 ? 3 : 2))) sdl_gram_pair_kernel(const PairArgs a)
+__global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(H <= 6 ? 3 : 2))) sdl_gram_pair_kernel(const PairArgs a)
 {
     constexpr int kOff = (H + 1) / 2;                // entries of the block rows x columns per row
     constexpr int kTri = H * (H + 1) / 2, kSums = kTri + H * kOff, kLeft = halved(kSums);
