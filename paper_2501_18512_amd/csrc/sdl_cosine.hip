@@ -384,10 +384,20 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 // What the kernel works on: the tiles of all sets one behind the other, shared out among the workgroups in order.  A workgroup
-// writes one matrix for each set that it has tiles of.  Three shares of the launch, each with as many workgroups as there is
+// writes one matrix for each set that it has tiles of.  Up to three shares of the launch, each with as many workgroups as there is
 // room for on the chip at once: 85 % of the tiles, then 10.5 % and 4.5 % in smaller parts, which fill what the first ones leave
-// free when they end (16 replicas: 492 us with equal parts for one round of workgroups, 478 so).
+// free when they end.  In a smaller launch the parts get as small as a few tiles, and more matrices take longer to add up than the parts
+// save: two shares, 93 and 7 %, up to kTwoShares parameters, one up to kOneShare.  Whole call, us, with one share / two / three:
+//   replicas        9                    12                   16
+//   0.3 M      18.4 18.2 18.4       19.0 19.0 18.9       21.6 23.8 23.7
+//   1 M        20.9 21.6 22.5       23.0 23.7 24.7       27.6 28.9 31.2
+//   4 M        32.8 33.7 35.9       37.3 38.9 41.9       47.5 47.3 49.8
+//   8 M        52.8 52.2 55.6       62.7 62.2 65.5       79.0 76.6 80.7
+//   18 M       94.5 89.4 90.3      113.4 110.1 112.1    140.9 137.3 139.8
+//   26 M        131  125  124        158  157  153        200  195  192
+//   302 M      1500 1447 1413       1836 1796 1765       2261 2207 2163
 constexpr int kShares = 3;
+constexpr uint64_t kOneShare = 6ull << 20, kTwoShares = 24ull << 20;
 struct Share {
     uint32_t first_wg, first_tile, per_wg, extra;     // workgroup first_wg + i takes per_wg tiles, one more if i < extra
 };
@@ -596,7 +606,7 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
-// 13 to 16 replicas and many parameters: the sums in whole numbers on the matrix cores.  A replica's outer gradients, times a power
+// 13 to 16 replicas and many parameters (see takes_digits): the sums in whole numbers on the matrix cores.  A replica's outer gradients, times a power
 // of two that brings the largest of them near 2^21, are rounded to multiples of 2^-22 and written as six signed digits of 8 bits; the
 // products of two replicas' digits are whole numbers that v_mfma_i32_16x16x64_i8 adds up without rounding, 64 parameters of all 256
 // entries at a time, and what 16384 parameters gave is converted and added up in fp64.
@@ -634,10 +644,9 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 constexpr int kDigitTile = kTile;                 // parameters a workgroup takes at a time, 64 of them a step, the wavefronts in turn
 constexpr int kDigitSteps = kDigitTile / kWave;
 constexpr uint32_t kFlushTiles = 64;              // after so many a sum has three products of 2^14 for each of 16384 parameters: 2^30
-// (A launch of fewer parameters has too few of these tiles to fill the chip evenly: 1 M parameters, M = 13 27.4 us by FMAs and 28.9, M = 16 30.8
-// and 30.0; 1.5 M 31.6 and 32.5, 35.8 and 33.9; 2.1 M 38.0 and 36.4, 41.1 and 36.5; 8 M 76 and 71, 89 and 75.)
-constexpr uint64_t kDigitParams = 1ull << 21;
-constexpr bool takes_digits(uint32_t M, uint64_t params) { return M > 12u && params >= kDigitParams; }
+// From how many parameters of a launch on.  (Whole call, us, FMAs and here: 2.1 M parameters M = 13 / 14 / 15 / 16 33.1 33.3, 33.3 33.6, 37.0 34.1,
+// 37.8 35.0; 3 M 39.7 41.0, 39.8 41.3, 44.9 41.5, 45.6 42.4; 4 M 47.8 46.8, 47.6 47.0, 54.7 47.6, 54.5 48.3; 1.5 M M = 16 31.7 32.5.)
+constexpr bool takes_digits(uint32_t M, uint64_t params) { return params >= (M > 14u ? 4ull << 19 : M > 12u ? 7ull << 19 : ~0ull); }
 
 constexpr float kBias = 12615808.0f;              // 2^23 + 0x408080
 constexpr float kRoom = 4161407.0f;               // 2^23 - 1 - 0x408080
@@ -1095,9 +1104,10 @@ int launch_pair(const float* g, const void* const* w, uint32_t M, Set* sets, uin
     for (uint32_t s = n_sets + 1u; s <= (uint32_t)kMaxSets; ++s) a.first_tile[s] = 0xffffffffu;
     const uint32_t resident = pair_resident(M, digits);
     uint32_t mats = 0, n_wg = 0, at = 0;
-    constexpr uint32_t kPercent[kShares] = {85, 70, 100};      // of what is left
+    constexpr uint32_t kPercents[kShares][kShares] = {{100, 0, 0}, {93, 100, 0}, {85, 70, 100}};      // of what is left
+    const uint32_t* const percent = kPercents[params <= kOneShare ? 0 : params <= kTwoShares ? 1 : 2];
     for (int i = 0; i < kShares; ++i) {
-        const uint32_t left = (uint32_t)tiles - at, n = (uint32_t)((uint64_t)left * kPercent[i] / 100u);
+        const uint32_t left = (uint32_t)tiles - at, n = (uint32_t)((uint64_t)left * percent[i] / 100u);
         const uint32_t wgs = n < resident ? n : resident;
         a.shares[i] = Share{n_wg, at, wgs ? n / wgs : 0u, wgs ? n % wgs : 0u};
         n_wg += wgs;

@@ -51,7 +51,7 @@ def test_sets_over_launches(M, n_sets, large):
 @pytest.mark.parametrize("M", [2, 9, 13])
 def test_sets_behind_element_2_to_the_32(M):
     first = (1 << 32) + 8
-    sizes = [first, 1000, 513, 2_200_000, 70_001]
+    sizes = [first, 1000, 513, 3_700_000, 70_001]
     plan = sdl.sdl_fragment_plan(sizes, [0, 1, 1, 1, 1], 2, 2, sdl.PATTERN_STRIDED, 10, 0)
     rest = sum(sizes[1:])
     g = torch.empty(first + rest, device="cuda")
