@@ -924,7 +924,9 @@ static_assert(sizeof(FinArgs) <= 4096, "kernel arguments");
 
 // One workgroup per output.  A thread adds every S-th matrix's value of one entry a <= b (neighbouring threads read
 // neighbouring entries), then the S sums of an entry are added as a tree.  Latency bound: a range should give a thread a
-// handful of matrices, so long ranges go through a first level of fin_chunk matrices per output.  (One wavefront per entry
+// handful of matrices, so long ranges go through a first level of fin_chunk matrices per output, and its loads are on the way eight at a
+// time, the last few as well (one after the other those took 2 us: whole call, 1 M parameters, M = 2 / 4 / 9 / 16 13.0 / 14.7 / 20.7 / 27.1 us,
+// now 11.7 / 13.2 / 19.5 / 25.4).  (One wavefront per entry
 // and a butterfly of lane exchanges took 5 us at 4 replicas and 25 us at 16, entry after entry.)
 __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f)
 {
@@ -941,8 +943,18 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
     b += a;
     if (slice < S) {
         double s = 0.0;
-#pragma unroll 8
-        for (uint32_t k = slice; k < count; k += S) s += base[(uint64_t)k * f.stride_k + a * M + b];
+        const double* const mine = base + a * M + b;
+        for (uint32_t k = slice; k < count; k += 8u * S) {
+            double x[8];
+#pragma unroll
+            for (uint32_t i = 0; i < 8u; ++i) {
+                const bool there = k + i * S < count;
+                x[i] = mine[(uint64_t)(there ? k + i * S : k) * f.stride_k];
+                x[i] = there ? x[i] : 0.0;
+            }
+#pragma unroll
+            for (uint32_t i = 0; i < 8u; ++i) s += x[i];
+        }
         part[threadIdx.x] = s;
     }
     __syncthreads();
