@@ -4,16 +4,16 @@
 // Four kernels.
 //   sdl_gram_kernel   up to 8 replicas: streams g and the M replicas once and accumulates the Gram matrix of
 //                     the outer gradients Delta_m = g - float(w_m).  A workgroup is one
-//                     64-lane wavefront; a set of parameters gets a share G of the launch's
-//                     workgroups in proportion to its size, and workgroup k of the set walks
-//                     the set's tiles of 512 consecutive parameters with a fixed stride
-//                     (tile k, k + G, k + 2G, ...), lane l owning the eight
+//                     64-lane wavefront or four of them; a set of parameters gets a share G of
+//                     the launch's workgroups in proportion to its size, and the set's
+//                     W = G or 4G wavefronts walk its tiles of 512 consecutive parameters with
+//                     a fixed stride (tile k, k + W, k + 2W, ...), lane l owning the eight
 //                     parameters [8l, 8l+8) of a tile, so every load instruction of the
 //                     wavefront covers one contiguous piece of an array (2 x 1 KiB of fp32,
 //                     1 KiB of bf16 through 128-bit accesses).  Each lane keeps its M(M+1)/2
 //                     sums in fp64 registers (products of fp32 values are exact in fp64); at
 //                     the end the wavefront folds them, half of the sums at each exchange, and
-//                     its lanes write one partial Gram matrix.  The next tile's loads are issued
+//                     the workgroup writes one partial Gram matrix.  The next tile's loads are issued
 //                     before the current tile is consumed.
 //   sdl_gram_pair_kernel  the same for 9 to 16 replicas: two wavefronts with half of the matrix each, which
 //                     exchange the outer gradients through LDS.
@@ -48,7 +48,23 @@ constexpr int kMaxPieces = kMaxSets + kWindows;
 // 209 / 371 and 66 / 90 / 153 / 319.
 constexpr uint32_t kFewSets = 48;
 constexpr uint64_t kManyParams = 1ull << 23;
-constexpr uint32_t kGroups = 8192;              // workgroups per launch up to 8 replicas, shared out among the sets (32 per compute unit)
+// Up to 8 replicas, the wavefronts of a workgroup and the workgroups of a launch, which are shared out among the sets.
+// Four wavefronts, whose sums are added in LDS, leave a quarter of the matrices to write and to add up.  The workgroups of all sets together are
+// no more than fit the chip (a launch's shares are rounded up, so as many fewer are dealt out as there are sets): with 8 per compute unit and some
+// more, as it was with one wavefront each, the last ones ran by themselves.  Whole call with 8192 workgroups of one wavefront and now, M = 2 / 4 / 8:
+// 1 M parameters 11.1 / 12.9 / 17.5 and 8.4 / 10.6 / 16.4 us (some of it by the one launch that adds up to four chunks, see finalize_sets), 4 M
+// 14.3 / 18.1 / 31.2 and 12.8 / 17.2 / 31.9, 32 M 50 / 69 / 118 and 48 / 67 / 115, 53 M in 39 sets 75.3 / 108 / 182 and 73.9 / 107 / 177, 302 M in
+// 48 sets 386 / 563 / 1020 and 379 / 554 / 962.  Beyond kFewFours 10 per compute unit: 80 M 110.5 / 154 / 246 with 2048, 106.3 / 154 / 248 with 2560, and
+// a launch of ragged sets with 80 M 107.0 / 155 / 261 and 103.3 / 154.5 / 258.
+// One wavefront where the accesses of the four together are the slower: 8 replicas in more than kFewSets sets (194 sets, 2.5 M parameters in all:
+// 25.6 us, with four 27.3), and from 5 replicas sets that are not aligned to 16 bytes, beyond kRaggedOne / (M - 4) parameters (M = 5 / 6 / 8: 1 M
+// 14.6 / 16.5 / 18.3 us with one, 12.3 / 14.2 / 17.7 with four; 3 M 19.6 / 22.5 / 28.2 and 19.1 / 23.3 / 28.9; 6 M 28.1 / 31.7 / 40.2 and 28.3 / 33.0 / 42.2).
+constexpr uint32_t kGramWaves = 4;
+constexpr uint32_t kFours = 2048;               // workgroups of four wavefronts: 8 per compute unit
+constexpr uint32_t kManyFours = 2560;           // beyond kFewFours parameters
+constexpr uint64_t kFewFours = 64u << 20;
+constexpr uint32_t kGroups = 8192;              // workgroups of one wavefront
+constexpr uint64_t kRaggedOne = 4u << 20;
 constexpr uint32_t kMaxGroups = 8192;           // what the workspace is sized for
 
 
@@ -66,6 +82,7 @@ struct GramArgs {
     const uint16_t* w[8];
     double* partial;               // [workgroup of the launch][M*M]
     uint32_t n_pieces;
+    uint32_t waves;                // of a workgroup
     uint32_t group_wg[kMaxPieces / 16 - 1];   // first workgroup of the 16th, 32nd, ... piece
     uint32_t first_wg[kMaxPieces + 1];        // of each piece, then the number of workgroups; 0xffffffff behind it
     uint32_t offset[kMaxPieces];              // first element in the flat arrays, low 32 bits
@@ -212,10 +229,12 @@ template <int N> __device__ __forceinline__ void halves_of(uint32_t lane, uint32
 
 // Up to 8 replicas: every lane holds the whole upper triangle.
 template <int M>
-__global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
+__global__ void __launch_bounds__(kGramWaves * kWave) sdl_gram_kernel(const GramArgs a)
 {
     constexpr int kSums = M * (M + 1) / 2, kLeft = halved(kSums);
-    const uint32_t lane = threadIdx.x;
+    __shared__ double wave_sums[kGramWaves][kSums];
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     // the first workgroups of 16 pieces are one scalar load, those of every 16th piece come first
     constexpr int kGroupsOf16 = kMaxPieces / 16, kFew = 6;
     uint32_t base = 0, s = 15;
@@ -233,7 +252,7 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
     for (int i = 15; i >= 1; --i)
         if (blockIdx.x < a.first_wg[base + i]) s = (uint32_t)(i - 1);
     s += base;
-    const uint32_t k = blockIdx.x - a.first_wg[s], high = a.high[s / 4u] >> (s % 4u * 8u);
+    const uint32_t k = blockIdx.x - a.first_wg[s], G = a.first_wg[s + 1u] - a.first_wg[s], high = a.high[s / 4u] >> (s % 4u * 8u);
     const bool fast = high & kFast;
     const uint64_t offset = (uint64_t)(high & (kFast - 1u)) << 32 | a.offset[s];
     const uint32_t numel = a.numel[s], n_tiles = numel / kTile + (numel % kTile ? 1u : 0u);
@@ -268,8 +287,8 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
         }
     };
 
-    // workgroup k's tiles: first, first + step, ... below end
-    const uint32_t first = k, step = a.first_wg[s + 1u] - a.first_wg[s], end = n_tiles;
+    // the wavefront's tiles: first, first + step, ... below end; neighbouring tiles go to neighbouring workgroups
+    const uint32_t first = wave * G + k, step = a.waves * G, end = n_tiles;
     auto load = [&](TileRegs<M>& r, uint32_t t) { load_tile<M>(r, a.g, w, offset + (uint64_t)t * kTile, valid_of(t), fast, lane); };
     if constexpr (M <= 3) {
         // Two sets of registers in turn, so that two tiles are on the way.  (A copy of what was loaded ahead, as below, has to wait for it.
@@ -298,15 +317,20 @@ __global__ void __launch_bounds__(kWave) sdl_gram_kernel(const GramArgs a)
     }
 
     halve<kSums, 0>(sum, lane);
-    double* out = a.partial + (uint64_t)blockIdx.x * M * M;
     uint32_t held, count;
     halves_of<kSums>(lane, &held, &count);
 #pragma unroll
-    for (uint32_t v = 0; v < (uint32_t)kLeft; ++v) {
-        if (v >= count) continue;
-        uint32_t r = 0, c = held + v;
+    for (uint32_t v = 0; v < (uint32_t)kLeft; ++v)
+        if (v < count) wave_sums[wave][held + v] = sum[v];
+    __syncthreads();
+    if (threadIdx.x < (uint32_t)kSums) {
+        uint32_t r = 0, c = threadIdx.x;
         while (c >= M - r) { c -= M - r; ++r; }
-        out[r * M + r + c] = sum[v];
+        const uint32_t i = threadIdx.x;
+        static_assert(kGramWaves == 4);
+        double total = wave_sums[0][i];
+        if (a.waves > 1u) total = (total + wave_sums[1][i]) + (wave_sums[2][i] + wave_sums[3][i]);
+        a.partial[(uint64_t)blockIdx.x * M * M + r * M + r + c] = total;
     }
 }
 
@@ -1000,7 +1024,7 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
 
 int launch_kernel(uint32_t M, const GramArgs& a, hipStream_t st)
 {
-    const dim3 grid(a.first_wg[a.n_pieces]), one(kWave);
+    const dim3 grid(a.first_wg[a.n_pieces]), one(a.waves * kWave);
     switch (M) {
     case 1: hipLaunchKernelGGL((sdl_gram_kernel<1>), grid, one, 0, st, a); break;
     case 2: hipLaunchKernelGGL((sdl_gram_kernel<2>), grid, one, 0, st, a); break;
@@ -1023,9 +1047,9 @@ bool all_aligned16(const float* g, const void* const* w, uint32_t M, uint64_t of
     return fast;
 }
 
-// Shares the launch's workgroups out among the sets in proportion to their tiles (at least
+// Shares the launch's workgroups of so many wavefronts out among the sets in proportion to their tiles (at least
 // one each); returns the total, at most groups + n_sets.
-uint32_t share_groups(Set* sets, uint32_t n_sets, uint32_t groups)
+uint32_t share_groups(Set* sets, uint32_t n_sets, uint32_t groups, uint32_t waves)
 {
     uint64_t total_tiles = 0;
     for (uint32_t s = 0; s < n_sets; ++s) total_tiles += (sets[s].numel + kTile - 1) / kTile;
@@ -1033,7 +1057,7 @@ uint32_t share_groups(Set* sets, uint32_t n_sets, uint32_t groups)
     for (uint32_t s = 0; s < n_sets; ++s) {
         const uint64_t tiles = (sets[s].numel + kTile - 1) / kTile;
         uint64_t G = total_tiles ? (tiles * groups + total_tiles - 1) / total_tiles : 1;
-        if (G > tiles) G = tiles;
+        if (G > (tiles + waves - 1) / waves) G = (tiles + waves - 1) / waves;
         if (G < 1) G = 1;
         sets[s].first_wg = next;
         sets[s].G = (uint32_t)G;
@@ -1044,10 +1068,11 @@ uint32_t share_groups(Set* sets, uint32_t n_sets, uint32_t groups)
 
 // Partial Gram matrices of up to kMaxSets sets (already given their workgroups) into
 // `partial`, one M x M matrix per workgroup of the launch.
-int launch_gram(const float* g, const void* const* w, uint32_t M, const Set* sets, uint32_t n_sets, double* partial,
+int launch_gram(const float* g, const void* const* w, uint32_t M, const Set* sets, uint32_t n_sets, uint32_t waves, double* partial,
                 hipStream_t st)
 {
     GramArgs a{};
+    a.waves = waves;
     a.g = g;
     a.partial = partial;
     for (uint32_t& x : a.group_wg) x = 0xffffffffu;
@@ -1166,18 +1191,29 @@ int launch_finalize(const FinArgs& f, uint32_t n_out, hipStream_t st)
     return hipGetLastError() == hipSuccess ? SDL_OK : SDL_ERR_DEVICE;
 }
 
-// Partial Gram matrices of up to kMaxSets sets into `partial`; where they lie goes into the sets.
+// Partial Gram matrices of up to kMaxSets sets into `partial`; where they lie goes into the sets.  Up to 8 replicas by the rule at kGramWaves.
 int launch_sums(const float* g, const void* const* w, uint32_t M, Set* sets, uint32_t n_sets, double* partial, uint32_t* n_mats,
                 hipStream_t st)
 {
     if (M > 8u) return launch_pair(g, w, M, sets, n_sets, partial, n_mats, st);
-    *n_mats = share_groups(sets, n_sets, kGroups);
-    return launch_gram(g, w, M, sets, n_sets, partial, st);
+    uint64_t params = 0;
+    bool fast = true;
+    for (uint32_t s = 0; s < n_sets; ++s) {
+        params += sets[s].numel;
+        fast = fast && all_aligned16(g, w, M, sets[s].offset);
+    }
+    const bool one = M > 4u && ((!fast && params * (M - 4u) > kRaggedOne) || (M == 8u && n_sets > kFewSets));
+    const uint32_t groups = one ? kGroups : params > kFewFours ? kManyFours : kFours;
+    const uint32_t waves = one ? 1u : kGramWaves;
+    *n_mats = share_groups(sets, n_sets, groups - n_sets, waves);
+    return launch_gram(g, w, M, sets, n_sets, waves, partial, st);
 }
 
 // One result per set from the partial matrices of its workgroups (at partial + first_wg; the sets' matrices lie one behind the other) and, if
 // union_out is not null, the result of all of them together.  Sets with many workgroups are first added up in chunks (into
 // tmp), so that no thread of the finalize kernel walks a long range.
+// Many is four chunks: a second launch costs 2 us, as much as a thread's 32 loads, eight at a time.  (At two chunks, 1 M parameters, M = 1 / 2 / 4
+// 11.3 / 11.4 / 13.3 us, at four 9.4 / 9.5 / 12.5; at eight slower with 6 replicas and more.)
 int finalize_sets(const double* partial, const Set* sets, uint32_t n_sets, uint32_t M, double* out, double* union_out,
                   double* tmp, hipStream_t st)
 {
@@ -1186,10 +1222,10 @@ int finalize_sets(const double* partial, const Set* sets, uint32_t n_sets, uint3
     uint32_t total = 0;
     bool two_level = false;
     for (uint32_t s = 0; s < n_sets; ++s) {
-        two_level = two_level || sets[s].G > 2 * chunk;
+        two_level = two_level || sets[s].G > 4 * chunk;
         total += sets[s].G;
     }
-    two_level = two_level || (union_out && total > 2 * chunk);
+    two_level = two_level || (union_out && total > 4 * chunk);
     FinArgs last{};
     last.out = out;
     last.last_out = union_out;

@@ -1,0 +1,43 @@
+"""Up to 8 replicas: a launch is at most 2048 workgroups of four wavefronts, 2560 beyond 64 * 2^20 parameters, or 8192 of one: for 8 replicas in more
+than 48 sets, and for sets that are not 16-byte aligned, M replicas and more than 4 * 2^20 / (M - 4) parameters.  Both sides of these edges, and
+numbers of tiles that leave wavefronts of a workgroup without one."""
+import pytest
+import torch
+
+import paper_2501_18512_amd as sdl
+
+pytestmark = pytest.mark.gpu
+
+FOUR = 64 << 20
+CASES = [[FOUR], [FOUR + 1], [700, FOUR // 3, 5, FOUR - FOUR // 3 - 705 - 513, 513],
+         [1], [511], [512], [513], [1536], [2047], [2049], [512 * 8192 - 1], [512 * 8192 + 513],
+         [1 + 37 * i for i in range(48)], [1 + 211 * i for i in range(49)], [5000 + i for i in range(224)],
+         [8, (1 << 20) - 8], [3, (1 << 20) - 3], [3, (1 << 20) - 2], [8, (2 << 20) - 8], [5, (2 << 20) + 1]]
+
+
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 6, 7, 8])
+@pytest.mark.parametrize("sizes", CASES, ids=lambda s: f"{len(s)}x{s[0]}")
+def test_both_sides_of_an_edge(M, sizes):
+    gen = torch.Generator("cuda").manual_seed(M)
+    n = sum(sizes)
+    g = torch.randn(n, device="cuda", generator=gen)
+    w = [(g - torch.randn(n, device="cuda", generator=gen)).to(torch.bfloat16) for _ in range(M)]
+    plan = sdl.sdl_fragment_plan(sizes, [0] * len(sizes), 1, 1, sdl.PATTERN_STRIDED, 10, 0)
+    results, workspace = sdl.alloc_cosine(M, len(sizes))
+    workspace.fill_(0xff)              # NaN: nothing may come from a matrix that nobody wrote
+    fragment = torch.empty(sdl.cosine_result_doubles(M), dtype=torch.float64, device="cuda")
+    sdl.sdl_outer_grad_cosine_plan(plan, 0, g, w, results, fragment, workspace)
+    want, at = [], 0
+    for s in sizes:
+        total = torch.zeros(M, M, dtype=torch.float64, device="cuda")
+        for lo in range(at, at + s, 1 << 19):
+            hi = min(lo + (1 << 19), at + s)
+            d = torch.stack([(g[lo:hi] - x[lo:hi].float()).double() for x in w])
+            total += d @ d.T
+        want.append(total)
+        at += s
+    got = [sdl.split_cosine_result(r, M)[0] for r in [*results, fragment]]
+    for a, b in zip(got, want + [sum(want)]):
+        norm = torch.diagonal(b).sqrt()
+        # the same exact products in another order: 2^19 of them one after the other, more than either side adds, err by 2^-34 at most
+        assert ((a - b).abs() <= 2.0 ** -34 * norm[:, None] * norm[None, :]).all()
