@@ -650,18 +650,18 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 // sums so far are put into fp64 and a new one is taken, with room for twice as much and more.  Infinities, NaN and differences below
 // 2^-98 (whose scale would not be a normal number) are added up 64 parameters at a time in fp64.
 //
-// Error against exact sums, 1e-16 of sqrt(G[a][a] G[b][b]), a = b / a != b, rms, by FMAs and here, at 13 and at 16 replicas, 20 M
-// parameters: normal 0.6/0.01 0.7/0.01 and 0.7/0.00 0.7/0.00; Student t3 0.9/0.02 0.8/0.01 and 0.5/0.00 1.2/0.00; with outliers 0.8/0.01
-// 0.8/0.00 and 0.7/0.00 0.9/0.00; replicas that agree, outliers in the same places, 1.4/0.9 0.9/1.0 and 0.9/0.5 0.8/0.9; differences
-// with all 24 bits 0.8/0.7 0.9/1.1 and 0.7/0.6 1.4/0.9; 2.1 M alike.  Sizes that vary by 2^40 from one parameter to the next: 1.0/0.00
-// 0.9/0.00 and 0.5/0.3 1.0/0.3, at 2.1 M 0.8/0.00 1.1/0.00 and 0.9/0.8 0.7/0.8.
+// Error against exact sums, 1e-16 of sqrt(G[a][a] G[b][b]), a = b / a != b, rms of six replicas and 12 seeds, 20 M parameters, by FMAs at 13 and
+// at 16 replicas, and here: normal 0.81/0.01 0.86/0.01, 0.78/0.00 0.95/0.00; Student t3 0.73/0.02 0.86/0.01, 0.65/0.00 0.84/0.00; with outliers
+// 0.87/0.01 0.84/0.01, 0.72/0.00 0.74/0.00; differences with all 24 bits 0.86/0.75 0.80/0.87, 0.72/0.65 0.70/0.79; 2.5 M and 5 M alike.  One seed:
+// replicas that agree, outliers in the same places, 1.4/0.9 0.9/1.0, 0.9/0.5 0.8/0.9; sizes that vary by 2^40 from one parameter to the next 1.0/0.00
+// 0.9/0.00, 0.5/0.3 1.0/0.3.
 //
 // Bound: vector instructions, 12.5 for a difference (two to form it, a half to look at its size, four for the digits, 3.5 that
 // bring each digit's bytes together and 2 for the signs), and the matrix instructions, 18 for 64 parameters of 16 cycles each, beside which
 // a SIMD issues little else: 346 us at 52.9 M parameters and 16 replicas without the loads, 250 without the matrix instructions either, 312
 // the loads alone, 397 in all (HBM 268).  Whole call, FMAs and here, M = 13 / 14 / 15 / 16: 52.9 M parameters 422 / 424 / 492 / 494
 // and 364 / 370 / 380 / 385; at odd elements 439 / 444 / 515 / 522 and 396 / 402 / 429 / 433.  (The time hardly depends
-// on the replicas, as a matrix instruction has 16 rows whatever they are: at 12 replicas 336 and 354.)  Tried, each beside 390 to 409: a tile of 512
+// on the replicas, as a matrix instruction has 16 rows whatever they are: at 12 replicas 306 and 354.)  Tried, each beside 390 to 409: a tile of 512
 // for each wavefront, 252 registers, 409; 256 parameters, two tiles in LDS 401; the digits' products one step behind, between the
 // vector instructions of the next, which takes 220 registers 427; workgroups that take turns at the tiles 397; subtraction by
 // v_dot2_f32_bf16, which does not round to nearest.
