@@ -408,8 +408,10 @@ int sdl_engine_bind_offload(sdl_engine_t* engine, sdl_offload_t* pool, void* con
  *     cos[a][b] = G[a][b] / (sqrt(G[a][a]) * sqrt(G[b][b])),  0 when either norm is 0
  *     mean      = average of cos[a][b] over the pairs a < b (0 when M == 1)
  * A result is SDL_COSINE_RESULT_DOUBLES(M) = 2*M*M + 1 doubles in device memory: G (row
- * major), then cos (row major), then mean.  Summation order is fixed by the sizes alone, so a
- * call is reproducible bit for bit; it differs from a sequential sum by fp64 rounding only.
+ * major), then cos (row major), then mean.  No product is rounded, and the order of the sums is
+ * fixed by the sizes (with 13 replicas and more, in large calls, by the sizes and the values),
+ * so a call is reproducible bit for bit wherever its arrays lie; it differs from a sequential
+ * sum by fp64 rounding only.
  * Reads 4 + 2*M bytes per parameter and writes nothing but the result.
  *
  * workspace: device memory of at least sdl_cosine_workspace_bytes(M, n_sets) bytes, 8-byte

@@ -631,45 +631,48 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 }
 
 // 13 to 16 replicas and many parameters (see takes_digits): the sums in whole numbers on the matrix cores.  A replica's outer gradients, times a power
-// of two that brings the largest of them near 2^21, are rounded to multiples of 2^-22 and written as six signed digits of 8 bits; the
+// of two that brings the largest of them near 2^21, are multiples of 2^-22 as a rule and written as six signed digits of 8 bits; the
 // products of two replicas' digits are whole numbers that v_mfma_i32_16x16x64_i8 adds up without rounding, 64 parameters of all 256
 // entries at a time, and what 16384 parameters gave is converted and added up in fp64.
 //
 // The digits.  x is a difference, t = x * scale, |t| <= kRoom.  As the sum with kBias is in [2^23, 2^24), fma(x, scale, kBias)
 // is the bit pattern of t rounded to a whole number, plus 0x408080: in each of the two low bytes, and in the seven bits above, a digit
 // with 128 (64) added, which the exclusive or (and an addition of 64 ahead of it) takes off all four bytes of a register at
-// once.  What the rounding left, at most 1/2, is exact as an fma; times 2^22 it gives three more digits in the same way.  A difference
-// has 24 bits, so whatever is larger than 2^-18 of the largest is exact, and smaller ones are off by 2^-44 of the largest at most.
-// Weights of the digits: 2^16, 2^8, 1 and 2^-6, 2^-14, 2^-22.  Three of the 21 products are left out: their weights are 2^-28,
-// 2^-36 and 2^-44, and the signs of their factors have nothing to do with each other.  (Without the square of weight 2^-28 the
-// diagonal would err by 2^-52 to one side where differences have 24 bits.)
+// once.  What the rounding left, at most 1/2, is exact as an fma; times 2^22 it gives three more digits in the same way.
+// Weights of the digits: 2^16, 2^8, 1 and 2^-6, 2^-14, 2^-22.
 // The products of the digits a < b are formed once and their transpose is added at the end: T + T^T is the matrix of sums if T has
-// half of the squares.
+// half of the squares.  The last digit is 0 for nearly all differences between weights and replicas (multiples of the last place of the smaller
+// of two numbers), and a step without one leaves its six products out; four of them, whose weights are 2^-22 and less, are kept in fp64 (`low`),
+// together with what the additions to the totals round off.
+//
+// Nothing is rounded ahead of a product.  A difference has 24 bits, so what is not below 2 / scale (`least`) is a multiple of 2^-22 / scale; if a step has
+// smaller ones they are looked at, and if one is no such multiple, the step's 64 parameters are added up in fp64 by v_mfma_f64_16x16x4_f64.  So are
+// infinities, NaN, and differences below 2^-98 where there are no larger ones (their scale would not be a normal number).
 //
 // The scale of a replica is that of the wavefront's parameters so far: where a difference exceeds what it has room for, the
-// sums so far are put into fp64 and a new one is taken, with room for twice as much and more.  Infinities, NaN and differences below
-// 2^-98 (whose scale would not be a normal number) are added up 64 parameters at a time in fp64.
+// sums so far are put into fp64 and a new one is taken, with room for twice as much and more.
 //
-// Error against exact sums, 1e-16 of sqrt(G[a][a] G[b][b]), a = b / a != b, rms of six replicas and 12 seeds, 20 M parameters, by FMAs at 13 and
-// at 16 replicas, and here: normal 0.81/0.01 0.86/0.01, 0.78/0.00 0.95/0.00; Student t3 0.73/0.02 0.86/0.01, 0.65/0.00 0.84/0.00; with outliers
-// 0.87/0.01 0.84/0.01, 0.72/0.00 0.74/0.00; differences with all 24 bits 0.86/0.75 0.80/0.87, 0.72/0.65 0.70/0.79; 2.5 M and 5 M alike.  One seed:
-// replicas that agree, outliers in the same places, 1.4/0.9 0.9/1.0, 0.9/0.5 0.8/0.9; sizes that vary by 2^40 from one parameter to the next 1.0/0.00
-// 0.9/0.00, 0.5/0.3 1.0/0.3.
+// Error against exact sums, 1e-16 of sqrt(G[a][a] G[b][b]), a = b / a != b, rms of six replicas and 8 seeds, 20 M parameters, by FMAs at 13 and
+// at 16 replicas, and here: normal 0.76/0.01 0.89/0.01, 0.74/0.00 0.92/0.00; Student t3 0.74/0.02 0.84/0.01, 0.64/0.00 0.70/0.00; with outliers
+// 0.99/0.01 0.85/0.01, 0.86/0.00 0.72/0.00; differences with all 24 bits 0.79/0.78 0.66/0.69, 0.69/0.72 0.81/0.74 (of 4 M and 12 seeds normal
+// 0.90/0.01 0.95/0.01, 0.96/0.00 0.93/0.00, 24 bits 0.87/0.91 0.68/0.83, 0.74/0.84 0.62/0.65).  Two seeds: replicas that agree, outliers in the same
+// places, 1.08/1.04 0.88/1.00, 0.62/0.89 0.62/0.77; sizes that vary by 2^40 from one parameter to the next 0.75/0.01 0.89/0.01, 0.49/0.01 0.88/0.01.
 //
-// Bound: vector instructions, 12.5 for a difference (two to form it, a half to look at its size, four for the digits, 3.5 that
-// bring each digit's bytes together and 2 for the signs), and the matrix instructions, 18 for 64 parameters of 16 cycles each, beside which
-// a SIMD issues little else: 346 us at 52.9 M parameters and 16 replicas without the loads, 250 without the matrix instructions either, 312
-// the loads alone, 397 in all (HBM 268).  Whole call, FMAs and here, M = 13 / 14 / 15 / 16: 52.9 M parameters 422 / 424 / 492 / 494
-// and 364 / 370 / 380 / 385; at odd elements 439 / 444 / 515 / 522 and 396 / 402 / 429 / 433.  (The time hardly depends
-// on the replicas, as a matrix instruction has 16 rows whatever they are: at 12 replicas 306 and 354.)  Tried, each beside 390 to 409: a tile of 512
-// for each wavefront, 252 registers, 409; 256 parameters, two tiles in LDS 401; the digits' products one step behind, between the
-// vector instructions of the next, which takes 220 registers 427; workgroups that take turns at the tiles 397; subtraction by
+// Bound: vector instructions, 13 for a difference (two to form it, a half each to look at the largest and the smallest, four for the digits, 3.5 that
+// bring each digit's bytes together and 2 for the signs) of four cycles each: they take 92 % of the SIMDs' cycles, the matrix instructions, 15 of 16
+// cycles for 64 parameters, 26 % beside them.  52.9 M parameters and 16 replicas: 300 us with neither loads nor matrix instructions, 329 without the
+// loads, 357 without the matrix instructions, 322 the loads and the staging alone, 385 in all (HBM 268).  Whole call, FMAs and here, M = 13 / 14 / 15 / 16: 52.9 M
+// parameters 419 / 425 / 503 / 509 and 367 / 373 / 382 / 387; at odd elements 443 / 447 / 525 / 533 and 397 / 403 / 423 / 428.  M = 16 with outliers 492 and
+// 417, t3 495 and 421, 24 bits 499 and 387, a tenth of the differences 0 496 and 428; steps in fp64 all along (sizes that vary by 2^40) 503 and 777.
+// (The time hardly depends on the replicas, as a matrix instruction has 16 rows whatever they are: at 12 replicas 306 and 354.)  Tried, each beside 390
+// to 409 with 18 products at every step: a tile of 512 for each wavefront, 252 registers, 409; 256 parameters, two tiles in LDS 401; the digits' products one
+// step behind, between the vector instructions of the next, which takes 220 registers 427; workgroups that take turns at the tiles 397; subtraction by
 // v_dot2_f32_bf16, which does not round to nearest.
 constexpr int kDigitTile = kTile;                 // parameters a workgroup takes at a time, 64 of them a step, the wavefronts in turn
 constexpr int kDigitSteps = kDigitTile / kWave;
 constexpr uint32_t kFlushTiles = 64;              // after so many a sum has three products of 2^14 for each of 16384 parameters: 2^30
-// From how many parameters of a launch on.  (Whole call, us, FMAs and here: 2.1 M parameters M = 13 / 14 / 15 / 16 33.1 33.3, 33.3 33.6, 37.0 34.1,
-// 37.8 35.0; 3 M 39.7 41.0, 39.8 41.3, 44.9 41.5, 45.6 42.4; 4 M 47.8 46.8, 47.6 47.0, 54.7 47.6, 54.5 48.3; 1.5 M M = 16 31.7 32.5.)
+// From how many parameters of a launch on.  (Whole call, us, FMAs and here: 1.5 M parameters M = 15 / 16 30.3 30.4, 30.9 30.9; 2.1 M 36.0 34.6, 36.4
+// 35.1; 3 M M = 13 / 14 / 15 / 16 39.2 39.1, 39.5 39.4, 43.1 39.9, 43.5 40.6; 3.7 M M = 13 / 14 43.6 43.7, 43.7 43.7; 4.2 M 46.7 46.1, 47.1 46.2.)
 constexpr bool takes_digits(uint32_t M, uint64_t params) { return params >= (M > 14u ? 4ull << 19 : M > 12u ? 7ull << 19 : ~0ull); }
 
 constexpr float kBias = 12615808.0f;              // 2^23 + 0x408080
@@ -679,15 +682,18 @@ constexpr float kFltMax = 3.402823466e+38f;
 
 enum Digit { kHi2, kHi1, kHi0, kLo2, kLo1, kLo0, kDigits };
 struct Product { int a, b, acc; };
-struct DigitSum { int weight; bool square; };     // 2^weight
-constexpr int kDigitSums = 14;
-constexpr DigitSum kSumOf[kDigitSums] = {{32, true}, {24, false}, {16, false}, {16, true}, {8, false}, {0, true}, {10, false},
-                                         {2, false}, {-6, false}, {-14, false}, {-22, false}, {-12, true}, {-20, false}, {-28, true}};
+struct DigitSum { double weight; };
+constexpr int kDigitSums = 13;
+constexpr double kHalf = 0.5;                     // of a digit's square
+constexpr DigitSum kSumOf[kDigitSums] = {{kHalf * 0x1p32}, {0x1p24}, {0x1p16}, {kHalf * 0x1p16}, {0x1p8}, {kHalf}, {0x1p10},
+                                         {0x1p2}, {0x1p-6}, {0x1p-14}, {kHalf * 0x1p-12}, {0x1p-20}, {kHalf * 0x1p-28}};
 constexpr Product kProducts[] = {
-    {kHi2, kHi2, 0}, {kHi2, kHi1, 1}, {kHi2, kHi0, 2}, {kHi1, kHi1, 3}, {kHi1, kHi0, 4}, {kHi0, kHi0, 5},
-    {kHi2, kLo2, 6}, {kHi2, kLo1, 7}, {kHi1, kLo2, 7}, {kHi2, kLo0, 8}, {kHi1, kLo1, 8}, {kHi0, kLo2, 8},
-    {kHi1, kLo0, 9}, {kHi0, kLo1, 9}, {kHi0, kLo0, 10}, {kLo2, kLo2, 11}, {kLo2, kLo1, 12}, {kLo1, kLo1, 13}};
+    {kHi2, kHi2, 0}, {kHi2, kHi1, 1}, {kHi2, kHi0, 2}, {kHi1, kHi1, 3}, {kHi1, kHi0, 4}, {kHi0, kHi0, 5}, {kHi2, kLo2, 6},
+    {kHi2, kLo1, 7}, {kHi1, kLo1, 8}, {kHi1, kLo2, 7}, {kHi0, kLo2, 8}, {kHi0, kLo1, 9}, {kLo2, kLo2, 10}, {kLo2, kLo1, 11}, {kLo1, kLo1, 12}};
+constexpr Product kLastDigit[] = {{kHi2, kLo0, 8}, {kHi1, kLo0, 9}};     // the others of the last digit go past the sums
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr double kDblMax = 1.7976931348623157e+308;
 
 __device__ __forceinline__ float from_lane(float x, uint32_t lane)
 {
@@ -752,53 +758,74 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
     for (int i = 0; i < H; ++i) w[i] = a.w[wave * H + i < M ? wave * H + i : 0u];
 
     i32x4 sum[kDigitSums];                           // [v] is row 4 q + v, column r
-    float scale = 0.0f, limit = -1.0f;               // of the lane's replica
+    double low[4];                                   // what the totals had no room for
+    float scale = 0.0f, limit = -1.0f, least = 0.0f; // of the lane's replica; what is not 0 and below `least` may have bits that the digits lack
     auto clear = [&]() {
 #pragma unroll
         for (int i = 0; i < kDigitSums; ++i) sum[i] = i32x4{0, 0, 0, 0};
     };
+    // adds x to entry v of the total, the rounding to `low`
+    auto add = [&](int v, double x) {
+        double* const total = &totals[wave][4u * lane_here() + (uint32_t)v];
+        const double before = *total, after = before + x, part = after - before;
+        const double rounding = (before - (after - part)) + (x - part);
+        low[v] += __builtin_fabs(after) <= kDblMax ? rounding : 0.0;
+        *total = after;
+    };
+    // 1 / (scale of row 4 q + v * scale of the lane's column), 0 where a scale is
+    auto unscale = [&](int v) -> double {
+        const float inv = scale > 0.0f ? u2f((254u << 23) - f2u(scale)) : 0.0f;
+        return (double)inv * (double)from_lane(inv, 4u * (lane_here() / 16u) + (uint32_t)v);
+    };
     auto flush = [&]() {
-        const uint32_t l = lane_here(), q = l / 16u;
-        double* const total = &totals[wave][4u * l];
-        const float inv = scale > 0.0f ? 1.0f / scale : 0.0f;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             double t = 0.0;
 #pragma unroll
-            for (int i = kDigitSums - 1; i >= 0; --i)
-                t += __builtin_ldexp((double)sum[i][v], kSumOf[i].weight - (kSumOf[i].square ? 1 : 0));
-            total[v] += t * ((double)inv * (double)from_lane(inv, 4u * q + (uint32_t)v));
+            for (int i = kDigitSums - 1; i >= 0; --i) t = __builtin_fma((double)sum[i][v], kSumOf[i].weight, t);
+            add(v, t * unscale(v));
         }
         clear();
     };
     // A step that the limits do not cover: true if its products have been added up here.
-    auto adjust = [&](const float (&d)[16], float largest) -> bool {
-        const uint32_t l = lane_here(), q = l / 16u, r = l % 16u;
-        double* const total = &totals[wave][4u * l];
-        float m = __builtin_elementwise_maximum(largest, from_lane(largest, l ^ 16u));
-        m = __builtin_elementwise_maximum(m, from_lane(m, l ^ 32u));
-        const bool fits = m <= limit;
-        if (__builtin_amdgcn_ballot_w64(!fits && (!(m <= kFltMax) || (m > 0.0f && m < 0x1p-98f)))) {
-#pragma unroll 1
-            for (uint32_t from = 0; from < (uint32_t)kWave; from += 16u) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const double half = 0.5 * (double)from_lane(d[e], from + r);
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        total[v] = __builtin_fma(half, (double)from_lane(d[e], from + 4u * q + (uint32_t)v), total[v]);
+    auto adjust = [&](const float (&d)[16], float largest, float smallest) -> bool {
+        const uint32_t l = lane_here(), r = l % 16u;
+        bool digits = true;
+        if (__builtin_amdgcn_ballot_w64(!(largest <= limit))) {
+            float m = __builtin_elementwise_maximum(largest, from_lane(largest, l ^ 16u));
+            m = __builtin_elementwise_maximum(m, from_lane(m, l ^ 32u));
+            const bool fits = m <= limit;
+            digits = !__builtin_amdgcn_ballot_w64(!fits && (!(m <= kFltMax) || (m > 0.0f && m < 0x1p-98f)));
+            if (digits && __builtin_amdgcn_ballot_w64(!fits)) {
+                if (__builtin_amdgcn_ballot_w64(scale != 0.0f)) flush();
+                if (!fits) {                         // 2^20 <= m * scale < 2^21
+                    const uint32_t e = f2u(m) >> 23;
+                    scale = m > 0.0f ? u2f((127u + 127u + 20u - e) << 23) : 0.0f;
+                    limit = m > 0.0f ? kRoom * u2f((e - 20u) << 23) : 0.0f;
+                    limit = limit <= kFltMax ? limit : kFltMax;
+                    least = m > 0.0f ? u2f((e - 19u) << 23) : 0.0f;
                 }
             }
-            return true;
         }
-        flush();
-        if (!fits) {                                 // 2^20 <= m * scale < 2^21
-            const uint32_t e = f2u(m) >> 23;
-            scale = m > 0.0f ? u2f((127u + 127u + 20u - e) << 23) : 0.0f;
-            limit = m > 0.0f ? kRoom * u2f((e - 20u) << 23) : 0.0f;
-            limit = limit <= kFltMax ? limit : kFltMax;
+        if (digits && __builtin_amdgcn_ballot_w64(!(smallest >= least))) {
+            const int last = (int)(f2u(scale) >> 23) - 127 + 22;     // of the last digit, 2^-last
+            float left = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) left = __builtin_fmaxf(left, __builtin_amdgcn_fractf(__builtin_ldexpf(d[j], last)));
+            digits = !__builtin_amdgcn_ballot_w64(left != 0.0f);
         }
-        return false;
+        if (digits) return false;
+        // v_mfma_f64_16x16x4_f64: lane 16 k + i gives row (left) or column (right) i of the k-th parameter and has entries 4 v + k, i; with the
+        // rows in this order they are 4 k + v, i
+        f64x4 products = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float row = from_lane(d[e], (l & 48u) + r % 4u * 4u + r / 4u);
+            products = __builtin_amdgcn_mfma_f64_16x16x4f64(0.5 * (double)row, (double)d[e], products, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) add(v, products[v]);
+        return true;
     };
     // 64 parameters of every replica; read_next reads what the next step needs into the registers that wv and gv are in.
     auto step = [&](const u32x4 (&wv)[2], const u32x4 (&gv)[4], auto read_next) {
@@ -810,14 +837,17 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(d[j]));     // formed here, not where it is first used
-        float largest = __builtin_fabsf(d[0]);                         // NaN if any is
+        float largest = __builtin_fabsf(d[0]), smallest = largest;      // NaN if any is
 #pragma unroll
-        for (int j = 1; j < 15; j += 2)
+        for (int j = 1; j < 15; j += 2) {
             largest = __builtin_elementwise_maximum(__builtin_elementwise_maximum(largest, __builtin_fabsf(d[j])), __builtin_fabsf(d[j + 1]));
+            smallest = __builtin_elementwise_minimum(__builtin_elementwise_minimum(smallest, __builtin_fabsf(d[j])), __builtin_fabsf(d[j + 1]));
+        }
         largest = __builtin_elementwise_maximum(largest, __builtin_fabsf(d[15]));
+        smallest = __builtin_elementwise_minimum(smallest, __builtin_fabsf(d[15]));
+        const bool added = __builtin_amdgcn_ballot_w64(!(largest <= limit) || !(smallest >= least)) && adjust(d, largest, smallest);
         read_next();
-        if (__builtin_amdgcn_ballot_w64(!(largest <= limit)))
-            if (adjust(d, largest)) return;
+        if (added) return;
         i32x4 digit[kDigits];
         auto planes = [&](int k, const uint32_t (&h)[4], int top, int middle, int low) {
             const uint32_t x = __builtin_amdgcn_perm(h[1], h[0], 0x05010400u), y = __builtin_amdgcn_perm(h[3], h[2], 0x05010400u);
@@ -841,6 +871,15 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (const Product& x : kProducts)
             sum[x.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(digit[x.a], digit[x.b], sum[x.acc], 0, 0, 0);
+        if (__builtin_amdgcn_ballot_w64((digit[kLo0][0] | digit[kLo0][1] | digit[kLo0][2] | digit[kLo0][3]) != 0)) {
+#pragma unroll
+            for (const Product& x : kLastDigit)
+                sum[x.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(digit[x.a], digit[x.b], sum[x.acc], 0, 0, 0);
+            auto product = [&](int a) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(digit[a], digit[kLo0], i32x4{0, 0, 0, 0}, 0, 0, 0); };
+            const i32x4 x = product(kHi0) * 64 + product(kLo2), y = product(kLo1) * 512 + product(kLo0);     // of 2^-28 and 2^-45, each below 2^30
+#pragma unroll
+            for (int v = 0; v < 4; ++v) low[v] = __builtin_fma(__builtin_fma((double)x[v], 0x1p-28, (double)y[v] * 0x1p-45), unscale(v), low[v]);
+        }
     };
 
     const uint32_t b = blockIdx.x;
@@ -858,9 +897,9 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
         const uint64_t offset = (uint64_t)(more & (kFast - 1u)) << 32 | a.offset[s];
         const bool fast = more & kFast;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) totals[wave][4u * lane_here() + i] = 0.0;
+        for (int i = 0; i < 4; ++i) totals[wave][4u * lane_here() + i] = low[i] = 0.0;
         clear();
-        scale = 0.0f;
+        scale = least = 0.0f;
         limit = -1.0f;
 
         HalfTile<H> raw;
@@ -886,14 +925,14 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
             *reinterpret_cast<u32x4*>(stage + R * kRowWords + lane * 8u + q * 4u + wave * 4u) = raw.g;
             if (k + 1u < last) load(k + 1u);
             lds_barrier();
-            if (tiles == kFlushTiles) { flush(); tiles = 0; }
-            ++tiles;
             read(wave);
 #pragma unroll 1
             for (uint32_t j = wave; j < (uint32_t)kDigitSteps; j += 2u)
                 step(wv, gv, [&]() { read((j + 2u) % kDigitSteps); });     // (behind the last: read and not used)
+            if (++tiles == kFlushTiles || k + 1u == last) { flush(); tiles = 0; }
         }
-        flush();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) totals[wave][4u * lane_here() + i] += low[i];
         __syncthreads();
         double* out = a.partial + (uint64_t)(uint32_t)((int32_t)b + a.slot[s]) * M * M;
         for (uint32_t i = wave * kWave + lane_here(); i < 256u; i += 2 * kWave) {

@@ -1,12 +1,13 @@
-"""15 and 16 replicas and 2^21 parameters in a launch or more, 13 and 14 and 7 * 2^19: the differences as digits of a multiple of 2^-22 of a
-scale of their replica's, with products that the matrix cores add up in whole numbers.  Sizes at the edges of the tiles (512 parameters, the
-wavefronts 64 at a time) and of the range, arrays at any element, and differences that the scale does not suit: growing by 2^60 along
-the array, none at all, below 2^-98, near the largest fp32 number, not finite.
+"""15 and 16 replicas and 2^21 parameters in a launch or more, 13 and 14 and 7 * 2^19: the differences as six digits of a multiple of 2^-22 of a
+scale of their replica's, with products that the matrix cores add up in whole numbers, and 64 parameters at a time in fp64 where a difference
+is no such multiple.  Sizes at the edges of the tiles (512 parameters, the wavefronts 64 at a time) and of the range, arrays at any element,
+and differences that the scale does not suit: growing by 2^60 along the array, none at all, below 2^-98, near the largest fp32 number, all
+alike with a few that are 2^10 to 2^28 times as large, not finite.
 
-Reference: fp64 products of the same fp32 differences.  A difference is off by at most 2^-44 of the largest of its replica's and
-the entry of a and b by 2^-44 of the sum of |a| times the largest of b, at most 2^-44 sqrt(n) of the product of the norms: 1.2e-10 at 7 * 2^19, if
-every error went the same way; rounded to nearest they add up like sqrt(n) of them, which leaves 2^-44.  The reference adds up
-2048 products at a time and then those sums: at most (2048 + 1800) 2^-53 = 4.3e-13."""
+Reference: exact sums (fp64 products of fp32 differences are exact; folded in halves with the error of every addition kept).  What may
+differ are roundings of fp64 additions: at most 64 in a row where 64 parameters are added up in fp64, 13 for the sums of digits, 4 for the
+two wavefronts and the transpose, and 25 for the partial matrices (8 and 3 in each of two levels, 3 more for a fragment): fewer than 128, each 2^-53
+of at most sqrt(G[a][a] G[b][b]), and so 2^-46 of that."""
 import os
 import re
 import shutil
@@ -57,19 +58,39 @@ def _inputs(kind, n, M, shift):
     return g[shift:], [x[shift:] for x in w]
 
 
-def _check(got, want, M):
+def _check(got, exact, M):
     G, cos, mean = (x.cpu().numpy() for x in sdl.split_cosine_result(got, M))
+    want, rest = exact
     norm = np.sqrt(np.diag(want))
     outer = np.outer(norm, norm)
-    assert (np.abs(G - want) <= 1e-12 * outer).all(), np.abs(G - want).max() / outer.max()
+    assert (np.abs((G - want) - rest) <= 2.0 ** -46 * outer).all(), np.nanmax(np.abs((G - want) - rest) / outer)
     want_cos = np.divide(want, outer, out=np.zeros_like(want), where=outer > 0)
-    np.testing.assert_allclose(cos, want_cos, atol=1e-12, rtol=0)
-    np.testing.assert_allclose(mean, want_cos[np.triu_indices(M, 1)].mean(), atol=1e-12, rtol=0)
+    np.testing.assert_allclose(cos, want_cos, atol=2.0 ** -45, rtol=0)
+    np.testing.assert_allclose(mean, want_cos[np.triu_indices(M, 1)].mean(), atol=2.0 ** -45, rtol=0)
 
 
-def _reference(g, w):
-    d = torch.stack([torch.nn.functional.pad((g - x.float()).double(), (0, -len(g) % 2048)) for x in w])
-    return sum(c @ c.T for c in d.split(2048, dim=1)).cpu().numpy()
+def _two_sum(a, b):
+    s = a + b
+    v = s - a
+    return s, (a - (s - v)) + (b - v)
+
+
+def _exact(g, w):
+    """The Gram matrix as a pair of fp64 matrices."""
+    M = len(w)
+    d = torch.stack([(g - x.float()).double() for x in w])
+    want, rest = np.zeros((M, M)), np.zeros((M, M))
+    for a in range(M):
+        hi = d[a] * d[a:]
+        lo = torch.zeros_like(hi)
+        while hi.shape[1] > 1:
+            n, h = hi.shape[1], (hi.shape[1] + 1) // 2
+            pad = torch.nn.functional.pad
+            hi, err = _two_sum(hi[:, :h], pad(hi[:, h:], (0, 2 * h - n)))
+            lo = lo[:, :h] + pad(lo[:, h:], (0, 2 * h - n)) + err
+        want[a, a:] = want[a:, a] = hi[:, 0].cpu().numpy()
+        rest[a, a:] = rest[a:, a] = lo[:, 0].cpu().numpy()
+    return want, rest
 
 
 @pytest.mark.gpu
@@ -81,7 +102,23 @@ def test_sums_of_digits(kind, extra, M, shift):
     g, w = _inputs(kind, n, M, shift)
     result, workspace = sdl.alloc_cosine(M)
     sdl.sdl_outer_grad_cosine(g, w, n, result[0], workspace)
-    _check(result[0], _reference(g, w), M)
+    _check(result[0], _exact(g, w), M)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", [13, 16])
+@pytest.mark.parametrize("every", [704, 17_226])
+@pytest.mark.parametrize("power", [10, 12, 14, 16, 18, 20, 24, 28])
+def test_equal_differences_and_a_few_large_ones(power, every, M):
+    """What one of them loses all of them lose, with one sign."""
+    n = LINE[M] + 700
+    g = torch.full((n,), 0.1 * (1 + 2.0 ** -9 + 2.0 ** -17 + 2.0 ** -23), device="cuda") * 2.0 ** -power
+    w = [torch.zeros(n, dtype=torch.bfloat16, device="cuda") for _ in range(M)]
+    for m in range(0, M, 2):
+        w[m][37 * m::every] = -0.1
+    result, workspace = sdl.alloc_cosine(M)
+    sdl.sdl_outer_grad_cosine(g, w, n, result[0], workspace)
+    _check(result[0], _exact(g, w), M)
 
 
 @pytest.mark.gpu
@@ -90,7 +127,7 @@ def test_sums_of_digits(kind, extra, M, shift):
 def test_non_finite_replica_stays_in_its_row(M, bad):
     n = LINE[M] + 17
     g, w = _inputs("normal", n, M, 0)
-    clean = _reference(g, w)
+    clean, rest = _exact(g, w)
     for m, at in ((0, 0), (M // 2, 70_003), (M - 1, n - 1)):
         v = list(w)
         v[m] = w[m].clone()
@@ -99,7 +136,7 @@ def test_non_finite_replica_stays_in_its_row(M, bad):
         sdl.sdl_outer_grad_cosine(g, v, n, result[0], workspace)
         G = sdl.split_cosine_result(result[0], M)[0].cpu().numpy()
         keep = np.arange(M) != m
-        np.testing.assert_allclose(G[np.ix_(keep, keep)], clean[np.ix_(keep, keep)], rtol=0, atol=1e-12 * clean.max())
+        assert (np.abs((G - clean) - rest)[np.ix_(keep, keep)] <= 2.0 ** -46 * clean.max()).all()
         want = (g - v[m].float()).double() @ torch.stack([(g - x.float()).double() for x in v]).T
         np.testing.assert_array_equal(np.sign(G[m]), np.sign(want.cpu().numpy()))     # inf, -inf or NaN alike
         assert not np.isfinite(G[m]).any()
@@ -118,7 +155,7 @@ def test_spans_that_share_workgroups(M, n_spans):
     results, workspace = sdl.alloc_cosine(M, len(spans))
     fragment = torch.empty(sdl.cosine_result_doubles(M), dtype=torch.float64, device="cuda")
     sdl.sdl_outer_grad_cosine_plan(plan, 0, g, w, results, fragment, workspace)
-    parts = [_reference(g[o:o + n], [x[o:o + n] for x in w]) for o, n, _ in spans]
-    for k, want in enumerate(parts):
-        _check(results[k], want, M)
-    _check(fragment, sum(parts), M)
+    parts = [_exact(g[o:o + n], [x[o:o + n] for x in w]) for o, n, _ in spans]
+    for k, exact in enumerate(parts):
+        _check(results[k], exact, M)
+    _check(fragment, (sum(want for want, _ in parts), sum(rest for _, rest in parts)), M)
