@@ -647,7 +647,8 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 //
 // Nothing is rounded ahead of a product.  A difference has 24 bits, so what is not below 2 / scale (`least`) is a multiple of 2^-22 / scale; if a step has
 // smaller ones they are looked at, and if one is no such multiple, the step's 64 parameters are added up in fp64 by v_mfma_f64_16x16x4_f64.  So are
-// infinities, NaN, and differences below 2^-98 where there are no larger ones (their scale would not be a normal number).
+// infinities, and differences below 2^-98 where there are no larger ones (their scale would not be a normal number).
+// NaN, as in a replica that has diverged, would send every step there: its entries are NaN whatever follows, so the step goes on with 0 for that replica.
 //
 // The scale of a replica is that of the wavefront's parameters so far: where a difference exceeds what it has room for, the
 // sums so far are put into fp64 and a new one is taken, with room for twice as much and more.
@@ -663,7 +664,7 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 // cycles for 64 parameters, 26 % beside them.  52.9 M parameters and 16 replicas: 300 us with neither loads nor matrix instructions, 329 without the
 // loads, 357 without the matrix instructions, 322 the loads and the staging alone, 385 in all (HBM 268).  Whole call, FMAs and here, M = 13 / 14 / 15 / 16: 52.9 M
 // parameters 419 / 425 / 503 / 509 and 367 / 373 / 382 / 387; at odd elements 443 / 447 / 525 / 533 and 397 / 403 / 423 / 428.  M = 16 with outliers 492 and
-// 417, t3 495 and 421, 24 bits 499 and 387, a tenth of the differences 0 496 and 428; steps in fp64 all along (sizes that vary by 2^40) 503 and 777.
+// 417, t3 495 and 421, 24 bits 499 and 387, a tenth of the differences 0 496 and 428, one replica NaN 515 and 453; steps in fp64 all along (sizes that vary by 2^40) 503 and 777.
 // (The time hardly depends on the replicas, as a matrix instruction has 16 rows whatever they are: at 12 replicas 306 and 354.)  Tried, each beside 390
 // to 409 with 18 products at every step: a tile of 512 for each wavefront, 252 registers, 409; 256 parameters, two tiles in LDS 401; the digits' products one
 // step behind, between the vector instructions of the next, which takes 220 registers 427; workgroups that take turns at the tiles 397; subtraction by
@@ -788,12 +789,21 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
         clear();
     };
     // A step that the limits do not cover: true if its products have been added up here.
-    auto adjust = [&](const float (&d)[16], float largest, float smallest) -> bool {
+    auto adjust = [&](float (&d)[16], float largest, float smallest) -> bool {
         const uint32_t l = lane_here(), r = l % 16u;
         bool digits = true;
         if (__builtin_amdgcn_ballot_w64(!(largest <= limit))) {
             float m = __builtin_elementwise_maximum(largest, from_lane(largest, l ^ 16u));
             m = __builtin_elementwise_maximum(m, from_lane(m, l ^ 32u));
+            if (__builtin_amdgcn_ballot_w64(m != m)) {       // NaN in the replica's entries, whatever else it holds: the others go on with digits
+                const bool nan = m != m;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) low[v] = nan ? (double)m : low[v];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) d[j] = nan ? 0.0f : d[j];
+                m = nan ? 0.0f : m;
+                smallest = nan ? least : smallest;
+            }
             const bool fits = m <= limit;
             digits = !__builtin_amdgcn_ballot_w64(!fits && (!(m <= kFltMax) || (m > 0.0f && m < 0x1p-98f)));
             if (digits && __builtin_amdgcn_ballot_w64(!fits)) {
