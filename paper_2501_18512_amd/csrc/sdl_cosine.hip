@@ -48,23 +48,23 @@ constexpr int kMaxPieces = kMaxSets + kWindows;
 // 209 / 371 and 66 / 90 / 153 / 319.
 constexpr uint32_t kFewSets = 48;
 constexpr uint64_t kManyParams = 1ull << 23;
-// Up to 8 replicas, the wavefronts of a workgroup and the workgroups of a launch, which are shared out among the sets.
-// Four wavefronts, whose sums are added in LDS, leave a quarter of the matrices to write and to add up.  The workgroups of all sets together are
-// no more than fit the chip (a launch's shares are rounded up, so as many fewer are dealt out as there are sets): with 8 per compute unit and some
-// more, as it was with one wavefront each, the last ones ran by themselves.  Whole call with 8192 workgroups of one wavefront and now, M = 2 / 4 / 8:
-// 1 M parameters 11.1 / 12.9 / 17.5 and 8.4 / 10.6 / 16.4 us (some of it by the one launch that adds up to four chunks, see finalize_sets), 4 M
-// 14.3 / 18.1 / 31.2 and 12.8 / 17.2 / 31.9, 32 M 50 / 69 / 118 and 48 / 67 / 115, 53 M in 39 sets 75.3 / 108 / 182 and 73.9 / 107 / 177, 302 M in
-// 48 sets 386 / 563 / 1020 and 379 / 554 / 962.  Beyond kFewFours 10 per compute unit: 80 M 110.5 / 154 / 246 with 2048, 106.3 / 154 / 248 with 2560, and
-// a launch of ragged sets with 80 M 107.0 / 155 / 261 and 103.3 / 154.5 / 258.
-// One wavefront where the accesses of the four together are the slower: 8 replicas in more than kFewSets sets (194 sets, 2.5 M parameters in all:
-// 25.6 us, with four 27.3), and from 5 replicas sets that are not aligned to 16 bytes, beyond kRaggedOne / (M - 4) parameters (M = 5 / 6 / 8: 1 M
-// 14.6 / 16.5 / 18.3 us with one, 12.3 / 14.2 / 17.7 with four; 3 M 19.6 / 22.5 / 28.2 and 19.1 / 23.3 / 28.9; 6 M 28.1 / 31.7 / 40.2 and 28.3 / 33.0 / 42.2).
+// Up to 8 replicas, the wavefronts of a workgroup and the workgroups of a launch, which are shared out among the sets. Four wavefronts, whose sums
+// are added in LDS, leave a quarter of the matrices to write and to add up.  A launch's shares are rounded up, so as many fewer workgroups are dealt
+// out as there are sets.  Whole call with 8192 workgroups of one wavefront and now, M = 1 / 2 / 4 / 8: 1 M parameters 8.6 / 9.7 / 12.5 / 18.0 and 7.7
+// / 8.3 / 10.7 / 16.5 us, 4 M 13.6 / 15.3 / 19.9 / 32.8 and 11.4 / 13.1 / 17.8 / 32.6, 32 M 39.3 / 49.5 / 68.4 / 113.4 and 36.3 / 46.9 / 64.9 /
+// 108.4, 53 M in 39 sets 57.6 / 74.3 / 103.9 / 172.1 and 55.1 / 72.5 / 100.5 / 168.2, 302 M in 48 sets 287.5 / 379.3 / 563 / 952 and 286.1 / 372.9 /
+// 557 / 945; with arrays at odd elements 32 M 42.2 / 53.8 / 78.7 / 131.6 and 39.5 / 50.7 / 76.2 / 129.8, and up to 3 % slower at 2 and 4 M with 7 and
+// 8 replicas (21.4 / 24.3 and 22.0 / 24.7; 28.7 / 34.0 and 28.7 / 34.7). 2048 of them are 8 for a compute unit, of which 8 / 7 / 5 / 5 / 4 / 3 / 3 /
+// 2 fit it at once by their registers.  Beyond kFewFours 10: M = 1 / 2 / 4 / 8 80 M 79.3 / 106.7 / 146.4 / 245.3 with 2048, 80.3 / 101.8 / 146.2 /
+// 247.3 with 2560, 302 M in 48 sets 289.6 / 379.8 / 563.6 / 954.5 and 285.9 / 374.8 / 556.9 / 951.0, 82 M in 39 sets 82.3 / 110.6 / 156.5 / 262.7 and
+// 83.9 / 108.3 / 158.9 / 264.8; at 8 M 14.9 / 17.6 / 24.3 / 40.6 and 16.4 / 19.1 / 25.3 / 43.3.
+// One wavefront for 8 replicas in more than kFewSets sets (194 sets, 2.5 M parameters in all: 26.8 us, with four 28.8; 195 sets, 35 M 168.9 and
+// 170.7). The addresses of the arrays have no say: they would change the order of the sums.
 constexpr uint32_t kGramWaves = 4;
 constexpr uint32_t kFours = 2048;               // workgroups of four wavefronts: 8 per compute unit
 constexpr uint32_t kManyFours = 2560;           // beyond kFewFours parameters
 constexpr uint64_t kFewFours = 64u << 20;
 constexpr uint32_t kGroups = 8192;              // workgroups of one wavefront
-constexpr uint64_t kRaggedOne = 4u << 20;
 constexpr uint32_t kMaxGroups = 8192;           // what the workspace is sized for
 
 
@@ -94,8 +94,8 @@ constexpr uint32_t kFast = 0x80;              // every array is 16-byte aligned 
 constexpr uint64_t kMaxOffset = 1ull << 39;
 
 // The lane's number, counted anew: what is computed from it is computed here, not ahead of a loop that needs the registers.  (The offsets
-// of a ragged tile's accesses, computed ahead, took 20 to 30 of them: sdl_gram_kernel at 4 / 7 / 8 replicas 117 / 193 / 228 registers, 96 / 168 /
-// 199 so; 302 M parameters, M = 7 875 us and 861, the others the same.)
+// of a ragged tile's accesses, computed ahead, took 20 to 30 of them: sdl_gram_kernel at 4 / 7 / 8 replicas 117 / 193 / 228 registers, 90 / 162 /
+// 193 so; 302 M parameters, M = 7 875 us and 861, the others the same.)
 __device__ __forceinline__ uint32_t lane_here()
 {
     uint32_t all = ~0u;
@@ -1246,12 +1246,8 @@ int launch_sums(const float* g, const void* const* w, uint32_t M, Set* sets, uin
 {
     if (M > 8u) return launch_pair(g, w, M, sets, n_sets, partial, n_mats, st);
     uint64_t params = 0;
-    bool fast = true;
-    for (uint32_t s = 0; s < n_sets; ++s) {
-        params += sets[s].numel;
-        fast = fast && all_aligned16(g, w, M, sets[s].offset);
-    }
-    const bool one = M > 4u && ((!fast && params * (M - 4u) > kRaggedOne) || (M == 8u && n_sets > kFewSets));
+    for (uint32_t s = 0; s < n_sets; ++s) params += sets[s].numel;
+    const bool one = M == 8u && n_sets > kFewSets;
     const uint32_t groups = one ? kGroups : params > kFewFours ? kManyFours : kFours;
     const uint32_t waves = one ? 1u : kGramWaves;
     *n_mats = share_groups(sets, n_sets, groups - n_sets, waves);

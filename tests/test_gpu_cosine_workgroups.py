@@ -1,6 +1,7 @@
 """Up to 8 replicas: a launch is at most 2048 workgroups of four wavefronts, 2560 beyond 64 * 2^20 parameters, or 8192 of one: for 8 replicas in more
-than 48 sets, and for sets that are not 16-byte aligned, M replicas and more than 4 * 2^20 / (M - 4) parameters.  Both sides of these edges, and
-numbers of tiles that leave wavefronts of a workgroup without one."""
+than 48 sets.  Both sides of these edges, numbers of tiles that leave wavefronts of a workgroup without one, and sets at odd elements.
+
+The order of the sums is fixed by the sizes and, with digits, the values: the same numbers at other addresses give the same bits."""
 import pytest
 import torch
 
@@ -41,3 +42,21 @@ def test_both_sides_of_an_edge(M, sizes):
         norm = torch.diagonal(b).sqrt()
         # the same exact products in another order: 2^19 of them one after the other, more than either side adds, err by 2^-34 at most
         assert ((a - b).abs() <= 2.0 ** -34 * norm[:, None] * norm[None, :]).all()
+
+
+@pytest.mark.parametrize("M", [1, 3, 5, 6, 7, 8, 9, 12, 13, 16])
+@pytest.mark.parametrize("sizes", [[3_000_017], [9_000_001], [1 + 20 * i for i in range(60)], [700, 4_000_000, 5, 513]], ids=lambda s: f"{len(s)}x{s[0]}")
+def test_same_bits_at_any_address(M, sizes):
+    gen = torch.Generator("cuda").manual_seed(M)
+    n = sum(sizes)
+    g = torch.randn(n, device="cuda", generator=gen)
+    w = [(g - torch.randn(n, device="cuda", generator=gen)).to(torch.bfloat16) for _ in range(M)]
+    plan = sdl.sdl_fragment_plan(sizes, [0] * len(sizes), 1, 1, sdl.PATTERN_STRIDED, 10, 0)
+    out = []
+    for shift in (0, 1, 3):
+        at = lambda x, k: torch.cat([x[:k], x])[k:]                    # the same numbers, k elements further on
+        results, workspace = sdl.alloc_cosine(M, len(sizes))
+        fragment = torch.empty(sdl.cosine_result_doubles(M), dtype=torch.float64, device="cuda")
+        sdl.sdl_outer_grad_cosine_plan(plan, 0, at(g, shift), [at(x, shift + m % 2 * (shift > 0)) for m, x in enumerate(w)], results, fragment, workspace)
+        out.append(torch.cat([results.flatten(), fragment]).view(torch.int64))
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
