@@ -62,25 +62,28 @@ static int address(PyObject* t, void** out)
     return PyErr_Occurred() ? -1 : 0;
 }
 
-/* The addresses of several; null behind them.  More than the library takes are looked at, for the library to refuse their number. */
+/* The addresses of several; null behind them.  More than the library takes are looked at, for the library to refuse their number.
+ * What is walked is a tuple of them: looking at a tensor may run Python code, in which a caller's list may change. */
 typedef struct {
     void* at[SDL_MAX_WORKERS];
     void** p;
+    Py_ssize_t n;
 } Addresses;
 
 static int addresses(PyObject* ts, Addresses* a)
 {
     PyObject* items;
-    Py_ssize_t i, n;
+    Py_ssize_t i;
     void* unused;
     a->p = NULL;
+    a->n = 0;
     memset(a->at, 0, sizeof(a->at));
     if (ts == Py_None) return 0;
-    items = PySequence_Fast(ts, "sdl calls take a sequence of tensors");
+    items = PySequence_Tuple(ts);
     if (!items) return -1;
-    n = PySequence_Fast_GET_SIZE(items);
-    for (i = 0; i < n; ++i)
-        if (address(PySequence_Fast_GET_ITEM(items, i), i < SDL_MAX_WORKERS ? &a->at[i] : &unused) < 0) {
+    a->n = PyTuple_GET_SIZE(items);
+    for (i = 0; i < a->n; ++i)
+        if (address(PyTuple_GET_ITEM(items, i), i < SDL_MAX_WORKERS ? &a->at[i] : &unused) < 0) {
             Py_DECREF(items);
             return -1;
         }
@@ -89,11 +92,11 @@ static int addresses(PyObject* ts, Addresses* a)
     return 0;
 }
 
-static int count(PyObject* ts, uint32_t* out)
+/* How many they were; what has no length (None, a generator) is refused. */
+static int count(PyObject* ts, const Addresses* a, uint32_t* out)
 {
-    const Py_ssize_t n = PyObject_Length(ts);
-    if (n < 0) return -1;
-    *out = (uint32_t)n;
+    if (PyObject_Length(ts) < 0) return -1;
+    *out = (uint32_t)a->n;
     return 0;
 }
 
@@ -183,7 +186,7 @@ FUNCTION(sdl_quantize_outer_grad)        /* g, w_send, n, fmt, codes, scales, st
     Addresses w, c, s;
     uint32_t M;
     uint64_t numel, fmt;
-    if (!argc_is(n, 7) || address(a[0], &g) || addresses(a[1], &w) || addresses(a[4], &c) || addresses(a[5], &s) || count(a[1], &M)
+    if (!argc_is(n, 7) || address(a[0], &g) || addresses(a[1], &w) || addresses(a[4], &c) || addresses(a[5], &s) || count(a[1], &w, &M)
         || whole(a[2], &numel) || whole(a[3], &fmt) || stream_of(a[6], &st)) return NULL;
     CALL(p_sdl_quantize_outer_grad(g, W(w), M, numel, (sdl_format_t)fmt, V(c), V(s), st));
 }
@@ -195,7 +198,7 @@ FUNCTION(sdl_dequant_reduce_nesterov)    /* g, mom, codes, scales, n, fmt, lr, m
     uint32_t M;
     uint64_t numel, fmt;
     float lr, mu;
-    if (!argc_is(n, 9) || address(a[0], &g) || address(a[1], &mom) || addresses(a[2], &c) || addresses(a[3], &s) || count(a[2], &M)
+    if (!argc_is(n, 9) || address(a[0], &g) || address(a[1], &mom) || addresses(a[2], &c) || addresses(a[3], &s) || count(a[2], &c, &M)
         || whole(a[4], &numel) || whole(a[5], &fmt) || real(a[6], &lr) || real(a[7], &mu) || stream_of(a[8], &st)) return NULL;
     CALL(p_sdl_dequant_reduce_nesterov(g, mom, W(c), W(s), M, numel, (sdl_format_t)fmt, lr, mu, st));
 }
@@ -207,7 +210,7 @@ FUNCTION(sdl_merge_overlap)              /* g_new, w_now, n, alpha, stream */
     uint32_t M;
     uint64_t numel;
     float alpha;
-    if (!argc_is(n, 5) || address(a[0], &g) || addresses(a[1], &w) || count(a[1], &M) || whole(a[2], &numel) || real(a[3], &alpha)
+    if (!argc_is(n, 5) || address(a[0], &g) || addresses(a[1], &w) || count(a[1], &w, &M) || whole(a[2], &numel) || real(a[3], &alpha)
         || stream_of(a[4], &st)) return NULL;
     CALL(p_sdl_merge_overlap(g, V(w), M, numel, alpha, st));
 }
@@ -220,7 +223,7 @@ FUNCTION(sdl_receive_outer_step)         /* g, mom, codes, scales, w_now, n, fmt
     uint64_t numel, fmt;
     float lr, mu, alpha;
     if (!argc_is(n, 11) || address(a[0], &g) || address(a[1], &mom) || addresses(a[2], &c) || addresses(a[3], &s) || addresses(a[4], &w)
-        || count(a[2], &M_c) || count(a[4], &M)) return NULL;
+        || count(a[2], &c, &M_c) || count(a[4], &w, &M)) return NULL;
     if (M != M_c) return PyLong_FromLong(SDL_ERR_INVALID_ARG);
     if (whole(a[5], &numel) || whole(a[6], &fmt) || real(a[7], &lr) || real(a[8], &mu) || real(a[9], &alpha) || stream_of(a[10], &st)) return NULL;
     CALL(p_sdl_receive_outer_step(g, mom, W(c), W(s), V(w), M, numel, (sdl_format_t)fmt, lr, mu, alpha, st));
@@ -234,7 +237,7 @@ FUNCTION(sdl_fragment_outer_step)        /* g, mom, w_send, w_now, n, fmt, lr, m
     uint64_t numel, fmt;
     float lr, mu, alpha;
     if (!argc_is(n, 12) || address(a[0], &g) || address(a[1], &mom) || addresses(a[2], &ws) || addresses(a[3], &wn) || addresses(a[9], &c)
-        || addresses(a[10], &s) || count(a[2], &M) || count(a[3], &M_now)) return NULL;
+        || addresses(a[10], &s) || count(a[2], &ws, &M) || count(a[3], &wn, &M_now)) return NULL;
     if (M != M_now) return PyLong_FromLong(SDL_ERR_INVALID_ARG);
     if (whole(a[4], &numel) || whole(a[5], &fmt) || real(a[6], &lr) || real(a[7], &mu) || real(a[8], &alpha) || stream_of(a[11], &st)) return NULL;
     CALL(p_sdl_fragment_outer_step(g, mom, W(ws), V(wn), M, numel, (sdl_format_t)fmt, lr, mu, alpha, V(c), V(s), st));
@@ -247,7 +250,7 @@ FUNCTION(sdl_quantize_outer_grad_plan)   /* plan, p, g, w_send, fmt, codes, scal
     uint32_t M;
     uint64_t p, fmt;
     if (!argc_is(n, 8) || address(a[2], &g) || addresses(a[3], &w) || addresses(a[5], &c) || addresses(a[6], &s) || handle(a[0], &plan)
-        || whole(a[1], &p) || count(a[3], &M) || whole(a[4], &fmt) || stream_of(a[7], &st)) return NULL;
+        || whole(a[1], &p) || count(a[3], &w, &M) || whole(a[4], &fmt) || stream_of(a[7], &st)) return NULL;
     CALL(p_sdl_quantize_outer_grad_plan(plan, (uint32_t)p, g, W(w), M, (sdl_format_t)fmt, V(c), V(s), st));
 }
 
@@ -259,7 +262,7 @@ FUNCTION(sdl_dequant_reduce_nesterov_plan)   /* plan, p, g, mom, codes, scales, 
     uint64_t p, fmt;
     float lr, mu;
     if (!argc_is(n, 10) || address(a[2], &g) || address(a[3], &mom) || addresses(a[4], &c) || addresses(a[5], &s) || handle(a[0], &plan)
-        || whole(a[1], &p) || count(a[4], &M) || whole(a[6], &fmt) || real(a[7], &lr) || real(a[8], &mu) || stream_of(a[9], &st)) return NULL;
+        || whole(a[1], &p) || count(a[4], &c, &M) || whole(a[6], &fmt) || real(a[7], &lr) || real(a[8], &mu) || stream_of(a[9], &st)) return NULL;
     CALL(p_sdl_dequant_reduce_nesterov_plan(plan, (uint32_t)p, g, mom, W(c), W(s), M, (sdl_format_t)fmt, lr, mu, st));
 }
 
@@ -270,7 +273,7 @@ FUNCTION(sdl_merge_overlap_plan)         /* plan, p, g_new, w_now, alpha, stream
     uint32_t M;
     uint64_t p;
     float alpha;
-    if (!argc_is(n, 6) || address(a[2], &g) || addresses(a[3], &w) || handle(a[0], &plan) || whole(a[1], &p) || count(a[3], &M)
+    if (!argc_is(n, 6) || address(a[2], &g) || addresses(a[3], &w) || handle(a[0], &plan) || whole(a[1], &p) || count(a[3], &w, &M)
         || real(a[4], &alpha) || stream_of(a[5], &st)) return NULL;
     CALL(p_sdl_merge_overlap_plan(plan, (uint32_t)p, g, V(w), M, alpha, st));
 }
@@ -283,7 +286,7 @@ FUNCTION(sdl_receive_outer_step_plan)    /* plan, p, g, mom, codes, scales, w_no
     uint64_t p, fmt;
     float lr, mu, alpha;
     if (!argc_is(n, 12) || address(a[2], &g) || address(a[3], &mom) || addresses(a[4], &c) || addresses(a[5], &s) || addresses(a[6], &w)
-        || handle(a[0], &plan) || whole(a[1], &p) || count(a[6], &M) || whole(a[7], &fmt) || real(a[8], &lr) || real(a[9], &mu) || real(a[10], &alpha)
+        || handle(a[0], &plan) || whole(a[1], &p) || count(a[6], &w, &M) || whole(a[7], &fmt) || real(a[8], &lr) || real(a[9], &mu) || real(a[10], &alpha)
         || stream_of(a[11], &st)) return NULL;
     CALL(p_sdl_receive_outer_step_plan(plan, (uint32_t)p, g, mom, W(c), W(s), V(w), M, (sdl_format_t)fmt, lr, mu, alpha, st));
 }
@@ -303,7 +306,7 @@ static int step_args(PyObject* const* a, PyObject* stream, PyObject* codes, PyOb
     uint32_t M_now;
     uint64_t p, fmt;
     if (address(a[2], &x->g) || address(a[3], &x->mom) || addresses(a[4], &x->ws) || addresses(a[5], &x->wn)
-        || (codes && (addresses(codes, c) || addresses(scales, s))) || count(a[4], &x->M) || count(a[5], &M_now)) return -1;
+        || (codes && (addresses(codes, c) || addresses(scales, s))) || count(a[4], &x->ws, &x->M) || count(a[5], &x->wn, &M_now)) return -1;
     if (x->M != M_now) return 1;
     if (handle(a[0], &x->plan) || whole(a[1], &p) || whole(a[6], &fmt) || real(a[7], &x->lr) || real(a[8], &x->mu) || real(a[9], &x->alpha)
         || stream_of(stream, &x->st)) return -1;

@@ -3,6 +3,9 @@ they are called with, every argument arrives where the C interface has it, as ct
 binding refuses is refused before the library is called."""
 import ctypes
 import inspect
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -177,3 +180,45 @@ def test_a_plan_that_has_been_given_back():
     given["plan"]._h = None
     with pytest.raises(sdl.SdlError):
         sdl.sdl_merge_overlap_plan(*given.values())
+
+
+CHANGES_ITS_LIST = r"""
+import sys
+import paper_2501_18512_amd as sdl
+
+class Tensor:
+    is_cuda = True
+    def __init__(self, at): self.at = at
+    def is_contiguous(self): return True
+    def data_ptr(self): return self.at
+
+class Clears(Tensor):
+    def is_contiguous(self):
+        tensors.clear()
+        junk.extend(Tensor(7) for _ in range(1000))      # what was freed is used again
+        return True
+
+junk = []
+tensors = [Clears(0)] + [Tensor(0) for _ in range(11)]   # null addresses: the library refuses them
+try:
+    sdl.sdl_merge_overlap(Tensor(64), tensors, 1, 0.5, stream=0)
+except sdl.SdlError as e:
+    print("refused", e.status, len(tensors))
+"""
+
+
+def test_a_list_that_changes_while_it_is_looked_at():
+    """In a process of its own: what reads the list's items after they have gone ends it."""
+    res = subprocess.run([sys.executable, "-c", CHANGES_ITS_LIST], capture_output=True, text=True, timeout=300,
+                         cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert res.returncode == 0 and res.stdout.split() == ["refused", "-1", "0"], (res.returncode, res.stdout, res.stderr[-2000:])
+
+
+def test_replicas_are_as_many_as_were_looked_at(calls):
+    class Growing(list):
+        def __iter__(self):
+            return iter(list.copy(self)[:2])
+    given = _arguments("sdl_merge_overlap", 5)
+    given["w_now"] = Growing(given["w_now"])
+    sdl.sdl_merge_overlap(*given.values())
+    assert calls["sdl_merge_overlap"][0][2] == 2
