@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import List, Optional, Sequence, Tuple
 
 import torch
@@ -169,7 +170,25 @@ def _stream(stream) -> int:
     return stream.cuda_stream
 
 
-# the device calls of every step convert their arguments in the extension module
+class _ArgumentError(ctypes.ArgumentError, TypeError):
+    """What a call made through ctypes raises for a value that is not of the argument's type."""
+
+
+def _converter(ctype):
+    """What ctypes passes on for an argument of that type."""
+    same = ctypes.CFUNCTYPE(ctype, ctype)(lambda x: x)
+
+    def convert(value):
+        try:
+            return same(value)
+        except ctypes.ArgumentError as e:
+            raise _ArgumentError(*e.args) from None
+    return convert
+
+
+# the device calls of every step convert their arguments in the extension module, which leaves what is not a plain integer or float to ctypes
+_binding.converters(ctypes.c_void_p, *map(_converter, (ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int, ctypes.c_float, ctypes.c_void_p)),
+                    lambda address: struct.unpack("P", struct.pack("P", address))[0])
 _binding.setup({name: ctypes.cast(getattr(_lib, name), ctypes.c_void_p).value for name in dir(_binding) if name.startswith("sdl_")},
                _stream, torch.cuda.is_initialized, _get_device, _raw_stream)
 

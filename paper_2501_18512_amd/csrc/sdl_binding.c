@@ -6,7 +6,8 @@
  * the arguments of the binding's function of the same name, in that order, and returns the library's status.
  *
  * The rules are the binding's: a tensor has to be on a device and contiguous; None is a null pointer and an integer an address; what
- * is neither and has no is_cuda is asked for data_ptr() alone.  Nothing is kept from one call for the next. */
+ * is neither and has no is_cuda is asked for data_ptr() alone; a number is what ctypes takes for the argument's C type.  Nothing is kept from
+ * one call for the next. */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -27,16 +28,39 @@ ENTRIES(DECLARE)
 
 static PyObject *s_is_cuda, *s_is_contiguous, *s_data_ptr, *s_h, *s_value;
 static PyObject *f_stream, *f_initialized, *f_device, *f_raw_stream;
+/* What ctypes makes of a value of a C type that is no plain integer or float: its own types, objects with _as_parameter_, ... or its
+ * refusal.  f_packed: the same of an address in an array. */
+static PyObject *t_void_p, *f_uint64, *f_uint32, *f_int, *f_float, *f_void_p, *f_packed;
+
+static int address_by(PyObject* convert, PyObject* v, void** out)
+{
+    PyObject* r = v ? PyObject_CallOneArg(convert, v) : NULL;
+    if (!r) return -1;
+    *out = r == Py_None ? NULL : (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(r);
+    Py_DECREF(r);
+    return PyErr_Occurred() ? -1 : 0;
+}
+
+/* An address given as a value: of a single array, or of one in a list. */
+static int address_of(PyObject* v, int in_list, void** out)
+{
+    if (!PyLong_Check(v)) return address_by(in_list ? f_packed : f_void_p, v, out);
+    *out = in_list ? PyLong_AsVoidPtr(v) : (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(v);
+    if (!PyErr_Occurred()) return 0;
+    PyErr_Clear();
+    return address_by(f_packed, v, out);
+}
 
 /* The address of a tensor, checked. */
-static int address(PyObject* t, void** out)
+static int address(PyObject* t, int in_list, void** out)
 {
     PyObject *v, *w;
     int on_device, contiguous;
-    if (t == Py_None || PyLong_Check(t)) {
-        *out = t == Py_None ? NULL : PyLong_AsVoidPtr(t);
-        return PyErr_Occurred() ? -1 : 0;
+    if (t == Py_None) {
+        *out = NULL;
+        return 0;
     }
+    if (PyLong_Check(t)) return address_of(t, in_list, out);
     v = PyObject_GetAttr(t, s_is_cuda);
     w = v ? PyObject_CallMethodNoArgs(t, s_is_contiguous) : NULL;
     if (w) {
@@ -57,9 +81,9 @@ static int address(PyObject* t, void** out)
     }
     v = PyObject_CallMethodNoArgs(t, s_data_ptr);
     if (!v) return -1;
-    *out = PyLong_AsVoidPtr(v);
+    on_device = address_of(v, in_list, out);
     Py_DECREF(v);
-    return PyErr_Occurred() ? -1 : 0;
+    return on_device;
 }
 
 /* The addresses of several; null behind them.  More than the library takes are looked at, for the library to refuse their number.
@@ -83,7 +107,7 @@ static int addresses(PyObject* ts, Addresses* a)
     if (!items) return -1;
     a->n = PyTuple_GET_SIZE(items);
     for (i = 0; i < a->n; ++i)
-        if (address(PyTuple_GET_ITEM(items, i), i < SDL_MAX_WORKERS ? &a->at[i] : &unused) < 0) {
+        if (address(PyTuple_GET_ITEM(items, i), 1, i < SDL_MAX_WORKERS ? &a->at[i] : &unused) < 0) {
             Py_DECREF(items);
             return -1;
         }
@@ -100,44 +124,52 @@ static int count(PyObject* ts, const Addresses* a, uint32_t* out)
     return 0;
 }
 
-static int whole(PyObject* v, uint64_t* out)
+static int whole(PyObject* v, PyObject* convert, uint64_t* out)
 {
-    if (PyFloat_Check(v)) {
-        PyErr_SetString(PyExc_TypeError, "an integer is required, not a float");
-        return -1;
-    }
-    *out = PyLong_AsUnsignedLongLongMask(v);
+    PyObject* r = PyLong_Check(v) ? NULL : PyObject_CallOneArg(convert, v);
+    if (!r && PyErr_Occurred()) return -1;
+    *out = PyLong_AsUnsignedLongLongMask(r ? r : v);
+    Py_XDECREF(r);
     return PyErr_Occurred() ? -1 : 0;
 }
 
 static int real(PyObject* v, float* out)
 {
-    *out = (float)PyFloat_AsDouble(v);
+    PyObject* r = NULL;
+    double d = PyFloat_Check(v) || PyLong_Check(v) ? PyFloat_AsDouble(v) : -1.0;
+    if (!PyFloat_Check(v) && (!PyLong_Check(v) || PyErr_Occurred())) {
+        PyErr_Clear();
+        r = PyObject_CallOneArg(f_float, v);
+        if (!r) return -1;
+        d = PyFloat_AsDouble(r);
+        Py_DECREF(r);
+    }
+    *out = (float)d;
     return PyErr_Occurred() ? -1 : 0;
 }
 
 /* The handle that an owner (a Plan) holds; NULL once it has been given back. */
 static int handle(PyObject* owner, void** out)
 {
-    PyObject* v;
+    int rc;
     PyObject* h = PyObject_GetAttr(owner, s_h);
-    if (!h) return -1;
-    if (h == Py_None) {
-        v = h;
-    } else {
-        v = PyObject_GetAttr(h, s_value);
+    if (h && (PyObject*)Py_TYPE(h) == t_void_p) {
+        PyObject* v = PyObject_GetAttr(h, s_value);
         Py_DECREF(h);
-        if (!v) return -1;
+        h = v;
     }
-    *out = v == Py_None ? NULL : PyLong_AsVoidPtr(v);
-    Py_DECREF(v);
-    return PyErr_Occurred() ? -1 : 0;
+    if (!h) return -1;
+    *out = NULL;
+    rc = h == Py_None ? 0 : address_of(h, 0, out);
+    Py_DECREF(h);
+    return rc;
 }
 
 /* The stream's handle: what the binding's _stream returns, for the current stream without going through the interpreter. */
 static int stream_of(PyObject* s, void** out)
 {
     PyObject *v = NULL, *d;
+    int rc = 0;
     if (s == Py_None && f_raw_stream != Py_None) {
         v = PyObject_CallNoArgs(f_initialized);
         if (!v) return -1;
@@ -154,9 +186,10 @@ static int stream_of(PyObject* s, void** out)
         }
     }
     if (!v && !(v = PyObject_CallOneArg(f_stream, s))) return -1;
-    *out = v == Py_None ? NULL : PyLong_AsVoidPtr(v);
+    *out = NULL;
+    if (v != Py_None) rc = address_of(v, 0, out);
     Py_DECREF(v);
-    return PyErr_Occurred() ? -1 : 0;
+    return rc;
 }
 
 static int argc_is(Py_ssize_t n, Py_ssize_t want)
@@ -186,8 +219,8 @@ FUNCTION(sdl_quantize_outer_grad)        /* g, w_send, n, fmt, codes, scales, st
     Addresses w, c, s;
     uint32_t M;
     uint64_t numel, fmt;
-    if (!argc_is(n, 7) || address(a[0], &g) || addresses(a[1], &w) || addresses(a[4], &c) || addresses(a[5], &s) || count(a[1], &w, &M)
-        || whole(a[2], &numel) || whole(a[3], &fmt) || stream_of(a[6], &st)) return NULL;
+    if (!argc_is(n, 7) || address(a[0], 0, &g) || addresses(a[1], &w) || addresses(a[4], &c) || addresses(a[5], &s) || count(a[1], &w, &M)
+        || whole(a[2], f_uint64, &numel) || whole(a[3], f_int, &fmt) || stream_of(a[6], &st)) return NULL;
     CALL(p_sdl_quantize_outer_grad(g, W(w), M, numel, (sdl_format_t)fmt, V(c), V(s), st));
 }
 
@@ -198,8 +231,8 @@ FUNCTION(sdl_dequant_reduce_nesterov)    /* g, mom, codes, scales, n, fmt, lr, m
     uint32_t M;
     uint64_t numel, fmt;
     float lr, mu;
-    if (!argc_is(n, 9) || address(a[0], &g) || address(a[1], &mom) || addresses(a[2], &c) || addresses(a[3], &s) || count(a[2], &c, &M)
-        || whole(a[4], &numel) || whole(a[5], &fmt) || real(a[6], &lr) || real(a[7], &mu) || stream_of(a[8], &st)) return NULL;
+    if (!argc_is(n, 9) || address(a[0], 0, &g) || address(a[1], 0, &mom) || addresses(a[2], &c) || addresses(a[3], &s) || count(a[2], &c, &M)
+        || whole(a[4], f_uint64, &numel) || whole(a[5], f_int, &fmt) || real(a[6], &lr) || real(a[7], &mu) || stream_of(a[8], &st)) return NULL;
     CALL(p_sdl_dequant_reduce_nesterov(g, mom, W(c), W(s), M, numel, (sdl_format_t)fmt, lr, mu, st));
 }
 
@@ -210,7 +243,7 @@ FUNCTION(sdl_merge_overlap)              /* g_new, w_now, n, alpha, stream */
     uint32_t M;
     uint64_t numel;
     float alpha;
-    if (!argc_is(n, 5) || address(a[0], &g) || addresses(a[1], &w) || count(a[1], &w, &M) || whole(a[2], &numel) || real(a[3], &alpha)
+    if (!argc_is(n, 5) || address(a[0], 0, &g) || addresses(a[1], &w) || count(a[1], &w, &M) || whole(a[2], f_uint64, &numel) || real(a[3], &alpha)
         || stream_of(a[4], &st)) return NULL;
     CALL(p_sdl_merge_overlap(g, V(w), M, numel, alpha, st));
 }
@@ -222,10 +255,10 @@ FUNCTION(sdl_receive_outer_step)         /* g, mom, codes, scales, w_now, n, fmt
     uint32_t M, M_c;
     uint64_t numel, fmt;
     float lr, mu, alpha;
-    if (!argc_is(n, 11) || address(a[0], &g) || address(a[1], &mom) || addresses(a[2], &c) || addresses(a[3], &s) || addresses(a[4], &w)
+    if (!argc_is(n, 11) || address(a[0], 0, &g) || address(a[1], 0, &mom) || addresses(a[2], &c) || addresses(a[3], &s) || addresses(a[4], &w)
         || count(a[2], &c, &M_c) || count(a[4], &w, &M)) return NULL;
     if (M != M_c) return PyLong_FromLong(SDL_ERR_INVALID_ARG);
-    if (whole(a[5], &numel) || whole(a[6], &fmt) || real(a[7], &lr) || real(a[8], &mu) || real(a[9], &alpha) || stream_of(a[10], &st)) return NULL;
+    if (whole(a[5], f_uint64, &numel) || whole(a[6], f_int, &fmt) || real(a[7], &lr) || real(a[8], &mu) || real(a[9], &alpha) || stream_of(a[10], &st)) return NULL;
     CALL(p_sdl_receive_outer_step(g, mom, W(c), W(s), V(w), M, numel, (sdl_format_t)fmt, lr, mu, alpha, st));
 }
 
@@ -236,10 +269,10 @@ FUNCTION(sdl_fragment_outer_step)        /* g, mom, w_send, w_now, n, fmt, lr, m
     uint32_t M, M_now;
     uint64_t numel, fmt;
     float lr, mu, alpha;
-    if (!argc_is(n, 12) || address(a[0], &g) || address(a[1], &mom) || addresses(a[2], &ws) || addresses(a[3], &wn) || addresses(a[9], &c)
+    if (!argc_is(n, 12) || address(a[0], 0, &g) || address(a[1], 0, &mom) || addresses(a[2], &ws) || addresses(a[3], &wn) || addresses(a[9], &c)
         || addresses(a[10], &s) || count(a[2], &ws, &M) || count(a[3], &wn, &M_now)) return NULL;
     if (M != M_now) return PyLong_FromLong(SDL_ERR_INVALID_ARG);
-    if (whole(a[4], &numel) || whole(a[5], &fmt) || real(a[6], &lr) || real(a[7], &mu) || real(a[8], &alpha) || stream_of(a[11], &st)) return NULL;
+    if (whole(a[4], f_uint64, &numel) || whole(a[5], f_int, &fmt) || real(a[6], &lr) || real(a[7], &mu) || real(a[8], &alpha) || stream_of(a[11], &st)) return NULL;
     CALL(p_sdl_fragment_outer_step(g, mom, W(ws), V(wn), M, numel, (sdl_format_t)fmt, lr, mu, alpha, V(c), V(s), st));
 }
 
@@ -249,8 +282,8 @@ FUNCTION(sdl_quantize_outer_grad_plan)   /* plan, p, g, w_send, fmt, codes, scal
     Addresses w, c, s;
     uint32_t M;
     uint64_t p, fmt;
-    if (!argc_is(n, 8) || address(a[2], &g) || addresses(a[3], &w) || addresses(a[5], &c) || addresses(a[6], &s) || handle(a[0], &plan)
-        || whole(a[1], &p) || count(a[3], &w, &M) || whole(a[4], &fmt) || stream_of(a[7], &st)) return NULL;
+    if (!argc_is(n, 8) || address(a[2], 0, &g) || addresses(a[3], &w) || addresses(a[5], &c) || addresses(a[6], &s) || handle(a[0], &plan)
+        || whole(a[1], f_uint32, &p) || count(a[3], &w, &M) || whole(a[4], f_int, &fmt) || stream_of(a[7], &st)) return NULL;
     CALL(p_sdl_quantize_outer_grad_plan(plan, (uint32_t)p, g, W(w), M, (sdl_format_t)fmt, V(c), V(s), st));
 }
 
@@ -261,8 +294,8 @@ FUNCTION(sdl_dequant_reduce_nesterov_plan)   /* plan, p, g, mom, codes, scales, 
     uint32_t M;
     uint64_t p, fmt;
     float lr, mu;
-    if (!argc_is(n, 10) || address(a[2], &g) || address(a[3], &mom) || addresses(a[4], &c) || addresses(a[5], &s) || handle(a[0], &plan)
-        || whole(a[1], &p) || count(a[4], &c, &M) || whole(a[6], &fmt) || real(a[7], &lr) || real(a[8], &mu) || stream_of(a[9], &st)) return NULL;
+    if (!argc_is(n, 10) || address(a[2], 0, &g) || address(a[3], 0, &mom) || addresses(a[4], &c) || addresses(a[5], &s) || handle(a[0], &plan)
+        || whole(a[1], f_uint32, &p) || count(a[4], &c, &M) || whole(a[6], f_int, &fmt) || real(a[7], &lr) || real(a[8], &mu) || stream_of(a[9], &st)) return NULL;
     CALL(p_sdl_dequant_reduce_nesterov_plan(plan, (uint32_t)p, g, mom, W(c), W(s), M, (sdl_format_t)fmt, lr, mu, st));
 }
 
@@ -273,7 +306,7 @@ FUNCTION(sdl_merge_overlap_plan)         /* plan, p, g_new, w_now, alpha, stream
     uint32_t M;
     uint64_t p;
     float alpha;
-    if (!argc_is(n, 6) || address(a[2], &g) || addresses(a[3], &w) || handle(a[0], &plan) || whole(a[1], &p) || count(a[3], &w, &M)
+    if (!argc_is(n, 6) || address(a[2], 0, &g) || addresses(a[3], &w) || handle(a[0], &plan) || whole(a[1], f_uint32, &p) || count(a[3], &w, &M)
         || real(a[4], &alpha) || stream_of(a[5], &st)) return NULL;
     CALL(p_sdl_merge_overlap_plan(plan, (uint32_t)p, g, V(w), M, alpha, st));
 }
@@ -285,8 +318,8 @@ FUNCTION(sdl_receive_outer_step_plan)    /* plan, p, g, mom, codes, scales, w_no
     uint32_t M;
     uint64_t p, fmt;
     float lr, mu, alpha;
-    if (!argc_is(n, 12) || address(a[2], &g) || address(a[3], &mom) || addresses(a[4], &c) || addresses(a[5], &s) || addresses(a[6], &w)
-        || handle(a[0], &plan) || whole(a[1], &p) || count(a[6], &w, &M) || whole(a[7], &fmt) || real(a[8], &lr) || real(a[9], &mu) || real(a[10], &alpha)
+    if (!argc_is(n, 12) || address(a[2], 0, &g) || address(a[3], 0, &mom) || addresses(a[4], &c) || addresses(a[5], &s) || addresses(a[6], &w)
+        || handle(a[0], &plan) || whole(a[1], f_uint32, &p) || count(a[6], &w, &M) || whole(a[7], f_int, &fmt) || real(a[8], &lr) || real(a[9], &mu) || real(a[10], &alpha)
         || stream_of(a[11], &st)) return NULL;
     CALL(p_sdl_receive_outer_step_plan(plan, (uint32_t)p, g, mom, W(c), W(s), V(w), M, (sdl_format_t)fmt, lr, mu, alpha, st));
 }
@@ -305,10 +338,10 @@ static int step_args(PyObject* const* a, PyObject* stream, PyObject* codes, PyOb
 {
     uint32_t M_now;
     uint64_t p, fmt;
-    if (address(a[2], &x->g) || address(a[3], &x->mom) || addresses(a[4], &x->ws) || addresses(a[5], &x->wn)
+    if (address(a[2], 0, &x->g) || address(a[3], 0, &x->mom) || addresses(a[4], &x->ws) || addresses(a[5], &x->wn)
         || (codes && (addresses(codes, c) || addresses(scales, s))) || count(a[4], &x->ws, &x->M) || count(a[5], &x->wn, &M_now)) return -1;
     if (x->M != M_now) return 1;
-    if (handle(a[0], &x->plan) || whole(a[1], &p) || whole(a[6], &fmt) || real(a[7], &x->lr) || real(a[8], &x->mu) || real(a[9], &x->alpha)
+    if (handle(a[0], &x->plan) || whole(a[1], f_uint32, &p) || whole(a[6], f_int, &fmt) || real(a[7], &x->lr) || real(a[8], &x->mu) || real(a[9], &x->alpha)
         || stream_of(stream, &x->st)) return -1;
     x->p = (uint32_t)p;
     x->fmt = (sdl_format_t)fmt;
@@ -367,8 +400,18 @@ static PyObject* setup(PyObject* self, PyObject* args)
     Py_RETURN_NONE;
 }
 
+/* ctypes.c_void_p, then the conversions in the order of their declaration */
+static PyObject* converters(PyObject* self, PyObject* args)
+{
+    PyObject** const all[] = {&t_void_p, &f_uint64, &f_uint32, &f_int, &f_float, &f_void_p, &f_packed};
+    size_t i;
+    if (!PyArg_ParseTuple(args, "OOOOOOO", all[0], all[1], all[2], all[3], all[4], all[5], all[6])) return NULL;
+    for (i = 0; i < sizeof(all) / sizeof(all[0]); ++i) Py_INCREF(*all[i]);
+    Py_RETURN_NONE;
+}
+
 #define METHOD(name) {#name, (PyCFunction)(void (*)(void))b_##name, METH_FASTCALL, NULL},
-static PyMethodDef methods[] = {{"setup", setup, METH_VARARGS, NULL}, ENTRIES(METHOD) {NULL, NULL, 0, NULL}};
+static PyMethodDef methods[] = {{"setup", setup, METH_VARARGS, NULL}, {"converters", converters, METH_VARARGS, NULL}, ENTRIES(METHOD) {NULL, NULL, 0, NULL}};
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", NULL, -1, methods, NULL, NULL, NULL, NULL};
 
 PyMODINIT_FUNC PyInit__binding(void)

@@ -2,8 +2,11 @@
 they are called with, every argument arrives where the C interface has it, as ctypes would convert it; and what the
 binding refuses is refused before the library is called."""
 import ctypes
+import decimal
+import fractions
 import inspect
 import os
+import struct
 import subprocess
 import sys
 
@@ -222,3 +225,69 @@ def test_replicas_are_as_many_as_were_looked_at(calls):
     given["w_now"] = Growing(given["w_now"])
     sdl.sdl_merge_overlap(*given.values())
     assert calls["sdl_merge_overlap"][0][2] == 2
+
+
+class _As:
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+class _Index:
+    def __index__(self):
+        return 5
+
+
+VALUES = [5, -1, True, (1 << 33) + 5, (1 << 70) + 5, 10 ** 400, 0.25, 1e300, np.int64(5), np.uint8(5), np.float32(0.25), np.float64(0.3), np.array(0.3), _Index(),
+          None, "x", b"x", object(), fractions.Fraction(5), decimal.Decimal(5), torch.tensor(5), torch.tensor(0.5),
+          *(t(5) for t in (ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int, ctypes.c_longlong, ctypes.c_void_p, ctypes.c_float, ctypes.c_double)),
+          *(_As(t(5)) for t in (int, float, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int, ctypes.c_float))]
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_numbers_are_what_ctypes_makes_of_them(calls, name):
+    """A value of any type reaches the library as a call through ctypes passes it on, or is refused as ctypes refuses it."""
+    given = _arguments(name, 2)
+    order = C_ORDER[name].split()
+    for k in [k for k in given if k in SCALARS and k != "stream"]:
+        at = order.index(k)
+        ctype = getattr(sdl._lib, name).argtypes[at]
+        by_ctypes = ctypes.CFUNCTYPE(ctype, ctype)(lambda x: x)
+        for value in VALUES:
+            calls.clear()
+            try:
+                want = by_ctypes(value)
+            except ctypes.ArgumentError:
+                with pytest.raises(ctypes.ArgumentError):
+                    getattr(sdl, name)(*dict(given, **{k: value}).values())
+                assert not calls
+                continue
+            getattr(sdl, name)(*dict(given, **{k: value}).values())
+            assert calls[name][0][at] == want or (want != want and calls[name][0][at] != calls[name][0][at]), (k, value)
+
+
+def test_addresses_streams_and_handles_of_other_types(calls):
+    given = _arguments("sdl_merge_overlap_plan", 2)
+    call = lambda **x: (sdl.sdl_merge_overlap_plan(*dict(given, **x).values()), calls.pop("sdl_merge_overlap_plan")[0])[1]
+    for value, want in ((None, None), (64, 64), (-64, 2 ** 64 - 64), (2 ** 70 + 64, 64), (Tensor(-64), 2 ** 64 - 64), (Tensor(ctypes.c_void_p(64)), 64),
+                        (Tensor(None), None), (Tensor(_As(64)), 64)):
+        assert call(g_new_base=value)[2] == want
+    for value in (Tensor(np.int64(64)), Tensor(64.0)):
+        with pytest.raises(ctypes.ArgumentError):
+            call(g_new_base=value)
+    for value in (np.int64(64), _Index(), 64):                    # in a list: as struct packs an address
+        call(w_now_base=[Tensor(64), Tensor(value)])
+    for value in (64.0, None, 2 ** 70):
+        with pytest.raises(struct.error):
+            call(w_now_base=[Tensor(64), Tensor(value)])
+    stream = lambda value: type("Stream", (), {"cuda_stream": value})()
+    for value, want in ((0, None), (5, 5), (2 ** 70 + 5, 5), (stream(5), 5), (stream(None), None), (stream(ctypes.c_void_p(5)), 5)):
+        assert call(stream=value)[6] == want
+    with pytest.raises(ctypes.ArgumentError):
+        call(stream=stream(np.int64(5)))
+    plan = lambda value: type("Owner", (), {"_h": value})()
+    for value, want in ((5, 5), (None, None), (ctypes.c_void_p(5), 5), (ctypes.c_void_p(None), None), (_As(5), 5)):
+        assert call(plan=plan(value))[0] == want
+    for value in (1.5, ctypes.c_uint64(5)):
+        with pytest.raises(ctypes.ArgumentError):
+            call(plan=plan(value))
+    assert not calls
