@@ -333,14 +333,15 @@ typedef struct {
     float lr, mu, alpha;
 } Step;
 
-/* -1: an exception is set; 1: the two lists differ in length */
-static int step_args(PyObject* const* a, PyObject* stream, PyObject* codes, PyObject* scales, Addresses* c, Addresses* s, Step* x)
+/* -1: an exception is set; 1: the two lists differ in length (which the staged form has never looked at: what w_now lacks is null, which
+ * the library refuses, and what it has beyond w_send is not read) */
+static int step_args(PyObject* const* a, PyObject* stream, int staged, PyObject* codes, PyObject* scales, Addresses* c, Addresses* s, Step* x)
 {
     uint32_t M_now;
     uint64_t p, fmt;
     if (address(a[2], 0, &x->g) || address(a[3], 0, &x->mom) || addresses(a[4], &x->ws) || addresses(a[5], &x->wn)
-        || (codes && (addresses(codes, c) || addresses(scales, s))) || count(a[4], &x->ws, &x->M) || count(a[5], &x->wn, &M_now)) return -1;
-    if (x->M != M_now) return 1;
+        || (codes && (addresses(codes, c) || addresses(scales, s))) || count(a[4], &x->ws, &x->M) || (!staged && count(a[5], &x->wn, &M_now))) return -1;
+    if (!staged && x->M != M_now) return 1;
     if (handle(a[0], &x->plan) || whole(a[1], f_uint32, &p) || whole(a[6], f_int, &fmt) || real(a[7], &x->lr) || real(a[8], &x->mu) || real(a[9], &x->alpha)
         || stream_of(stream, &x->st)) return -1;
     x->p = (uint32_t)p;
@@ -351,7 +352,7 @@ static int step_args(PyObject* const* a, PyObject* stream, PyObject* codes, PyOb
 FUNCTION(sdl_fragment_outer_step_plan)
 {
     Step x;
-    int rc = argc_is(n, 11) ? step_args(a, a[10], NULL, NULL, NULL, NULL, &x) : -1;
+    int rc = argc_is(n, 11) ? step_args(a, a[10], 0, NULL, NULL, NULL, NULL, &x) : -1;
     if (rc) return rc < 0 ? NULL : PyLong_FromLong(SDL_ERR_INVALID_ARG);
     CALL(p_sdl_fragment_outer_step_plan(x.plan, x.p, x.g, x.mom, W(x.ws), V(x.wn), x.M, x.fmt, x.lr, x.mu, x.alpha, x.st));
 }
@@ -359,7 +360,7 @@ FUNCTION(sdl_fragment_outer_step_plan)
 FUNCTION(sdl_fragment_outer_step_plan_static)
 {
     Step x;
-    int rc = argc_is(n, 11) ? step_args(a, a[10], NULL, NULL, NULL, NULL, &x) : -1;
+    int rc = argc_is(n, 11) ? step_args(a, a[10], 0, NULL, NULL, NULL, NULL, &x) : -1;
     if (rc) return rc < 0 ? NULL : PyLong_FromLong(SDL_ERR_INVALID_ARG);
     CALL(p_sdl_fragment_outer_step_plan_static(x.plan, x.p, x.g, x.mom, W(x.ws), V(x.wn), x.M, x.fmt, x.lr, x.mu, x.alpha, x.st));
 }
@@ -368,7 +369,7 @@ FUNCTION(sdl_fragment_outer_step_plan_ex)    /* ..., codes, scales, stream */
 {
     Step x;
     Addresses c, s;
-    int rc = argc_is(n, 13) ? step_args(a, a[12], a[10], a[11], &c, &s, &x) : -1;
+    int rc = argc_is(n, 13) ? step_args(a, a[12], 0, a[10], a[11], &c, &s, &x) : -1;
     if (rc) return rc < 0 ? NULL : PyLong_FromLong(SDL_ERR_INVALID_ARG);
     CALL(p_sdl_fragment_outer_step_plan_ex(x.plan, x.p, x.g, x.mom, W(x.ws), V(x.wn), x.M, x.fmt, x.lr, x.mu, x.alpha, V(c), V(s), x.st));
 }
@@ -377,7 +378,7 @@ FUNCTION(sdl_fragment_outer_step_staged_ex)  /* ..., codes, scales, stream */
 {
     Step x;
     Addresses c, s;
-    int rc = argc_is(n, 13) ? step_args(a, a[12], a[10], a[11], &c, &s, &x) : -1;
+    int rc = argc_is(n, 13) ? step_args(a, a[12], 1, a[10], a[11], &c, &s, &x) : -1;
     if (rc) return rc < 0 ? NULL : PyLong_FromLong(SDL_ERR_INVALID_ARG);
     CALL(p_sdl_fragment_outer_step_staged_ex(x.plan, x.p, x.g, x.mom, W(x.ws), V(x.wn), x.M, x.fmt, x.lr, x.mu, x.alpha, V(c), V(s), x.st));
 }

@@ -151,6 +151,8 @@ def test_what_is_refused(calls, name):
         with pytest.raises(AttributeError):
             call(*dict(given, **{k: ["x", "y"] if k in LISTS else object()}).values())
     counted = [k for k in tensors if k in ("w_send", "w_now", "w_send_base", "w_now_base")] or ["codes"]
+    if name == "sdl_fragment_outer_step_staged_ex":
+        counted = counted[:1]                    # the replicas are as many as in w_send
     with pytest.raises(TypeError):
         call(*dict(given, **{counted[-1]: None}).values())
     with pytest.raises(TypeError):
@@ -291,3 +293,21 @@ def test_addresses_streams_and_handles_of_other_types(calls):
         with pytest.raises(ctypes.ArgumentError):
             call(plan=plan(value))
     assert not calls
+
+
+def test_the_staged_step_takes_more_replicas_to_write_than_to_read(calls):
+    name = "sdl_fragment_outer_step_staged_ex"
+    given = _arguments(name, 3)
+    for w_now in (given["w_now_base"], (t for t in given["w_now_base"]), None):
+        sdl.sdl_fragment_outer_step_staged_ex(*dict(given, w_send_base=given["w_send_base"][:2], w_now_base=w_now).values())
+    at = {k: i for i, k in enumerate(C_ORDER[name].split())}
+    assert [c[at["M"]] for c in calls[name]] == [2, 2, 2] and [bool(c[at["w_now_base"]]) for c in calls[name]] == [True, True, False]
+
+
+@pytest.mark.parametrize("w_now", [[64], None])
+def test_the_staged_step_without_a_replica_to_write_is_refused_by_the_library(w_now):
+    """(On a plan of one span, with addresses that are not read on the way to the refusal.)"""
+    plan = sdl.sdl_fragment_plan([512], [0], 1, 1, sdl.PATTERN_STRIDED, 10, 0)
+    with pytest.raises(sdl.SdlError) as e:
+        sdl.sdl_fragment_outer_step_staged_ex(plan, 0, 64, 64, [64, 64], w_now, sdl.FMT_FP32, 0.7, 0.9, 0.5, None, None, 0)
+    assert e.value.status == -1
