@@ -1,10 +1,13 @@
 """Host code under AddressSanitizer / UndefinedBehaviorSanitizer (CPU only): the plan, the schedule
 and the engine's state machine are compiled with g++ -fsanitize=address,undefined together with a
 randomised driver (tests/host_fuzz/plan_fuzz.cpp); the device entry points that the engine calls
-are replaced by stand-ins that do nothing."""
+are replaced by stand-ins that do nothing.  The Python extension that converts the arguments of the device calls runs in an
+interpreter of its own (tests/host_fuzz/binding_fuzz.py)."""
 import os
 import shutil
 import subprocess
+import sys
+import sysconfig
 
 import pytest
 
@@ -102,3 +105,24 @@ def test_offloaded_engine_data_path_under_sanitizers(tmp_path):
     walked = int(res.stdout.split("offload engines walked")[1].split()[0])
     refused = int(res.stdout.split("refused")[1].split()[0])
     assert walked > 1000 and refused > 20
+
+
+@pytest.mark.skipif(shutil.which("gcc") is None, reason="needs gcc")
+def test_binding_extension_under_sanitizers(tmp_path):
+    """csrc/sdl_binding.c in an interpreter with the sanitizers' runtime loaded ahead: random arguments, good and bad ones, lists that change while they
+    are looked at, and stand-ins for the library's functions that read every address they are told of."""
+    runtime = _run(["gcc", "-print-file-name=libasan.so"]).stdout.strip()
+    if not os.path.isabs(runtime):
+        pytest.skip("needs the AddressSanitizer runtime")
+    ext, lib = (str(tmp_path / n) for n in ("_binding.so", "standins.so"))
+    fuzz = os.path.join(ROOT, "tests", "host_fuzz")
+    flags = ["-g", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-fno-omit-frame-pointer", "-shared", "-fPIC", "-I",
+             os.path.join(ROOT, "include")]
+    _run(["gcc", *flags, "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "sdl_binding.c"), "-o", ext])
+    _run(["gcc", *flags, os.path.join(fuzz, "binding_standins.c"), "-o", lib])
+    # every object an allocation of its own, so that a use after it was freed is seen
+    env = dict(os.environ, LD_PRELOAD=" ".join([runtime, *os.environ.get("LD_PRELOAD", "").split()]), ASAN_OPTIONS="detect_leaks=0:verify_asan_link_order=0", PYTHONMALLOC="malloc")
+    res = subprocess.run([sys.executable, os.path.join(fuzz, "binding_fuzz.py"), ext, lib], capture_output=True, text=True, env=env, timeout=600)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    _, calls, _, refused = res.stdout.split()
+    assert int(calls) > 10000 and int(refused) > 5000, res.stdout
