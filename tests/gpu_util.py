@@ -178,3 +178,52 @@ class FlatModel:
                 changed += assert_bf16_within_ulp(host_bits(self.w_now[m][o:o + n]), ref.w_now[m],
                                                   tag + f" w_now[{m}]")
         return changed
+
+
+# ------------------------------------------------------------- sums of products, exactly
+
+def _two_sum(a, b):
+    s = a + b
+    v = s - a
+    return s, (a - (s - v)) + (b - v)
+
+
+def gram_of(d):
+    """Gram matrices of d [..., M, n], fp32 numbers held as fp64, each as a pair of fp64 matrices: products of two fp32 numbers are exact in fp64, and
+    they are folded in halves with the error of every addition kept, which leaves about 1e-30."""
+    M = d.shape[-2]
+    want, rest = (torch.zeros(*d.shape[:-1], M, dtype=torch.float64, device=d.device) for _ in range(2))
+    if d.shape[-1] == 0:
+        return want, rest
+    pad = torch.nn.functional.pad
+    for a in range(M):
+        hi = d[..., a:a + 1, :] * d[..., a:, :]
+        lo = torch.zeros_like(hi)
+        while hi.shape[-1] > 1:
+            n, h = hi.shape[-1], (hi.shape[-1] + 1) // 2
+            hi, err = _two_sum(hi[..., :h], pad(hi[..., h:], (0, 2 * h - n)))
+            lo = lo[..., :h] + pad(lo[..., h:], (0, 2 * h - n)) + err
+        for out, x in ((want, hi), (rest, lo)):
+            out[..., a, a:] = x[..., 0]
+            out[..., a:, a] = x[..., 0]
+    return want, rest
+
+
+def exact_gram(g, w, chunk=1 << 22):
+    """The Gram matrix of the outer gradients g - w[m], as a pair of fp64 matrices."""
+    want, rest = gram_of(torch.zeros(len(w), 0, dtype=torch.float64, device=g.device))
+    for lo in range(0, g.numel(), chunk):
+        part, part_rest = gram_of(torch.stack([(g[lo:lo + chunk] - x[lo:lo + chunk].float()).double() for x in w]))
+        want, err = _two_sum(want, part)
+        rest = rest + part_rest + err
+    return want, rest
+
+
+def gram_error(got, want, rest):
+    """Largest error in units of 2^-53 sqrt(G[a][a] G[b][b]): at most the number of fp64 additions that an entry's products go through one after
+    the other, as each rounds a sum of at most that size to 2^-53 of it."""
+    norm = torch.diagonal(want, dim1=-2, dim2=-1).sqrt()
+    unit = 2.0 ** -53 * norm[..., :, None] * norm[..., None, :]
+    error = ((got - want) - rest).abs()
+    assert (error[unit == 0] == 0).all()
+    return float((error / unit)[unit > 0].max()) if (unit > 0).any() else 0.0

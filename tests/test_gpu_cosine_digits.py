@@ -18,6 +18,7 @@ import pytest
 import torch
 
 import paper_2501_18512_amd as sdl
+from gpu_util import exact_gram
 from paper_2501_18512_amd import build
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -69,28 +70,8 @@ def _check(got, exact, M):
     np.testing.assert_allclose(mean, want_cos[np.triu_indices(M, 1)].mean(), atol=2.0 ** -45, rtol=0)
 
 
-def _two_sum(a, b):
-    s = a + b
-    v = s - a
-    return s, (a - (s - v)) + (b - v)
-
-
 def _exact(g, w):
-    """The Gram matrix as a pair of fp64 matrices."""
-    M = len(w)
-    d = torch.stack([(g - x.float()).double() for x in w])
-    want, rest = np.zeros((M, M)), np.zeros((M, M))
-    for a in range(M):
-        hi = d[a] * d[a:]
-        lo = torch.zeros_like(hi)
-        while hi.shape[1] > 1:
-            n, h = hi.shape[1], (hi.shape[1] + 1) // 2
-            pad = torch.nn.functional.pad
-            hi, err = _two_sum(hi[:, :h], pad(hi[:, h:], (0, 2 * h - n)))
-            lo = lo[:, :h] + pad(lo[:, h:], (0, 2 * h - n)) + err
-        want[a, a:] = want[a:, a] = hi[:, 0].cpu().numpy()
-        rest[a, a:] = rest[a:, a] = lo[:, 0].cpu().numpy()
-    return want, rest
+    return tuple(x.cpu().numpy() for x in exact_gram(g, w))
 
 
 @pytest.mark.gpu
