@@ -651,7 +651,10 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 // NaN, as in a replica that has diverged, would send every step there: its entries are NaN whatever follows, so the step goes on with 0 for that replica.
 //
 // The scale of a replica is that of the wavefront's parameters so far: where a difference exceeds what it has room for, the
-// sums so far are put into fp64 and a new one is taken, with room for twice as much and more.
+// sums so far are put into fp64 and a new one is taken, with room for twice as much and more.  That costs as much as a step, and 16 replicas whose largest
+// differences grow one after the other would have it 16 times: they all make room at once for the largest difference of any of them, if it is not more than
+// kAlike times their own.  (Each by itself, t3 / with outliers: M = 16, 2.1 M parameters 43 / 44 us, now 36 / 36, 52.9 M 428 / 425 and 392 / 390; M = 13, 35 M
+// in 195 sets, most of them small, 375 / 381 and 332 / 334.)
 //
 // Error against exact sums, 1e-16 of sqrt(G[a][a] G[b][b]), a = b / a != b, rms of six replicas and 8 seeds, 20 M parameters, by FMAs at 13 and
 // at 16 replicas, and here: normal 0.76/0.01 0.89/0.01, 0.74/0.00 0.92/0.00; Student t3 0.74/0.02 0.84/0.01, 0.64/0.00 0.70/0.00; with outliers
@@ -660,11 +663,12 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 // places, 1.08/1.04 0.88/1.00, 0.62/0.89 0.62/0.77; sizes that vary by 2^40 from one parameter to the next 0.75/0.01 0.89/0.01, 0.49/0.01 0.88/0.01.
 //
 // Bound: vector instructions, 13 for a difference (two to form it, a half each to look at the largest and the smallest, four for the digits, 3.5 that
-// bring each digit's bytes together and 2 for the signs) of four cycles each: they take 92 % of the SIMDs' cycles, the matrix instructions, 15 of 16
-// cycles for 64 parameters, 26 % beside them.  52.9 M parameters and 16 replicas: 300 us with neither loads nor matrix instructions, 329 without the
-// loads, 357 without the matrix instructions, 322 the loads and the staging alone, 385 in all (HBM 268).  Whole call, FMAs and here, M = 13 / 14 / 15 / 16: 52.9 M
-// parameters 419 / 425 / 503 / 509 and 367 / 373 / 382 / 387; at odd elements 443 / 447 / 525 / 533 and 397 / 403 / 423 / 428.  M = 16 with outliers 492 and
-// 417, t3 495 and 421, 24 bits 499 and 387, a tenth of the differences 0 496 and 428, one replica NaN 515 and 453; steps in fp64 all along (sizes that vary by 2^40) 503 and 777.
+// bring each digit's bytes together and 2 for the signs) of four cycles each: they take 93 % of the SIMDs' cycles, the matrix instructions, 15 of
+// 16 cycles for 64 parameters, 27 % beside them.  52.9 M parameters and 16 replicas: 300 us with neither loads nor matrix instructions, 329 without the
+// loads, 357 without the matrix instructions, 322 the loads and the staging alone, 385 in all (HBM 268).  Whole call, FMAs and here, M = 13 / 14 / 15 / 16:
+// 52.9 M parameters 413 / 416 / 492 / 496 and 361 / 367 / 377 / 381; at odd elements 433 / 439 / 513 / 521 and 393 / 397 / 418 / 423.  M = 16 with
+// outliers 494 and 386, t3 495 and 389, 24 bits 500 and 389, a tenth of the differences 0 496 and 427, one replica NaN 510 and 439; steps in fp64
+// all along (sizes that vary by 2^40) 504 and 759.
 // (The time hardly depends on the replicas, as a matrix instruction has 16 rows whatever they are: at 12 replicas 306 and 354.)  Tried, each beside 390
 // to 409 with 18 products at every step: a tile of 512 for each wavefront, 252 registers, 409; 256 parameters, two tiles in LDS 401; the digits' products one
 // step behind, between the vector instructions of the next, which takes 220 registers 427; workgroups that take turns at the tiles 397; subtraction by
@@ -672,13 +676,21 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 constexpr int kDigitTile = kTile;                 // parameters a workgroup takes at a time, 64 of them a step, the wavefronts in turn
 constexpr int kDigitSteps = kDigitTile / kWave;
 constexpr uint32_t kFlushTiles = 64;              // after so many a sum has three products of 2^14 for each of 16384 parameters: 2^30
-// From how many parameters of a launch on.  (Whole call, us, FMAs and here: 1.5 M parameters M = 15 / 16 30.3 30.4, 30.9 30.9; 2.1 M 36.0 34.6, 36.4
-// 35.1; 3 M M = 13 / 14 / 15 / 16 39.2 39.1, 39.5 39.4, 43.1 39.9, 43.5 40.6; 3.7 M M = 13 / 14 43.6 43.7, 43.7 43.7; 4.2 M 46.7 46.1, 47.1 46.2.)
-constexpr bool takes_digits(uint32_t M, uint64_t params) { return params >= (M > 14u ? 4ull << 19 : M > 12u ? 7ull << 19 : ~0ull); }
+// From how many parameters of a launch on.  Whole call, us, FMAs and here, normal differences / t3 / with outliers (a tenth of the differences 0 takes up to 8 % more):
+//   replicas            13                                     14                                     16
+//   1.5 M                                                                                     30.5 30.7  30.6 31.9  30.5 31.9
+//   2.1 M                                                                                     35.8 34.8  35.9 35.8  35.8 35.5
+//   3 M                                                                                       42.9 40.9  43.2 42.1  43.0 41.4
+//   4.2 M     46.8 46.0  46.9 47.6  46.6 46.8   46.7 46.2  47.1 48.0  46.8 47.2
+//   5 M       52.6 51.2  52.6 52.6  52.5 52.1   52.8 51.6  52.7 53.2  52.8 52.6
+//   6 M       60.2 57.4  60.4 60.1  60.1 59.1   60.3 58.8  60.6 61.6  60.6 59.4
+// and 15 replicas like 16.
+constexpr bool takes_digits(uint32_t M, uint64_t params) { return params >= (M > 14u ? 4ull << 19 : M > 12u ? 10ull << 19 : ~0ull); }
 
 constexpr float kBias = 12615808.0f;              // 2^23 + 0x408080
 constexpr float kRoom = 4161407.0f;               // 2^23 - 1 - 0x408080
 constexpr float kLoScale = 4194304.0f;            // 2^22
+constexpr float kAlike = 64.0f;                   // what replicas' largest differences may differ by for one to take another's scale
 constexpr float kFltMax = 3.402823466e+38f;
 
 enum Digit { kHi2, kHi1, kHi0, kLo2, kLo1, kLo0, kDigits };
@@ -699,6 +711,21 @@ constexpr double kDblMax = 1.7976931348623157e+308;
 __device__ __forceinline__ float from_lane(float x, uint32_t lane)
 {
     return u2f((uint32_t)__builtin_amdgcn_ds_bpermute((int)(lane << 2), (int)f2u(x)));
+}
+
+// The largest of the four lanes l % 16, and of the 16 lanes of a quarter; NaN if any is.
+__device__ __forceinline__ float max_of_quarters(float x)
+{
+    u32x2 y = __builtin_amdgcn_permlane32_swap(f2u(x), f2u(x), false, false);
+    x = __builtin_elementwise_maximum(u2f(y.x), u2f(y.y));
+    y = __builtin_amdgcn_permlane16_swap(f2u(x), f2u(x), false, false);
+    return __builtin_elementwise_maximum(u2f(y.x), u2f(y.y));
+}
+template <int RING = 8> __device__ __forceinline__ float max_of_rows(float x)
+{
+    x = __builtin_elementwise_maximum(x, u2f((uint32_t)__builtin_amdgcn_mov_dpp((int)f2u(x), 0x120 + RING, 0xF, 0xF, true)));
+    if constexpr (RING > 1) return max_of_rows<RING / 2>(x);
+    return x;
 }
 
 // What a wavefront loads of a tile: half of the replicas, and of every lane's 8 parameters of g the first or the last four.
@@ -793,8 +820,7 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
         const uint32_t l = lane_here(), r = l % 16u;
         bool digits = true;
         if (__builtin_amdgcn_ballot_w64(!(largest <= limit))) {
-            float m = __builtin_elementwise_maximum(largest, from_lane(largest, l ^ 16u));
-            m = __builtin_elementwise_maximum(m, from_lane(m, l ^ 32u));
+            float m = max_of_quarters(largest);
             if (__builtin_amdgcn_ballot_w64(m != m)) {       // NaN in the replica's entries, whatever else it holds: the others go on with digits
                 const bool nan = m != m;
 #pragma unroll
@@ -808,12 +834,13 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
             digits = !__builtin_amdgcn_ballot_w64(!fits && (!(m <= kFltMax) || (m > 0.0f && m < 0x1p-98f)));
             if (digits && __builtin_amdgcn_ballot_w64(!fits)) {
                 if (__builtin_amdgcn_ballot_w64(scale != 0.0f)) flush();
-                if (!fits) {                         // 2^20 <= m * scale < 2^21
-                    const uint32_t e = f2u(m) >> 23;
-                    scale = m > 0.0f ? u2f((127u + 127u + 20u - e) << 23) : 0.0f;
-                    limit = m > 0.0f ? kRoom * u2f((e - 20u) << 23) : 0.0f;
+                const float want = __builtin_fminf(max_of_rows(m), m * kAlike);
+                if (!(want <= limit)) {              // 2^20 <= want * scale < 2^21
+                    const uint32_t e = f2u(want) >> 23;
+                    scale = want > 0.0f ? u2f((127u + 127u + 20u - e) << 23) : 0.0f;
+                    limit = want > 0.0f ? kRoom * u2f((e - 20u) << 23) : 0.0f;
                     limit = limit <= kFltMax ? limit : kFltMax;
-                    least = m > 0.0f ? u2f((e - 19u) << 23) : 0.0f;
+                    least = want > 0.0f ? u2f((e - 19u) << 23) : 0.0f;
                 }
             }
         }
@@ -1006,16 +1033,23 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
     __shared__ double G[SDL_MAX_WORKERS * SDL_MAX_WORKERS];
     __shared__ double C[SDL_MAX_WORKERS * SDL_MAX_WORKERS];
     __shared__ double part[kFinThreads];
+    __shared__ double rest[kFinThreads];                 // what the additions of a slice have rounded off
     const bool all = f.last_out && blockIdx.x + 1u == gridDim.x;
     const uint32_t first = f.first[all ? 0u : blockIdx.x], count = f.first[blockIdx.x + (all ? 0u : 1u)] - first;
     const uint32_t M = f.M, entries = M * (M + 1u) / 2u, S = fin_slices(M);
     const double* base = f.in + (uint64_t)first * f.stride_k;
     const uint32_t entry = threadIdx.x % entries, slice = threadIdx.x / entries;
+    const bool keep = M > 12u;
+    // adds x to s and returns what that rounds off
+    auto add = [](double& s, double x) {
+        const double before = s, part = (s = before + x) - before;
+        return (before - (s - part)) + (x - part);
+    };
     uint32_t a = 0, b = entry;             // entry number -> (a, b), row by row of the upper triangle
     while (b >= M - a) { b -= M - a; ++a; }
     b += a;
     if (slice < S) {
-        double s = 0.0;
+        double s = 0.0, r = 0.0;
         const double* const mine = base + a * M + b;
         for (uint32_t k = slice; k < count; k += 8u * S) {
             double x[8];
@@ -1026,21 +1060,27 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
                 x[i] = there ? x[i] : 0.0;
             }
 #pragma unroll
-            for (uint32_t i = 0; i < 8u; ++i) s += x[i];
+            for (uint32_t i = 0; i < 8u; ++i) r += add(s, x[i]);
         }
         part[threadIdx.x] = s;
+        if (keep) rest[threadIdx.x] = r;
     }
     __syncthreads();
     // the slices, pair by pair (a sum in sequence would lose a digit that the partial matrices still have)
     for (uint32_t n = S; n > 1u;) {
         const uint32_t half = (n + 1u) / 2u;
-        if (slice + half < n) part[threadIdx.x] += part[threadIdx.x + half * entries];
+        if (slice + half < n) {
+            const double r = add(part[threadIdx.x], part[threadIdx.x + half * entries]);
+            if (keep) rest[threadIdx.x] += rest[threadIdx.x + half * entries] + r;
+        }
         n = half;
         __syncthreads();
     }
     if (threadIdx.x < entries) {
-        G[a * M + b] = part[threadIdx.x];
-        G[b * M + a] = part[threadIdx.x];
+        double s = part[threadIdx.x];
+        if (keep && __builtin_fabs(s) <= kDblMax) s += rest[threadIdx.x];
+        G[a * M + b] = s;
+        G[b * M + a] = s;
     }
     __syncthreads();
     double* o = all ? f.last_out : f.out + (uint64_t)blockIdx.x * f.out_stride;

@@ -1,4 +1,4 @@
-"""15 and 16 replicas and 2^21 parameters in a launch or more, 13 and 14 and 7 * 2^19: the differences as six digits of a multiple of 2^-22 of a
+"""15 and 16 replicas and 2^21 parameters in a launch or more, 13 and 14 and 10 * 2^19: the differences as six digits of a multiple of 2^-22 of a
 scale of their replica's, with products that the matrix cores add up in whole numbers, and 64 parameters at a time in fp64 where a difference
 is no such multiple.  Sizes at the edges of the tiles (512 parameters, the wavefronts 64 at a time) and of the range, arrays at any element,
 and differences that the scale does not suit: growing by 2^60 along the array, none at all, below 2^-98, near the largest fp32 number, all
@@ -22,7 +22,7 @@ from gpu_util import exact_gram
 from paper_2501_18512_amd import build
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-LINE = {13: 7 << 19, 14: 7 << 19, 15: 1 << 21, 16: 1 << 21}
+LINE = {13: 10 << 19, 14: 10 << 19, 15: 1 << 21, 16: 1 << 21}
 
 
 @pytest.mark.skipif(shutil.which(HIPCC) is None, reason="needs hipcc")
@@ -43,12 +43,18 @@ def _inputs(kind, n, M, shift):
         scale = torch.exp2(torch.arange(n + shift, device="cuda") * (60.0 / n) - 40.0)
     g = draw() * 0.02 * scale
     w = [(g - draw() * 1e-3 * scale).to(torch.bfloat16) for _ in range(M)]
+    if kind == "t3":
+        w = [(g - draw() * 1e-3 / (sum(draw().square() for _ in range(3)) / 3).sqrt()).to(torch.bfloat16) for _ in range(M)]
     if kind == "outliers":
         for x in w:
             x[torch.randint(n, (n // 1000,), device="cuda", generator=gen)] += 0.1
     if kind in ("tiny", "huge"):
         power = 2.0 ** (-110 if kind == "tiny" else 120)
         g, w = g * power, [x * power for x in w]
+    if kind == "ladder":                 # each replica's differences half of those of the one before, large ones in all of them at the end
+        w = [(g - draw() * 2.0 ** (-9 - m)).to(torch.bfloat16) for m in range(M)]
+        for x in w:
+            x[n - 5000::500] += 1
     if kind == "uneven":                 # no difference, differences below 2^-98, a scale of their own
         g = g.to(torch.bfloat16).float()
         w[1] = g.to(torch.bfloat16)
@@ -77,7 +83,7 @@ def _exact(g, w):
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,shift", [(13, 0), (14, 1), (15, 0), (16, 1), (16, 0)])
 @pytest.mark.parametrize("kind,extra", [("normal", -1), ("normal", 0), ("normal", 1), ("outliers", 511), ("growing", 513), ("tiny", 65),
-                                        ("huge", 700), ("uneven", 0)])
+                                        ("huge", 700), ("uneven", 0), ("ladder", 190)])
 def test_sums_of_digits(kind, extra, M, shift):
     n = LINE[M] + extra
     g, w = _inputs(kind, n, M, shift)
@@ -156,26 +162,44 @@ def test_replicas_without_numbers(M, nan, inf):
     assert np.isnan(G[list(nan)]).all()
 
 
+def _time_of(n, first, second):
+    """us of a call on either list of replicas: the two in turn, the median of each."""
+    M = len(first[1])
+    result, workspace = sdl.alloc_cosine(M)
+    times = [], []
+    for turn in range(24):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        g, w = (first, second)[turn % 2]
+        start.record()
+        for _ in range(5):
+            sdl.sdl_outer_grad_cosine(g, w, n, result[0], workspace)
+        end.record()
+        end.synchronize()
+        times[turn % 2].append(start.elapsed_time(end) * 200)
+    out = [sorted(x[2:])[5] for x in times]
+    print("{:.1f} us, {:.1f} us".format(*out), flush=True)
+    return out
+
+
 @pytest.mark.gpu
 def test_a_replica_without_numbers_takes_no_longer():
     """One replica all NaN: the others' sums stay on the matrix cores (1.2 times a call without it; 1.8 with every step in fp64, 7.5 lane by
-    lane).  Both calls in turn, the median of each."""
-    M, n = 16, 20_000_000
-    g, w = _inputs("normal", n, M, 0)
+    lane)."""
+    n = 20_000_000
+    g, w = _inputs("normal", n, 16, 0)
     bad = [torch.full_like(x, float("nan")) if m == 3 else x for m, x in enumerate(w)]
-    result, workspace = sdl.alloc_cosine(M)
-    times = {0: [], 1: []}
-    for turn in range(24):
-        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        start.record()
-        for _ in range(5):
-            sdl.sdl_outer_grad_cosine(g, bad if turn % 2 else w, n, result[0], workspace)
-        end.record()
-        end.synchronize()
-        times[turn % 2].append(start.elapsed_time(end))
-    usual, nan = (sorted(x[2:])[5] for x in times.values())
-    print(f"{usual * 200:.1f} us, {nan * 200:.1f} us with a replica of NaN", flush=True)
+    usual, nan = _time_of(n, (g, w), (g, bad))
     assert nan <= 1.5 * usual
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["outliers", "t3"])
+def test_large_differences_here_and_there_take_no_longer(kind):
+    """Replicas whose largest differences grow one after the other make room for them at once (1.03 times a call on normal differences; 1.3 with a
+    new scale for each)."""
+    n = 4_000_000
+    usual, other = _time_of(n, _inputs("normal", n, 16, 0), _inputs(kind, n, 16, 0))
+    assert other <= 1.15 * usual
 
 
 @pytest.mark.gpu

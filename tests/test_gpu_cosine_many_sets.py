@@ -63,7 +63,7 @@ def test_sets_over_launches(M, n_sets, large):
     _check(*_run(plan, 0, M, g, w), M, d)
 
 
-@pytest.mark.parametrize("M", [2, 9, 13])
+@pytest.mark.parametrize("M", [2, 9, 13, 16])
 def test_sets_behind_element_2_to_the_32(M):
     first = (1 << 32) + 8
     sizes = [first, 1000, 513, 3_700_000, 70_001]
