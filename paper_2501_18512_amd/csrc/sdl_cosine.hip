@@ -656,11 +656,12 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 // kAlike times their own.  (Each by itself, t3 / with outliers: M = 16, 2.1 M parameters 43 / 44 us, now 36 / 36, 52.9 M 428 / 425 and 392 / 390; M = 13, 35 M
 // in 195 sets, most of them small, 375 / 381 and 332 / 334.)
 //
-// Error against exact sums, 1e-16 of sqrt(G[a][a] G[b][b]), a = b / a != b, rms of six replicas and 8 seeds, 20 M parameters, by FMAs at 13 and
-// at 16 replicas, and here: normal 0.76/0.01 0.89/0.01, 0.74/0.00 0.92/0.00; Student t3 0.74/0.02 0.84/0.01, 0.64/0.00 0.70/0.00; with outliers
-// 0.99/0.01 0.85/0.01, 0.86/0.00 0.72/0.00; differences with all 24 bits 0.79/0.78 0.66/0.69, 0.69/0.72 0.81/0.74 (of 4 M and 12 seeds normal
-// 0.90/0.01 0.95/0.01, 0.96/0.00 0.93/0.00, 24 bits 0.87/0.91 0.68/0.83, 0.74/0.84 0.62/0.65).  Two seeds: replicas that agree, outliers in the same
-// places, 1.08/1.04 0.88/1.00, 0.62/0.89 0.62/0.77; sizes that vary by 2^40 from one parameter to the next 0.75/0.01 0.89/0.01, 0.49/0.01 0.88/0.01.
+// Error against exact sums, 1e-16 of sqrt(G[a][a] G[b][b]), a = b / a != b, rms of six replicas and 20 seeds, 20 M parameters, by FMAs (whose partial
+// matrices a tree adds up) at 13 and at 16 replicas, and here: normal 0.77/0.01 0.91/0.01, 0.59/0.00 0.73/0.00; Student t3 0.67/0.02 0.76/0.01,
+// 0.40/0.00 0.55/0.00; with outliers 0.98/0.01 0.86/0.01, 0.46/0.00 0.53/0.00; differences with all 24 bits 0.83/0.73 0.80/0.72, 0.38/0.40
+// 0.59/0.52.  8 M: normal 0.97/0.01 0.93/0.01, 0.67/0.00 0.77/0.00; 24 bits 0.81/0.87 0.67/0.71, 0.46/0.49 0.53/0.56.  Four seeds: replicas that agree,
+// outliers in the same places, 0.95/1.03 0.86/0.86, 0.46/0.42 0.46/0.60; sizes that vary by 2^40 from one parameter to the next 0.71/0.01
+// 0.78/0.01, 0.57/0.01 0.56/0.01.
 //
 // Bound: vector instructions, 13 for a difference (two to form it, a half each to look at the largest and the smallest, four for the digits, 3.5 that
 // bring each digit's bytes together and 2 for the signs) of four cycles each: they take 93 % of the SIMDs' cycles, the matrix instructions, 15 of
@@ -992,6 +993,7 @@ __host__ __device__ constexpr uint32_t fin_slices(uint32_t M)
     return s < 64u ? s : 64u;
 }
 constexpr uint32_t fin_chunk(uint32_t M) { return 8u * fin_slices(M); }
+constexpr uint32_t kFewSlices = 13;                                       // from so many replicas on 11 threads and fewer
 
 // matrices of a launch, without one for each set
 constexpr uint32_t mats_per_launch(uint32_t M) { return M > 8u ? kShares * pair_resident(M, M > 12u) : kGroups; }
@@ -1033,23 +1035,16 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
     __shared__ double G[SDL_MAX_WORKERS * SDL_MAX_WORKERS];
     __shared__ double C[SDL_MAX_WORKERS * SDL_MAX_WORKERS];
     __shared__ double part[kFinThreads];
-    __shared__ double rest[kFinThreads];                 // what the additions of a slice have rounded off
     const bool all = f.last_out && blockIdx.x + 1u == gridDim.x;
     const uint32_t first = f.first[all ? 0u : blockIdx.x], count = f.first[blockIdx.x + (all ? 0u : 1u)] - first;
     const uint32_t M = f.M, entries = M * (M + 1u) / 2u, S = fin_slices(M);
     const double* base = f.in + (uint64_t)first * f.stride_k;
     const uint32_t entry = threadIdx.x % entries, slice = threadIdx.x / entries;
-    const bool keep = M > 12u;
-    // adds x to s and returns what that rounds off
-    auto add = [](double& s, double x) {
-        const double before = s, part = (s = before + x) - before;
-        return (before - (s - part)) + (x - part);
-    };
     uint32_t a = 0, b = entry;             // entry number -> (a, b), row by row of the upper triangle
     while (b >= M - a) { b -= M - a; ++a; }
     b += a;
     if (slice < S) {
-        double s = 0.0, r = 0.0;
+        double s = 0.0;
         const double* const mine = base + a * M + b;
         for (uint32_t k = slice; k < count; k += 8u * S) {
             double x[8];
@@ -1060,27 +1055,38 @@ __global__ void __launch_bounds__(kFinThreads) sdl_gram_finalize(const FinArgs f
                 x[i] = there ? x[i] : 0.0;
             }
 #pragma unroll
-            for (uint32_t i = 0; i < 8u; ++i) r += add(s, x[i]);
+            for (uint32_t i = 0; i < 8u; ++i) s += x[i];
         }
         part[threadIdx.x] = s;
-        if (keep) rest[threadIdx.x] = r;
     }
     __syncthreads();
-    // the slices, pair by pair (a sum in sequence would lose a digit that the partial matrices still have)
-    for (uint32_t n = S; n > 1u;) {
-        const uint32_t half = (n + 1u) / 2u;
-        if (slice + half < n) {
-            const double r = add(part[threadIdx.x], part[threadIdx.x + half * entries]);
-            if (keep) rest[threadIdx.x] += rest[threadIdx.x + half * entries] + r;
+    if (M >= kFewSlices) {
+        // up to 11 slices, one after the other, and what the additions round off at the end: no slower than a tree with its barriers (1 M
+        // parameters, M = 13 / 16 24.0 / 26.3 us, now 23.6 / 26.2), and one rounding.  (By the tree the sums of digits, which are exact but leave
+        // more matrices, were no closer to the exact sum than those of FMAs: 8 M parameters, M = 16 rms 1.02e-16 and 0.94e-16, now 0.80e-16.)
+        if (threadIdx.x < entries) {
+            double s = part[threadIdx.x], rest = 0.0;
+            for (uint32_t k = 1; k < S; ++k) {
+                const double x = part[threadIdx.x + k * entries], t = s + x, y = t - s;
+                rest += (s - (t - y)) + (x - y);
+                s = t;
+            }
+            if (__builtin_fabs(s) <= kDblMax) s += rest;
+            G[a * M + b] = s;
+            G[b * M + a] = s;
         }
-        n = half;
-        __syncthreads();
-    }
-    if (threadIdx.x < entries) {
-        double s = part[threadIdx.x];
-        if (keep && __builtin_fabs(s) <= kDblMax) s += rest[threadIdx.x];
-        G[a * M + b] = s;
-        G[b * M + a] = s;
+    } else {
+        // the slices, pair by pair (a sum in sequence would lose a digit that the partial matrices still have)
+        for (uint32_t n = S; n > 1u;) {
+            const uint32_t half = (n + 1u) / 2u;
+            if (slice + half < n) part[threadIdx.x] += part[threadIdx.x + half * entries];
+            n = half;
+            __syncthreads();
+        }
+        if (threadIdx.x < entries) {
+            G[a * M + b] = part[threadIdx.x];
+            G[b * M + a] = part[threadIdx.x];
+        }
     }
     __syncthreads();
     double* o = all ? f.last_out : f.out + (uint64_t)blockIdx.x * f.out_stride;

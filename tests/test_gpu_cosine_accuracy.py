@@ -114,3 +114,18 @@ def test_equal_replicas_have_equal_entries(M, n):
     G, cos, _ = sdl.split_cosine_result(result[0], M)
     assert (G == G[0, 0]).all(), (G / G[0, 0] - 1).abs().max().item()
     assert (cos - 1).abs().max().item() <= 4 * 2.0 ** -52
+
+
+@pytest.mark.parametrize("n", [8_000_000, 20_000_000])
+def test_digits_are_as_exact_as_fmas(n):
+    """13 and 16 replicas in a large call against 12, whose sums are plain FMAs: the same diagonal entries, 12 seeds.  (The same inputs give the
+    same bits, so there is no scatter to allow for.)"""
+    errors = {M: [] for M in (12, 13, 16)}
+    for seed in range(12):
+        g, w = _inputs("normal", n, 16, seed)
+        exact = [_exact((g - x.float()).double().square_()) for x in w[:12]]
+        for M in errors:
+            errors[M] += _rms_error(g, w, M, range(12), exact)
+    rms = {M: (sum(e * e for e in x) / len(x)) ** 0.5 for M, x in errors.items()}
+    print(f"n={n}: " + ", ".join(f"M={M} {x:.2e}" for M, x in rms.items()), flush=True)
+    assert max(rms[13], rms[16]) <= rms[12]
