@@ -645,9 +645,10 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 // of two numbers), and a step without one leaves its six products out; four of them, whose weights are 2^-22 and less, are kept in fp64 (`low`),
 // together with what the additions to the totals round off.
 //
-// Nothing is rounded ahead of a product.  A difference has 24 bits, so what is not below 2 / scale (`least`) is a multiple of 2^-22 / scale; if a step has
-// smaller ones they are looked at, and if one is no such multiple, the step's 64 parameters are added up in fp64 by v_mfma_f64_16x16x4_f64.  So are
-// infinities, and differences below 2^-98 where there are no larger ones (their scale would not be a normal number).
+// Nothing is rounded ahead of a product.  A difference has 24 bits, so what is not below 2 / scale (`least`) is a multiple of 2^-22 / scale, and so is 0.
+// If a step has others they are looked at, and if one is no such multiple, the step's 64 parameters are added up in fp64 by v_mfma_f64_16x16x4_f64.
+// (With 0 among those that are looked at: a tenth of the differences 0, 52.9 M parameters and 16 replicas 427 us, now 414.)  In fp64 go infinities as
+// well, and differences below 2^-98 where there are no larger ones (their scale would not be a normal number).
 // NaN, as in a replica that has diverged, would send every step there: its entries are NaN whatever follows, so the step goes on with 0 for that replica.
 //
 // The scale of a replica is that of the wavefront's parameters so far: where a difference exceeds what it has room for, the
@@ -668,7 +669,7 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 // 16 cycles for 64 parameters, 27 % beside them.  52.9 M parameters and 16 replicas: 300 us with neither loads nor matrix instructions, 329 without the
 // loads, 357 without the matrix instructions, 322 the loads and the staging alone, 385 in all (HBM 268).  Whole call, FMAs and here, M = 13 / 14 / 15 / 16:
 // 52.9 M parameters 413 / 416 / 492 / 496 and 361 / 367 / 377 / 381; at odd elements 433 / 439 / 513 / 521 and 393 / 397 / 418 / 423.  M = 16 with
-// outliers 494 and 386, t3 495 and 389, 24 bits 500 and 389, a tenth of the differences 0 496 and 427, one replica NaN 510 and 439; steps in fp64
+// outliers 494 and 386, t3 495 and 389, 24 bits 500 and 389, a tenth of the differences 0 495 and 414, one replica NaN 510 and 439; steps in fp64
 // all along (sizes that vary by 2^40) 504 and 759.
 // (The time hardly depends on the replicas, as a matrix instruction has 16 rows whatever they are: at 12 replicas 306 and 354.)  Tried, each beside 390
 // to 409 with 18 products at every step: a tile of 512 for each wavefront, 252 registers, 409; 256 parameters, two tiles in LDS 401; the digits' products one
@@ -677,7 +678,8 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
 constexpr int kDigitTile = kTile;                 // parameters a workgroup takes at a time, 64 of them a step, the wavefronts in turn
 constexpr int kDigitSteps = kDigitTile / kWave;
 constexpr uint32_t kFlushTiles = 64;              // after so many a sum has three products of 2^14 for each of 16384 parameters: 2^30
-// From how many parameters of a launch on.  Whole call, us, FMAs and here, normal differences / t3 / with outliers (a tenth of the differences 0 takes up to 8 % more):
+// From how many parameters of a launch on.  Whole call, us, FMAs and here, normal differences / t3 / with outliers (a tenth of the differences 0: 2.1 M and 16
+// replicas 38.0 36.5, 5.3 M and 13 / 14 56.8 58.2 / 54.6 57.0, 6 M 60.0 61.2 / 60.3 61.4, 8 M and 13 78.5 76.1):
 //   replicas            13                                     14                                     16
 //   1.5 M                                                                                     30.5 30.7  30.6 31.9  30.5 31.9
 //   2.1 M                                                                                     35.8 34.8  35.9 35.8  35.8 35.5
@@ -845,7 +847,15 @@ __global__ void __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(
                 }
             }
         }
+        uint32_t smallest_but_0 = ~0u;               // twice its bits, less 1, which of 0 is the largest number
         if (digits && __builtin_amdgcn_ballot_w64(!(smallest >= least))) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const uint32_t x = (f2u(d[j]) << 1) - 1u;
+                smallest_but_0 = x < smallest_but_0 ? x : smallest_but_0;
+            }
+        }
+        if (digits && __builtin_amdgcn_ballot_w64(smallest_but_0 < (f2u(least) << 1) - 1u)) {
             const int last = (int)(f2u(scale) >> 23) - 127 + 22;     // of the last digit, 2^-last
             float left = 0.0f;
 #pragma unroll

@@ -55,6 +55,12 @@ def _inputs(kind, n, M, shift):
         w = [(g - draw() * 2.0 ** (-9 - m)).to(torch.bfloat16) for m in range(M)]
         for x in w:
             x[n - 5000::500] += 1
+    if kind == "zeros":                  # no difference for a third of the replicas, and what the digits lack bits for beside it or elsewhere
+        g[::7] = g[::7].to(torch.bfloat16).float()
+        g[5::999] *= 2.0 ** -60
+        for m, x in enumerate(w):
+            x[::7] = g[::7].to(torch.bfloat16) if m % 3 == 0 else x[::7]
+            x[5::999] = 0
     if kind == "uneven":                 # no difference, differences below 2^-98, a scale of their own
         g = g.to(torch.bfloat16).float()
         w[1] = g.to(torch.bfloat16)
@@ -83,7 +89,7 @@ def _exact(g, w):
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,shift", [(13, 0), (14, 1), (15, 0), (16, 1), (16, 0)])
 @pytest.mark.parametrize("kind,extra", [("normal", -1), ("normal", 0), ("normal", 1), ("outliers", 511), ("growing", 513), ("tiny", 65),
-                                        ("huge", 700), ("uneven", 0), ("ladder", 190)])
+                                        ("huge", 700), ("uneven", 0), ("ladder", 190), ("zeros", 77)])
 def test_sums_of_digits(kind, extra, M, shift):
     n = LINE[M] + extra
     g, w = _inputs(kind, n, M, shift)
