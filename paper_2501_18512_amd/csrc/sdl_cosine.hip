@@ -56,7 +56,7 @@ constexpr uint64_t kManyParams = 1ull << 23;
 // 557 / 945; with arrays at odd elements 32 M 42.2 / 53.8 / 78.7 / 131.6 and 39.5 / 50.7 / 76.2 / 129.8, and up to 3 % slower at 2 and 4 M with 7 and
 // 8 replicas (21.4 / 24.3 and 22.0 / 24.7; 28.7 / 34.0 and 28.7 / 34.7). 2048 of them are 8 for a compute unit, of which 8 / 7 / 5 / 5 / 4 / 3 / 3 /
 // 2 fit it at once by their registers.  Beyond kFewFours 10, from which 2 replicas gain 2 to 4 %; the others lie within 3 % (39 equal sets and 8: 5 % slower).
-// // M = 1 / 2 / 3 / 4 / 6 / 8, 2048 / 2560: 72 M 71.1 72.4 / 99.5 96.1 / 115.9 117.4 / 137.8 138.4 / 182.0 181.9 / 228.4 228.3, 130 M 129.0 129.9 /
+// M = 1 / 2 / 3 / 4 / 6 / 8, 2048 / 2560: 72 M 71.1 72.4 / 99.5 96.1 / 115.9 117.4 / 137.8 138.4 / 182.0 181.9 / 228.4 228.3, 130 M 129.0 129.9 /
 // 175.0 167.3 / 204.1 204.9 / 240.9 242.7 / 317.9 317.6 / 388.4 391.6, 170 M 167.3 168.0 / 223.7 215.3 / 264.6 267.6 / 314.1 318.4 / 403.6 399.5 /
 // 514.2 507.0; 302 M in 48 sets, M = 1 / 2 / 4 / 8, 289.6 285.9 / 379.8 374.8 / 563.6 556.9 / 954.5 951.0; 82 M in 39 equal sets 89.9 92.2 / 120.8
 // 117.3 / 143.0 144.7 / 171.5 171.3 / 227.2 229.0 / 283.3 297.5; at 8 M, M = 1 / 2 / 4 / 8, 14.9 16.4 / 17.6 19.1 / 24.3 25.3 / 40.6 43.3.
